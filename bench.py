@@ -504,7 +504,7 @@ def main() -> int:
     t_per = layers[0].tensors_per_expert
     sel = [layers[0].infos[int(e) * t_per + m] for e in routes[0][0] for m in range(t_per)]
     shapes = zm.decode_launch_shapes(sel, zm.STORES_STREAMING)
-    kernel_names = ["zm_decode_kernel<%d,%d,%s>" % (sh.round_symbols, sh.waves_per_workgroup, "true" if sh.streaming_stores else "false")
+    kernel_names = ["zm_decode_kernel<%d,%d,%s>" % (sh.round_symbols, sh.waves_per_workgroup, "kStreaming" if sh.streaming_stores else "not streaming")
                     for sh in shapes]
 
     result = {

@@ -44,6 +44,7 @@ namespace {
 
 constexpr int kMaxTasks = 48;     // tensors per launch; 80 B each keeps the kernel arguments under 4 KiB
 constexpr uint32_t kTile = 512;
+constexpr int kRawBuffer = 0x00027000;   // last word of a descriptor of untyped memory
 constexpr int kGroup = 8;         // tiles whose sign-mantissa loads are in flight together
 
 // One tensor to decode.  Its parts may live in separate allocations (a cache may keep only some of them
@@ -98,35 +99,49 @@ __device__ __forceinline__ void recover4(uint32_t e4, uint32_t sm4, uint32_t &w0
     w23 = __builtin_amdgcn_perm(hi4, lo4, 0x07030602u);
 }
 
-// kStreaming: the stores are marked non-temporal (the output is larger than the last-level cache, or the
-// caller said that its buffers are not cache-resident); else they are ordinary stores, whose lines tend to
-// stay cached for a consumer or for the next call that rewrites the same buffers.
-template <bool kStreaming = false>
-__device__ __forceinline__ void recover_and_store(uint16_t *dst, uint2 e, uint2 sm)
+// How a wave writes its bf16 words.
+//   kOrdinary   the lines stay dirty in the L2 caches; what is left of them is written back when the kernel ends
+//   kThrough    device-scope stores: the L2 caches keep the line and pass it on to the last-level cache at once
+//   kStreaming  non-temporal: the output is larger than the last-level cache, or the caller said that its buffers are
+//               not cache-resident
+enum Stores { kOrdinary, kThrough, kStreaming };
+
+// Where they go: the first n_values of stream_base, lane j's eight words of tile k at k * kTile + 8 * j.  Buffer stores,
+// because 128-bit device-scope stores exist as these only; the descriptor covers the wave's words and nothing else.
+template <Stores kStores>
+struct Sink {
+    __amdgpu_buffer_rsrc_t words;
+    uint32_t lane_offset;
+    // stream_base and n_values are the same for all lanes
+    __device__ __forceinline__ Sink(uint16_t *stream_base, uint32_t n_values, uint32_t lane)
+        : words(__builtin_amdgcn_make_buffer_rsrc(stream_base, 0, static_cast<int>(2u * n_values), kRawBuffer)),
+          lane_offset(lane * 16u) {}
+
+    __device__ __forceinline__ void store(uint32_t tile, uint4 w) const
+    {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        constexpr int kFlags = kStores == kStreaming ? 2 : kStores == kThrough ? 16 : 0;      // the instruction's nt and sc1 bits
+        __builtin_amdgcn_raw_buffer_store_b128((u32x4){w.x, w.y, w.z, w.w}, words, static_cast<int>(lane_offset + tile * (2u * kTile)), 0, kFlags);
+    }
+
+    // for a lane that owns fewer than eight values of the tile: one word at a time, and those past the end of the
+    // stream are past the end of the descriptor too, which drops them
+    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w) const
+    {
+        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q)
+            __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1))), words,
+                                                  static_cast<int>(lane_offset + tile * (2u * kTile) + 2u * q), 0, 0);
+    }
+};
+
+__device__ __forceinline__ uint4 recover8(uint2 e, uint2 sm)
 {
     uint4 w;
     recover4(e.x, sm.x, w.x, w.y);
     recover4(e.y, sm.y, w.z, w.w);
-    if constexpr (kStreaming) {
-        // four adjacent word stores that the compiler merges into one 128-bit non-temporal store; written as a
-        // vector store the same code needs 11 more registers and loses two waves per SIMD
-        uint32_t *p = reinterpret_cast<uint32_t *>(__builtin_assume_aligned(dst, 16));
-        __builtin_nontemporal_store(w.x, p); __builtin_nontemporal_store(w.y, p + 1);
-        __builtin_nontemporal_store(w.z, p + 2); __builtin_nontemporal_store(w.w, p + 3);
-    } else {
-        *reinterpret_cast<uint4 *>(dst) = w;
-    }
-}
-
-// Same for a lane that owns fewer than eight values of the tile.
-__device__ __forceinline__ void recover_and_store_partial(uint16_t *dst, uint2 e, uint2 sm, int32_t left)
-{
-    uint32_t ws[4];
-    recover4(e.x, sm.x, ws[0], ws[1]);
-    recover4(e.y, sm.y, ws[2], ws[3]);
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        if (q < left) dst[q] = static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1)));
+    return w;
 }
 
 constexpr uint32_t kTableEntries = 256;   // the LDS table resolves the first eight bits of a code
@@ -253,8 +268,114 @@ struct Decoder {
     }
 };
 
-// R: symbols per round; kWaves: waves (streams) per workgroup; kStreaming: non-temporal stores
-template <int R, int kWaves, bool kStreaming>
+// One byte per value of a stream (sign-mantissa bytes, or a raw chunk's exponent bytes), read as 64 bits per lane and
+// tile.  The descriptor covers the stream's bytes, rounded up to whole groups of eight (the section is padded): a lane
+// or a tile past them reads zeros and touches no memory.
+struct ByteSource {
+    __amdgpu_buffer_rsrc_t bytes;
+    uint32_t lane_offset;
+    __device__ __forceinline__ ByteSource(const uint8_t *stream_base, uint32_t n_values, uint32_t lane)
+        : bytes(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(stream_base), 0, static_cast<int>((n_values + 7u) & ~7u), kRawBuffer)),
+          lane_offset(lane * 8u) {}
+    __device__ __forceinline__ uint2 load(uint32_t tile) const
+    {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(bytes, static_cast<int>(lane_offset + tile * kTile), 0, 0);
+        return make_uint2(v.x, v.y);
+    }
+};
+
+// Merges and stores one lane's eight values of a tile, or those that it has.
+template <Stores kStores>
+__device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t tile, uint2 e, uint2 sm, int32_t mine)
+{
+    const int32_t left = mine - static_cast<int32_t>(tile * kTile);
+    const uint4 w = recover8(e, sm);
+    if (left >= 8) out.store(tile, w);
+    else if (left > 0) out.store_partial(tile, w);
+}
+
+// Decodes a coded stream from both ends: pair p is tile p (upward chain) and tile tiles - 1 - p (downward chain), and
+// up[p % kPairs] / down[p % kPairs] receive their sign-mantissa bytes.  The first kAhead pairs' have been asked for by
+// the caller, the others of the first kPairs pairs are asked for when pair p - kAhead is done.
+constexpr int kPairs = kGroup / 2;
+
+// Streams of whole tiles, a multiple of eight of them.  kOneGroup: exactly eight, the common case, straight-line code.
+// In longer ones the next group's bytes are asked for when a group is done: they come while its first pair is decoded.
+// (Asking for them pair by pair, two or four pairs ahead, was 10 % slower: a wave waits for each such load behind its
+// own stores.)
+template <int R, int kAhead, bool kOneGroup, Stores kStores>
+__device__ __forceinline__ void decode_stream(Decoder<R> &dec, const uint16_t *tab, const uint16_t *full_table, uint32_t max_len,
+                                              const Sink<kStores> &out, const ByteSource &sm, uint32_t tiles,
+                                              uint2 (&up)[kPairs], uint2 (&down)[kPairs])
+{
+    for (uint32_t first = 0;;) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            const uint32_t lo = first + i, hi = tiles - 1u - lo;
+            // a tile's eight symbols come in two quads: the upward chain gives values 0..3 first, the
+            // downward chain values 4..7 first
+            const uint2 a = dec.quad(tab, full_table, max_len), b = dec.quad(tab, full_table, max_len);
+            out.store(lo, recover8(make_uint2(a.x, b.x), up[i]));
+            out.store(hi, recover8(make_uint2(b.y, a.y), down[i]));
+            if (i + kAhead < kPairs) {
+                up[i + kAhead] = sm.load(lo + kAhead);
+                down[i + kAhead] = sm.load(hi - kAhead);
+            }
+        }
+        first += kPairs;
+        if (kOneGroup || 2u * first >= tiles) return;
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            up[i] = sm.load(first + i);
+            down[i] = sm.load(tiles - 1u - first - i);
+        }
+    }
+}
+
+// Any other stream: short ones, last ones.  With an odd number of tiles the last pair is the middle tile alone, whose
+// low half comes from the upward and whose high half from the downward chain.  The caller has asked for two pairs; kept
+// rolled, since the unrolled loop with its partial tiles costs the whole kernel 20 registers.
+template <int R, Stores kStores>
+__device__ __forceinline__ void decode_any_stream(Decoder<R> &dec, const uint16_t *tab, const uint16_t *full_table, uint32_t max_len,
+                                                  const Sink<kStores> &out, const ByteSource &sm, uint32_t tiles, int32_t mine,
+                                                  uint2 (&up)[kPairs], uint2 (&down)[kPairs])
+{
+#pragma unroll 1
+    for (uint32_t lo = 0;; ++lo) {
+        const uint32_t hi = tiles - 1u - lo;
+        const uint2 a = dec.quad(tab, full_table, max_len);
+        if (lo == hi) {
+            finish_tile(out, lo, make_uint2(a.x, a.y), up[0], mine);
+            return;
+        }
+        const uint2 b = dec.quad(tab, full_table, max_len);
+        finish_tile(out, lo, make_uint2(a.x, b.x), up[0], mine);
+        finish_tile(out, hi, make_uint2(b.y, a.y), down[0], mine);
+        if (lo + 1u >= hi) return;
+        up[0] = up[1]; down[0] = down[1];
+        up[1] = sm.load(lo + 2u);
+        down[1] = sm.load(hi - 2u);
+    }
+}
+
+// A chunk that is stored raw: its exponent bytes lie in memory as they are.  Four tiles are asked for before the first
+// is merged.
+template <Stores kStores>
+__device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const ByteSource &raw, const ByteSource &sm,
+                                                 uint32_t tiles, int32_t mine)
+{
+    for (uint32_t first = 0; first < tiles; first += kPairs) {
+        uint2 e[kPairs], s[kPairs];
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) { e[k] = raw.load(first + k); s[k] = sm.load(first + k); }
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) finish_tile(out, first + k, e[k], s[k], mine);
+    }
+}
+
+// R: symbols per round; kWaves: waves (streams) per workgroup; kStores: how the output is written
+template <int R, int kWaves, Stores kStores>
 __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
 {
     // The decode table of the workgroup's tensor for the first eight bits of a code, at a fixed LDS address:
@@ -287,8 +408,6 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
         sn = rest < W ? static_cast<uint32_t>(rest) : W;
         tiles = (sn + kTile - 1) / kTile;
     }
-    const bool full = sn != 0 && sn % (kGroup * kTile) == 0;       // the common shape: whole groups of eight tiles
-    const uint8_t *sm_base = t.sm + v0 + lane * 8u;
     const int32_t mine = static_cast<int32_t>(sn) - static_cast<int32_t>(lane * 8u);   // values left from this lane's first one
 
     uint4 held_a = make_uint4(0u, 0u, 0u, 0u), held_b = held_a;   // first 2 KiB of the stream
@@ -326,22 +445,25 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
         }
     }
     // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
-    // stream is staged and decoding starts.  A straight-line stream is decoded from both ends: pair i is tile i
-    // (upward chain) and tile 7 - i of the group (downward chain); up[i] / down[i] hold their bytes.
-    // With ordinary stores the first kAhead pairs are asked for here and pair i + kAhead when pair i is done:
+    // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
+    // With device-scope stores the first kAhead pairs are asked for here and pair i + kAhead when pair i is done:
     // the requests of the thousands of waves that start together are spread out and everyone's first tiles
     // arrive sooner.  A wave waits for such a later load behind its own earlier stores, though, and non-temporal
-    // stores take long to be acknowledged: with them all eight tiles are asked for up front.  So they are with
-    // long codes, whose look-ups in device memory would wait behind the later requests as well.
-    constexpr int kPairs = kGroup / 2;
-    constexpr int kAhead = (kStreaming || R == 2) ? kPairs : 2;
-    const bool straight = full && mode == ZM_MODE_CODED;
+    // stores take long to be acknowledged: with them all eight tiles of a group are asked for up front.  So they are
+    // with long codes, whose look-ups in device memory would wait behind the later requests as well, and in streams of
+    // several groups, of which fewer start together.
+    constexpr int kAhead = (kStores == kStreaming || R == 2) ? kPairs : 2;
+    const bool coded = mode == ZM_MODE_CODED;
+    const bool whole = sn % (kGroup * kTile) == 0;
     uint2 up[kPairs], down[kPairs];
-    if (straight) {
+    const ByteSource sm(t.sm + v0, sn, lane);
+    if (coded && active) {
 #pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-            up[i] = *reinterpret_cast<const uint2 *>(sm_base + i * kTile);
-            down[i] = *reinterpret_cast<const uint2 *>(sm_base + (tiles - 1u - i) * kTile);
+        for (int i = 0; i < kPairs; ++i) {
+            if (i < 2 || (whole && (i < kAhead || tiles > kGroup))) {
+                up[i] = sm.load(i);
+                down[i] = sm.load(tiles - 1u - i);
+            }
         }
     }
 
@@ -408,13 +530,13 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
     if (!active) return;
 
-    uint16_t *out_base = t.out + v0 + lane * 8u;
+    const Sink<kStores> out(t.out + v0, sn, lane);
 
     const uint16_t *full_table = reinterpret_cast<const uint16_t *>(t.lut);
     Decoder<R> dec;
     dec.words = words; dec.last_word = P.stream_cap_words - 1u;
     dec.sub = sub; dec.sub_bits = sub_bits;
-    if (mode == ZM_MODE_CODED) {
+    if (coded) {
         // a6: this lane's bitstream has 8 * tiles + quantum * (its length byte) bits and starts where
         // the bitstreams of the lanes below it end
         const uint32_t units = reinterpret_cast<const uint8_t *>(words)[lane];
@@ -423,64 +545,10 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
         dec.start(first, first + bits);
     }
 
-    if (straight) {
-        // Common case, straight-line: a coded stream of whole groups of kGroup tiles (one group at the
-        // default stream length).  Group number q is the tiles 4q..4q+3 (upward chain) and, from the other
-        // end, tiles - 1 - 4q down to tiles - 4 - 4q (downward chain).  The first group's loads were issued
-        // above; from here on the wave only computes and stores, and asks for the next group's sign-mantissa
-        // bytes when a group is done.
-        const uint32_t groups = tiles / kGroup;
-        for (uint32_t q = 0;;) {
-            const uint32_t lo_tile = q * kPairs, hi_tile = tiles - 1u - q * kPairs;
-#pragma unroll
-            for (int i = 0; i < kPairs; ++i) {
-                // a tile's eight symbols come in two quads: the upward chain gives values 0..3 first, the
-                // downward chain values 4..7 first
-                const uint2 a = dec.quad(tab, full_table, max_len), b = dec.quad(tab, full_table, max_len);
-                recover_and_store<kStreaming>(out_base + (lo_tile + i) * kTile, make_uint2(a.x, b.x), up[i]);
-                recover_and_store<kStreaming>(out_base + (hi_tile - i) * kTile, make_uint2(b.y, a.y), down[i]);
-                if (q == 0 && i + kAhead < kPairs) {
-                    up[i + kAhead] = *reinterpret_cast<const uint2 *>(sm_base + (i + kAhead) * kTile);
-                    down[i + kAhead] = *reinterpret_cast<const uint2 *>(sm_base + (tiles - 1u - (i + kAhead)) * kTile);
-                }
-            }
-            if (++q == groups) break;
-#pragma unroll
-            for (int i = 0; i < kPairs; ++i) {
-                up[i] = *reinterpret_cast<const uint2 *>(sm_base + (q * kPairs + i) * kTile);
-                down[i] = *reinterpret_cast<const uint2 *>(sm_base + (tiles - 1u - q * kPairs - i) * kTile);
-            }
-        }
-    } else {
-        // General case: raw chunks, short last streams, streams that are not whole groups of kGroup tiles.
-        // Pair p is tile p and tile tiles - 1 - p; with an odd number of tiles the last pair is the middle
-        // tile alone, whose low half comes from the upward and whose high half from the downward chain.
-        auto load_sm = [&](uint32_t tile) {
-            return mine - static_cast<int32_t>(tile * kTile) > 0 ? *reinterpret_cast<const uint2 *>(sm_base + tile * kTile)
-                                                                   : make_uint2(0u, 0u);
-        };
-        auto finish = [&](uint32_t tile, uint2 ev, uint2 smv) {
-            const int32_t left = mine - static_cast<int32_t>(tile * kTile);
-            if (mode != ZM_MODE_CODED) ev = left > 0 ? *reinterpret_cast<const uint2 *>(raw + tile * kTile + lane * 8u) : make_uint2(0u, 0u);
-            if (left >= 8) recover_and_store<kStreaming>(out_base + tile * kTile, ev, smv);
-            else if (left > 0) recover_and_store_partial(out_base + tile * kTile, ev, smv, left);
-        };
-        for (uint32_t p = 0; 2u * p < tiles; ++p) {
-            const uint32_t lo_tile = p, hi_tile = tiles - 1u - p;
-            const uint2 sm_lo = load_sm(lo_tile), sm_hi = load_sm(hi_tile);
-            uint2 a = make_uint2(0u, 0u), b = a;
-            if (mode == ZM_MODE_CODED) {
-                a = dec.quad(tab, full_table, max_len);
-                if (lo_tile != hi_tile) b = dec.quad(tab, full_table, max_len);
-            }
-            if (lo_tile != hi_tile) {
-                finish(lo_tile, make_uint2(a.x, b.x), sm_lo);
-                finish(hi_tile, make_uint2(b.y, a.y), sm_hi);
-            } else {
-                finish(lo_tile, make_uint2(a.x, a.y), sm_lo);
-            }
-        }
-    }
+    if (!coded) merge_raw_stream(out, ByteSource(raw, sn, lane), sm, tiles, mine);
+    else if (sn == kGroup * kTile) decode_stream<R, kAhead, true>(dec, tab, full_table, max_len, out, sm, tiles, up, down);
+    else if (whole) decode_stream<R, kPairs, false>(dec, tab, full_table, max_len, out, sm, tiles, up, down);
+    else decode_any_stream(dec, tab, full_table, max_len, out, sm, tiles, mine, up, down);
 }
 
 
@@ -488,13 +556,17 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
 // 8j..8j+7 -- a 64-bit load from each input, one 128-bit store, all contiguous across the wave.
 constexpr int kRecoverTilesPerWave = 1;   // measured on 58.7 M-value tensors: 1 tile 68.9 %, 2: 68.3 %, 4: 67.4 %, 8: 65.7 % of 8 TB/s
 
-template <bool kStreaming>
+template <Stores kStores>
 __global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restrict__ e, const uint8_t *__restrict__ sm,
                                                          uint16_t *__restrict__ out, uint64_t n)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * 4u + (threadIdx.x >> 6);
-    const uint64_t base = wave * (kRecoverTilesPerWave * kTile) + lane * 8u;
+    const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t first = wave * (kRecoverTilesPerWave * kTile);
+    if (first >= n) return;
+    const uint64_t base = first + lane * 8u;
+    const uint64_t rest = n - first;
+    const Sink<kStores> sink(out + first, rest < kRecoverTilesPerWave * kTile ? static_cast<uint32_t>(rest) : kRecoverTilesPerWave * kTile, lane);
     uint2 ev[kRecoverTilesPerWave], sv[kRecoverTilesPerWave];
 #pragma unroll
     for (int k = 0; k < kRecoverTilesPerWave; ++k) {
@@ -515,8 +587,9 @@ __global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restri
 #pragma unroll
     for (int k = 0; k < kRecoverTilesPerWave; ++k) {
         const uint64_t i = base + static_cast<uint64_t>(k) * kTile;
-        if (i + 8 <= n) recover_and_store<kStreaming>(out + i, ev[k], sv[k]);
-        else if (i < n) recover_and_store_partial(out + i, ev[k], sv[k], static_cast<int32_t>(n - i));
+        const uint4 w = recover8(ev[k], sv[k]);
+        if (i + 8 <= n) sink.store(static_cast<uint32_t>(k), w);
+        else if (i < n) sink.store_partial(static_cast<uint32_t>(k), w);
     }
 }
 
@@ -535,12 +608,23 @@ constexpr size_t kLdsLimit = 64 * 1024;
 template <int R>
 constexpr size_t kStaticLds = 2 * kTableEntries + (R == 2 ? 2 * kLongSlots * 16 + 2 * kLongSlots : 0);
 constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cache
+// A launch that writes no more than the L2 caches hold (eight of 4 MiB) would leave nearly all of it dirty there and end
+// with writing it back; device-scope stores spread that over the launch.  Experts of 1024 x 2048 x 3 (12.6 MB of bf16),
+// us per call with ordinary / device-scope stores:
+//                                        one           two           three           four
+//   inputs and outputs cached            6.2 /  4.9    9.0 /  6.5    11.1 /  8.9     13.3 / 12.1
+//   three sets in turn, all cached       6.6 /  5.1    9.2 /  8.0    11.2 / 10.7     13.3 / 14.5
+//   inputs from HBM, outputs cached      7.4 /  6.7   10.2 /  8.9    12.8 / 11.8     15.7 / 15.0
+//   neither cached                       7.9 /  7.2   11.2 / 10.2    14.7 / 14.1     18.0 / 17.6
+// A kernel that reads the words afterwards takes no longer.  The line lies where three sets in turn stop gaining
+// (38 MB: between 5 % slower and 6 % faster, depending on the shape); from 64 MB on both are within 2 % of each other.
+constexpr uint64_t kThroughBytes = 36ull << 20;
 
-template <int R, int kWaves, bool kStreaming>
+template <int R, int kWaves, Stores kStores>
 int launch_kernel(const Launch &L, uint32_t blocks, size_t lds, hipStream_t stream)
 {
     void *args[] = {const_cast<Launch *>(&L)};
-    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<R, kWaves, kStreaming>);
+    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<R, kWaves, kStores>);
     // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
     return hipLaunchKernel(fn, dim3(blocks, L.n_tasks), dim3(64 * kWaves), args, lds, stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
@@ -576,7 +660,9 @@ int launch_tasks(Launch &L, size_t cap, int stores, hipStream_t stream, Recorder
         ++rec->n;
         return ZM_OK;
     }
-    return streaming ? launch_kernel<R, kWaves, true>(L, blocks, lds, stream) : launch_kernel<R, kWaves, false>(L, blocks, lds, stream);
+    if (streaming) return launch_kernel<R, kWaves, kStreaming>(L, blocks, lds, stream);
+    return out_bytes <= kThroughBytes ? launch_kernel<R, kWaves, kThrough>(L, blocks, lds, stream)
+                                      : launch_kernel<R, kWaves, kOrdinary>(L, blocks, lds, stream);
 }
 
 // Collects the tensors of one round length and launches them, at most kMaxTasks per launch.
@@ -743,10 +829,14 @@ extern "C" int zm_recover(const void *exponents, const void *sign_mantissa, size
     uint64_t n = n_values;
     void *args[] = {&e, &sm, &out, &n};
     // A launch that moves more than half of the last-level cache (four bytes per value) writes with non-temporal
-    // stores: measured on 58.7 M-value tensors 71.6 against 68.9 % of the HBM roofline; on 2.9 M-value tensors,
-    // whose buffers stay cached between calls, ordinary stores are the faster ones (43.3 against 40.4 %).
-    const void *fn = 4 * n > kLastLevelCacheBytes / 2 ? reinterpret_cast<const void *>(&zm_recover_kernel<true>)
-                                                  : reinterpret_cast<const void *>(&zm_recover_kernel<false>);
+    // stores: measured on 58.7 M-value tensors 71.6 against 68.9 % of the HBM roofline.  Smaller ones write with device-scope
+    // stores, us per call against ordinary ones, three sets in turn / outputs not cached: 8.4 M values 6.2 / 8.3 against
+    // 6.3 / 8.3, 16.8 M 10.7 / 13.9 against 10.9 / 14.2, 25 M 19.0 / 19.3 against 19.6 / 20.2.  Up to kOrdinaryValues the
+    // ordinary ones are ahead where the outputs are not cached: 2.9 M values 4.1 against 4.2, 4.2 M 4.9 against 5.1.
+    constexpr uint64_t kOrdinaryValues = 5ull << 20;
+    const void *fn = 4 * n > kLastLevelCacheBytes / 2 ? reinterpret_cast<const void *>(&zm_recover_kernel<kStreaming>)
+                     : n > kOrdinaryValues            ? reinterpret_cast<const void *>(&zm_recover_kernel<kThrough>)
+                                                      : reinterpret_cast<const void *>(&zm_recover_kernel<kOrdinary>);
     return hipLaunchKernel(fn, dim3(static_cast<uint32_t>(blocks)), dim3(256),
                            args, 0, static_cast<hipStream_t>(stream)) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
