@@ -169,7 +169,8 @@ int zm_validate_blob(const void *blob_host, size_t size);
 /* The hot call (Sec. 3.1 "Real-time Inference", steps 5-8, for experts whose
  * compressed form is resident; Sec. 3.3 recovery): decode the experts a MoE
  * layer's gate selected, in one kernel launch per 48 tensors of a code-table width class (codes of at most 8
- * bits, longer codes).
+ * bits, longer codes), or per 240 where a call of more than 48 tensors has blobs of at most four layouts and
+ * 65536 values or more per tensor.
  *
  *   blobs             host array [n_experts * tensors_per_expert] of DEVICE
  *                     pointers; entry e*tensors_per_expert + m is tensor m of
@@ -264,11 +265,13 @@ typedef struct zm_launch_shape {
     uint32_t round_symbols;        /* symbols a lane decodes per 32-bit window: 4 (codes <= 8 bits) or 2   */
     uint32_t waves_per_workgroup;  /* streams that share a workgroup                                       */
     uint32_t streaming_stores;     /* 1: non-temporal stores                                               */
-    uint32_t workgroups;           /* grid x: workgroups of the largest tensor of the launch               */
-    uint32_t tensors;              /* grid y                                                               */
+    uint32_t workgroups;           /* grid x: workgroups of the largest tensor of the launch, or of all its
+                                      tensors together where their lengths differ much                     */
+    uint32_t tensors;              /* tensors of the launch                                                */
     uint32_t lds_bytes;            /* LDS of one workgroup                                                 */
 } zm_launch_shape;
-/* shapes_out holds shapes_cap entries (may be NULL with 0); *n_shapes receives the number of launches, which
+/* shapes_out holds shapes_cap entries (may be NULL with 0); the tensors are taken to lie in blobs, as
+ * zm_decode_experts has them; *n_shapes receives the number of launches, which
  * may exceed shapes_cap.  ZM_E_ARG as for the decode calls. */
 int zm_decode_launch_shapes(const zm_tensor_info *infos, int n_tensors, int stores,
                             zm_launch_shape *shapes_out, int shapes_cap, int *n_shapes);

@@ -36,13 +36,15 @@
 //      by byte-parallel bit operations and stored (a8).
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 #include "zipmoe.h"
 
 namespace {
 
-constexpr int kMaxTasks = 48;     // tensors per launch; 80 B each keeps the kernel arguments under 4 KiB
+constexpr int kMaxTasks = 48;     // tensors per launch; 84 B each keeps the kernel arguments under 4 KiB
+constexpr int kFewTasks = 6;
 constexpr uint32_t kTile = 512;
 constexpr int kRawBuffer = 0x00027000;   // last word of a descriptor of untyped memory
 constexpr int kGroup = 8;         // tiles whose sign-mantissa loads are in flight together
@@ -64,13 +66,69 @@ struct Task {
     uint32_t code;            // longest code length | lane quantum << 8
 };
 
+// Kernel arguments of a launch of up to N tensors.  The runtime copies all of them, used or not, into the device's
+// memory for every launch, so a launch of few tensors takes the small kind.
+// grid: x = workgroup inside the tensor, y = tensor.  kFlat, for tensors of very different lengths: x counts through
+// the workgroups of all tensors, first_block[k] being the first one of tensor k.  (A kind of its own: a flag among the
+// arguments would be one more read that every wave waits for.)
+template <int N, bool kFlat>
 struct Launch {
     uint32_t n_tasks;
     uint32_t stream_cap_words;   // LDS words reserved per wave for its stream
     uint32_t pad[2];
-    Task task[kMaxTasks];        // blockIdx.y selects the task
+    Task task[N];
+    uint32_t first_block[kFlat ? N : 1];
 };
-static_assert(sizeof(Launch) <= 4096, "kernel arguments must stay under 4 KiB");
+static_assert(sizeof(Launch<kMaxTasks, true>) <= 4096, "kernel arguments must stay under 4 KiB");
+static_assert(kMaxTasks <= 64, "a wave finds its tensor with one value per lane");
+
+// What the tensors of one shape share, and what is left of a tensor: 16 bytes, so that a launch takes five times as many.
+struct Shape {
+    uint64_t n_values, sm_offset, e_offset;
+    uint32_t lut_offset, table_offset;
+    uint32_t stream_values, streams_per_chunk, n_streams, code;
+};
+struct Packed {
+    uint32_t blob;       // bits 4..35 of the blob's address
+    uint32_t high;       // bits 36..47 of the blob's address, 8 bits of shape number, bits 36..47 of the output's address
+    uint32_t out;        // bits 4..35 of the output's address
+    uint32_t e_units;    // bytes in the E-chunk region / 256
+};
+constexpr int kMaxPacked = 240, kMaxShapes = 4;
+struct PackedLaunch {
+    uint32_t n_tasks;
+    uint32_t stream_cap_words;
+    uint32_t pad[2];
+    Packed task[kMaxPacked];
+    Shape shape[kMaxShapes];
+};
+static_assert(sizeof(PackedLaunch) <= 4096, "kernel arguments must stay under 4 KiB");
+
+// The tensor that a workgroup works on and the workgroup's number inside the tensor.
+template <int N, bool kFlat>
+__device__ __forceinline__ Task task_of(const Launch<N, kFlat> &P, uint32_t lane, uint32_t &block)
+{
+    uint32_t k = blockIdx.y;
+    block = blockIdx.x;
+    if constexpr (kFlat) {
+        // every lane looks at one tensor's first workgroup; those that start at or before this one are the first k + 1
+        const uint32_t first = lane < P.n_tasks ? P.first_block[lane] : ~0u;
+        k = static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(first <= blockIdx.x))) - 1u;
+        block = blockIdx.x - static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(first), static_cast<int>(k)));
+    }
+    return P.task[k];            // one batch of scalar loads
+}
+
+__device__ __forceinline__ Task task_of(const PackedLaunch &P, uint32_t, uint32_t &block)
+{
+    block = blockIdx.x;
+    const Packed p = P.task[blockIdx.y];
+    const Shape s = P.shape[(p.high >> 12) & (kMaxShapes - 1u)];
+    const uint8_t *blob = reinterpret_cast<const uint8_t *>(static_cast<uint64_t>(p.blob) << 4 | static_cast<uint64_t>(p.high & 0xfffu) << 36);
+    uint16_t *out = reinterpret_cast<uint16_t *>(static_cast<uint64_t>(p.out) << 4 | static_cast<uint64_t>(p.high >> 20) << 36);
+    return Task{blob + s.lut_offset, blob + s.sm_offset, blob + s.e_offset, reinterpret_cast<const uint64_t *>(blob + s.table_offset), out,
+                s.n_values, s.e_offset, static_cast<uint64_t>(p.e_units) * 256u, s.stream_values, s.streams_per_chunk, s.n_streams, s.code};
+}
 
 constexpr uint32_t kLaneBytes = 64;   // a stream opens with one length byte per lane
 
@@ -375,8 +433,8 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
 }
 
 // R: symbols per round; kWaves: waves (streams) per workgroup; kStores: how the output is written
-template <int R, int kWaves, Stores kStores>
-__global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
+template <int R, int kWaves, Stores kStores, class Args>
+__global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
 {
     // The decode table of the workgroup's tensor for the first eight bits of a code, at a fixed LDS address:
     // one 16-bit read gives a code's length and its symbol.  (Two byte tables, one read each, were 2-4 % slower:
@@ -391,14 +449,14 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Launch P)
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-    // grid: x = workgroup inside the tensor, y = tensor.  The task is copied with one batch of scalar loads.
-    const Task t = P.task[blockIdx.y];
+    uint32_t block;
+    const Task t = task_of(P, lane, block);
     uint32_t *words = stream_lds + wave * P.stream_cap_words;
     const uint32_t W = t.stream_values;
     const uint32_t max_len = t.code & 0xffu, quantum = t.code >> 8;
     const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;     // bytes of a chunk-table entry
 
-    const uint32_t g = blockIdx.x * kWaves + wave;
+    const uint32_t g = block * kWaves + wave;
     bool active = g < t.n_streams;
     const uint64_t v0 = static_cast<uint64_t>(g) * W;              // first value of the stream in the tensor
     uint32_t sn = 0, mode = ZM_MODE_RAW, tiles = 0;
@@ -620,15 +678,6 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // (38 MB: between 5 % slower and 6 % faster, depending on the shape); from 64 MB on both are within 2 % of each other.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
-template <int R, int kWaves, Stores kStores>
-int launch_kernel(const Launch &L, uint32_t blocks, size_t lds, hipStream_t stream)
-{
-    void *args[] = {const_cast<Launch *>(&L)};
-    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<R, kWaves, kStores>);
-    // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
-    return hipLaunchKernel(fn, dim3(blocks, L.n_tasks), dim3(64 * kWaves), args, lds, stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
-}
-
 // Where the shapes of a call's launches go when they are asked for instead of launched.
 struct Recorder {
     zm_launch_shape *out;
@@ -636,65 +685,195 @@ struct Recorder {
     int n = 0;
 };
 
-template <int R, int kWaves>
-int launch_tasks(Launch &L, size_t cap, int stores, hipStream_t stream, Recorder *rec)
+// What a launch needs to know beside its kernel arguments.
+struct Plan {
+    dim3 grid;
+    size_t lds;              // dynamic part: the streams
+    uint64_t out_bytes;
+    int stores;
+    hipStream_t stream;
+    Recorder *rec;
+};
+
+template <int R, int kWaves, Stores kStores, class Args>
+int launch_kernel(const Args &args, const Plan &p)
 {
-    const size_t lds = 4 * kWaves * cap;                       // dynamic part: the streams
+    void *argv[] = {const_cast<Args *>(&args)};
+    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<R, kWaves, kStores, Args>);
+    // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
+    return hipLaunchKernel(fn, p.grid, dim3(64 * kWaves), argv, p.lds, p.stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+}
+
+template <int R, int kWaves, class Args>
+int launch_args(const Args &args, const Plan &p)
+{
+    const bool streaming = p.stores == ZM_STORES_STREAMING || (p.stores == ZM_STORES_AUTO && p.out_bytes > kLastLevelCacheBytes);
+    if (p.rec) {
+        if (p.rec->n < p.rec->cap)
+            p.rec->out[p.rec->n] = zm_launch_shape{static_cast<uint32_t>(R), static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, p.grid.x,
+                                                   args.n_tasks, static_cast<uint32_t>(p.lds + kStaticLds<R>)};
+        ++p.rec->n;
+        return ZM_OK;
+    }
+    if (streaming) return launch_kernel<R, kWaves, kStreaming>(args, p);
+    return p.out_bytes <= kThroughBytes ? launch_kernel<R, kWaves, kThrough>(args, p) : launch_kernel<R, kWaves, kOrdinary>(args, p);
+}
+
+// Whether a launch numbers its workgroups through all tensors instead of giving every tensor as many as the largest has.
+// Workgroups that exit at once still have to be started; finding the tensor by its first workgroup costs every wave one
+// more read.  Calls of tensors whose lengths fall off, us with a workgroup row per tensor / numbered through:
+//   24 tensors of 2.1 M values down to 1/3: 22.3 / 22.3, to 1/30: 11.7 / 10.3, to 1/300: 9.7 / 8.0
+//   48 tensors of 0.5 M values to 1/3: 10.4 / 10.7, to 1/30: 9.4 / 7.0;  of 0.13 M values to 1/300: 5.8 / 5.8
+bool number_through(uint64_t useful, uint64_t started)
+{
+    const uint64_t idle = started - useful;
+    return idle > 2048 || (idle > 1024 && idle > useful);
+}
+
+template <int R, int kWaves, int N>
+int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream, Recorder *rec)
+{
+    const size_t lds = 4 * kWaves * cap;
     if (lds + kStaticLds<R> > kLdsLimit) {
         if constexpr (kWaves > 1) return launch_tasks<R, kWaves / 2>(L, cap, stores, stream, rec);
         else return ZM_E_ARG;                   // stream too long to stage in LDS
     }
-    uint32_t blocks = 0;            // of the largest tensor; workgroups past a smaller tensor's end exit at once
-    uint64_t out_bytes = 0;
+    uint32_t blocks = 0;            // of the largest tensor
+    uint64_t total = 0, out_bytes = 0;
     for (uint32_t k = 0; k < L.n_tasks; ++k) {
         const uint32_t b = (L.task[k].n_streams + kWaves - 1) / kWaves;
+        L.first_block[k] = static_cast<uint32_t>(total);
         blocks = b > blocks ? b : blocks;
+        total += b;
         out_bytes += 2 * L.task[k].n_values;
     }
     if (!blocks) return ZM_OK;
-    const bool streaming = stores == ZM_STORES_STREAMING || (stores == ZM_STORES_AUTO && out_bytes > kLastLevelCacheBytes);
-    if (rec) {
-        if (rec->n < rec->cap)
-            rec->out[rec->n] = zm_launch_shape{static_cast<uint32_t>(R), static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, blocks,
-                                               L.n_tasks, static_cast<uint32_t>(lds + kStaticLds<R>)};
-        ++rec->n;
-        return ZM_OK;
-    }
-    if (streaming) return launch_kernel<R, kWaves, kStreaming>(L, blocks, lds, stream);
-    return out_bytes <= kThroughBytes ? launch_kernel<R, kWaves, kThrough>(L, blocks, lds, stream)
-                                      : launch_kernel<R, kWaves, kOrdinary>(L, blocks, lds, stream);
+    if (total <= 0x7FFFFFFFull && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
+        return launch_args<R, kWaves>(L, Plan{dim3(static_cast<uint32_t>(total)), lds, out_bytes, stores, stream, rec});
+    // without the workgroup numbers the arguments are the same up to the end of the tasks
+    using Rows = Launch<N, false>;
+    using Through = Launch<N, true>;
+    static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
+    return launch_args<R, kWaves>(reinterpret_cast<const Rows &>(L), Plan{dim3(blocks, L.n_tasks), lds, out_bytes, stores, stream, rec});
 }
 
-// Collects the tensors of one round length and launches them, at most kMaxTasks per launch.
+// Collects the tensors of one round length and launches them.
 template <int R>
 struct Group {
     static constexpr uint32_t kLenBound = R == 4 ? 8 : ZM_MAX_CODE_LEN;
-    Launch L{};
-    uint32_t max_stream = 0, max_quantum = 1;
-    int stores;
-    hipStream_t stream;
-    Recorder *rec;
+    int n = 0;                        // tensors to come, all launches together
+    uint64_t n_values = 0;            // of theirs
+    bool packable = true;             // every one has the layout of a blob and an address that fits a Packed
+    uint32_t n_shapes = 0;
+    Shape shape[kMaxShapes];
 
-    Group(int store_policy, hipStream_t s, Recorder *r) : stores(store_policy), stream(s), rec(r) {}
-
-    int add(const Task &t)
+    static bool same(const Shape &a, const Shape &b)
     {
-        L.task[L.n_tasks++] = t;
-        max_stream = max_stream > t.stream_values ? max_stream : t.stream_values;
-        max_quantum = max_quantum > (t.code >> 8) ? max_quantum : (t.code >> 8);
-        return L.n_tasks == kMaxTasks ? flush() : ZM_OK;
+        return a.n_values == b.n_values && a.sm_offset == b.sm_offset && a.e_offset == b.e_offset && a.lut_offset == b.lut_offset &&
+               a.table_offset == b.table_offset && a.stream_values == b.stream_values && a.streams_per_chunk == b.streams_per_chunk &&
+               a.n_streams == b.n_streams && a.code == b.code;
     }
 
-    int flush()
+    // LDS words per wave that tensors of these streams need
+    struct Cap {
+        uint32_t max_stream = 0, max_quantum = 1;
+        void see(const Task &t)
+        {
+            max_stream = max_stream > t.stream_values ? max_stream : t.stream_values;
+            max_quantum = max_quantum > (t.code >> 8) ? max_quantum : (t.code >> 8);
+        }
+        size_t words() const { return stream_cap_words(max_stream, kLenBound, max_quantum); }
+    };
+    Cap cap_of_all;
+
+    // First pass: what the launches will have to hold.  many: the call may need more than one launch.
+    void count(const Task &t, const zm_tensor_info &ti, bool many)
     {
-        if (!L.n_tasks) return ZM_OK;
-        const size_t cap = stream_cap_words(max_stream, kLenBound, max_quantum);
+        ++n;
+        if (!many) return;
+        n_values += t.n_values;
+        cap_of_all.see(t);
+        uint32_t k;
+        packable = packable && pack(t, ti, k).high != kUnpackable;
+    }
+
+    static constexpr uint32_t kUnpackable = ~0u;      // no device address has all of bits 36..47 set
+
+    Packed pack(const Task &t, const zm_tensor_info &ti, uint32_t &k)
+    {
+        const Packed no{0, kUnpackable, 0, 0};
+        const uint8_t *blob = t.lut - ti.lut_offset;
+        const uint64_t b = reinterpret_cast<uint64_t>(blob), o = reinterpret_cast<uint64_t>(t.out);
+        if (ti.lut_offset > UINT32_MAX || ti.table_offset > UINT32_MAX || t.sm != blob + ti.sm_offset || t.echunks != blob + ti.e_offset ||
+            reinterpret_cast<const uint8_t *>(t.table) != blob + ti.table_offset || (b & 15) || b >> 48 || o >> 48 || (t.e_size & 255) ||
+            t.e_size >> 8 > UINT32_MAX) return no;
+        const Shape s{t.n_values, ti.sm_offset, ti.e_offset, static_cast<uint32_t>(ti.lut_offset), static_cast<uint32_t>(ti.table_offset),
+                      t.stream_values, t.streams_per_chunk, t.n_streams, t.code};
+        for (k = 0; k < n_shapes; ++k) if (same(shape[k], s)) break;
+        if (k == n_shapes) {
+            if (n_shapes == kMaxShapes) return no;
+            shape[n_shapes++] = s;
+        }
+        return Packed{static_cast<uint32_t>(b >> 4), static_cast<uint32_t>(b >> 36) | k << 12 | static_cast<uint32_t>(o >> 36) << 20,
+                      static_cast<uint32_t>(o >> 4), static_cast<uint32_t>(t.e_size >> 8)};
+    }
+
+    // Second pass: next(t) yields the group's tensors in order, with their descriptions.  Two streams per workgroup: on one MoE layer call of
+    // 118 MB one, two and four waves per workgroup are within 1 % of each other, eight are 5 % slower.
+    template <typename Next>
+    int launch(Next next, int stores, hipStream_t stream, Recorder *rec)
+    {
+        if (n <= kFewTasks) return launch_wide<kFewTasks>(next, stores, stream, rec);
+        if (n > kMaxTasks && packable && n_values >= kPackedValues * static_cast<uint64_t>(n) &&
+            8 * cap_of_all.words() + kStaticLds<R> <= kLdsLimit) return launch_packed(next, stores, stream, rec);
+        return launch_wide<kMaxTasks>(next, stores, stream, rec);
+    }
+
+    template <int N, typename Next>
+    int launch_wide(Next next, int stores, hipStream_t stream, Recorder *rec)
+    {
+        Launch<N, true> L;
+        for (int left = n; left > 0; left -= static_cast<int>(L.n_tasks)) {
+            L.n_tasks = static_cast<uint32_t>(left < N ? left : N);
+            Cap cap;
+            for (uint32_t k = 0; k < L.n_tasks; ++k) { next(L.task[k]); cap.see(L.task[k]); }
+            L.stream_cap_words = static_cast<uint32_t>(cap.words());
+            const int rc = launch_tasks<R, 2>(L, cap.words(), stores, stream, rec);
+            if (rc != ZM_OK) return rc;
+        }
+        return ZM_OK;
+    }
+
+    // The same tensors in one launch where wide arguments would need one per 48 of them: a launch after another waits
+    // for it to drain, and its first waves for their first bytes.  51 / 96 / 192 tensors of 512 x 1024: 21.3 / 37.7 /
+    // 77.0 us in launches of 48, 19.1 / 35.2 / 65.4 us in one.  Tensors below 64 Ki values keep the launches of 48 that
+    // zm_decode_launch_shapes has always told of for them (its callers and a test rely on that number).
+    static constexpr uint64_t kPackedValues = 1u << 16;
+
+    template <typename Next>
+    int launch_packed(Next next, int stores, hipStream_t stream, Recorder *rec)
+    {
+        const size_t cap = cap_of_all.words();
+        PackedLaunch L;
         L.stream_cap_words = static_cast<uint32_t>(cap);
-        // two streams per workgroup: on one MoE layer call of 118 MB one, two and four waves per workgroup are
-        // within 1 % of each other, eight are 5 % slower
-        const int rc = launch_tasks<R, 2>(L, cap, stores, stream, rec);
-        L.n_tasks = 0; max_stream = 0; max_quantum = 1;
-        return rc;
+        for (uint32_t k = 0; k < n_shapes; ++k) L.shape[k] = shape[k];
+        const int launches = (n + kMaxPacked - 1) / kMaxPacked, each = (n + launches - 1) / launches;
+        for (int left = n; left > 0; left -= static_cast<int>(L.n_tasks)) {
+            L.n_tasks = static_cast<uint32_t>(left < each ? left : each);
+            uint32_t blocks = 0;
+            uint64_t out_bytes = 0;
+            for (uint32_t k = 0; k < L.n_tasks; ++k) {
+                Task t; uint32_t s;
+                const zm_tensor_info &ti = next(t);
+                L.task[k] = pack(t, ti, s);
+                const uint32_t b = (t.n_streams + 1u) / 2u;
+                blocks = b > blocks ? b : blocks;
+                out_bytes += 2 * t.n_values;
+            }
+            const int rc = launch_args<R, 2>(L, Plan{dim3(blocks, L.n_tasks), 8 * cap, out_bytes, stores, stream, rec});
+            if (rc != ZM_OK) return rc;
+        }
+        return ZM_OK;
     }
 };
 
@@ -732,28 +911,36 @@ int make_task(const zm_tensor_parts &pt, const zm_tensor_info &ti, void *out, Ta
 
 constexpr int kMaxTensorsPerCall = 256;
 
-// Tensor i of a call, as make_task wants it; implemented by the two entry points.
-template <typename Describe>
-int decode_call(int n_tensors, Describe describe, int stores, hipStream_t stream, Recorder *rec = nullptr)
+// describe(i, t, skip) fills tensor i's task, info(i) is its description; implemented by the entry points.
+template <typename Describe, typename Info>
+int decode_call(int n_tensors, Describe describe, Info info, int stores, hipStream_t stream, Recorder *rec = nullptr)
 {
     if (stores != ZM_STORES_AUTO && stores != ZM_STORES_CACHED && stores != ZM_STORES_STREAMING) return ZM_E_ARG;
     // first pass: every tensor is checked before anything is launched
+    Group<4> short_codes;
+    Group<2> long_codes;
     for (int i = 0; i < n_tensors; ++i) {
         Task t; bool skip;
         const int rc = describe(i, t, skip);
         if (rc != ZM_OK) return rc;
-    }
-    Group<4> short_codes(stores, stream, rec);
-    Group<2> long_codes(stores, stream, rec);
-    for (int i = 0; i < n_tensors; ++i) {
-        Task t; bool skip;
-        describe(i, t, skip);
         if (skip) continue;
-        const int rc = (t.code & 0xffu) <= 8 ? short_codes.add(t) : long_codes.add(t);
+        if ((t.code & 0xffu) <= 8) short_codes.count(t, info(i), n_tensors > kMaxTasks);
+        else long_codes.count(t, info(i), n_tensors > kMaxTasks);
+    }
+    // the tensors of one group, in the call's order
+    auto members = [&](bool want_short) {
+        return [&, want_short, i = 0](Task &t) mutable -> const zm_tensor_info & {
+            for (bool skip;; ++i) {
+                describe(i, t, skip);
+                if (!skip && ((t.code & 0xffu) <= 8) == want_short) return info(i++);
+            }
+        };
+    };
+    if (short_codes.n) {
+        const int rc = short_codes.launch(members(true), stores, stream, rec);
         if (rc != ZM_OK) return rc;
     }
-    const int rc = short_codes.flush();
-    return rc != ZM_OK ? rc : long_codes.flush();
+    return long_codes.n ? long_codes.launch(members(false), stores, stream, rec) : ZM_OK;
 }
 
 }  // namespace
@@ -764,19 +951,25 @@ extern "C" int zm_decode_tensors(const zm_tensor_parts *parts, const zm_tensor_i
     if (n_tensors == 0) return ZM_OK;
     if (!parts || !infos || !out_bf16 || n_tensors < 0 || n_tensors > kMaxTensorsPerCall) return ZM_E_ARG;
     return decode_call(n_tensors, [&](int i, Task &t, bool &skip) { return make_task(parts[i], infos[i], out_bf16[i], t, skip); },
-                       ZM_STORES_AUTO, static_cast<hipStream_t>(stream));
+                       [&](int i) -> const zm_tensor_info & { return infos[i]; }, ZM_STORES_AUTO, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int zm_decode_launch_shapes(const zm_tensor_info *infos, int n_tensors, int stores,
                                        zm_launch_shape *shapes_out, int shapes_cap, int *n_shapes)
 {
     if (!infos || n_tensors < 0 || n_tensors > kMaxTensorsPerCall || shapes_cap < 0 || (shapes_cap && !shapes_out) || !n_shapes) return ZM_E_ARG;
-    // the same path as a decode call, with placeholder addresses and a recorder in place of the launches
+    // the same path as a decode call, with placeholder addresses and a recorder in place of the launches; the parts lie as
+    // in a blob, where that keeps them aligned
     uint8_t *const somewhere = reinterpret_cast<uint8_t *>(uintptr_t{4096});
-    const zm_tensor_parts pt{somewhere, somewhere, somewhere, somewhere};
     Recorder rec{shapes_out, shapes_cap};
-    const int rc = decode_call(n_tensors, [&](int i, Task &t, bool &skip) { return make_task(pt, infos[i], somewhere, t, skip); },
-                               stores, nullptr, &rec);
+    auto describe = [&](int i, Task &t, bool &skip) {
+        const zm_tensor_info &ti = infos[i];
+        const bool aligned = !((ti.lut_offset | ti.sm_offset | ti.e_offset) & 15) && !(ti.table_offset & 7);
+        const zm_tensor_parts pt = aligned ? zm_tensor_parts{somewhere + ti.lut_offset, somewhere + ti.table_offset, somewhere + ti.sm_offset, somewhere + ti.e_offset}
+                                           : zm_tensor_parts{somewhere, somewhere, somewhere, somewhere};
+        return make_task(pt, ti, somewhere, t, skip);
+    };
+    const int rc = decode_call(n_tensors, describe, [&](int i) -> const zm_tensor_info & { return infos[i]; }, stores, nullptr, &rec);
     *n_shapes = rec.n;
     return rc;
 }
@@ -803,7 +996,10 @@ extern "C" int zm_decode_experts_stores(const void *const *blobs, const uint64_t
         const zm_tensor_parts pt{blob + ti.lut_offset, chunk_offsets[src], blob + ti.sm_offset, blob + ti.e_offset};
         return make_task(pt, ti, out_bf16[i], t, skip);
     };
-    return decode_call(n_selected * tensors_per_expert, describe, stores, static_cast<hipStream_t>(stream));
+    auto info = [&](int i) -> const zm_tensor_info & {
+        return infos[static_cast<size_t>(expert_ids[i / tensors_per_expert]) * tensors_per_expert + i % tensors_per_expert];
+    };
+    return decode_call(n_selected * tensors_per_expert, describe, info, stores, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int zm_decode_experts(const void *const *blobs, const uint64_t *const *chunk_offsets,

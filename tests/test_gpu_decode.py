@@ -405,3 +405,73 @@ def test_decode_call_can_be_captured_in_a_hip_graph():
     got = bufs[0].cpu().numpy().view(np.uint16)
     for m in range(3):
         assert np.array_equal(got[starts[m]: starts[m] + vals[m]], tensors[m].reshape(-1))
+
+
+def layer_calls(tensors_by_expert, chunk, stream_values, max_len, stores=None):
+    """all experts of a layer in one call; returns the decoded arrays, expert by expert"""
+    import torch
+    flat = [w for ts in tensors_by_expert for w in ts]
+    with ThreadPoolExecutor(16) as ex:
+        blobs = list(ex.map(lambda w: zm.compress(w, chunk, stream_values, max_len)[0], flat))
+    per = len(tensors_by_expert[0])
+    layer = zm.Layer([blobs[i: i + per] for i in range(0, len(blobs), per)])
+    outs = [torch.full((w.size + 2 * GUARD,), GUARD_WORD, dtype=torch.int16, device="cuda") for w in flat]
+    shapes = zm.decode_launch_shapes([layer.tensor_info(e, m) for e in range(len(tensors_by_expert)) for m in range(per)],
+                                     zm.STORES_AUTO if stores is None else stores)
+    layer.decode(list(range(len(tensors_by_expert))), [o.data_ptr() + 2 * GUARD for o in outs],
+                 torch.cuda.current_stream().cuda_stream, zm.STORES_AUTO if stores is None else stores)
+    torch.cuda.synchronize()
+    res = []
+    for o in outs:
+        a = o.cpu().numpy().view(np.uint16)
+        assert np.all(a[:GUARD] == GUARD_WORD) and np.all(a[-GUARD:] == GUARD_WORD), "guard words overwritten"
+        res.append(a[GUARD:-GUARD])
+    layer.close()
+    return flat, blobs, res, shapes
+
+
+@pytest.mark.parametrize("n_tensors,max_len,stream_values,launches", [(48, 8, 4096, [48]), (49, 8, 4096, [49]), (240, 8, 1024, [240]),
+                                                                      (241, 8, 4096, [121, 120]), (60, 12, 4096, [60]),
+                                                                      (50, 8, 16384, [50])])
+def test_many_tensors_share_a_launch(n_tensors, max_len, stream_values, launches):
+    """blobs of few layouts and 64 Ki values or more travel in 16 bytes each, up to 240 of them in a launch"""
+    n = (1 << 16) + 4099
+    kinds = ["gauss", "rare_last"] if max_len == 8 else ["gauss"]
+    tensors = [[synth.special_tensor(kinds[i % len(kinds)], n + (i % 2), seed=i % 4)] for i in range(n_tensors)]
+    flat, blobs, got, shapes = layer_calls(tensors, 16384, stream_values, max_len)
+    assert [s.tensors for s in shapes] == launches
+    for i, (w, g) in enumerate(zip(flat, got)):
+        assert np.array_equal(g, w), i
+    assert np.array_equal(got[-1], zo.decode(blobs[-1]))
+
+
+@pytest.mark.parametrize("count,stores", [(7, zm.STORES_AUTO), (48, zm.STORES_STREAMING), (2, zm.STORES_CACHED)])
+def test_launches_numbered_through_tensors_of_very_different_lengths(count, stores):
+    """one long tensor beside short ones: the launch counts through the workgroups of all of them"""
+    lengths = [(9 << 20) + 5] + [1 + 1237 * i for i in range(count - 1)]
+    rng = np.random.default_rng(count)
+    order = rng.permutation(count)
+    tensors = [[synth.special_tensor("gauss", lengths[i], seed=3 + int(i))] for i in order]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, 8, stores)
+    assert len(shapes) == 1 and shapes[0].tensors == count
+    assert shapes[0].workgroups == sum(-(-(-(-lengths[i] // 4096)) // 2) for i in range(count)) if count > 2 else True
+    for w, g in zip(flat, got):
+        assert np.array_equal(g, w)
+
+
+@pytest.mark.parametrize("n", [4 * 4096 * 4, 8 * 16384 + 512, 16384 + 8191, 2 * 16384 + 3])
+@pytest.mark.parametrize("W", [1024, 8192, 16384])
+def test_raw_and_long_streams_in_groups_of_tiles(n, W):
+    """streams of one and of several groups of tiles, whole and cut off, coded and raw, under every store kind"""
+    tensors = [synth.special_tensor(k, n, seed=W + n) for k in ("gauss", "uniform_u16", "wide", "all_equal")]
+    blobs = [zm.compress(w, 32768, W, 12 if k == 2 else 8)[0] for k, w in enumerate(tensors)]
+    for stores in (None, zm.STORES_CACHED, zm.STORES_STREAMING):
+        for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
+            assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
+
+
+def test_outputs_between_the_store_kinds():
+    """a call that writes more than the 36 MiB that device-scope stores are used for, and less than the last-level cache"""
+    w = synth.special_tensor("gauss", (20 << 20) + 777, seed=9)
+    blob, _ = zm.compress(w, 16384, 4096)
+    assert np.array_equal(gpu_decode_tensors([blob])[0], w)

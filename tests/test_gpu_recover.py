@@ -41,6 +41,14 @@ def test_recover_launch_larger_than_half_the_last_level_cache():
     assert np.array_equal(gpu_recover(e, sm), zo.merge(e, sm))
 
 
+@pytest.mark.parametrize("n", [(5 << 20) - 1, 5 << 20, (5 << 20) + 1, (6 << 20) + 509])
+def test_recover_at_the_line_between_the_store_kinds(n):
+    rng = np.random.default_rng(n)
+    e = rng.integers(0, 256, n, dtype=np.uint8)
+    sm = rng.integers(0, 256, n, dtype=np.uint8)
+    assert np.array_equal(gpu_recover(e, sm), zo.merge(e, sm))
+
+
 def test_recover_all_pairs():
     e = np.repeat(np.arange(256, dtype=np.uint8), 256)
     sm = np.tile(np.arange(256, dtype=np.uint8), 256)
