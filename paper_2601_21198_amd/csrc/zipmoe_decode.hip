@@ -7,7 +7,7 @@
 // step of Sec. 3.3) without the exponents ever leaving registers.
 //
 // Work decomposition
-//   grid    x: workgroups of kWaves consecutive streams, y: tensor
+//   grid    x: workgroups of kWaves consecutive streams, y: tensor (or x through all tensors)
 //   wave    one stream: stream_values consecutive values, tiles of 512
 //   lane j  owns values 8j..8j+7 of every tile: one 64-bit load of
 //           sign-mantissa bytes and one 128-bit store of bf16 words per tile,
@@ -18,10 +18,9 @@
 //      lane bitstreams back to back) are requested with 128-bit loads (a4) -- first, because decoding can not
 //      start without them -- and go to LDS;
 //   2. the sign-mantissa bytes of the stream's tiles are requested: all eight of a group with non-temporal
-//      stores, the first four with ordinary stores (the others as tiles are finished);
-//   3. the decode table's first 256 entries go to LDS (a3) as 16-bit entries, code length in the low byte and
-//      symbol in the high byte, at a fixed LDS address, replicated to the full index width; longer codes
-//      are resolved from the tensor's full table in device memory;
+//      stores, the first four otherwise (the others as tiles are finished);
+//   3. the decode table goes to LDS (a3) as 16-bit entries, code length in the low byte and symbol in the high byte:
+//      256 entries for codes of at most eight bits; longer codes take 16 more for each beginning that they share;
 //   4. a wavefront prefix sum over the 64 lane-length bytes gives every lane the first and the last bit of
 //      its own bitstream (a6): what varies from lane to lane is where its input lies, its output positions
 //      are fixed;
@@ -75,7 +74,8 @@ template <int N, bool kFlat>
 struct Launch {
     uint32_t n_tasks;
     uint32_t stream_cap_words;   // LDS words reserved per wave for its stream
-    uint32_t pad[2];
+    uint32_t long_slots;         // long codes: shared eight-bit beginnings that the LDS table has room for
+    uint32_t pad;
     Task task[N];
     uint32_t first_block[kFlat ? N : 1];
 };
@@ -98,7 +98,8 @@ constexpr int kMaxPacked = 240, kMaxShapes = 4;
 struct PackedLaunch {
     uint32_t n_tasks;
     uint32_t stream_cap_words;
-    uint32_t pad[2];
+    uint32_t long_slots;
+    uint32_t pad;
     Packed task[kMaxPacked];
     Shape shape[kMaxShapes];
 };
@@ -128,6 +129,12 @@ __device__ __forceinline__ Task task_of(const PackedLaunch &P, uint32_t, uint32_
     uint16_t *out = reinterpret_cast<uint16_t *>(static_cast<uint64_t>(p.out) << 4 | static_cast<uint64_t>(p.high >> 20) << 36);
     return Task{blob + s.lut_offset, blob + s.sm_offset, blob + s.e_offset, reinterpret_cast<const uint64_t *>(blob + s.table_offset), out,
                 s.n_values, s.e_offset, static_cast<uint64_t>(p.e_units) * 256u, s.stream_values, s.streams_per_chunk, s.n_streams, s.code};
+}
+
+// LDS words of a table of long codes with `slots` shared beginnings (LongTable), a multiple of four
+__host__ __device__ constexpr uint32_t long_table_words(uint32_t slots)
+{
+    return (256u + ((1u << (ZM_MAX_CODE_LEN - 8)) - 1u) * slots + 7u) / 8u * 4u;
 }
 
 constexpr uint32_t kLaneBytes = 64;   // a stream opens with one length byte per lane
@@ -202,33 +209,45 @@ __device__ __forceinline__ uint4 recover8(uint2 e, uint2 sm)
     return w;
 }
 
-constexpr uint32_t kTableEntries = 256;   // the LDS table resolves the first eight bits of a code
-constexpr uint32_t kLongSlots = 16;       // eight-bit beginnings of longer codes that get a block of the second LDS table
-constexpr uint32_t kLongFlag = 0x80u;     // set in the length byte of a first-table entry whose code has more than eight bits
+constexpr uint32_t kTableEntries = 256;   // the LDS table of codes of at most eight bits resolves them all at once
+
+// The LDS table of a tensor whose codes have up to L = 9..12 bits.  Take the next L bits of a stream as a number v, first
+// bit highest.  The canonical code orders them by length: beginnings of eight bits that longer codes share come last.
+// With T beginnings that decide the code by themselves, the table holds one entry for each of these and then the
+// 2^(L-8) entries of every other beginning, and the entry of v is max(v >> (L-8), v - skip): up to T the first term is the
+// larger one, from there on the second, and they meet in T.  So a code of any length takes one LDS read and no branch.
+// (Before, the table held the 256 beginnings, and a wave in which one lane met a long code, one step in two, branched to
+// a second look-up; and a window was refilled after every two symbols.  One / two / four / eight experts of 1024 x 2048 x 3
+// with codes of up to 12 bits, streaming stores: 9.5 / 13.2 / 19.8 / 31.8 us then, 7.0 / 9.8 / 15.6 / 27.7 us now.)  At most half as many beginnings are shared as there are symbols: each by two codes or more.
+struct LongTable {
+    uint32_t shift;      // 32 - L
+    int32_t skip;        // (T << (L-8)) - T
+
+    // bits: what is left of a 32-bit window, first bit highest; zeros behind its last bit
+    __device__ __forceinline__ uint32_t index(uint32_t bits) const
+    {
+        const int32_t whole = static_cast<int32_t>(bits >> 24), late = static_cast<int32_t>(bits >> shift) - skip;
+        return static_cast<uint32_t>(whole > late ? whole : late);
+    }
+};
 
 // Lock-step decoder state of one lane (a5): two chains, one reading the lane's bitstream upwards from its
 // first bit (the first half of the lane's symbols, in order), one reading it downwards from its last bit (the
 // second half, last symbol first).
-// R = 4: every code has at most 8 bits, four symbols per 32-bit window.  R = 2: codes of up to ZM_MAX_CODE_LEN
-// bits, two symbols per window; the LDS table still resolves eight bits, and a lane that meets a longer code
-// (its table entry carries a length above 8: no code of at most 8 bits begins with these bits) takes its entry
-// from a second LDS table that holds, for each eight-bit beginning of longer codes, the 16 entries its further
-// bits select -- or, when a tensor has more than kLongSlots such beginnings, from the tensor's full decode table in
-// device memory.  Long codes are the rare ones by construction and sit together at the end of the code space.
-template <int R>
+// kLong = false: every code has at most eight bits, four symbols per 32-bit window.  kLong = true: codes of up to
+// ZM_MAX_CODE_LEN bits.  Two symbols per window are safe; four nearly always fit as well, since long codes are the rare
+// ones by construction: quad tries four, and its caller falls back to safe_quad where a lane's four have more than 32
+// bits between them.
+template <bool kLong>
 struct Decoder {
     const uint32_t *words;        // the stream as staged in LDS (length bytes included)
     uint32_t last_word;           // highest index a read may use
+    LongTable table;              // kLong only
     // upward chain: words q and q+1 of the bitstream, bits of lo already used (< 32 at the start of a round), index of word q+2
     uint32_t lo = 0, hi = 0, pos = 0, next = 0;
     // downward chain: dhi is the word that holds the bits just below the read position, of which its low dpos
     // bits (0..31) are still unread, dlo the word below it, dnext the index of the word below that
     uint32_t dlo = 0, dhi = 0, dpos = 0, dnext = 0;
-    // R = 2 only: the LDS table of the codes longer than eight bits (kLongSlots blocks of 16 entries, one block per
-    // eight-bit beginning that such codes share) and the bits it resolves beyond the first eight; 0 = the tensor has
-    // more such beginnings than blocks, and long codes are looked up in device memory
-    const uint16_t *sub = nullptr;
-    uint32_t sub_bits = 0;
 
     // first_bit, end_bit: where this lane's bitstream starts and ends, counted from the first payload bit
     __device__ __forceinline__ void start(uint32_t first_bit, uint32_t end_bit)
@@ -245,84 +264,82 @@ struct Decoder {
         dnext = w - 2u;
     }
 
-    // R = 2: the entry of a code longer than eight bits, whose first-table entry v carries kLongFlag.
-    __device__ __forceinline__ uint32_t long_code(const uint16_t *full_table, uint32_t max_len, uint32_t win, uint32_t acc,
-                                                  uint32_t v) const
+    // The entry (length | symbol << 8) of the code that starts `used & 31` bits into a window whose first bit is its
+    // lowest (short codes) or its highest (long codes).
+    __device__ __forceinline__ uint32_t look(const uint16_t *tab, uint32_t win, uint32_t used) const
     {
-        if (sub_bits) {
-            // the entry's high byte names the block of this beginning; the code's further bits index it
-            const uint32_t more = __builtin_amdgcn_ubfe(win, acc + 8u, 4) & ((1u << sub_bits) - 1u);
-            return sub[((v >> 8) & (kLongSlots - 1u)) * 16u + more];
-        }
-        const uint32_t full = full_table[(win >> (acc & 31u)) & ((1u << max_len) - 1u)];
-        return __builtin_amdgcn_perm(0u, full, 0x0c0c0001u);      // symbol | length << 8  ->  length | symbol << 8
+        if constexpr (kLong) return tab[table.index(win << (used & 31u))];
+        else return tab[__builtin_amdgcn_ubfe(win, used, 8)];
     }
 
-    // One round: R symbols of each chain.  up / down receive the R entries in the order read.
-    __device__ __forceinline__ void round(const uint16_t *tab, const uint16_t *full_table, uint32_t max_len,
-                                          uint32_t (&up)[R], uint32_t (&down)[R])
+    // One round: R symbols of each chain.  up / down receive the R entries in the order read; the result is the larger
+    // of the two chains' bits used, of which no more than 32 are real.
+    template <int R>
+    __device__ __forceinline__ uint32_t round(const uint16_t *tab, uint32_t (&up)[R], uint32_t (&down)[R])
     {
         // the words the chains take if the round crosses a word boundary: asked for now, used after the round
         const uint32_t fresh = words[min(next, last_word)];
         const uint32_t dfresh = words[min(dnext, last_word)];
         // R symbols out of one 32-bit window per chain.  acc sums the entries: its low byte is the bit offset of
-        // the next code in the window (at most 32), the bytes above hold a sum of symbols that nothing reads.
-        // The field extract takes the low five bits of acc as its offset; when they wrap (32 bits used) no
-        // further code is extracted.  The downward window is reversed so that its next bit is bit 0 too.
-        const uint32_t win = __builtin_amdgcn_alignbit(hi, lo, pos);
-        const uint32_t dwin = __builtin_bitreverse32(__builtin_amdgcn_alignbit(dhi, dlo, dpos));
+        // the next code in the window, the bytes above hold a sum of symbols that nothing reads.  Short codes: the field
+        // extract takes the low five bits of acc as its offset; when they wrap (32 bits used) no further code is
+        // extracted.  One chain's window is reversed, so that the next bit of both is the lowest or the highest.
+        uint32_t win = __builtin_amdgcn_alignbit(hi, lo, pos), dwin = __builtin_amdgcn_alignbit(dhi, dlo, dpos);
+        if constexpr (kLong) win = __builtin_bitreverse32(win);
+        else dwin = __builtin_bitreverse32(dwin);
         uint32_t acc = 0, dacc = 0;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            // the entries (length | symbol << 8) of the codes that start at bit (acc & 31) of the two windows
-            uint32_t v = tab[__builtin_amdgcn_ubfe(win, acc, 8)];
-            uint32_t dv = tab[__builtin_amdgcn_ubfe(dwin, dacc, 8)];
-            if constexpr (R == 2) {
-                // both look-ups are out before either is tested: one branch per step, rarely taken
-                if ((v | dv) & kLongFlag) {
-                    if (v & kLongFlag) v = long_code(full_table, max_len, win, acc, v);
-                    if (dv & kLongFlag) dv = long_code(full_table, max_len, dwin, dacc, dv);
-                }
-            }
+            const uint32_t v = look(tab, win, acc), dv = look(tab, dwin, dacc);
             up[k] = v;
             down[k] = dv;
             acc += v;
             dacc += dv;
         }
-        // written without branches so that (with short codes) a whole tile pair is one basic block
-        pos += acc & 0xffu;
+        // written without branches so that a whole tile pair is one basic block
+        const uint32_t used = acc & 0xffu, dused = dacc & 0xffu;
+        pos += used;
         const bool take = pos >= 32u;
         lo = take ? hi : lo;
         hi = take ? fresh : hi;
         next += take ? 1u : 0u;
         pos &= 31u;
-        const int32_t left = static_cast<int32_t>(dpos) - static_cast<int32_t>(dacc & 0xffu);    // -32..31
+        const int32_t left = static_cast<int32_t>(dpos) - static_cast<int32_t>(dused);    // -32..31
         const bool dtake = left < 0;
         dhi = dtake ? dlo : dhi;
         dlo = dtake ? dfresh : dlo;
         dnext -= dtake ? 1u : 0u;
         dpos = static_cast<uint32_t>(left) & 31u;
+        return max(used, dused);
     }
 
     // Four symbols of each chain: .x = the upward chain's, .y = the downward chain's, both packed in value order
-    // (byte 0 = the symbol with the lowest index), i.e. half a tile's exponent bytes for this lane each.
-    __device__ __forceinline__ uint2 quad(const uint16_t *tab, const uint16_t *full_table, uint32_t max_len)
+    // (byte 0 = the symbol with the lowest index), i.e. half a tile's exponent bytes for this lane each.  most: the
+    // largest number of bits that a round has used.
+    __device__ __forceinline__ uint2 quad(const uint16_t *tab, uint32_t &most)
     {
-        // byte 1 (the symbol) of each entry, packed with byte permutes (0x0c selects a zero byte)
-        if constexpr (R == 4) {
-            uint32_t up[4], down[4];
-            round(tab, full_table, max_len, up, down);
-            const uint32_t u01 = __builtin_amdgcn_perm(up[1], up[0], 0x0c0c0501u), u23 = __builtin_amdgcn_perm(up[3], up[2], 0x0c0c0501u);
-            const uint32_t d01 = __builtin_amdgcn_perm(down[2], down[3], 0x0c0c0501u), d23 = __builtin_amdgcn_perm(down[0], down[1], 0x0c0c0501u);
-            return make_uint2(__builtin_amdgcn_perm(u23, u01, 0x05040100u), __builtin_amdgcn_perm(d23, d01, 0x05040100u));
-        } else {
+        uint32_t up[4], down[4];
+        most = max(most, round(tab, up, down));
+        return make_uint2(pack(up[0], up[1], up[2], up[3]), pack(down[3], down[2], down[1], down[0]));
+    }
+
+    __device__ __forceinline__ uint2 safe_quad(const uint16_t *tab)
+    {
+        if constexpr (kLong) {
             uint32_t ua[2], da[2], ub[2], db[2];
-            round(tab, full_table, max_len, ua, da);
-            round(tab, full_table, max_len, ub, db);
-            const uint32_t u01 = __builtin_amdgcn_perm(ua[1], ua[0], 0x0c0c0501u), u23 = __builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0501u);
-            const uint32_t d01 = __builtin_amdgcn_perm(db[0], db[1], 0x0c0c0501u), d23 = __builtin_amdgcn_perm(da[0], da[1], 0x0c0c0501u);
-            return make_uint2(__builtin_amdgcn_perm(u23, u01, 0x05040100u), __builtin_amdgcn_perm(d23, d01, 0x05040100u));
+            round(tab, ua, da);
+            round(tab, ub, db);
+            return make_uint2(pack(ua[0], ua[1], ub[0], ub[1]), pack(db[1], db[0], da[1], da[0]));
+        } else {
+            uint32_t most = 0;
+            return quad(tab, most);
         }
+    }
+
+    // byte 1 (the symbol) of four entries, packed with byte permutes (0x0c selects a zero byte)
+    static __device__ __forceinline__ uint32_t pack(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+    {
+        return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0501u), __builtin_amdgcn_perm(b, a, 0x0c0c0501u), 0x05040100u);
     }
 };
 
@@ -362,18 +379,27 @@ constexpr int kPairs = kGroup / 2;
 // In longer ones the next group's bytes are asked for when a group is done: they come while its first pair is decoded.
 // (Asking for them pair by pair, two or four pairs ahead, was 10 % slower: a wave waits for each such load behind its
 // own stores.)
-template <int R, int kAhead, bool kOneGroup, Stores kStores>
-__device__ __forceinline__ void decode_stream(Decoder<R> &dec, const uint16_t *tab, const uint16_t *full_table, uint32_t max_len,
-                                              const Sink<kStores> &out, const ByteSource &sm, uint32_t tiles,
-                                              uint2 (&up)[kPairs], uint2 (&down)[kPairs])
+// Returns the first pair that is not done: with long codes, a pair in which a lane's four symbols had more bits than a
+// window is left alone, with the decoder as it was in front of it.
+template <bool kLong, int kAhead, bool kOneGroup, Stores kStores>
+__device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+                                                  uint32_t tiles, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
     for (uint32_t first = 0;;) {
 #pragma unroll
         for (int i = 0; i < kPairs; ++i) {
             const uint32_t lo = first + i, hi = tiles - 1u - lo;
+            const Decoder<kLong> before = dec;
+            uint32_t most = 0;
             // a tile's eight symbols come in two quads: the upward chain gives values 0..3 first, the
             // downward chain values 4..7 first
-            const uint2 a = dec.quad(tab, full_table, max_len), b = dec.quad(tab, full_table, max_len);
+            const uint2 a = dec.quad(tab, most), b = dec.quad(tab, most);
+            if constexpr (kLong) {
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(most > 32u) != 0, 0)) {
+                    dec = before;
+                    return lo;
+                }
+            }
             out.store(lo, recover8(make_uint2(a.x, b.x), up[i]));
             out.store(hi, recover8(make_uint2(b.y, a.y), down[i]));
             if (i + kAhead < kPairs) {
@@ -382,7 +408,7 @@ __device__ __forceinline__ void decode_stream(Decoder<R> &dec, const uint16_t *t
             }
         }
         first += kPairs;
-        if (kOneGroup || 2u * first >= tiles) return;
+        if (kOneGroup || 2u * first >= tiles) return first;
 #pragma unroll
         for (int i = 0; i < kPairs; ++i) {
             up[i] = sm.load(first + i);
@@ -391,23 +417,23 @@ __device__ __forceinline__ void decode_stream(Decoder<R> &dec, const uint16_t *t
     }
 }
 
-// Any other stream: short ones, last ones.  With an odd number of tiles the last pair is the middle tile alone, whose
-// low half comes from the upward and whose high half from the downward chain.  The caller has asked for two pairs; kept
-// rolled, since the unrolled loop with its partial tiles costs the whole kernel 20 registers.
-template <int R, Stores kStores>
-__device__ __forceinline__ void decode_any_stream(Decoder<R> &dec, const uint16_t *tab, const uint16_t *full_table, uint32_t max_len,
-                                                  const Sink<kStores> &out, const ByteSource &sm, uint32_t tiles, int32_t mine,
-                                                  uint2 (&up)[kPairs], uint2 (&down)[kPairs])
+// Any stream, from pair `lo` on: short ones, last ones, ones dense in long codes.  With an odd number of tiles the last
+// pair is the middle tile alone, whose low half comes from the upward and whose high half from the downward chain.  The
+// caller has asked for two pairs (up[0], up[1]); kept rolled, since the unrolled loop with its partial tiles costs the
+// whole kernel 20 registers.
+template <bool kLong, Stores kStores>
+__device__ __forceinline__ void decode_any_stream(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+                                                  uint32_t lo, uint32_t tiles, int32_t mine, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
 #pragma unroll 1
-    for (uint32_t lo = 0;; ++lo) {
+    for (;; ++lo) {
         const uint32_t hi = tiles - 1u - lo;
-        const uint2 a = dec.quad(tab, full_table, max_len);
+        const uint2 a = dec.safe_quad(tab);
         if (lo == hi) {
             finish_tile(out, lo, make_uint2(a.x, a.y), up[0], mine);
             return;
         }
-        const uint2 b = dec.quad(tab, full_table, max_len);
+        const uint2 b = dec.safe_quad(tab);
         finish_tile(out, lo, make_uint2(a.x, b.x), up[0], mine);
         finish_tile(out, hi, make_uint2(b.y, a.y), down[0], mine);
         if (lo + 1u >= hi) return;
@@ -432,26 +458,23 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
     }
 }
 
-// R: symbols per round; kWaves: waves (streams) per workgroup; kStores: how the output is written
-template <int R, int kWaves, Stores kStores, class Args>
+// kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is written
+template <bool kLong, int kWaves, Stores kStores, class Args>
 __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
 {
-    // The decode table of the workgroup's tensor for the first eight bits of a code, at a fixed LDS address:
-    // one 16-bit read gives a code's length and its symbol.  (Two byte tables, one read each, were 2-4 % slower:
-    // twice the LDS instructions, whose random accesses collide on banks.)
-    __shared__ __align__(16) uint16_t tab[kTableEntries];
-    // second table for codes longer than eight bits (R = 2): kLongSlots blocks of 16 entries, and the eight-bit
-    // beginning each block belongs to
-    __shared__ __align__(16) uint16_t sub[R == 2 ? kLongSlots * 16 : 4];
-    __shared__ uint16_t long_prefix[R == 2 ? kLongSlots : 2];
-    extern __shared__ __align__(16) uint32_t stream_lds[];
+    // The decode table of the workgroup's tensor, at a fixed LDS address: one 16-bit read gives a code's length and its
+    // symbol.  (Two byte tables, one read each, were 2-4 % slower: twice the LDS instructions, whose random accesses
+    // collide on banks.)  That of long codes lies in front of the streams, as long as the launch's widest tensor needs.
+    __shared__ __align__(16) uint16_t short_tab[kLong ? 8 : kTableEntries];
+    extern __shared__ __align__(16) uint32_t dynamic_lds[];
+    uint16_t *const tab = kLong ? reinterpret_cast<uint16_t *>(dynamic_lds) : short_tab;
 
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     uint32_t block;
     const Task t = task_of(P, lane, block);
-    uint32_t *words = stream_lds + wave * P.stream_cap_words;
+    uint32_t *words = dynamic_lds + (kLong ? long_table_words(P.long_slots) : 0u) + wave * P.stream_cap_words;
     const uint32_t W = t.stream_values;
     const uint32_t max_len = t.code & 0xffu, quantum = t.code >> 8;
     const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;     // bytes of a chunk-table entry
@@ -470,6 +493,7 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
 
     uint4 held_a = make_uint4(0u, 0u, 0u, 0u), held_b = held_a;   // first 2 KiB of the stream
     uint32_t n_held = 0;
+    bool dense = false;          // long codes: four symbols of a lane are likely to have more bits than a window
     if (active) {
         const uint32_t c = g / t.streams_per_chunk, s = g % t.streams_per_chunk;
         // one read of the chunk's table entry gives the chunk's place and mode and this stream's extent
@@ -490,6 +514,7 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
                 active = false;
             } else {
                 const uint32_t nvec = min((o1 - o0) >> 4, P.stream_cap_words >> 2);
+                if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
                 const uint4 *src = reinterpret_cast<const uint4 *>(t.echunks + at + o0);
                 uint4 *dst = reinterpret_cast<uint4 *>(words);
                 n_held = min(nvec, 128u);
@@ -508,9 +533,8 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     // the requests of the thousands of waves that start together are spread out and everyone's first tiles
     // arrive sooner.  A wave waits for such a later load behind its own earlier stores, though, and non-temporal
     // stores take long to be acknowledged: with them all eight tiles of a group are asked for up front.  So they are
-    // with long codes, whose look-ups in device memory would wait behind the later requests as well, and in streams of
-    // several groups, of which fewer start together.
-    constexpr int kAhead = (kStores == kStreaming || R == 2) ? kPairs : 2;
+    // in streams of several groups, of which fewer start together.
+    constexpr int kAhead = kStores == kStreaming ? kPairs : 2;
     const bool coded = mode == ZM_MODE_CODED;
     const bool whole = sn % (kGroup * kTile) == 0;
     uint2 up[kPairs], down[kPairs];
@@ -525,56 +549,52 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
         }
     }
 
-    // a3: decode table -> LDS, its first 256 entries with the two bytes of an entry swapped (length low),
-    // replicated over the index bits above the longest code.  Four entries per lane, all loads issued before the
-    // first is used.  Every wave of the workgroup writes the same bytes (LDS word writes are atomic), so a wave may
-    // read as soon as its own writes are done: no workgroup barrier.
-    uint32_t sub_bits = 0;
+    // a3: decode table -> LDS with the two bytes of an entry swapped (length low).  Every wave of the workgroup writes the
+    // same bytes (LDS word writes are atomic), so a wave may read as soon as its own writes are done: no workgroup barrier.
+    LongTable table{0u, 0};
     {
         const uint16_t *src = reinterpret_cast<const uint16_t *>(t.lut);
         const uint32_t mask = (1u << max_len) - 1u;
         const uint32_t i = 4u * lane;
-        uint32_t a = src[i & mask], b = src[(i + 1) & mask], c = src[(i + 2) & mask], d = src[(i + 3) & mask];
-        if constexpr (R == 2) {
-            // Entries with a length above eight mark the eight-bit beginnings of longer codes.  They are numbered in
-            // index order; if there are at most kLongSlots of them, entry number s gets block s of the second table
-            // (its symbol byte is replaced by s) and the block is filled with the 2^(max_len - 8) entries of the
-            // full table that share these eight bits.
-            const uint32_t la = (a >> 8) > 8u, lb = (b >> 8) > 8u, lc = (c >> 8) > 8u, ld = (d >> 8) > 8u;
-            const uint64_t ma = __builtin_amdgcn_ballot_w64(la), mb = __builtin_amdgcn_ballot_w64(lb),
-                           mc = __builtin_amdgcn_ballot_w64(lc), md = __builtin_amdgcn_ballot_w64(ld);
-            const uint32_t n_long = __builtin_popcountll(ma) + __builtin_popcountll(mb) + __builtin_popcountll(mc) + __builtin_popcountll(md);
-            // every such entry is flagged in its length byte (lengths stay below 16)
-            a |= la ? kLongFlag << 8 : 0u; b |= lb ? kLongFlag << 8 : 0u; c |= lc ? kLongFlag << 8 : 0u; d |= ld ? kLongFlag << 8 : 0u;
-            if (n_long != 0 && n_long <= kLongSlots && max_len > 8u) {
-                const uint64_t below = (1ull << lane) - 1ull;
-                const uint32_t sa = __builtin_popcountll(ma & below) + __builtin_popcountll(mb & below) +
-                                    __builtin_popcountll(mc & below) + __builtin_popcountll(md & below);
-                const uint32_t sb = sa + la, sc = sb + lb, sd = sc + lc;
-                if (la) { long_prefix[sa] = static_cast<uint16_t>(i); a = (a & 0xff00u) | sa; }
-                if (lb) { long_prefix[sb] = static_cast<uint16_t>(i + 1u); b = (b & 0xff00u) | sb; }
-                if (lc) { long_prefix[sc] = static_cast<uint16_t>(i + 2u); c = (c & 0xff00u) | sc; }
-                if (ld) { long_prefix[sd] = static_cast<uint16_t>(i + 3u); d = (d & 0xff00u) | sd; }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-                sub_bits = max_len - 8u;
-                // lane l fills entries 4l..4l+3 of the second table: block (4l)/16, further bits (4l)%16 + 0..3
-                const uint32_t block = lane >> 2, first = (lane & 3u) * 4u;
-                uint32_t e[4];
+        if constexpr (!kLong) {
+            uint2 e;                     // entries 4 * lane .. + 3, replicated over the index bits above the longest code
+            if (max_len == 8u) {
+                e = reinterpret_cast<const uint2 *>(src)[lane];
+            } else {
+                e = make_uint2(src[i & mask] | static_cast<uint32_t>(src[(i + 1) & mask]) << 16,
+                               src[(i + 2) & mask] | static_cast<uint32_t>(src[(i + 3) & mask]) << 16);
+            }
+            reinterpret_cast<uint2 *>(tab)[lane] = make_uint2(__builtin_amdgcn_perm(e.x, e.x, 0x02030001u), __builtin_amdgcn_perm(e.y, e.y, 0x02030001u));
+        } else {
+            // The blob's table is indexed with a code's first bit lowest, so the number v of LongTable has to be reversed;
+            // its first 256 entries are those of the eight-bit beginnings, with a length above eight at shared ones.
+            // The last 64 values of v belong to long codes if any are; they are asked for before it is known how many
+            // more there are, which on Gaussian weights is none.
+            const uint32_t more = max_len - 8u;
+            const uint2 e = reinterpret_cast<const uint2 *>(src)[lane];
+            const uint32_t tail = src[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
+            uint32_t n_shared = 0;
 #pragma unroll
-                for (uint32_t j = 0; j < 4; ++j) {
-                    const uint32_t more = first + j;
-                    e[j] = 0u;
-                    if (block < n_long && more < (1u << sub_bits))
-                        e[j] = src[(static_cast<uint32_t>(long_prefix[block]) + (more << 8)) & mask];
-                }
-                const uint32_t e01 = e[0] | (e[1] << 16), e23 = e[2] | (e[3] << 16);
-                reinterpret_cast<uint2 *>(sub)[lane] = make_uint2(__builtin_amdgcn_perm(e01, e01, 0x02030001u), __builtin_amdgcn_perm(e23, e23, 0x02030001u));
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t v = (k & 2 ? e.y : e.x) >> (16 * (k & 1)) & 0xffffu;
+                n_shared += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64((v >> 8) > 8u)));
+            }
+            n_shared = min(n_shared, P.long_slots);              // what the table has room for
+            const uint32_t whole_codes = kTableEntries - n_shared, late = n_shared << more;
+            table.shift = 32u - max_len;
+            table.skip = static_cast<int32_t>((whole_codes << more) - whole_codes);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t v = (k & 2 ? e.y : e.x) >> (16 * (k & 1)) & 0xffffu;
+                const uint32_t at = __builtin_bitreverse32(i + k) >> 24;
+                if (at < whole_codes) tab[at] = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, v, 0x0c0c0001u));
+            }
+            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, tail, 0x0c0c0001u));
+            for (uint32_t k = lane; k + 64u < late; k += 64u) {
+                const uint32_t v = src[__builtin_bitreverse32((whole_codes << more) + k) >> (32u - max_len)];
+                tab[whole_codes + k] = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, v, 0x0c0c0001u));
             }
         }
-        const uint32_t ab = a | (b << 16), cd = c | (d << 16);
-        reinterpret_cast<uint2 *>(tab)[lane] = make_uint2(__builtin_amdgcn_perm(ab, ab, 0x02030001u), __builtin_amdgcn_perm(cd, cd, 0x02030001u));
     }
 
     if (n_held) {
@@ -590,10 +610,9 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
 
     const Sink<kStores> out(t.out + v0, sn, lane);
 
-    const uint16_t *full_table = reinterpret_cast<const uint16_t *>(t.lut);
-    Decoder<R> dec;
+    Decoder<kLong> dec;
     dec.words = words; dec.last_word = P.stream_cap_words - 1u;
-    dec.sub = sub; dec.sub_bits = sub_bits;
+    dec.table = table;
     if (coded) {
         // a6: this lane's bitstream has 8 * tiles + quantum * (its length byte) bits and starts where
         // the bitstreams of the lanes below it end
@@ -603,10 +622,19 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
         dec.start(first, first + bits);
     }
 
-    if (!coded) merge_raw_stream(out, ByteSource(raw, sn, lane), sm, tiles, mine);
-    else if (sn == kGroup * kTile) decode_stream<R, kAhead, true>(dec, tab, full_table, max_len, out, sm, tiles, up, down);
-    else if (whole) decode_stream<R, kPairs, false>(dec, tab, full_table, max_len, out, sm, tiles, up, down);
-    else decode_any_stream(dec, tab, full_table, max_len, out, sm, tiles, mine, up, down);
+    if (!coded) {
+        merge_raw_stream(out, ByteSource(raw, sn, lane), sm, tiles, mine);
+        return;
+    }
+    uint32_t done = 0;
+    if (whole && !dense) {
+        done = tiles == kGroup ? decode_stream<kLong, kAhead, true>(dec, tab, out, sm, tiles, up, down)
+                               : decode_stream<kLong, kPairs, false>(dec, tab, out, sm, tiles, up, down);
+        if (!kLong || 2u * done >= tiles) return;
+        up[0] = sm.load(done); down[0] = sm.load(tiles - 1u - done);
+        up[1] = sm.load(done + 1u); down[1] = sm.load(tiles - 2u - done);
+    }
+    decode_any_stream(dec, tab, out, sm, done, tiles, mine, up, down);
 }
 
 
@@ -661,10 +689,13 @@ inline size_t stream_cap_words(uint32_t stream_values, uint32_t max_len_bound, u
     return ((bytes + 15) & ~static_cast<size_t>(15)) / 4;
 }
 
+// Streams share a workgroup's LDS up to this size; one that is longer by itself is refused.  A table of long codes
+// (0.5 to 4.3 KB) comes on top, so that the line does not depend on the tensor's symbols.
 constexpr size_t kLdsLimit = 64 * 1024;
-// LDS a workgroup holds beside its streams: the first table, and with long codes the second one and its index
-template <int R>
-constexpr size_t kStaticLds = 2 * kTableEntries + (R == 2 ? 2 * kLongSlots * 16 + 2 * kLongSlots : 0);
+template <bool kLong>
+constexpr size_t kBesideStreams = kLong ? 1056 : 2 * kTableEntries;
+template <bool kLong>
+constexpr size_t kStaticLds = kLong ? 16 : 2 * kTableEntries;
 constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cache
 // A launch that writes no more than the L2 caches hold (eight of 4 MiB) would leave nearly all of it dirty there and end
 // with writing it back; device-scope stores spread that over the launch.  Experts of 1024 x 2048 x 3 (12.6 MB of bf16),
@@ -695,28 +726,28 @@ struct Plan {
     Recorder *rec;
 };
 
-template <int R, int kWaves, Stores kStores, class Args>
+template <bool kLong, int kWaves, Stores kStores, class Args>
 int launch_kernel(const Args &args, const Plan &p)
 {
     void *argv[] = {const_cast<Args *>(&args)};
-    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<R, kWaves, kStores, Args>);
+    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, Args>);
     // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
     return hipLaunchKernel(fn, p.grid, dim3(64 * kWaves), argv, p.lds, p.stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
 
-template <int R, int kWaves, class Args>
+template <bool kLong, int kWaves, class Args>
 int launch_args(const Args &args, const Plan &p)
 {
     const bool streaming = p.stores == ZM_STORES_STREAMING || (p.stores == ZM_STORES_AUTO && p.out_bytes > kLastLevelCacheBytes);
     if (p.rec) {
         if (p.rec->n < p.rec->cap)
-            p.rec->out[p.rec->n] = zm_launch_shape{static_cast<uint32_t>(R), static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, p.grid.x,
-                                                   args.n_tasks, static_cast<uint32_t>(p.lds + kStaticLds<R>)};
+            p.rec->out[p.rec->n] = zm_launch_shape{kLong ? 2u : 4u, static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, p.grid.x,
+                                                   args.n_tasks, static_cast<uint32_t>(p.lds + kStaticLds<kLong>)};
         ++p.rec->n;
         return ZM_OK;
     }
-    if (streaming) return launch_kernel<R, kWaves, kStreaming>(args, p);
-    return p.out_bytes <= kThroughBytes ? launch_kernel<R, kWaves, kThrough>(args, p) : launch_kernel<R, kWaves, kOrdinary>(args, p);
+    if (streaming) return launch_kernel<kLong, kWaves, kStreaming>(args, p);
+    return p.out_bytes <= kThroughBytes ? launch_kernel<kLong, kWaves, kThrough>(args, p) : launch_kernel<kLong, kWaves, kOrdinary>(args, p);
 }
 
 // Whether a launch numbers its workgroups through all tensors instead of giving every tensor as many as the largest has.
@@ -730,12 +761,12 @@ bool number_through(uint64_t useful, uint64_t started)
     return idle > 2048 || (idle > 1024 && idle > useful);
 }
 
-template <int R, int kWaves, int N>
+template <bool kLong, int kWaves, int N>
 int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream, Recorder *rec)
 {
-    const size_t lds = 4 * kWaves * cap;
-    if (lds + kStaticLds<R> > kLdsLimit) {
-        if constexpr (kWaves > 1) return launch_tasks<R, kWaves / 2>(L, cap, stores, stream, rec);
+    const size_t streams = 4 * kWaves * cap, lds = streams + (kLong ? 4 * long_table_words(L.long_slots) : 0);   // dynamic part
+    if (streams + kBesideStreams<kLong> > kLdsLimit) {
+        if constexpr (kWaves > 1) return launch_tasks<kLong, kWaves / 2>(L, cap, stores, stream, rec);
         else return ZM_E_ARG;                   // stream too long to stage in LDS
     }
     uint32_t blocks = 0;            // of the largest tensor
@@ -749,18 +780,18 @@ int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream,
     }
     if (!blocks) return ZM_OK;
     if (total <= 0x7FFFFFFFull && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
-        return launch_args<R, kWaves>(L, Plan{dim3(static_cast<uint32_t>(total)), lds, out_bytes, stores, stream, rec});
+        return launch_args<kLong, kWaves>(L, Plan{dim3(static_cast<uint32_t>(total)), lds, out_bytes, stores, stream, rec});
     // without the workgroup numbers the arguments are the same up to the end of the tasks
     using Rows = Launch<N, false>;
     using Through = Launch<N, true>;
     static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
-    return launch_args<R, kWaves>(reinterpret_cast<const Rows &>(L), Plan{dim3(blocks, L.n_tasks), lds, out_bytes, stores, stream, rec});
+    return launch_args<kLong, kWaves>(reinterpret_cast<const Rows &>(L), Plan{dim3(blocks, L.n_tasks), lds, out_bytes, stores, stream, rec});
 }
 
 // Collects the tensors of one round length and launches them.
-template <int R>
+template <bool kLong>
 struct Group {
-    static constexpr uint32_t kLenBound = R == 4 ? 8 : ZM_MAX_CODE_LEN;
+    static constexpr uint32_t kLenBound = kLong ? ZM_MAX_CODE_LEN : 8;
     int n = 0;                        // tensors to come, all launches together
     uint64_t n_values = 0;            // of theirs
     bool packable = true;             // every one has the layout of a blob and an address that fits a Packed
@@ -776,9 +807,11 @@ struct Group {
 
     // LDS words per wave that tensors of these streams need
     struct Cap {
-        uint32_t max_stream = 0, max_quantum = 1;
-        void see(const Task &t)
+        uint32_t max_stream = 0, max_quantum = 1, long_slots = 0;
+        void see(const Task &t, const zm_tensor_info &ti)
         {
+            const uint32_t slots = (ti.n_present < kTableEntries ? ti.n_present : kTableEntries) / 2;
+            long_slots = long_slots > slots ? long_slots : slots;
             max_stream = max_stream > t.stream_values ? max_stream : t.stream_values;
             max_quantum = max_quantum > (t.code >> 8) ? max_quantum : (t.code >> 8);
         }
@@ -792,7 +825,7 @@ struct Group {
         ++n;
         if (!many) return;
         n_values += t.n_values;
-        cap_of_all.see(t);
+        cap_of_all.see(t, ti);
         uint32_t k;
         packable = packable && pack(t, ti, k).high != kUnpackable;
     }
@@ -825,7 +858,7 @@ struct Group {
     {
         if (n <= kFewTasks) return launch_wide<kFewTasks>(next, stores, stream, rec);
         if (n > kMaxTasks && packable && n_values >= kPackedValues * static_cast<uint64_t>(n) &&
-            8 * cap_of_all.words() + kStaticLds<R> <= kLdsLimit) return launch_packed(next, stores, stream, rec);
+            8 * cap_of_all.words() + kBesideStreams<kLong> <= kLdsLimit) return launch_packed(next, stores, stream, rec);
         return launch_wide<kMaxTasks>(next, stores, stream, rec);
     }
 
@@ -836,9 +869,13 @@ struct Group {
         for (int left = n; left > 0; left -= static_cast<int>(L.n_tasks)) {
             L.n_tasks = static_cast<uint32_t>(left < N ? left : N);
             Cap cap;
-            for (uint32_t k = 0; k < L.n_tasks; ++k) { next(L.task[k]); cap.see(L.task[k]); }
+            for (uint32_t k = 0; k < L.n_tasks; ++k) {
+                const zm_tensor_info &ti = next(L.task[k]);
+                cap.see(L.task[k], ti);
+            }
+            L.long_slots = cap.long_slots;
             L.stream_cap_words = static_cast<uint32_t>(cap.words());
-            const int rc = launch_tasks<R, 2>(L, cap.words(), stores, stream, rec);
+            const int rc = launch_tasks<kLong, 2>(L, cap.words(), stores, stream, rec);
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;
@@ -856,6 +893,7 @@ struct Group {
         const size_t cap = cap_of_all.words();
         PackedLaunch L;
         L.stream_cap_words = static_cast<uint32_t>(cap);
+        L.long_slots = cap_of_all.long_slots;
         for (uint32_t k = 0; k < n_shapes; ++k) L.shape[k] = shape[k];
         const int launches = (n + kMaxPacked - 1) / kMaxPacked, each = (n + launches - 1) / launches;
         for (int left = n; left > 0; left -= static_cast<int>(L.n_tasks)) {
@@ -870,7 +908,7 @@ struct Group {
                 blocks = b > blocks ? b : blocks;
                 out_bytes += 2 * t.n_values;
             }
-            const int rc = launch_args<R, 2>(L, Plan{dim3(blocks, L.n_tasks), 8 * cap, out_bytes, stores, stream, rec});
+            const int rc = launch_args<kLong, 2>(L, Plan{dim3(blocks, L.n_tasks), 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, stores, stream, rec});
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;
@@ -917,8 +955,8 @@ int decode_call(int n_tensors, Describe describe, Info info, int stores, hipStre
 {
     if (stores != ZM_STORES_AUTO && stores != ZM_STORES_CACHED && stores != ZM_STORES_STREAMING) return ZM_E_ARG;
     // first pass: every tensor is checked before anything is launched
-    Group<4> short_codes;
-    Group<2> long_codes;
+    Group<false> short_codes;
+    Group<true> long_codes;
     for (int i = 0; i < n_tensors; ++i) {
         Task t; bool skip;
         const int rc = describe(i, t, skip);

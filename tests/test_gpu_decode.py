@@ -475,3 +475,61 @@ def test_outputs_between_the_store_kinds():
     w = synth.special_tensor("gauss", (20 << 20) + 777, seed=9)
     blob, _ = zm.compress(w, 16384, 4096)
     assert np.array_equal(gpu_decode_tensors([blob])[0], w)
+
+
+def bursts(n, n_rare, burst, gap, seed):
+    """exponents of short codes, with runs of `burst` rare ones every `gap` values: few bits a value, but four codes in a
+    row that do not fit a 32-bit window"""
+    rng = np.random.default_rng(seed)
+    e = (120 - rng.geometric(0.6, n).clip(1, 9)).astype(np.uint16)
+    for at in range(seed % 7, n, gap):
+        m = min(burst, n - at)
+        e[at: at + m] = 121 + rng.integers(0, n_rare, m)
+    return (e << 7) | rng.integers(0, 128, n, dtype=np.uint16)
+
+
+@pytest.mark.parametrize("W", [512, 2048, 4096, 16384])
+@pytest.mark.parametrize("n_rare,burst,gap", [(100, 8, 400), (100, 6, 4000), (100, 300, 20000), (60, 12, 300), (120, 1, 50)])
+def test_long_codes_in_a_row(W, n_rare, burst, gap):
+    """streams whose four-symbol windows overflow in some rounds, from the first pair of tiles to the last"""
+    tensors, blobs = [], []
+    for k, max_len in enumerate((9, 10, 11, 12)):
+        w = bursts(3 * 16384 + 4096 * k + 77, n_rare, burst, gap, 5 + k)
+        while (1 << max_len) < np.unique(zo.split(w)[0]).size:
+            max_len += 1
+        tensors.append(w)
+        blobs.append(zm.compress(w, 16384, W, max_len)[0])
+        assert zm.blob_info(blobs[-1][:384]).max_len > 8
+        assert blobs[-1].size < 0.78 * 2 * w.size           # few enough bits a value for the four-symbol rounds
+    for stores in (None, zm.STORES_STREAMING):
+        for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
+            assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
+
+
+@pytest.mark.parametrize("n_symbols", [3, 9, 17, 64, 129, 200, 256])
+def test_long_code_tables_of_every_width(n_symbols):
+    """exponent counts that fall off geometrically or not at all: from one shared eight-bit beginning to all that fit"""
+    rng = np.random.default_rng(n_symbols)
+    tensors, blobs = [], []
+    for max_len in (9, 10, 11, 12):
+        for p in (0.55, 0.85, 0.98):
+            if (1 << max_len) < n_symbols:
+                continue
+            e = np.minimum(rng.geometric(1 - p, 40000) - 1, n_symbols - 1).astype(np.uint16)
+            e[:n_symbols] = np.arange(n_symbols)
+            w = (e << 7) | rng.integers(0, 128, e.size, dtype=np.uint16)
+            tensors.append(w)
+            blobs.append(zm.compress(w, 16384, 4096, max_len)[0])
+    for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs)):
+        assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
+
+
+def test_longest_stream_of_long_codes_beside_the_widest_table():
+    """the longest stream that one wave can stage, of a tensor with every exponent: its table comes on top"""
+    w = synth.special_tensor("many_long", 40960 + 700, seed=2)
+    blob, _ = zm.compress(w, 40960, 40960, 12)
+    assert zm.blob_info(blob[:384]).max_len > 8
+    assert np.array_equal(gpu_decode_tensors([blob])[0], w)
+    big, _ = zm.compress(synth.special_tensor("many_long", 45056, seed=4), 45056, 45056, 12)
+    with pytest.raises(zm.ZipMoEError):
+        gpu_decode_tensors([big])
