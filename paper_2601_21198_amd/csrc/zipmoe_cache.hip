@@ -17,7 +17,8 @@
 //
 // On MI355X the tier below HBM is (pinned) host memory.  Copies run on a stream
 // of their own and overlap the decode of the experts that need none; the decode
-// itself is zm_decode_tensors.
+// itself is zm_decode_tensors.  Where the host memory is mapped for the device, as
+// pinned memory is, one kernel fetches all missing parts of a call.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -96,6 +97,63 @@ bool config_ok(const zm_cache_config *c)
     return true;
 }
 
+// ---- host to device ----
+
+// What one launch fetches: parts in mapped host memory and their places in the arena, in vectors of 16 bytes.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct Part {
+    const u32x4 *src;
+    u32x4 *dst;
+    uint64_t n;
+};
+constexpr int kMaxParts = 128;
+struct Parts {
+    uint32_t n_parts;
+    uint32_t pad;
+    Part part[kMaxParts];
+};
+static_assert(sizeof(Parts) <= 4096, "kernel arguments must stay under 4 KiB");
+
+// Bound by the host link.  Sixty-four workgroups with one vector per lane on its way fill it; more of them, or more
+// vectors per lane, slow it down, and they leave the other compute units to the decode that runs beside.  From pinned
+// memory, GB/s of this kernel / of one asynchronous copy: 0.25 MB 34 / 19, 2.2 MB 53 / 47, 6.3 MB 55 / 53, 34 MB 57 / 56; and
+// the parts of a call follow each other without the 10 us that every copy costs beside its bytes.
+constexpr uint32_t kFetchBlocks = 64;
+
+__global__ void __launch_bounds__(256) zm_cache_fetch_kernel(const Parts P)
+{
+    for (uint32_t k = 0; k < P.n_parts; ++k) {
+        const Part p = P.part[k];
+        for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * 256u + threadIdx.x; i < p.n; i += kFetchBlocks * 256u) p.dst[i] = p.src[i];
+    }
+}
+
+int fetch_parts(Parts &parts, hipStream_t stream)
+{
+    if (parts.n_parts == 0) return ZM_OK;
+    void *args[] = {&parts};
+    const hipError_t rc = hipLaunchKernel(reinterpret_cast<const void *>(&zm_cache_fetch_kernel), dim3(kFetchBlocks), dim3(256), args, 0, stream);
+    parts.n_parts = 0;
+    return rc == hipSuccess ? ZM_OK : ZM_E_HIP;
+}
+
+// Device address of `bytes` bytes of host memory, or null if they are not all mapped for the current device (pageable
+// memory, for which copies stay the way) or not aligned to 16.
+const uint8_t *mapped(const uint8_t *host, size_t bytes)
+{
+    auto device_address = [](const uint8_t *p) -> const uint8_t * {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+            (void)hipGetLastError();                 // "not a pointer the runtime knows" is an answer, not an error to keep
+            return nullptr;
+        }
+        return a.type == hipMemoryTypeHost ? static_cast<const uint8_t *>(a.devicePointer) : nullptr;
+    };
+    if (!bytes) return nullptr;
+    const uint8_t *first = device_address(host), *last = device_address(host + bytes - 1);
+    return first && last == first + (bytes - 1) && !(reinterpret_cast<uintptr_t>(first) & 15) ? first : nullptr;
+}
+
 // rank of `expert` in the activation counts: how many experts come before it when sorted by
 // count, highest first, ties by lower id first
 int rank_of(const uint64_t *counts, int n, int expert)
@@ -124,6 +182,7 @@ struct zm_cache {
     std::vector<zm_tensor_info> infos;
     std::vector<const uint8_t *> host;         // per tensor: the blob (used by fetches only when there are no images)
     std::vector<const uint8_t *> image;        // per expert: packed SM sections then E-chunk regions, or empty
+    std::vector<const uint8_t *> source;       // device address of every image, or blob where there are none; empty: copies
     uint8_t *arena = nullptr;
     std::vector<uint64_t> count;
     std::vector<int8_t> pool_of;               // per expert: pool or kUncached
@@ -233,6 +292,15 @@ int zm_cache_create(const zm_cache_config *config, const void *const *host_blobs
         zm_cache_destroy(c);
         return ZM_E_HIP;
     }
+    // what fetches read is fetched by a kernel if all of it is mapped for the device
+    try {
+        const std::vector<const uint8_t *> &from = c->image.empty() ? c->host : c->image;
+        c->source.resize(from.size());
+        for (size_t i = 0; i < from.size(); ++i) {
+            c->source[i] = mapped(from[i], c->image.empty() ? c->infos[i].blob_size : c->lay.sm_bytes + c->lay.e_bytes);
+            if (!c->source[i]) { c->source.clear(); break; }
+        }
+    } catch (const std::bad_alloc &) { zm_cache_destroy(c); return ZM_E_NOMEM; }
     // decode tables and chunk tables of every tensor stay resident: a few KB per tensor
     const size_t n = c->infos.size();
     for (size_t i = 0; i < n; ++i) {
@@ -282,10 +350,29 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
         for (int s : c->limbo[p]) c->owner[p][s] = -1;
         c->limbo[p].clear();
     }
-    // copies of this fetch must not overtake what the caller still has queued on its stream
-    // (the previous fetch's outputs may live in the transient buffers)
-    if (hipEventRecord(c->ev_start, main_stream) != hipSuccess ||
-        hipStreamWaitEvent(c->copy_stream, c->ev_start, 0) != hipSuccess) return ZM_E_HIP;
+    // copies of this fetch must not overtake what the caller still has queued on its stream (the previous fetch's outputs
+    // may live in the transient buffers); a fetch without copies leaves both streams alone
+    bool any_copy = false;
+    auto begin_copies = [&]() {
+        if (any_copy) return ZM_OK;
+        any_copy = true;
+        return hipEventRecord(c->ev_start, main_stream) == hipSuccess && hipStreamWaitEvent(c->copy_stream, c->ev_start, 0) == hipSuccess
+                   ? ZM_OK : ZM_E_HIP;
+    };
+    // a part that comes from the host: `bytes` of it at `offset` of image or blob number `i`
+    Parts parts;
+    parts.n_parts = 0;
+    auto from_host = [&](uint8_t *dst, const std::vector<const uint8_t *> &host, size_t i, size_t offset, size_t bytes) -> int {
+        if (begin_copies() != ZM_OK) return ZM_E_HIP;
+        if (c->source.empty())
+            return hipMemcpyAsync(dst, host[i] + offset, bytes, hipMemcpyHostToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+        parts.part[parts.n_parts++] = Part{reinterpret_cast<const u32x4 *>(c->source[i] + offset), reinterpret_cast<u32x4 *>(dst), bytes / 16};
+        return parts.n_parts == kMaxParts ? fetch_parts(parts, c->copy_stream) : ZM_OK;
+    };
+    auto on_device = [&](uint8_t *dst, const uint8_t *src, size_t bytes) -> int {
+        if (begin_copies() != ZM_OK) return ZM_E_HIP;
+        return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+    };
 
     for (int j = 0; j < n_selected; ++j) ++c->count[expert_ids[j]];
 
@@ -334,7 +421,6 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
     zm_tensor_info *infos_now = c->infos_now.data(), *infos_later = c->infos_later.data();
     void **out_now = c->out_now.data(), **out_later = c->out_later.data();
     int n_now = 0, n_later = 0;
-    bool any_copy = false;
     for (int j = 0; j < n_selected; ++j) {
         const Plan &pl = plan[j];
         const int e = pl.expert;
@@ -362,18 +448,15 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
         if (by_region) {
             uint8_t *sm_to = keep_sm ? keep_sm : (have_sm ? nullptr : tr_sm);
             uint8_t *e_to = keep_e ? keep_e : (have_e ? nullptr : tr_e);
-            const uint8_t *img = c->image[e];
-            hipError_t rc = hipSuccess;
+            int rc = ZM_OK;
             if (sm_to && e_to && !have_sm && !have_e && e_to == sm_to + c->lay.sm_bytes) {
-                rc = hipMemcpyAsync(sm_to, img, c->lay.sm_bytes + c->lay.e_bytes, hipMemcpyHostToDevice, c->copy_stream);
+                rc = from_host(sm_to, c->image, e, 0, c->lay.sm_bytes + c->lay.e_bytes);
             } else {
-                if (sm_to) rc = have_sm ? hipMemcpyAsync(sm_to, have_sm, c->lay.sm_bytes, hipMemcpyDeviceToDevice, c->copy_stream)
-                                        : hipMemcpyAsync(sm_to, img, c->lay.sm_bytes, hipMemcpyHostToDevice, c->copy_stream);
-                if (rc == hipSuccess && e_to)
-                    rc = have_e ? hipMemcpyAsync(e_to, have_e, c->lay.e_bytes, hipMemcpyDeviceToDevice, c->copy_stream)
-                                : hipMemcpyAsync(e_to, img + c->lay.sm_bytes, c->lay.e_bytes, hipMemcpyHostToDevice, c->copy_stream);
+                if (sm_to) rc = have_sm ? on_device(sm_to, have_sm, c->lay.sm_bytes) : from_host(sm_to, c->image, e, 0, c->lay.sm_bytes);
+                if (rc == ZM_OK && e_to)
+                    rc = have_e ? on_device(e_to, have_e, c->lay.e_bytes) : from_host(e_to, c->image, e, c->lay.sm_bytes, c->lay.e_bytes);
             }
-            if (rc != hipSuccess) { c->broken = true; return ZM_E_HIP; }
+            if (rc != ZM_OK) { c->broken = true; return rc; }
             region_copied = sm_to || e_to;
         }
         for (int m = 0; m < T; ++m) {
@@ -387,17 +470,15 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
             const uint8_t *sm_src = have_sm ? have_sm + c->lay.sm_off[m] : nullptr;
             uint8_t *sm_dst = keep_sm ? keep_sm + c->lay.sm_off[m] : (sm_src ? nullptr : tr_sm + c->lay.sm_off[m]);
             if (sm_dst && !by_region) {
-                const hipError_t rc = sm_src ? hipMemcpyAsync(sm_dst, sm_src, sm_len, hipMemcpyDeviceToDevice, c->copy_stream)
-                                             : hipMemcpyAsync(sm_dst, c->host[i] + ti.sm_offset, sm_len, hipMemcpyHostToDevice, c->copy_stream);
-                if (rc != hipSuccess) { c->broken = true; return ZM_E_HIP; }
+                const int rc = sm_src ? on_device(sm_dst, sm_src, sm_len) : from_host(sm_dst, c->host, i, ti.sm_offset, sm_len);
+                if (rc != ZM_OK) { c->broken = true; return rc; }
                 copied = true;
             }
             const uint8_t *e_src = have_e ? have_e + c->lay.e_off[m] : nullptr;
             uint8_t *e_dst = keep_e ? keep_e + c->lay.e_off[m] : (e_src ? nullptr : tr_e + c->lay.e_off[m]);
             if (e_dst && !by_region) {
-                const hipError_t rc = e_src ? hipMemcpyAsync(e_dst, e_src, e_len, hipMemcpyDeviceToDevice, c->copy_stream)
-                                            : hipMemcpyAsync(e_dst, c->host[i] + ti.e_offset, e_len, hipMemcpyHostToDevice, c->copy_stream);
-                if (rc != hipSuccess) { c->broken = true; return ZM_E_HIP; }
+                const int rc = e_src ? on_device(e_dst, e_src, e_len) : from_host(e_dst, c->host, i, ti.e_offset, e_len);
+                if (rc != ZM_OK) { c->broken = true; return rc; }
                 copied = true;
             }
             zm_tensor_parts pt;
@@ -406,12 +487,13 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
             pt.sm = sm_dst ? sm_dst : sm_src;
             pt.echunks = e_dst ? e_dst : e_src;
             out = keep_full ? keep_full + c->lay.full_off[m] : tr_full + c->lay.full_off[m];
-            if (copied) { parts_later[n_later] = pt; infos_later[n_later] = ti; out_later[n_later++] = out; any_copy = true; }
+            if (copied) { parts_later[n_later] = pt; infos_later[n_later] = ti; out_later[n_later++] = out; }
             else { parts_now[n_now] = pt; infos_now[n_now] = ti; out_now[n_now++] = out; }
         }
     }
     // experts whose parts are all resident decode while the copies for the others are in flight
-    int rc = zm_decode_tensors(parts_now, infos_now, n_now, out_now, stream);
+    int rc = fetch_parts(parts, c->copy_stream);
+    if (rc == ZM_OK) rc = zm_decode_tensors(parts_now, infos_now, n_now, out_now, stream);
     if (rc == ZM_OK && any_copy) {
         if (hipEventRecord(c->ev_copied, c->copy_stream) != hipSuccess ||
             hipStreamWaitEvent(main_stream, c->ev_copied, 0) != hipSuccess) rc = ZM_E_HIP;

@@ -154,3 +154,26 @@ def test_back_to_back_fetches_without_host_synchronisation(packed):
     for got, want in zip(saved, wanted):
         assert np.array_equal(got.cpu().numpy().view(np.uint16), want)
     cache.close()
+
+
+@pytest.mark.parametrize("packed,n_tensors", [(True, 2), (False, 2), (False, 40)])
+@pytest.mark.parametrize("pinned", [True, False])
+def test_missing_parts_come_from_pinned_and_from_pageable_memory(monkeypatch, packed, n_tensors, pinned):
+    """pinned memory is read by the fetch kernel (up to 128 parts a launch), pageable memory is copied"""
+    import torch
+    shapes = tuple(5000 + 513 * i for i in range(n_tensors))
+    tensors, blobs = make_layer(5, shapes, seed=n_tensors)
+    if not pinned:
+        empty = torch.empty
+        monkeypatch.setattr(torch, "empty", lambda *a, pin_memory=False, **kw: empty(*a, **kw))
+    cache = zm.ExpertCache(blobs, (0, 1, 1, 1), 0, max_selected=4, packed=packed)
+    monkeypatch.undo()
+    assert all(h.is_pinned() == pinned for h in cache.host)
+    stream = torch.cuda.current_stream().cuda_stream
+    for ids in ([0, 1, 2, 3], [4, 0, 1], [3, 4, 2, 1], [0]):
+        ptrs, _ = cache.fetch(ids, stream)
+        torch.cuda.synchronize()
+        for j, e in enumerate(ids):
+            for m, n in enumerate(shapes):
+                assert np.array_equal(read_back(cache, ptrs[j][m], n), tensors[e][m]), (ids, e, m)
+    cache.close()
