@@ -119,46 +119,83 @@ size_t stream_byte_bound(uint32_t stream_values)
     return align_up(kLanes + (kLanes * (syms * ZM_MAX_CODE_LEN + 255) + 7) / 8, 16);
 }
 
-// Packs exponents e[0..n) of one stream: 64 length bytes, then the lanes' bitstreams back to back (LSB first),
-// zero bits to a multiple of 16 bytes.  A lane's bitstream holds the codes of its first half of symbols from its
-// first bit upwards and those of its second half, last symbol first, from its last bit downwards; the unused
-// bits sit in the middle.  Returns the bytes written.
-size_t pack_stream(const uint8_t *e, uint32_t n, const Book &b, uint32_t quantum, uint8_t *out)
-{
-    const uint32_t tiles = (n + kTile - 1) / kTile;
-    const uint32_t syms = tiles * kRun;                 // per lane
-    uint8_t *payload = out + kLanes;
-    uint64_t acc = 0;                                    // bits not yet written, lowest first
+// Bits appended to a byte stream, lowest first.  Up to seven wait in `acc`; eight bytes from `p` on may be overwritten.
+struct BitSink {
+    uint8_t *p;
+    uint64_t acc = 0;
     uint32_t fill = 0;
-    size_t at = 0;                                       // payload bytes written
-    auto put = [&](uint32_t bits, uint32_t count) {      // count <= 32
-        acc |= static_cast<uint64_t>(bits) << fill;
+
+    inline void put(uint64_t bits, uint32_t count)       // count <= 56
+    {
+        acc |= bits << fill;
         fill += count;
-        while (fill >= 8) { payload[at++] = static_cast<uint8_t>(acc); acc >>= 8; fill -= 8; }
-    };
-    auto symbol = [&](uint32_t lane, uint32_t j) -> uint32_t {
-        const uint32_t idx = (j / kRun) * kTile + lane * kRun + (j % kRun);
-        return idx < n ? e[idx] : b.pad;
-    };
+        store_le<uint64_t>(p, acc);
+        p += fill >> 3;
+        acc >>= fill & ~7u;
+        fill &= 7u;
+    }
+};
+
+// The codes of four symbols one after the other: at most 48 bits.  entry: code | length << 16.
+inline void put_four(BitSink &to, const uint32_t entry[256], const uint8_t *e)
+{
+    const uint32_t a = entry[e[0]], b = entry[e[1]], c = entry[e[2]], d = entry[e[3]];
+    const uint32_t la = a >> 16, lab = la + (b >> 16), lcd = (c >> 16) + (d >> 16);
+    const uint64_t ab = (a & 0xffffu) | static_cast<uint64_t>(b & 0xffffu) << la;
+    const uint64_t cd = (c & 0xffffu) | static_cast<uint64_t>(d & 0xffffu) << (c >> 16);
+    to.put(ab | cd << lab, lab + lcd);
+}
+
+// Codes as pack_stream looks them up, and the place where it keeps a lane's second half.
+struct Packer {
+    uint32_t up[256], down[256];      // code with its first bit lowest / highest, | length << 16
+    std::vector<uint8_t> half;
+
+    Packer(const Book &b, uint32_t stream_values) : half(stream_values / kLanes * ZM_MAX_CODE_LEN / 16 + 16)
+    {
+        for (int s = 0; s < 256; ++s) {
+            up[s] = b.wire[s] | static_cast<uint32_t>(b.len[s]) << 16;
+            down[s] = b.canon[s] | static_cast<uint32_t>(b.len[s]) << 16;
+        }
+    }
+};
+
+// Packs the exponents of one stream of `tiles` tiles (padded to whole tiles): 64 length bytes, then the lanes' bitstreams
+// back to back (LSB first), zero bits to a multiple of 16 bytes.  A lane's bitstream holds the codes of its first half
+// of symbols from its first bit upwards and those of its second half, last symbol first, from its last bit downwards;
+// the unused bits sit in the middle.  Returns the bytes written; eight more may be overwritten.
+size_t pack_stream(const uint8_t *e, uint32_t tiles, Packer &book, uint32_t quantum, uint8_t *out)
+{
+    const uint32_t syms = tiles * kRun;                 // per lane
+    BitSink to{out + kLanes};
     for (uint32_t lane = 0; lane < kLanes; ++lane) {
-        uint32_t used = 0;
-        for (uint32_t j = 0; j < syms; ++j) used += b.len[symbol(lane, j)];
-        const uint32_t units = (used - syms + quantum - 1) / quantum;
-        out[lane] = static_cast<uint8_t>(units);
+        const uint8_t *first = e + lane * kRun;
+        const uint8_t *start = to.p;
+        const uint32_t start_fill = to.fill;
         // in ascending bit order: the first half's codes, first bit lowest; the zero bits in the middle; the
         // second half's codes from the half's first symbol (read last) to the lane's last symbol (read first),
-        // each with its first bit highest
-        for (uint32_t j = 0; j < syms / 2; ++j) { const uint32_t s = symbol(lane, j); put(b.wire[s], b.len[s]); }
+        // each with its first bit highest.  A half is a whole number of fours.
+        for (uint32_t j = 0; j < syms / 2; j += 4) put_four(to, book.up, first + j / kRun * kTile + j % kRun);
+        BitSink late{book.half.data()};
+        for (uint32_t j = syms / 2; j < syms; j += 4) put_four(late, book.down, first + j / kRun * kTile + j % kRun);
+        const uint32_t late_bits = static_cast<uint32_t>(late.p - book.half.data()) * 8 + late.fill;
+        const uint32_t used = static_cast<uint32_t>(to.p - start) * 8 + to.fill - start_fill + late_bits;
+        const uint32_t units = (used - syms + quantum - 1) / quantum;
+        out[lane] = static_cast<uint8_t>(units);
         for (uint32_t fillers = syms + quantum * units - used; fillers; ) {
             const uint32_t k = std::min(fillers, 32u);
-            put(0, k);
+            to.put(0, k);
             fillers -= k;
         }
-        for (uint32_t j = syms / 2; j < syms; ++j) { const uint32_t s = symbol(lane, j); put(b.canon[s], b.len[s]); }
+        store_le<uint64_t>(late.p, late.acc);
+        const uint8_t *from = book.half.data();
+        uint32_t left = late_bits;
+        for (; left > 32; left -= 32, from += 4) to.put(load_le<uint32_t>(from), 32);
+        to.put(load_le<uint32_t>(from) & (0xffffffffu >> (32 - left)), left);     // every half has at least one symbol: left >= 1
     }
-    if (fill) put(0, 8 - fill);
-    const size_t total = align_up(kLanes + at, 16);
-    std::memset(payload + at, 0, total - kLanes - at);
+    if (to.fill) to.put(0, 8 - to.fill);
+    const size_t used = static_cast<size_t>(to.p - out), total = align_up(used, 16);
+    std::memset(to.p, 0, total - used);
     return total;
 }
 
@@ -344,14 +381,21 @@ const char *zm_strerror(int status)
 int zm_exponent_histogram(const uint16_t *bf16, size_t n_values, uint64_t hist[256])
 {
     if ((!bf16 && n_values) || !hist) return ZM_E_ARG;
-    uint64_t h[4][256] = {};
+    // eight tables: equal exponents follow each other often, and an increment waits for the one before it in its table
+    uint64_t h[8][256] = {};
     size_t i = 0;
-    for (; i + 4 <= n_values; i += 4) {
-        ++h[0][(bf16[i] >> 7) & 0xFF]; ++h[1][(bf16[i + 1] >> 7) & 0xFF];
-        ++h[2][(bf16[i + 2] >> 7) & 0xFF]; ++h[3][(bf16[i + 3] >> 7) & 0xFF];
+    for (; i + 8 <= n_values; i += 8) {
+        uint64_t a, b;
+        std::memcpy(&a, bf16 + i, 8);
+        std::memcpy(&b, bf16 + i + 4, 8);
+        ++h[0][(a >> 7) & 0xFF]; ++h[1][(a >> 23) & 0xFF]; ++h[2][(a >> 39) & 0xFF]; ++h[3][(a >> 55) & 0xFF];
+        ++h[4][(b >> 7) & 0xFF]; ++h[5][(b >> 23) & 0xFF]; ++h[6][(b >> 39) & 0xFF]; ++h[7][(b >> 55) & 0xFF];
     }
     for (; i < n_values; ++i) ++h[0][(bf16[i] >> 7) & 0xFF];
-    for (int s = 0; s < 256; ++s) hist[s] = h[0][s] + h[1][s] + h[2][s] + h[3][s];
+    for (int s = 0; s < 256; ++s) {
+        hist[s] = 0;
+        for (const auto &table : h) hist[s] += table[s];
+    }
     return ZM_OK;
 }
 
@@ -402,37 +446,43 @@ int zm_encode(const uint16_t *bf16, size_t n_values, uint32_t chunk_values, uint
     const uint64_t sm_off = align_up(table_off + static_cast<uint64_t>(stride) * (chunks + 1), 256);
     const uint64_t e_off = align_up(sm_off + n_values, 256);
     try {
-        std::memset(blob, 0, e_off);
+        std::memset(blob, 0, sm_off);
+        std::memset(blob + sm_off + n_values, 0, e_off - sm_off - n_values);
         std::memcpy(blob + kHeaderBytes, book.len, 256);
         fill_decode_table(book, blob + lut_off);
 
-        // split (Sec. 3.1): sign-mantissa bytes go straight to their section, exponent bytes to scratch
-        std::vector<uint8_t> expo(n_values ? n_values : 1);
         uint8_t *sm = blob + sm_off;
-        for (size_t i = 0; i < n_values; ++i) {
-            const uint32_t w = bf16[i];
-            const uint32_t ex = (w >> 7) & 0xFF;
-            if (!book.len[ex]) return ZM_E_ARG;
-            expo[i] = static_cast<uint8_t>(ex);
-            sm[i] = static_cast<uint8_t>(((w >> 8) & 0x80) | (w & 0x7F));
-        }
-
         const uint32_t quantum = lane_quantum_for(L, stream_values);
         const uint32_t max_streams = chunk_values / stream_values;
-        std::vector<uint8_t> coded(static_cast<size_t>(max_streams) * stream_byte_bound(stream_values));
+        // scratch for one chunk: its exponent bytes, and its coded form with the bytes a BitSink may overwrite
+        const size_t longest = static_cast<size_t>(align_up(std::min<uint64_t>(chunk_values, std::max<uint64_t>(n_values, 1)), kTile));
+        std::vector<uint8_t> expo(longest);
+        std::vector<uint8_t> coded(std::min<size_t>(max_streams, (longest + stream_values - 1) / stream_values) * stream_byte_bound(stream_values) + 8);
+        Packer packer(book, stream_values);
         uint64_t pos = e_off;
         for (size_t c = 0; c < chunks; ++c) {
             const size_t first = c * static_cast<size_t>(chunk_values);
             const uint32_t cn = static_cast<uint32_t>(std::min<size_t>(chunk_values, n_values - first));
             const uint32_t streams = (cn + stream_values - 1) / stream_values;
             const uint64_t raw_bytes = align_up(cn, 16);
+            // split (Sec. 3.1): sign-mantissa bytes go straight to their section, exponent bytes to scratch
+            for (size_t i = 0; i < cn; ++i) {
+                const uint32_t w = bf16[first + i];
+                expo[i] = static_cast<uint8_t>(w >> 7);
+                sm[first + i] = static_cast<uint8_t>(((w >> 8) & 0x80) | (w & 0x7F));
+            }
+            uint8_t seen[256] = {};
+            for (size_t i = 0; i < cn; ++i) seen[expo[i]] = 1;
+            for (int s = 0; s < 256; ++s) if (seen[s] && !book.len[s]) return ZM_E_ARG;
+            // positions past the end of the last tile hold the pad symbol
+            std::memset(expo.data() + cn, static_cast<int>(book.pad), align_up(cn, kTile) - cn);
             uint8_t *entry = blob + table_off + static_cast<uint64_t>(stride) * c;      // zero so far
             size_t at = 0;                                                               // bytes
             bool smaller = true;
             for (uint32_t s = 0; s < streams; ++s) {
                 store_le<uint32_t>(entry + 8 + 4 * s, static_cast<uint32_t>(at));
                 const uint32_t sn = std::min(stream_values, cn - s * stream_values);
-                at += pack_stream(&expo[first + static_cast<size_t>(s) * stream_values], sn, book, quantum, &coded[at]);
+                at += pack_stream(&expo[static_cast<size_t>(s) * stream_values], (sn + kTile - 1) / kTile, packer, quantum, &coded[at]);
                 if (at >= raw_bytes) { smaller = false; break; }
             }
             uint64_t mode;
@@ -442,8 +492,8 @@ int zm_encode(const uint16_t *bf16, size_t n_values, uint32_t chunk_values, uint
                 mode = ZM_MODE_CODED;
             } else {
                 std::memset(entry, 0, stride);
-                std::memset(blob + pos, 0, raw_bytes);
-                std::memcpy(blob + pos, &expo[first], cn);
+                std::memset(blob + pos + cn, 0, raw_bytes - cn);
+                std::memcpy(blob + pos, expo.data(), cn);
                 mode = ZM_MODE_RAW;
             }
             store_le<uint64_t>(entry, pos | mode);

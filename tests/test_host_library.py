@@ -394,3 +394,27 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, cwd=ROOT)
     assert r.returncode != 0 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("W", [512, 1024, 4096, 32768])
+@pytest.mark.parametrize("max_len", [1, 2, 8, 9, 12])
+def test_encoder_agrees_with_the_reference_at_the_edges_of_tiles_and_codes(W, max_len):
+    """byte for byte, for lengths around a tile, a stream and a chunk, and codes from one bit to the longest"""
+    rng = np.random.default_rng(W + max_len)
+    C = 2 * W
+    for n in (1, 7, 8, 9, 511, 512, 513, W - 1, W, W + 1, C, C + W + 515):
+        e = np.minimum(rng.geometric(0.35, n) - 1, (1 << max_len) - 1 if max_len < 8 else 255)
+        if max_len >= 8 and n > 4096:
+            e[: 200] = np.arange(200)                     # many rare exponents: codes of every length up to the limit
+        w = ((e.astype(np.uint16) & 0xFF) << 7) | rng.integers(0, 128, n, dtype=np.uint16) | (rng.integers(0, 2, n, dtype=np.uint16) << 15)
+        lengths = zm.build_codebook(zm.exponent_histogram(w), max_len)
+        blob, _ = zm.encode(w, C, W, lengths)
+        assert np.array_equal(blob, zo.encode(w, C, W, lengths)), (n, W, max_len)
+
+
+def test_encoder_refuses_a_value_without_a_code_in_the_last_chunk():
+    w = np.full(3 * 4096 + 5, 0x3C00, np.uint16)
+    lengths = zm.build_codebook(zm.exponent_histogram(w), 8)
+    w[-1] = 0x4C00
+    with pytest.raises(zm.ZipMoEError):
+        zm.encode(w, 4096, 4096, lengths)
