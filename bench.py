@@ -29,8 +29,8 @@ HBM_PEAK_GBPS = 8000.0        # MI355X published peak HBM3E bandwidth
 # copy of known size; the summaries are under profiles/).  Valid only for the kernel source they were taken
 # with: the entry is reported only while the source's hash still matches, else "traffic" is null.
 MEASURED_TRAFFIC = {
-    "kernel_sha256_16": "333d1b74932d3db6",
-    "bytes_per_launch": {"cfg5": 117.14e6, "cfg3": 170.39e6, "cfg4": 1195.78e6, "split-cfg4": 234.96e6},
+    "kernel_sha256_16": "36f7d76f68eb4b8e",
+    "bytes_per_launch": {"cfg5": 117.19e6, "cfg3": 170.44e6, "cfg4": 1195.81e6, "split-cfg4": 234.96e6},
 }
 
 
@@ -173,7 +173,8 @@ def bench_split(args, wl, workers: int, steps: int, warmup: int) -> int:
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": measured_traffic("split-" + args.workload),
                      # the library stores non-temporally when a launch moves more than 128 MiB (4 bytes per value)
-                     "kernel": "zm_recover_kernel<%s>" % ("true" if 4 * max(h[2] for h in dev) > (128 << 20) else "false"),
+                     "kernel": "zm_recover_kernel<%s>" % ("kStreaming" if 4 * max(h[2] for h in dev) > (128 << 20) else
+                                                           "kThrough" if max(h[2] for h in dev) > (5 << 20) else "kOrdinary"),
                      "us_per_launch": round(kernel_s * 1e6, 2), "algorithmic_bytes_per_launch": alg},
         "host_decode": {"value": round(2.0 * n_total / host_dt / 1e9, 3), "unit": "GB/s of bf16", "threads": workers,
                         "note": "zm_decode_exponents_host over the same tensors, one after the other"},
@@ -504,7 +505,8 @@ def main() -> int:
     t_per = layers[0].tensors_per_expert
     sel = [layers[0].infos[int(e) * t_per + m] for e in routes[0][0] for m in range(t_per)]
     shapes = zm.decode_launch_shapes(sel, zm.STORES_STREAMING)
-    kernel_names = ["zm_decode_kernel<%d,%d,%s>" % (sh.round_symbols, sh.waves_per_workgroup, "kStreaming" if sh.streaming_stores else "not streaming")
+    kernel_names = ["zm_decode_kernel<%s,%d,%s>" % ("true" if sh.round_symbols == 2 else "false", sh.waves_per_workgroup,
+                                                     "kStreaming" if sh.streaming_stores else "kThrough or kOrdinary")
                     for sh in shapes]
 
     result = {

@@ -28,8 +28,8 @@
 //      and the second half, last symbol first, from its last bit downwards, so every lane runs two independent
 //      decode chains at once (the lookups of one overlap the latency of the other).  Per chain it keeps two
 //      words of the bitstream, a bit position and the index of its next word; per round it extracts a 32-bit
-//      window with one funnel shift (bit-reversed for the downward chain) and decodes R symbols by table
-//      lookup; the next word is requested at the start of the round, so that a chain that crosses a word
+//      window with one funnel shift (one chain's is bit-reversed) and decodes four symbols by table lookup, or
+//      two where longer codes do not fit; the next word is requested at the start of the round, so that a chain that crosses a word
 //      boundary finds it there;
 //   6. the eight decoded exponent bytes are merged with the sign-mantissa bytes
 //      by byte-parallel bit operations and stored (a8).
@@ -43,7 +43,7 @@
 namespace {
 
 constexpr int kMaxTasks = 48;     // tensors per launch; 84 B each keeps the kernel arguments under 4 KiB
-constexpr int kFewTasks = 6;
+constexpr int kFewTasks = 6;      // tensors of a launch with small arguments: two experts of three matrices
 constexpr uint32_t kTile = 512;
 constexpr int kRawBuffer = 0x00027000;   // last word of a descriptor of untyped memory
 constexpr int kGroup = 8;         // tiles whose sign-mantissa loads are in flight together
@@ -719,6 +719,7 @@ struct Recorder {
 // What a launch needs to know beside its kernel arguments.
 struct Plan {
     dim3 grid;
+    uint32_t n_tasks;
     size_t lds;              // dynamic part: the streams
     uint64_t out_bytes;
     int stores;
@@ -726,28 +727,29 @@ struct Plan {
     Recorder *rec;
 };
 
+// args: an Args, or something that begins like one
 template <bool kLong, int kWaves, Stores kStores, class Args>
-int launch_kernel(const Args &args, const Plan &p)
+int launch_kernel(void *args, const Plan &p)
 {
-    void *argv[] = {const_cast<Args *>(&args)};
+    void *argv[] = {args};
     const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, Args>);
     // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
     return hipLaunchKernel(fn, p.grid, dim3(64 * kWaves), argv, p.lds, p.stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
 
 template <bool kLong, int kWaves, class Args>
-int launch_args(const Args &args, const Plan &p)
+int launch_args(void *args, const Plan &p)
 {
     const bool streaming = p.stores == ZM_STORES_STREAMING || (p.stores == ZM_STORES_AUTO && p.out_bytes > kLastLevelCacheBytes);
     if (p.rec) {
         if (p.rec->n < p.rec->cap)
             p.rec->out[p.rec->n] = zm_launch_shape{kLong ? 2u : 4u, static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, p.grid.x,
-                                                   args.n_tasks, static_cast<uint32_t>(p.lds + kStaticLds<kLong>)};
+                                                   p.n_tasks, static_cast<uint32_t>(p.lds + kStaticLds<kLong>)};
         ++p.rec->n;
         return ZM_OK;
     }
-    if (streaming) return launch_kernel<kLong, kWaves, kStreaming>(args, p);
-    return p.out_bytes <= kThroughBytes ? launch_kernel<kLong, kWaves, kThrough>(args, p) : launch_kernel<kLong, kWaves, kOrdinary>(args, p);
+    if (streaming) return launch_kernel<kLong, kWaves, kStreaming, Args>(args, p);
+    return p.out_bytes <= kThroughBytes ? launch_kernel<kLong, kWaves, kThrough, Args>(args, p) : launch_kernel<kLong, kWaves, kOrdinary, Args>(args, p);
 }
 
 // Whether a launch numbers its workgroups through all tensors instead of giving every tensor as many as the largest has.
@@ -779,13 +781,13 @@ int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream,
         out_bytes += 2 * L.task[k].n_values;
     }
     if (!blocks) return ZM_OK;
-    if (total <= 0x7FFFFFFFull && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
-        return launch_args<kLong, kWaves>(L, Plan{dim3(static_cast<uint32_t>(total)), lds, out_bytes, stores, stream, rec});
     // without the workgroup numbers the arguments are the same up to the end of the tasks
     using Rows = Launch<N, false>;
     using Through = Launch<N, true>;
     static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
-    return launch_args<kLong, kWaves>(reinterpret_cast<const Rows &>(L), Plan{dim3(blocks, L.n_tasks), lds, out_bytes, stores, stream, rec});
+    if (total <= 0x7FFFFFFFull && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
+        return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, out_bytes, stores, stream, rec});
+    return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, out_bytes, stores, stream, rec});
 }
 
 // Collects the tensors of one round length and launches them.
@@ -908,7 +910,7 @@ struct Group {
                 blocks = b > blocks ? b : blocks;
                 out_bytes += 2 * t.n_values;
             }
-            const int rc = launch_args<kLong, 2>(L, Plan{dim3(blocks, L.n_tasks), 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, stores, stream, rec});
+            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, stores, stream, rec});
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;
