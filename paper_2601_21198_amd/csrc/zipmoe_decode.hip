@@ -649,9 +649,9 @@ __global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restri
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t first = wave * (kRecoverTilesPerWave * kTile);
-    if (first >= n) return;
+    if (kStores != kStreaming && first >= n) return;
     const uint64_t base = first + lane * 8u;
-    const uint64_t rest = n - first;
+    const uint64_t rest = first < n ? n - first : 0u;
     const Sink<kStores> sink(out + first, rest < kRecoverTilesPerWave * kTile ? static_cast<uint32_t>(rest) : kRecoverTilesPerWave * kTile, lane);
     uint2 ev[kRecoverTilesPerWave], sv[kRecoverTilesPerWave];
 #pragma unroll
@@ -674,8 +674,16 @@ __global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restri
     for (int k = 0; k < kRecoverTilesPerWave; ++k) {
         const uint64_t i = base + static_cast<uint64_t>(k) * kTile;
         const uint4 w = recover8(ev[k], sv[k]);
-        if (i + 8 <= n) sink.store(static_cast<uint32_t>(k), w);
-        else if (i < n) sink.store_partial(static_cast<uint32_t>(k), w);
+        if (i + 8 > n) {
+            if (i < n) sink.store_partial(static_cast<uint32_t>(k), w);
+        } else if constexpr (kStores == kStreaming) {
+            // four adjacent word stores, which the compiler merges into one
+            uint32_t *p = reinterpret_cast<uint32_t *>(__builtin_assume_aligned(out + i, 16));
+            __builtin_nontemporal_store(w.x, p); __builtin_nontemporal_store(w.y, p + 1);
+            __builtin_nontemporal_store(w.z, p + 2); __builtin_nontemporal_store(w.w, p + 3);
+        } else {
+            sink.store(static_cast<uint32_t>(k), w);
+        }
     }
 }
 
