@@ -369,8 +369,9 @@ class ExpertLayer:
         """Pre-marshals one call: returns a zero-argument function that enqueues it on ``stream``."""
         ids = (ctypes.c_int32 * len(expert_ids))(*[int(e) for e in expert_ids])
         t = self.tensors_per_expert
-        offsets = [2 * s for s in starts[:t]]
-        outs = (ctypes.c_void_p * (len(expert_ids) * t))(*[base + o for base in [b.data_ptr() for b in out_buffers] for o in offsets])
+        bases = [b.data_ptr() for b in out_buffers]
+        offsets = [2 * starts[m] for m in range(t)] if bases else []      # one for every tensor of an expert, or an IndexError
+        outs = (ctypes.c_void_p * (len(expert_ids) * t))(*[base + o for base in bases for o in offsets])
         f = lib().zm_decode_experts_stores
         args = (self._ptr_blobs, self._ptr_tables, self._ptr_infos, self.n_experts, t, ids, len(expert_ids), outs, stores)
 

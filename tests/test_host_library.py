@@ -418,3 +418,25 @@ def test_encoder_refuses_a_value_without_a_code_in_the_last_chunk():
     w[-1] = 0x4C00
     with pytest.raises(zm.ZipMoEError):
         zm.encode(w, 4096, 4096, lengths)
+
+
+def test_a_call_needs_a_start_for_every_tensor_of_an_expert():
+    """make_call only computes addresses, so a layer in host memory shows what it passes on"""
+    import collections
+    import torch
+    blobs = [[zm.compress(synth.special_tensor("gauss", 600, m), 4096, 4096)[0] for m in range(3)] for _ in range(2)]
+    layer = zm.ExpertLayer(blobs, device="cpu")
+    bufs, starts, _ = layer.alloc_outputs(2)
+    want = [b.data_ptr() + 2 * s for b in bufs for s in starts]
+    assert list(layer.make_call([1, 0], bufs, starts).keepalive[1]) == want
+    # whatever can be indexed, rows of one tensor as buffers, more starts than tensors
+    assert list(layer.make_call([1, 0], bufs, collections.deque(starts)).keepalive[1]) == want
+    assert list(layer.make_call([1, 0], bufs, dict(enumerate(starts))).keepalive[1]) == want
+    assert list(layer.make_call([1, 0], bufs, starts + [7]).keepalive[1]) == want
+    rows = torch.empty(2, 1824, dtype=torch.int16)
+    assert list(layer.make_call([1, 0], rows, starts).keepalive[1]) == [r.data_ptr() + 2 * s for r in rows for s in starts]
+    assert list(layer.make_call([], [], []).keepalive[1]) == []
+    # a missing start would move every address behind it
+    for short in (starts[:2], starts[:1], []):
+        with pytest.raises(IndexError):
+            layer.make_call([1, 0], bufs, short)
