@@ -793,7 +793,8 @@ int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream,
     using Rows = Launch<N, false>;
     using Through = Launch<N, true>;
     static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
-    if (total <= 0x7FFFFFFFull && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
+    // a launch admits 2^32 - 1 threads in x
+    if (total <= UINT32_MAX / (64u * kWaves) && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
         return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, out_bytes, stores, stream, rec});
     return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, out_bytes, stores, stream, rec});
 }

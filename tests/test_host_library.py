@@ -440,3 +440,20 @@ def test_a_call_needs_a_start_for_every_tensor_of_an_expert():
     for short in (starts[:2], starts[:1], []):
         with pytest.raises(IndexError):
             layer.make_call([1, 0], bufs, short)
+
+
+@pytest.mark.parametrize("streams_each,rows", [(16 << 20, False), (40 << 20, True)])
+def test_launches_stay_below_the_runtimes_bound_on_threads(streams_each, rows):
+    """a launch has fewer than 2^32 threads in x: tensors whose workgroups are more together get a row each"""
+    base = zm.blob_info(zm.compress(synth.special_tensor("gauss", 5000, 3), 4096, 512)[0])
+
+    def tensor(n):
+        t = zm.TensorInfo.from_buffer_copy(base)
+        t.n_values, t.n_chunks = n, -(-n // base.chunk_values)
+        t.e_offset = t.sm_offset + (n + 255) // 256 * 256
+        t.blob_size = t.e_offset + 256
+        return t
+
+    shapes = zm.decode_launch_shapes([tensor(512 * streams_each), tensor(512 * streams_each), tensor(512)])
+    assert [(s.tensors, s.workgroups) for s in shapes] == [(3, streams_each // 2 if rows else streams_each + 1)]
+    assert all(s.workgroups * 64 * s.waves_per_workgroup < 1 << 32 for s in shapes)
