@@ -805,6 +805,8 @@ struct Group {
     static constexpr uint32_t kLenBound = kLong ? ZM_MAX_CODE_LEN : 8;
     int n = 0;                        // tensors to come, all launches together
     uint64_t n_values = 0;            // of theirs
+    uint64_t blocks = 0;              // workgroups of two streams that they need
+    uint32_t most_blocks = 0;         // of the largest one
     bool packable = true;             // every one has the layout of a blob and an address that fits a Packed
     uint32_t n_shapes = 0;
     Shape shape[kMaxShapes];
@@ -836,6 +838,9 @@ struct Group {
         ++n;
         if (!many) return;
         n_values += t.n_values;
+        const uint32_t b = (t.n_streams + 1u) / 2u;
+        blocks += b;
+        most_blocks = most_blocks > b ? most_blocks : b;
         cap_of_all.see(t, ti);
         uint32_t k;
         packable = packable && pack(t, ti, k).high != kUnpackable;
@@ -869,7 +874,7 @@ struct Group {
     {
         if (n <= kFewTasks) return launch_wide<kFewTasks>(next, stores, stream, rec);
         if (n > kMaxTasks && packable && n_values >= kPackedValues * static_cast<uint64_t>(n) &&
-            8 * cap_of_all.words() + kBesideStreams<kLong> <= kLdsLimit) return launch_packed(next, stores, stream, rec);
+            rows_pay() && 8 * cap_of_all.words() + kBesideStreams<kLong> <= kLdsLimit) return launch_packed(next, stores, stream, rec);
         return launch_wide<kMaxTasks>(next, stores, stream, rec);
     }
 
@@ -897,6 +902,18 @@ struct Group {
     // 77.0 us in launches of 48, 19.1 / 35.2 / 65.4 us in one.  Tensors below 64 Ki values keep the launches of 48 that
     // zm_decode_launch_shapes has always told of for them (its callers and a test rely on that number).
     static constexpr uint64_t kPackedValues = 1u << 16;
+    // Packed launches have a row of workgroups per tensor, as many as the largest needs.  Workgroups that exit at once take
+    // 0.2 ns each to start and a launch saved is worth 1.3 to 3.4 us, so lengths that fall off too far take the launches of
+    // 48, which are numbered through; beside four times fewer that work, the idle ones start unnoticed.  us packed / in
+    // launches of 48: one tensor of 14.7 M values and 191 of 0.13 M (113 K idle per launch saved, 70 for one that works)
+    // 91.5 / 28.9; one of 2.9 M and 60 of 65536 (21 K, 25) 12.4 / 9.2; one of 2.1 M and 100 of 0.5 M (10 K, 3) 30.1 / 33.1.
+    static constexpr uint64_t kIdlePerLaunch = 16384;
+    bool rows_pay() const
+    {
+        const uint64_t idle = static_cast<uint64_t>(most_blocks) * static_cast<uint64_t>(n) - blocks;
+        return idle <= kIdlePerLaunch * static_cast<uint64_t>(launches_of(kMaxTasks) - launches_of(kMaxPacked)) || idle <= 4 * blocks;
+    }
+    int launches_of(int tensors) const { return (n + tensors - 1) / tensors; }
 
     template <typename Next>
     int launch_packed(Next next, int stores, hipStream_t stream, Recorder *rec)
@@ -906,7 +923,7 @@ struct Group {
         L.stream_cap_words = static_cast<uint32_t>(cap);
         L.long_slots = cap_of_all.long_slots;
         for (uint32_t k = 0; k < n_shapes; ++k) L.shape[k] = shape[k];
-        const int launches = (n + kMaxPacked - 1) / kMaxPacked, each = (n + launches - 1) / launches;
+        const int launches = launches_of(kMaxPacked), each = (n + launches - 1) / launches;
         for (int left = n; left > 0; left -= static_cast<int>(L.n_tasks)) {
             L.n_tasks = static_cast<uint32_t>(left < each ? left : each);
             uint32_t blocks = 0;

@@ -457,3 +457,23 @@ def test_launches_stay_below_the_runtimes_bound_on_threads(streams_each, rows):
     shapes = zm.decode_launch_shapes([tensor(512 * streams_each), tensor(512 * streams_each), tensor(512)])
     assert [(s.tensors, s.workgroups) for s in shapes] == [(3, streams_each // 2 if rows else streams_each + 1)]
     assert all(s.workgroups * 64 * s.waves_per_workgroup < 1 << 32 for s in shapes)
+
+
+@pytest.mark.parametrize("big,small,count,launches", [
+    (14_680_064, 131_072, 191, [(48, 1792 + 47 * 16), (48, 16), (48, 16), (48, 16)]),     # 336 K workgroups of 339 K would be idle
+    (2_883_584, 65_536, 60, [(48, 352 + 47 * 8), (13, 8)]),
+    (2_097_152, 524_288, 100, [(101, 256)]),                                              # three idle beside one
+    (524_288, 524_288, 191, [(192, 64)])])
+def test_one_launch_of_many_tensors_only_where_their_lengths_agree(big, small, count, launches):
+    """a shared launch has a row of workgroups per tensor: with one long tensor among many nearly all would be idle"""
+    base = zm.blob_info(zm.compress(synth.special_tensor("gauss", 5000, 3), 16384, 4096)[0])
+
+    def tensor(n):
+        t = zm.TensorInfo.from_buffer_copy(base)
+        t.n_values, t.n_chunks = n, -(-n // base.chunk_values)
+        t.e_offset = t.sm_offset + (n + 255) // 256 * 256
+        t.blob_size = t.e_offset + (n + 255) // 256 * 256
+        return t
+
+    shapes = zm.decode_launch_shapes([tensor(big)] + [tensor(small)] * count)
+    assert [(s.tensors, s.workgroups) for s in shapes] == launches
