@@ -364,7 +364,7 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
     parts.n_parts = 0;
     auto from_host = [&](uint8_t *dst, const std::vector<const uint8_t *> &host, size_t i, size_t offset, size_t bytes) -> int {
         if (begin_copies() != ZM_OK) return ZM_E_HIP;
-        if (c->source.empty())
+        if (c->source.empty() || ((offset | bytes) & 15))     // the kernel moves whole vectors only
             return hipMemcpyAsync(dst, host[i] + offset, bytes, hipMemcpyHostToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
         parts.part[parts.n_parts++] = Part{reinterpret_cast<const u32x4 *>(c->source[i] + offset), reinterpret_cast<u32x4 *>(dst), bytes / 16};
         return parts.n_parts == kMaxParts ? fetch_parts(parts, c->copy_stream) : ZM_OK;
