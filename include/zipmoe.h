@@ -334,8 +334,8 @@ int zm_decode_host_tensors(const void *const *host_blobs, const zm_tensor_info *
  * F < C < S < E: F keeps recovered bf16 tensors, C keeps E-chunks and SM-chunks,
  * S keeps SM-chunks, E keeps E-chunks.  Whatever an expert's pool does not hold
  * is fetched from the host copy of its blobs (Sec. 6: host memory is the tier
- * below device memory) with asynchronous copies that overlap the decode of the
- * experts that need none.  Every fetch counts one activation of each named
+ * below device memory), by a kernel where that copy is mapped for the device, as
+ * pinned memory is, by copies else, while the experts that need none decode.  Every fetch counts one activation of each named
  * expert; an expert whose rank r in the activation counts (0 = most activated,
  * ties to the lower id) satisfies r < tau_i = slots[0] + .. + slots[i] +
  * tolerance is dispatched to the first such pool i (pools of capacity 0 are
@@ -384,9 +384,12 @@ int zm_cache_pack_expert(const zm_cache_config *config, const zm_tensor_info *in
 /* Creates a cache.  host_blobs: host array [n_experts * tensors_per_expert] of
  * HOST pointers to the validated blobs.  host_images: NULL, or host array
  * [n_experts] of images made by zm_cache_pack_expert.  Without images the blobs
- * are what fetches copy from (pinned memory makes the copies asynchronous) and
+ * are what fetches read (pinned memory makes that asynchronous) and
  * must stay valid for the life of the cache; with images the images must, and
- * the blobs are only read during this call.  arena: DEVICE
+ * the blobs are only read during this call.  Every fetch asks anew whether the
+ * memory it reads is mapped, so it may be pinned and unpinned between fetches,
+ * but has to stay as it was when a fetch was issued until the stream has passed
+ * that fetch (and, if it was captured, for as long as the graph is replayed).  arena: DEVICE
  * memory of at least zm_cache_arena_bytes bytes, 256-byte aligned, owned by the
  * caller and used by the cache until zm_cache_destroy.  The decode tables and
  * chunk tables of all tensors are uploaded at once (the call returns when they

@@ -137,22 +137,32 @@ int fetch_parts(Parts &parts, hipStream_t stream)
     return rc == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
 
-// Device address of `bytes` bytes of host memory, or null if they are not all mapped for the current device (pageable
-// memory, for which copies stay the way) or not aligned to 16.
-const uint8_t *mapped(const uint8_t *host, size_t bytes)
-{
-    auto device_address = [](const uint8_t *p) -> const uint8_t * {
-        hipPointerAttribute_t a{};
-        if (hipPointerGetAttributes(&a, p) != hipSuccess) {
-            (void)hipGetLastError();                 // "not a pointer the runtime knows" is an answer, not an error to keep
-            return nullptr;
+// Host memory that a kernel may read, asked for range by range: what has been found mapped stays known until the object
+// goes, which is to be within one call, since the caller may unmap and map his memory between calls.
+class Mapped {
+    const uint8_t *first = nullptr, *end = nullptr;     // the allocation of the range asked for last
+
+public:
+    // Whether one allocation that is mapped for the device, at the address that the host has for it, covers the range.
+    // (Asking for both ends would not do: between two mapped pieces there may be pages that are not.)
+    bool covers(const uint8_t *p, size_t bytes)
+    {
+        if (!first || p < first || p >= end) {
+            first = end = nullptr;
+            hipPointerAttribute_t a{};
+            hipDeviceptr_t base = nullptr;
+            size_t size = 0;
+            hipError_t rc = hipPointerGetAttributes(&a, p);
+            const bool host = rc == hipSuccess && a.type == hipMemoryTypeHost && a.devicePointer == p;
+            if (host) rc = hipMemGetAddressRange(&base, &size, a.devicePointer);
+            if (rc != hipSuccess) (void)hipGetLastError();     // "not memory the runtime knows" is an answer, not an error to keep
+            if (rc != hipSuccess || !host || !base) return false;
+            first = static_cast<const uint8_t *>(base);
+            end = first + size;
         }
-        return a.type == hipMemoryTypeHost ? static_cast<const uint8_t *>(a.devicePointer) : nullptr;
-    };
-    if (!bytes) return nullptr;
-    const uint8_t *first = device_address(host), *last = device_address(host + bytes - 1);
-    return first && last == first + (bytes - 1) && !(reinterpret_cast<uintptr_t>(first) & 15) ? first : nullptr;
-}
+        return p >= first && p < end && bytes <= static_cast<size_t>(end - p);
+    }
+};
 
 // rank of `expert` in the activation counts: how many experts come before it when sorted by
 // count, highest first, ties by lower id first
@@ -182,7 +192,6 @@ struct zm_cache {
     std::vector<zm_tensor_info> infos;
     std::vector<const uint8_t *> host;         // per tensor: the blob (used by fetches only when there are no images)
     std::vector<const uint8_t *> image;        // per expert: packed SM sections then E-chunk regions, or empty
-    std::vector<const uint8_t *> source;       // device address of every image, or blob where there are none; empty: copies
     uint8_t *arena = nullptr;
     std::vector<uint64_t> count;
     std::vector<int8_t> pool_of;               // per expert: pool or kUncached
@@ -292,15 +301,6 @@ int zm_cache_create(const zm_cache_config *config, const void *const *host_blobs
         zm_cache_destroy(c);
         return ZM_E_HIP;
     }
-    // what fetches read is fetched by a kernel if all of it is mapped for the device
-    try {
-        const std::vector<const uint8_t *> &from = c->image.empty() ? c->host : c->image;
-        c->source.resize(from.size());
-        for (size_t i = 0; i < from.size(); ++i) {
-            c->source[i] = mapped(from[i], c->image.empty() ? c->infos[i].blob_size : c->lay.sm_bytes + c->lay.e_bytes);
-            if (!c->source[i]) { c->source.clear(); break; }
-        }
-    } catch (const std::bad_alloc &) { zm_cache_destroy(c); return ZM_E_NOMEM; }
     // decode tables and chunk tables of every tensor stay resident: a few KB per tensor
     const size_t n = c->infos.size();
     for (size_t i = 0; i < n; ++i) {
@@ -362,11 +362,14 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
     // a part that comes from the host: `bytes` of it at `offset` of image or blob number `i`
     Parts parts;
     parts.n_parts = 0;
+    Mapped mapped;
     auto from_host = [&](uint8_t *dst, const std::vector<const uint8_t *> &host, size_t i, size_t offset, size_t bytes) -> int {
         if (begin_copies() != ZM_OK) return ZM_E_HIP;
-        if (c->source.empty() || ((offset | bytes) & 15))     // the kernel moves whole vectors only
-            return hipMemcpyAsync(dst, host[i] + offset, bytes, hipMemcpyHostToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
-        parts.part[parts.n_parts++] = Part{reinterpret_cast<const u32x4 *>(c->source[i] + offset), reinterpret_cast<u32x4 *>(dst), bytes / 16};
+        const uint8_t *src = host[i] + offset;
+        // the kernel moves whole vectors only
+        if (((reinterpret_cast<uintptr_t>(src) | bytes) & 15) || !mapped.covers(src, bytes))
+            return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+        parts.part[parts.n_parts++] = Part{reinterpret_cast<const u32x4 *>(src), reinterpret_cast<u32x4 *>(dst), bytes / 16};
         return parts.n_parts == kMaxParts ? fetch_parts(parts, c->copy_stream) : ZM_OK;
     };
     auto on_device = [&](uint8_t *dst, const uint8_t *src, size_t bytes) -> int {

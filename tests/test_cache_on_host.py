@@ -36,3 +36,12 @@ def test_parts_that_are_no_whole_vectors_are_copied_to_their_last_byte(program):
     # an image's regions are whole vectors whatever the blobs are
     assert fetch(program, "odd-end", "packed") == (0, 2, 0, 0, 0)
     assert fetch(program, "odd-sections", "packed") == (0, 2, 0, 0, 0)
+
+
+@pytest.mark.parametrize("source,parts", [("blobs", 4), ("packed", 2)])
+def test_the_kernel_reads_nothing_that_is_not_mapped_when_the_fetch_is_issued(program, source, parts):
+    # unpinned after the cache was made, and still valid
+    assert fetch(program, "unmapped-later", source) == (0, 0, parts, 0, 0)
+    # first and last page mapped, by an allocation each, and pageable memory between them: what lies in the last page alone
+    # is the blobs' E regions
+    assert fetch(program, "hole", source) == ((0, 2, 2, 0, 0) if source == "blobs" else (0, 0, 2, 0, 0))

@@ -177,3 +177,30 @@ def test_missing_parts_come_from_pinned_and_from_pageable_memory(monkeypatch, pa
             for m, n in enumerate(shapes):
                 assert np.array_equal(read_back(cache, ptrs[j][m], n), tensors[e][m]), (ids, e, m)
     cache.close()
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("pinned", [True, False])
+def test_a_fetch_can_be_captured_and_replayed(monkeypatch, packed, pinned):
+    """nothing is kept between these fetches, so every replay reads the host's bytes again"""
+    import torch
+    shapes = (5000, 12345)
+    tensors, blobs = make_layer(3, shapes, seed=11)
+    if not pinned:
+        empty = torch.empty
+        monkeypatch.setattr(torch, "empty", lambda *a, pin_memory=False, **kw: empty(*a, **kw))
+    cache = zm.ExpertCache(blobs, (0, 0, 0, 0), 0, max_selected=2, packed=packed)
+    monkeypatch.undo()
+    cache.fetch([0, 1], torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ptrs, _ = cache.fetch([2, 0], torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        cache.arena[cache.arena.numel() // 4:].zero_()              # the buffers of parts and words; the tables lie before them
+        graph.replay()
+        torch.cuda.synchronize()
+        for j, e in enumerate((2, 0)):
+            for m, n in enumerate(shapes):
+                assert np.array_equal(read_back(cache, ptrs[j][m], n), tensors[e][m]), (e, m)
+    cache.close()
