@@ -218,7 +218,8 @@ constexpr uint32_t kTableEntries = 256;   // the LDS table of codes of at most e
 // larger one, from there on the second, and they meet in T.  So a code of any length takes one LDS read and no branch.
 // (Before, the table held the 256 beginnings, and a wave in which one lane met a long code, one step in two, branched to
 // a second look-up; and a window was refilled after every two symbols.  One / two / four / eight experts of 1024 x 2048 x 3
-// with codes of up to 12 bits, streaming stores: 9.5 / 13.2 / 19.8 / 31.8 us then, 7.0 / 9.8 / 15.6 / 27.7 us now.)  At most half as many beginnings are shared as there are symbols: each by two codes or more.
+// with codes of up to 12 bits, streaming stores: 9.5 / 13.2 / 19.8 / 31.8 us then, 7.0 / 9.8 / 15.6 / 27.7 us now.)  At most half as many beginnings are shared as there are symbols: each by two codes or more.  The table has room
+// for that many; where a description counts fewer symbols than the blob's table has, codes are looked up in that one.
 struct LongTable {
     uint32_t shift;      // 32 - L
     int32_t skip;        // (T << (L-8)) - T
@@ -231,6 +232,9 @@ struct LongTable {
     }
 };
 
+// Symbol low, length high, as blobs have it, to length low, symbol high.
+__device__ __forceinline__ uint16_t swap_entry(uint32_t v) { return static_cast<uint16_t>(__builtin_amdgcn_perm(0u, v, 0x0c0c0001u)); }
+
 // Lock-step decoder state of one lane (a5): two chains, one reading the lane's bitstream upwards from its
 // first bit (the first half of the lane's symbols, in order), one reading it downwards from its last bit (the
 // second half, last symbol first).
@@ -238,7 +242,8 @@ struct LongTable {
 // ZM_MAX_CODE_LEN bits.  Two symbols per window are safe; four nearly always fit as well, since long codes are the rare
 // ones by construction: quad tries four, and its caller falls back to safe_quad where a lane's four have more than 32
 // bits between them.
-template <bool kLong>
+// kFromBlob: the table in LDS does not hold all of the tensor's codes, and tab is the blob's own.
+template <bool kLong, bool kFromBlob = false>
 struct Decoder {
     const uint32_t *words;        // the stream as staged in LDS (length bytes included)
     uint32_t last_word;           // highest index a read may use
@@ -268,7 +273,8 @@ struct Decoder {
     // lowest (short codes) or its highest (long codes).
     __device__ __forceinline__ uint32_t look(const uint16_t *tab, uint32_t win, uint32_t used) const
     {
-        if constexpr (kLong) return tab[table.index(win << (used & 31u))];
+        if constexpr (kFromBlob) return swap_entry(tab[__builtin_bitreverse32(win << (used & 31u) >> table.shift) >> table.shift]);
+        else if constexpr (kLong) return tab[table.index(win << (used & 31u))];
         else return tab[__builtin_amdgcn_ubfe(win, used, 8)];
     }
 
@@ -421,8 +427,8 @@ __device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uin
 // pair is the middle tile alone, whose low half comes from the upward and whose high half from the downward chain.  The
 // caller has asked for two pairs (up[0], up[1]); kept rolled, since the unrolled loop with its partial tiles costs the
 // whole kernel 20 registers.
-template <bool kLong, Stores kStores>
-__device__ __forceinline__ void decode_any_stream(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+template <bool kLong, bool kFromBlob, Stores kStores>
+__device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
                                                   uint32_t lo, uint32_t tiles, int32_t mine, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
 #pragma unroll 1
@@ -552,6 +558,7 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     // a3: decode table -> LDS with the two bytes of an entry swapped (length low).  Every wave of the workgroup writes the
     // same bytes (LDS word writes are atomic), so a wave may read as soon as its own writes are done: no workgroup barrier.
     LongTable table{0u, 0};
+    bool narrow = false;         // long codes: the table has no room for all shared beginnings
     {
         const uint16_t *src = reinterpret_cast<const uint16_t *>(t.lut);
         const uint32_t mask = (1u << max_len) - 1u;
@@ -579,7 +586,8 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
                 const uint32_t v = (k & 2 ? e.y : e.x) >> (16 * (k & 1)) & 0xffffu;
                 n_shared += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64((v >> 8) > 8u)));
             }
-            n_shared = min(n_shared, P.long_slots);              // what the table has room for
+            narrow = n_shared > P.long_slots;
+            n_shared = min(n_shared, P.long_slots);
             const uint32_t whole_codes = kTableEntries - n_shared, late = n_shared << more;
             table.shift = 32u - max_len;
             table.skip = static_cast<int32_t>((whole_codes << more) - whole_codes);
@@ -587,12 +595,12 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
             for (int k = 0; k < 4; ++k) {
                 const uint32_t v = (k & 2 ? e.y : e.x) >> (16 * (k & 1)) & 0xffffu;
                 const uint32_t at = __builtin_bitreverse32(i + k) >> 24;
-                if (at < whole_codes) tab[at] = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, v, 0x0c0c0001u));
+                if (at < whole_codes) tab[at] = swap_entry(v);
             }
-            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, tail, 0x0c0c0001u));
+            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = swap_entry(tail);
             for (uint32_t k = lane; k + 64u < late; k += 64u) {
                 const uint32_t v = src[__builtin_bitreverse32((whole_codes << more) + k) >> (32u - max_len)];
-                tab[whole_codes + k] = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, v, 0x0c0c0001u));
+                tab[whole_codes + k] = swap_entry(v);
             }
         }
     }
@@ -610,22 +618,29 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
 
     const Sink<kStores> out(t.out + v0, sn, lane);
 
-    Decoder<kLong> dec;
-    dec.words = words; dec.last_word = P.stream_cap_words - 1u;
-    dec.table = table;
-    if (coded) {
-        // a6: this lane's bitstream has 8 * tiles + quantum * (its length byte) bits and starts where
-        // the bitstreams of the lanes below it end
-        const uint32_t units = reinterpret_cast<const uint8_t *>(words)[lane];
-        const uint32_t bits = 8u * tiles + quantum * units;
-        const uint32_t first = wave_exclusive_sum(bits);
-        dec.start(first, first + bits);
-    }
-
     if (!coded) {
         merge_raw_stream(out, ByteSource(raw, sn, lane), sm, tiles, mine);
         return;
     }
+    // a6: this lane's bitstream has 8 * tiles + quantum * (its length byte) bits and starts where
+    // the bitstreams of the lanes below it end
+    const uint32_t units = reinterpret_cast<const uint8_t *>(words)[lane];
+    const uint32_t bits = 8u * tiles + quantum * units;
+    const uint32_t first = wave_exclusive_sum(bits);
+    if constexpr (kLong) {
+        if (__builtin_expect(narrow, 0)) {
+            Decoder<true, true> dec;
+            dec.words = words; dec.last_word = P.stream_cap_words - 1u;
+            dec.table = table;
+            dec.start(first, first + bits);
+            decode_any_stream(dec, reinterpret_cast<const uint16_t *>(t.lut), out, sm, 0u, tiles, mine, up, down);
+            return;
+        }
+    }
+    Decoder<kLong> dec;
+    dec.words = words; dec.last_word = P.stream_cap_words - 1u;
+    dec.table = table;
+    dec.start(first, first + bits);
     uint32_t done = 0;
     if (whole && !dense) {
         done = tiles == kGroup ? decode_stream<kLong, kAhead, true>(dec, tab, out, sm, tiles, up, down)

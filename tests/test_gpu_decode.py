@@ -533,3 +533,25 @@ def test_longest_stream_of_long_codes_beside_the_widest_table():
     big, _ = zm.compress(synth.special_tensor("many_long", 45056, seed=4), 45056, 45056, 12)
     with pytest.raises(zm.ZipMoEError):
         gpu_decode_tensors([big])
+
+
+@pytest.mark.parametrize("n_present", [0, 9, 40, 300, 1 << 31])
+@pytest.mark.parametrize("C,W,max_len", [(16384, 4096, 12), (16384, 4096, 9), (4096, 1024, 11), (32768, 32768, 12)])
+def test_long_codes_do_not_depend_on_the_count_of_symbols_in_a_description(monkeypatch, n_present, C, W, max_len):
+    """the LDS table is sized by it, the values come from the blob's own table all the same"""
+    tensors = [synth.special_tensor(kind, n, seed=n) for kind in ("many_long", "wide", "gauss", "uniform_u16") for n in (3 * 16384 + 1234, 32768, 513)]
+    blobs = [zm.compress(w, C, W, max_len)[0] for w in tensors]
+    assert max(zm.blob_info(b).max_len for b in blobs) == max_len and max(zm.blob_info(b).n_present for b in blobs) == 256
+    describe = zm.blob_info
+
+    def with_another_count(blob):
+        info = describe(blob)
+        info.n_present = n_present
+        return info
+
+    monkeypatch.setattr(zm, "blob_info", with_another_count)
+    # each by itself, so that no other tensor of the launch makes room for it, then all in one launch
+    for w, b in zip(tensors, blobs):
+        assert np.array_equal(gpu_decode_tensors([b], stores=zm.STORES_STREAMING)[0], w)
+    for w, g in zip(tensors, gpu_decode_tensors(blobs)):
+        assert np.array_equal(g, w)
