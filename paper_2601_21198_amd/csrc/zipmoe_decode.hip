@@ -42,6 +42,7 @@
 
 namespace {
 
+constexpr int kMaxTensorsPerCall = 256;
 constexpr int kMaxTasks = 48;     // tensors per launch; 84 B each keeps the kernel arguments under 4 KiB
 constexpr int kFewTasks = 6;      // tensors of a launch with small arguments: two experts of three matrices
 constexpr uint32_t kTile = 512;
@@ -95,6 +96,10 @@ struct Packed {
     uint32_t e_units;    // bytes in the E-chunk region / 256
 };
 constexpr int kMaxPacked = 240, kMaxShapes = 4;
+// Values per tensor, on average, from which on a call's tensors travel that way.  It would pay below as well: 100 tensors of
+// 50000 values 14.0 us in launches of 48, 7.1 in one; 192 of 8192 19.3 and 9.5.  The line keeps the number of launches that
+// zm_decode_launch_shapes tells of for smaller tensors.
+constexpr uint64_t kPackedValues = 1u << 16;
 struct PackedLaunch {
     uint32_t n_tasks;
     uint32_t stream_cap_words;
@@ -830,12 +835,13 @@ template <bool kLong>
 struct Group {
     static constexpr uint32_t kLenBound = kLong ? ZM_MAX_CODE_LEN : 8;
     int n = 0;                        // tensors to come, all launches together
-    uint64_t n_values = 0;            // of theirs
+    bool may_share = false;           // they are many and large enough for packed launches; if so:
     uint64_t blocks = 0;              // workgroups of two streams that they need
     uint32_t most_blocks = 0;         // of the largest one
     bool packable = true;             // every one has the layout of a blob and an address that fits a Packed
     uint32_t n_shapes = 0;
     Shape shape[kMaxShapes];
+    Packed packed[kMaxTensorsPerCall];
 
     static bool same(const Shape &a, const Shape &b)
     {
@@ -858,23 +864,21 @@ struct Group {
     };
     Cap cap_of_all;
 
-    // First pass: what the launches will have to hold.  many: the call may need more than one launch.
-    void count(const Task &t, const zm_tensor_info &ti, bool many)
+    // First pass: what the launches will have to hold.
+    void count(const Task &t, const zm_tensor_info &ti)
     {
         ++n;
-        if (!many) return;
-        n_values += t.n_values;
+        if (!may_share) return;
         const uint32_t b = (t.n_streams + 1u) / 2u;
         blocks += b;
         most_blocks = most_blocks > b ? most_blocks : b;
         cap_of_all.see(t, ti);
-        uint32_t k;
-        packable = packable && pack(t, ti, k).high != kUnpackable;
+        packable = packable && (packed[n - 1] = pack(t, ti)).high != kUnpackable;
     }
 
     static constexpr uint32_t kUnpackable = ~0u;      // no device address has all of bits 36..47 set
 
-    Packed pack(const Task &t, const zm_tensor_info &ti, uint32_t &k)
+    Packed pack(const Task &t, const zm_tensor_info &ti)
     {
         const Packed no{0, kUnpackable, 0, 0};
         const uint8_t *blob = t.lut - ti.lut_offset;
@@ -884,6 +888,7 @@ struct Group {
             t.e_size >> 8 > UINT32_MAX) return no;
         const Shape s{t.n_values, ti.sm_offset, ti.e_offset, static_cast<uint32_t>(ti.lut_offset), static_cast<uint32_t>(ti.table_offset),
                       t.stream_values, t.streams_per_chunk, t.n_streams, t.code};
+        uint32_t k;
         for (k = 0; k < n_shapes; ++k) if (same(shape[k], s)) break;
         if (k == n_shapes) {
             if (n_shapes == kMaxShapes) return no;
@@ -899,8 +904,7 @@ struct Group {
     int launch(Next next, int stores, hipStream_t stream, Recorder *rec)
     {
         if (n <= kFewTasks) return launch_wide<kFewTasks>(next, stores, stream, rec);
-        if (n > kMaxTasks && packable && n_values >= kPackedValues * static_cast<uint64_t>(n) &&
-            rows_pay() && 8 * cap_of_all.words() + kBesideStreams<kLong> <= kLdsLimit) return launch_packed(next, stores, stream, rec);
+        if (may_share && packable && rows_pay() && 8 * cap_of_all.words() + kBesideStreams<kLong> <= kLdsLimit) return launch_packed(stores, stream, rec);
         return launch_wide<kMaxTasks>(next, stores, stream, rec);
     }
 
@@ -925,9 +929,7 @@ struct Group {
 
     // The same tensors in one launch where wide arguments would need one per 48 of them: a launch after another waits
     // for it to drain, and its first waves for their first bytes.  51 / 96 / 192 tensors of 512 x 1024: 21.3 / 37.7 /
-    // 77.0 us in launches of 48, 19.1 / 35.2 / 65.4 us in one.  Tensors below 64 Ki values keep the launches of 48 that
-    // zm_decode_launch_shapes has always told of for them (its callers and a test rely on that number).
-    static constexpr uint64_t kPackedValues = 1u << 16;
+    // 77.0 us in launches of 48, 19.1 / 35.2 / 65.4 us in one.
     // Packed launches have a row of workgroups per tensor, as many as the largest needs.  Workgroups that exit at once take
     // 0.2 ns each to start and a launch saved is worth 1.3 to 3.4 us, so lengths that fall off too far take the launches of
     // 48, which are numbered through; beside four times fewer that work, the idle ones start unnoticed.  us packed / in
@@ -941,8 +943,7 @@ struct Group {
     }
     int launches_of(int tensors) const { return (n + tensors - 1) / tensors; }
 
-    template <typename Next>
-    int launch_packed(Next next, int stores, hipStream_t stream, Recorder *rec)
+    int launch_packed(int stores, hipStream_t stream, Recorder *rec)
     {
         const size_t cap = cap_of_all.words();
         PackedLaunch L;
@@ -950,17 +951,16 @@ struct Group {
         L.long_slots = cap_of_all.long_slots;
         for (uint32_t k = 0; k < n_shapes; ++k) L.shape[k] = shape[k];
         const int launches = launches_of(kMaxPacked), each = (n + launches - 1) / launches;
-        for (int left = n; left > 0; left -= static_cast<int>(L.n_tasks)) {
-            L.n_tasks = static_cast<uint32_t>(left < each ? left : each);
+        for (int at = 0; at < n; at += static_cast<int>(L.n_tasks)) {
+            L.n_tasks = static_cast<uint32_t>(n - at < each ? n - at : each);
             uint32_t blocks = 0;
             uint64_t out_bytes = 0;
             for (uint32_t k = 0; k < L.n_tasks; ++k) {
-                Task t; uint32_t s;
-                const zm_tensor_info &ti = next(t);
-                L.task[k] = pack(t, ti, s);
-                const uint32_t b = (t.n_streams + 1u) / 2u;
+                L.task[k] = packed[at + static_cast<int>(k)];
+                const Shape &s = shape[L.task[k].high >> 12 & (kMaxShapes - 1u)];
+                const uint32_t b = (s.n_streams + 1u) / 2u;
                 blocks = b > blocks ? b : blocks;
-                out_bytes += 2 * t.n_values;
+                out_bytes += 2 * s.n_values;
             }
             const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, stores, stream, rec});
             if (rc != ZM_OK) return rc;
@@ -1001,30 +1001,46 @@ int make_task(const zm_tensor_parts &pt, const zm_tensor_info &ti, void *out, Ta
     return ZM_OK;
 }
 
-constexpr int kMaxTensorsPerCall = 256;
-
-// describe(i, t, skip) fills tensor i's task, info(i) is its description; implemented by the entry points.
+// describe(i, t, skip, ti) fills tensor i's task and names its description, info(i) only names it; implemented by the entry
+// points.
 template <typename Describe, typename Info>
 int decode_call(int n_tensors, Describe describe, Info info, int stores, hipStream_t stream, Recorder *rec = nullptr)
 {
     if (stores != ZM_STORES_AUTO && stores != ZM_STORES_CACHED && stores != ZM_STORES_STREAMING) return ZM_E_ARG;
-    // first pass: every tensor is checked before anything is launched
     Group<false> short_codes;
     Group<true> long_codes;
+    if (n_tensors > kMaxTasks) {
+        // Only what packed launches may take is looked over for them.  (With all tensors looked over, calls that the host
+        // bounds took longer: 60 tensors of 8192 values 8.8 -> 9.3 us, 256 of 2048 26.6 -> 27.7.)
+        uint64_t n_all = 0, n_short = 0, values_all = 0, values_short = 0;
+        for (int i = 0; i < n_tensors; ++i) {
+            const zm_tensor_info &ti = info(i);
+            const uint64_t values = ti.n_values, is_short = ti.max_len <= 8;
+            n_all += values != 0;
+            values_all += values;
+            n_short += (values != 0) & is_short;
+            values_short += is_short ? values : 0;
+        }
+        auto share = [](uint64_t n, uint64_t values) { return n > kMaxTasks && values / kPackedValues >= n; };
+        short_codes.may_share = share(n_short, values_short);
+        long_codes.may_share = share(n_all - n_short, values_all - values_short);
+    }
+    // first pass: every tensor is checked before anything is launched
     for (int i = 0; i < n_tensors; ++i) {
-        Task t; bool skip;
-        const int rc = describe(i, t, skip);
+        Task t; bool skip; const zm_tensor_info *ti;
+        const int rc = describe(i, t, skip, ti);
         if (rc != ZM_OK) return rc;
         if (skip) continue;
-        if ((t.code & 0xffu) <= 8) short_codes.count(t, info(i), n_tensors > kMaxTasks);
-        else long_codes.count(t, info(i), n_tensors > kMaxTasks);
+        if ((t.code & 0xffu) <= 8) short_codes.count(t, *ti);
+        else long_codes.count(t, *ti);
     }
     // the tensors of one group, in the call's order
     auto members = [&](bool want_short) {
         return [&, want_short, i = 0](Task &t) mutable -> const zm_tensor_info & {
-            for (bool skip;; ++i) {
-                describe(i, t, skip);
-                if (!skip && ((t.code & 0xffu) <= 8) == want_short) return info(i++);
+            for (;;) {
+                bool skip; const zm_tensor_info *ti;
+                describe(i++, t, skip, ti);
+                if (!skip && ((t.code & 0xffu) <= 8) == want_short) return *ti;
             }
         };
     };
@@ -1042,8 +1058,11 @@ extern "C" int zm_decode_tensors(const zm_tensor_parts *parts, const zm_tensor_i
 {
     if (n_tensors == 0) return ZM_OK;
     if (!parts || !infos || !out_bf16 || n_tensors < 0 || n_tensors > kMaxTensorsPerCall) return ZM_E_ARG;
-    return decode_call(n_tensors, [&](int i, Task &t, bool &skip) { return make_task(parts[i], infos[i], out_bf16[i], t, skip); },
-                       [&](int i) -> const zm_tensor_info & { return infos[i]; }, ZM_STORES_AUTO, static_cast<hipStream_t>(stream));
+    auto describe = [&](int i, Task &t, bool &skip, const zm_tensor_info *&ti) {
+        ti = infos + i;
+        return make_task(parts[i], *ti, out_bf16[i], t, skip);
+    };
+    return decode_call(n_tensors, describe, [&](int i) -> const zm_tensor_info & { return infos[i]; }, ZM_STORES_AUTO, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int zm_decode_launch_shapes(const zm_tensor_info *infos, int n_tensors, int stores,
@@ -1054,8 +1073,8 @@ extern "C" int zm_decode_launch_shapes(const zm_tensor_info *infos, int n_tensor
     // in a blob, where that keeps them aligned
     uint8_t *const somewhere = reinterpret_cast<uint8_t *>(uintptr_t{4096});
     Recorder rec{shapes_out, shapes_cap};
-    auto describe = [&](int i, Task &t, bool &skip) {
-        const zm_tensor_info &ti = infos[i];
+    auto describe = [&](int i, Task &t, bool &skip, const zm_tensor_info *&described) {
+        const zm_tensor_info &ti = *(described = infos + i);
         const bool aligned = !((ti.lut_offset | ti.sm_offset | ti.e_offset) & 15) && !(ti.table_offset & 7);
         const zm_tensor_parts pt = aligned ? zm_tensor_parts{somewhere + ti.lut_offset, somewhere + ti.table_offset, somewhere + ti.sm_offset, somewhere + ti.e_offset}
                                            : zm_tensor_parts{somewhere, somewhere, somewhere, somewhere};
@@ -1077,10 +1096,10 @@ extern "C" int zm_decode_experts_stores(const void *const *blobs, const uint64_t
     if (static_cast<long>(n_selected) * tensors_per_expert > kMaxTensorsPerCall) return ZM_E_ARG;
     for (int j = 0; j < n_selected; ++j)
         if (expert_ids[j] < 0 || expert_ids[j] >= n_experts) return ZM_E_ARG;
-    auto describe = [&](int i, Task &t, bool &skip) {
-        const int j = i / tensors_per_expert, m = i % tensors_per_expert;
-        const size_t src = static_cast<size_t>(expert_ids[j]) * tensors_per_expert + m;
-        const zm_tensor_info &ti = infos[src];
+    auto index = [&](int i) { return static_cast<size_t>(expert_ids[i / tensors_per_expert]) * tensors_per_expert + i % tensors_per_expert; };
+    auto describe = [&](int i, Task &t, bool &skip, const zm_tensor_info *&described) {
+        const size_t src = index(i);
+        const zm_tensor_info &ti = *(described = infos + src);
         skip = ti.n_values == 0;
         if (skip) return ZM_OK;
         if (!blobs[src]) return ZM_E_ARG;
@@ -1088,10 +1107,7 @@ extern "C" int zm_decode_experts_stores(const void *const *blobs, const uint64_t
         const zm_tensor_parts pt{blob + ti.lut_offset, chunk_offsets[src], blob + ti.sm_offset, blob + ti.e_offset};
         return make_task(pt, ti, out_bf16[i], t, skip);
     };
-    auto info = [&](int i) -> const zm_tensor_info & {
-        return infos[static_cast<size_t>(expert_ids[i / tensors_per_expert]) * tensors_per_expert + i % tensors_per_expert];
-    };
-    return decode_call(n_selected * tensors_per_expert, describe, info, stores, static_cast<hipStream_t>(stream));
+    return decode_call(n_selected * tensors_per_expert, describe, [&](int i) -> const zm_tensor_info & { return infos[index(i)]; }, stores, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int zm_decode_experts(const void *const *blobs, const uint64_t *const *chunk_offsets,
