@@ -101,7 +101,8 @@ typedef struct zm_tensor_info {
     uint32_t n_chunks;
     uint32_t max_len;        /* L, longest code length in use (>= 1)              */
     uint32_t lane_quantum;   /* q: unit, in bits, of the per-lane length bytes    */
-    uint32_t n_present;      /* exponent values that occur                        */
+    uint32_t n_present;      /* exponent values that occur; decode calls reserve
+                                their tables of codes longer than 8 bits by it    */
     uint32_t table_stride;   /* bytes of one chunk-table entry                    */
     uint32_t reserved;
 } zm_tensor_info;
@@ -169,8 +170,9 @@ int zm_validate_blob(const void *blob_host, size_t size);
 /* The hot call (Sec. 3.1 "Real-time Inference", steps 5-8, for experts whose
  * compressed form is resident; Sec. 3.3 recovery): decode the experts a MoE
  * layer's gate selected, in one kernel launch per 48 tensors of a code-table width class (codes of at most 8
- * bits, longer codes), or per 240 where a call of more than 48 tensors has blobs of at most four layouts and
- * 65536 values or more per tensor.
+ * bits, longer codes), or per 240 where more than 48 tensors of a class have blobs of at most four layouts, 65536
+ * values or more per tensor on average, and lengths that agree (a shared launch starts as many workgroups for every
+ * tensor as the longest needs: few of them, or at most four for one that has work, may find none).
  *
  *   blobs             host array [n_experts * tensors_per_expert] of DEVICE
  *                     pointers; entry e*tensors_per_expert + m is tensor m of
@@ -262,7 +264,8 @@ void zm_layer_destroy(zm_layer *layer);
  * themselves and without launching anything (for benchmarks and profiles that have to name the kernel):
  * one entry per kernel launch, in launch order.  Host only. */
 typedef struct zm_launch_shape {
-    uint32_t round_symbols;        /* symbols a lane decodes per 32-bit window: 4 (codes <= 8 bits) or 2   */
+    uint32_t round_symbols;        /* symbols that are sure to fit a 32-bit window: 4 (codes <= 8 bits) or 2
+                                      (longer codes, of which four are tried first)                        */
     uint32_t waves_per_workgroup;  /* streams that share a workgroup                                       */
     uint32_t streaming_stores;     /* 1: non-temporal stores                                               */
     uint32_t workgroups;           /* grid x: workgroups of the largest tensor of the launch, or of all its
