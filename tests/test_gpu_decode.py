@@ -445,16 +445,18 @@ def test_many_tensors_share_a_launch(n_tensors, max_len, stream_values, launches
     assert np.array_equal(got[-1], zo.decode(blobs[-1]))
 
 
-@pytest.mark.parametrize("count,stores", [(7, zm.STORES_AUTO), (48, zm.STORES_STREAMING), (2, zm.STORES_CACHED)])
-def test_launches_numbered_through_tensors_of_very_different_lengths(count, stores):
-    """one long tensor beside short ones: the launch counts through the workgroups of all of them"""
-    lengths = [(9 << 20) + 5] + [1 + 1237 * i for i in range(count - 1)]
-    rng = np.random.default_rng(count)
-    order = rng.permutation(count)
-    tensors = [[synth.special_tensor("gauss", lengths[i], seed=3 + int(i))] for i in order]
-    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, 8, stores)
-    assert len(shapes) == 1 and shapes[0].tensors == count
-    assert shapes[0].workgroups == sum(-(-(-(-lengths[i] // 4096)) // 2) for i in range(count)) if count > 2 else True
+@pytest.mark.parametrize("count,stores,through", [(7, zm.STORES_AUTO, True), (48, zm.STORES_STREAMING, True), (3, zm.STORES_AUTO, True),
+                                                  (6, zm.STORES_STREAMING, True), (2, zm.STORES_CACHED, False)])
+@pytest.mark.parametrize("max_len", [8, 12])
+def test_launches_numbered_through_tensors_of_very_different_lengths(count, stores, through, max_len):
+    """one long tensor beside short ones: the launch counts through the workgroups of all of them, unless few would be idle"""
+    lengths = [(9 << 20) + 5] + [(1 if max_len == 8 else 3000) + 1237 * i for i in range(count - 1)]
+    order = np.random.default_rng(count).permutation(count)
+    tensors = [[synth.special_tensor("gauss" if max_len == 8 else "wide", lengths[i], seed=3 + int(i))] for i in order]
+    flat, blobs, got, shapes = layer_calls(tensors, 16384, 4096, max_len, stores)
+    assert all((zm.blob_info(b).max_len > 8) == (max_len > 8) for b in blobs)
+    workgroups = [-(-(-(-n // 4096)) // 2) for n in lengths]
+    assert [(s.tensors, s.workgroups) for s in shapes] == [(count, sum(workgroups) if through else max(workgroups))]
     for w, g in zip(flat, got):
         assert np.array_equal(g, w)
 
@@ -468,6 +470,34 @@ def test_raw_and_long_streams_in_groups_of_tiles(n, W):
     for stores in (None, zm.STORES_CACHED, zm.STORES_STREAMING):
         for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
             assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
+
+
+@pytest.mark.parametrize("layouts,stores,max_len,launches", [(4, zm.STORES_CACHED, 8, [60]), (4, zm.STORES_STREAMING, 8, [60]), (4, zm.STORES_CACHED, 12, [60]),
+                                                             (4, zm.STORES_STREAMING, 12, [60]), (5, zm.STORES_CACHED, 8, [48, 12])])
+def test_many_tensors_share_a_launch_with_every_kind_of_store(layouts, stores, max_len, launches):
+    """more than the 36 MiB up to which device-scope stores are used; and more layouts than a shared launch has room for"""
+    tensors = [[synth.special_tensor("gauss" if max_len == 8 else "wide", 340_000 + 4099 * (i % layouts), seed=i % 4)] for i in range(60)]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, max_len, stores)
+    assert sum(2 * w.size for w in flat[:48]) <= 36 << 20 < sum(2 * w.size for w in flat)
+    assert [s.tensors for s in shapes] == launches
+    for i, (w, g) in enumerate(zip(flat, got)):
+        assert np.array_equal(g, w), i
+
+
+def test_more_tensors_of_long_codes_than_one_launch_takes():
+    tensors = [[synth.special_tensor("wide", (1 << 16) + 4099 + i % 3, seed=i % 4)] for i in range(241)]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, 12)
+    assert [(s.tensors, s.round_symbols) for s in shapes] == [(121, 2), (120, 2)]
+    for i, (w, g) in enumerate(zip(flat, got)):
+        assert np.array_equal(g, w), i
+
+
+@pytest.mark.parametrize("n", [(18 << 20) - 1, 18 << 20, (18 << 20) + 1])
+def test_outputs_at_the_line_between_the_store_kinds(n):
+    """36 MiB in one launch"""
+    w = synth.special_tensor("gauss", n, seed=n & 7)
+    blob, _ = zm.compress(w, 16384, 4096)
+    assert np.array_equal(gpu_decode_tensors([blob], stores=zm.STORES_CACHED)[0], w)
 
 
 def test_outputs_between_the_store_kinds():
