@@ -224,8 +224,10 @@ constexpr uint32_t kTableEntries = 256;   // the LDS table of codes of at most e
 // larger one, from there on the second, and they meet in T.  So a code of any length takes one LDS read and no branch.
 // (Before, the table held the 256 beginnings, and a wave in which one lane met a long code, one step in two, branched to
 // a second look-up; and a window was refilled after every two symbols.  One / two / four / eight experts of 1024 x 2048 x 3
-// with codes of up to 12 bits, streaming stores: 9.5 / 13.2 / 19.8 / 31.8 us then, 7.0 / 9.8 / 15.6 / 27.7 us now.)  At most half as many beginnings are shared as there are symbols: each by two codes or more.  The table has room
-// for that many; where a description counts fewer symbols than the blob's table has, codes are looked up in that one.
+// with codes of up to 12 bits, streaming stores, inputs in the last-level cache: 9.5 / 13.2 / 19.8 / 31.8 us then,
+// 7.0 / 9.8 / 15.6 / 27.8 us now.)
+// At most half as many beginnings are shared as there are symbols: each by two codes or more.  The table has room for that
+// many; where a description counts fewer symbols than the blob's table has, codes are looked up in that one.
 struct LongTable {
     uint32_t shift;      // 32 - L
     int32_t skip;        // (T << (L-8)) - T
@@ -795,9 +797,10 @@ int launch_args(void *args, const Plan &p)
 
 // Whether a launch numbers its workgroups through all tensors instead of giving every tensor as many as the largest has.
 // Workgroups that exit at once still have to be started; finding the tensor by its first workgroup costs every wave one
-// more read.  Calls of tensors whose lengths fall off, us with a workgroup row per tensor / numbered through:
-//   24 tensors of 2.1 M values down to 1/3: 22.3 / 22.3, to 1/30: 11.7 / 10.3, to 1/300: 9.7 / 8.0
-//   48 tensors of 0.5 M values to 1/3: 10.4 / 10.7, to 1/30: 9.4 / 7.0;  of 0.13 M values to 1/300: 5.8 / 5.8
+// more read.  Calls of tensors whose lengths fall off, with everything marshalled beforehand (from Python a call of 24 tensors
+// is bound by its marshalling), us with a workgroup row per tensor / numbered through:
+//   24 tensors of 2.1 M values down to 1/3: 17.6 / 17.7, to 1/30: 10.0 / 9.0, to 1/300: 9.5 / 7.5
+//   48 tensors of 0.5 M values to 1/3: 9.4 / 9.4, to 1/30: 9.1 / 6.8;  of 0.13 M values to 1/300: 5.9 / 5.9
 bool number_through(uint64_t useful, uint64_t started)
 {
     const uint64_t idle = started - useful;
