@@ -506,7 +506,7 @@ def main() -> int:
     sel = [layers[0].infos[int(e) * t_per + m] for e in routes[0][0] for m in range(t_per)]
     shapes = zm.decode_launch_shapes(sel, zm.STORES_STREAMING)
     kernel_names = ["zm_decode_kernel<%s,%d,%s>" % ("true" if sh.round_symbols == 2 else "false", sh.waves_per_workgroup,
-                                                     "kStreaming" if sh.streaming_stores else "kThrough or kOrdinary")
+                                                     "kStreaming or kStreamingMany" if sh.streaming_stores else "kThrough or kOrdinary")
                     for sh in shapes]
 
     result = {

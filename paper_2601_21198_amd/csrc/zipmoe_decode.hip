@@ -175,7 +175,8 @@ __device__ __forceinline__ void recover4(uint32_t e4, uint32_t sm4, uint32_t &w0
 //   kThrough    device-scope stores: the L2 caches keep the line and pass it on to the last-level cache at once
 //   kStreaming  non-temporal: the output is larger than the last-level cache, or the caller said that its buffers are
 //               not cache-resident
-enum Stores { kOrdinary, kThrough, kStreaming };
+//   kStreamingMany  the same in launches of many streams of one group of tiles, with per-lane addresses
+enum Stores { kOrdinary, kThrough, kStreaming, kStreamingMany };
 
 // Where they go: the first n_values of stream_base, lane j's eight words of tile k at k * kTile + 8 * j.  Buffer stores,
 // because 128-bit device-scope stores exist as these only; the descriptor covers the wave's words and nothing else.
@@ -195,9 +196,9 @@ struct Sink {
         __builtin_amdgcn_raw_buffer_store_b128((u32x4){w.x, w.y, w.z, w.w}, words, static_cast<int>(lane_offset + tile * (2u * kTile)), 0, kFlags);
     }
 
-    // for a lane that owns fewer than eight values of the tile: one word at a time, and those past the end of the
+    // for a lane that owns `left` < 8 values of the tile: one word at a time, and those past the end of the
     // stream are past the end of the descriptor too, which drops them
-    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w) const
+    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w, uint32_t) const
     {
         const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
@@ -205,6 +206,31 @@ struct Sink {
             __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1))), words,
                                                   static_cast<int>(lane_offset + tile * (2u * kTile) + 2u * q), 0, 0);
     }
+};
+
+// Non-temporal, at an address that is a multiple of 16: four adjacent word stores, which the compiler merges into one.
+__device__ __forceinline__ void store_streaming(uint16_t *p, uint4 w)
+{
+    uint32_t *q = reinterpret_cast<uint32_t *>(__builtin_assume_aligned(p, 16));
+    __builtin_nontemporal_store(w.x, q); __builtin_nontemporal_store(w.y, q + 1);
+    __builtin_nontemporal_store(w.z, q + 2); __builtin_nontemporal_store(w.w, q + 3);
+}
+
+// The first `left` < 8 values of w.
+__device__ __forceinline__ void store_some(uint16_t *p, uint4 w, uint32_t left)
+{
+    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q)
+        if (q < left) p[q] = static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1)));
+}
+
+template <>
+struct Sink<kStreamingMany> {
+    uint16_t *lane_words;
+    __device__ __forceinline__ Sink(uint16_t *stream_base, uint32_t, uint32_t lane) : lane_words(stream_base + 8u * lane) {}
+    __device__ __forceinline__ void store(uint32_t tile, uint4 w) const { store_streaming(lane_words + tile * kTile, w); }
+    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w, uint32_t left) const { store_some(lane_words + tile * kTile, w, left); }
 };
 
 __device__ __forceinline__ uint4 recover8(uint2 e, uint2 sm)
@@ -360,17 +386,25 @@ struct Decoder {
 // One byte per value of a stream (sign-mantissa bytes, or a raw chunk's exponent bytes), read as 64 bits per lane and
 // tile.  The descriptor covers the stream's bytes, rounded up to whole groups of eight (the section is padded): a lane
 // or a tile past them reads zeros and touches no memory.
+template <Stores kStores>
 struct ByteSource {
     __amdgpu_buffer_rsrc_t bytes;
     uint32_t lane_offset;
+    const uint8_t *lane_bytes;
     __device__ __forceinline__ ByteSource(const uint8_t *stream_base, uint32_t n_values, uint32_t lane)
         : bytes(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(stream_base), 0, static_cast<int>((n_values + 7u) & ~7u), kRawBuffer)),
-          lane_offset(lane * 8u) {}
+          lane_offset(lane * 8u), lane_bytes(stream_base + 8u * lane) {}
     __device__ __forceinline__ uint2 load(uint32_t tile) const
     {
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(bytes, static_cast<int>(lane_offset + tile * kTile), 0, 0);
         return make_uint2(v.x, v.y);
+    }
+    // of a tile that lies in the stream
+    __device__ __forceinline__ uint2 load_inside(uint32_t tile) const
+    {
+        if constexpr (kStores == kStreamingMany) return *reinterpret_cast<const uint2 *>(lane_bytes + tile * kTile);
+        else return load(tile);
     }
 };
 
@@ -381,7 +415,7 @@ __device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t t
     const int32_t left = mine - static_cast<int32_t>(tile * kTile);
     const uint4 w = recover8(e, sm);
     if (left >= 8) out.store(tile, w);
-    else if (left > 0) out.store_partial(tile, w);
+    else if (left > 0) out.store_partial(tile, w, static_cast<uint32_t>(left));
 }
 
 // Decodes a coded stream from both ends: pair p is tile p (upward chain) and tile tiles - 1 - p (downward chain), and
@@ -396,7 +430,7 @@ constexpr int kPairs = kGroup / 2;
 // Returns the first pair that is not done: with long codes, a pair in which a lane's four symbols had more bits than a
 // window is left alone, with the decoder as it was in front of it.
 template <bool kLong, int kAhead, bool kOneGroup, Stores kStores>
-__device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+__device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource<kStores> &sm,
                                                   uint32_t tiles, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
     for (uint32_t first = 0;;) {
@@ -417,16 +451,16 @@ __device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uin
             out.store(lo, recover8(make_uint2(a.x, b.x), up[i]));
             out.store(hi, recover8(make_uint2(b.y, a.y), down[i]));
             if (i + kAhead < kPairs) {
-                up[i + kAhead] = sm.load(lo + kAhead);
-                down[i + kAhead] = sm.load(hi - kAhead);
+                up[i + kAhead] = sm.load_inside(lo + kAhead);
+                down[i + kAhead] = sm.load_inside(hi - kAhead);
             }
         }
         first += kPairs;
         if (kOneGroup || 2u * first >= tiles) return first;
 #pragma unroll
         for (int i = 0; i < kPairs; ++i) {
-            up[i] = sm.load(first + i);
-            down[i] = sm.load(tiles - 1u - first - i);
+            up[i] = sm.load_inside(first + i);
+            down[i] = sm.load_inside(tiles - 1u - first - i);
         }
     }
 }
@@ -436,7 +470,7 @@ __device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uin
 // caller has asked for two pairs (up[0], up[1]); kept rolled, since the unrolled loop with its partial tiles costs the
 // whole kernel 20 registers.
 template <bool kLong, bool kFromBlob, Stores kStores>
-__device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+__device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource<kStores> &sm,
                                                   uint32_t lo, uint32_t tiles, int32_t mine, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
 #pragma unroll 1
@@ -460,7 +494,7 @@ __device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec
 // A chunk that is stored raw: its exponent bytes lie in memory as they are.  Four tiles are asked for before the first
 // is merged.
 template <Stores kStores>
-__device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const ByteSource &raw, const ByteSource &sm,
+__device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const ByteSource<kStores> &raw, const ByteSource<kStores> &sm,
                                                  uint32_t tiles, int32_t mine)
 {
     for (uint32_t first = 0; first < tiles; first += kPairs) {
@@ -548,12 +582,18 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     // arrive sooner.  A wave waits for such a later load behind its own earlier stores, though, and non-temporal
     // stores take long to be acknowledged: with them all eight tiles of a group are asked for up front.  So they are
     // in streams of several groups, of which fewer start together.
-    constexpr int kAhead = kStores == kStreaming ? kPairs : 2;
+    constexpr int kAhead = kStores == kStreaming || kStores == kStreamingMany ? kPairs : 2;
     const bool coded = mode == ZM_MODE_CODED;
     const bool whole = sn % (kGroup * kTile) == 0;
     uint2 up[kPairs], down[kPairs];
-    const ByteSource sm(t.sm + v0, sn, lane);
-    if (coded && active) {
+    const ByteSource<kStores> sm(t.sm + v0, sn, lane);
+    if (kStores == kStreamingMany && coded && active && whole) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            up[i] = sm.load_inside(i);
+            down[i] = sm.load_inside(tiles - 1u - i);
+        }
+    } else if (coded && active) {
 #pragma unroll
         for (int i = 0; i < kPairs; ++i) {
             if (i < 2 || (whole && (i < kAhead || tiles > kGroup))) {
@@ -627,7 +667,7 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     const Sink<kStores> out(t.out + v0, sn, lane);
 
     if (!coded) {
-        merge_raw_stream(out, ByteSource(raw, sn, lane), sm, tiles, mine);
+        merge_raw_stream(out, ByteSource<kStores>(raw, sn, lane), sm, tiles, mine);
         return;
     }
     // a6: this lane's bitstream has 8 * tiles + quantum * (its length byte) bits and starts where
@@ -651,8 +691,9 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     dec.start(first, first + bits);
     uint32_t done = 0;
     if (whole && !dense) {
-        done = tiles == kGroup ? decode_stream<kLong, kAhead, true>(dec, tab, out, sm, tiles, up, down)
-                               : decode_stream<kLong, kPairs, false>(dec, tab, out, sm, tiles, up, down);
+        // kStreamingMany: streams have no more than one group
+        done = kStores == kStreamingMany || tiles == kGroup ? decode_stream<kLong, kAhead, true>(dec, tab, out, sm, tiles, up, down)
+                                                            : decode_stream<kLong, kPairs, false>(dec, tab, out, sm, tiles, up, down);
         if (!kLong || 2u * done >= tiles) return;
         up[0] = sm.load(done); down[0] = sm.load(tiles - 1u - done);
         up[1] = sm.load(done + 1u); down[1] = sm.load(tiles - 2u - done);
@@ -702,21 +743,15 @@ __global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restri
         const uint4 w = recover8(ev[k], sv[k]);
         if constexpr (kStores == kThrough) {
             if (i + 8 <= n) sink.store(static_cast<uint32_t>(k), w);
-            else if (i < n) sink.store_partial(static_cast<uint32_t>(k), w);
+            else if (i < n) sink.store_partial(static_cast<uint32_t>(k), w, static_cast<uint32_t>(n - i));
         } else if (i + 8 <= n) {
             if constexpr (kStores == kStreaming) {
-                // four adjacent word stores, which the compiler merges into one
-                uint32_t *p = reinterpret_cast<uint32_t *>(__builtin_assume_aligned(out + i, 16));
-                __builtin_nontemporal_store(w.x, p); __builtin_nontemporal_store(w.y, p + 1);
-                __builtin_nontemporal_store(w.z, p + 2); __builtin_nontemporal_store(w.w, p + 3);
+                store_streaming(out + i, w);
             } else {
                 *reinterpret_cast<uint4 *>(out + i) = w;
             }
         } else if (i < n) {
-            const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (uint32_t q = 0; q < 8; ++q)
-                if (q < n - i) out[i + q] = static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1)));
+            store_some(out + i, w, static_cast<uint32_t>(n - i));
         }
     }
 }
@@ -752,6 +787,13 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // three rows and lose in that one); from 64 MB on both are within 2 % of each other.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
+// Launches of more streams than this, of one group of tiles each, take kStreamingMany.  Its kernel has 78 registers and six waves
+// per SIMD where kStreaming has 70 and seven, which long launches have no use for (7168 streams then are at work at a time)
+// and short ones have.  Experts of 2048 x 1408 x 3 (2112 streams each), us with kStreaming / kStreamingMany, nothing cached:
+//   1: 7.62 / 7.68   2: 13.07 / 13.12   4: 22.94 / 22.94   5: 27.29 / 26.92   8: 41.17 / 40.98   10: 48.40 / 47.96
+// all cached, 4: 19.07 / 19.24; streams of 1024 values, 4: 19.26 / 20.36; of 16384 values, 8: 54.48 / 54.61.
+constexpr uint64_t kManyStreams = 9216;
+
 // Where the shapes of a call's launches go when they are asked for instead of launched.
 struct Recorder {
     zm_launch_shape *out;
@@ -765,6 +807,8 @@ struct Plan {
     uint32_t n_tasks;
     size_t lds;              // dynamic part: the streams
     uint64_t out_bytes;
+    uint64_t n_streams;
+    uint32_t max_stream;     // values of the longest one
     int stores;
     hipStream_t stream;
     Recorder *rec;
@@ -791,6 +835,9 @@ int launch_args(void *args, const Plan &p)
         ++p.rec->n;
         return ZM_OK;
     }
+    if constexpr (!kLong && kWaves == 2) {
+        if (streaming && p.n_streams > kManyStreams && p.max_stream == kGroup * kTile) return launch_kernel<kLong, kWaves, kStreamingMany, Args>(args, p);
+    }
     if (streaming) return launch_kernel<kLong, kWaves, kStreaming, Args>(args, p);
     return p.out_bytes <= kThroughBytes ? launch_kernel<kLong, kWaves, kThrough, Args>(args, p) : launch_kernel<kLong, kWaves, kOrdinary, Args>(args, p);
 }
@@ -808,21 +855,22 @@ bool number_through(uint64_t useful, uint64_t started)
 }
 
 template <bool kLong, int kWaves, int N>
-int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream, Recorder *rec)
+int launch_tasks(Launch<N, true> &L, size_t cap, uint32_t max_stream, int stores, hipStream_t stream, Recorder *rec)
 {
     const size_t streams = 4 * kWaves * cap, lds = streams + (kLong ? 4 * long_table_words(L.long_slots) : 0);   // dynamic part
     if (streams + kBesideStreams<kLong> > kLdsLimit) {
-        if constexpr (kWaves > 1) return launch_tasks<kLong, kWaves / 2>(L, cap, stores, stream, rec);
+        if constexpr (kWaves > 1) return launch_tasks<kLong, kWaves / 2>(L, cap, max_stream, stores, stream, rec);
         else return ZM_E_ARG;                   // stream too long to stage in LDS
     }
     uint32_t blocks = 0;            // of the largest tensor
-    uint64_t total = 0, out_bytes = 0;
+    uint64_t total = 0, out_bytes = 0, n_streams = 0;
     for (uint32_t k = 0; k < L.n_tasks; ++k) {
         const uint32_t b = (L.task[k].n_streams + kWaves - 1) / kWaves;
         L.first_block[k] = static_cast<uint32_t>(total);
         blocks = b > blocks ? b : blocks;
         total += b;
         out_bytes += 2 * L.task[k].n_values;
+        n_streams += L.task[k].n_streams;
     }
     if (!blocks) return ZM_OK;
     // without the workgroup numbers the arguments are the same up to the end of the tasks
@@ -831,8 +879,8 @@ int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream,
     static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
     // a launch admits 2^32 - 1 threads in x
     if (total <= UINT32_MAX / (64u * kWaves) && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
-        return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, out_bytes, stores, stream, rec});
-    return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, out_bytes, stores, stream, rec});
+        return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, out_bytes, n_streams, max_stream, stores, stream, rec});
+    return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, out_bytes, n_streams, max_stream, stores, stream, rec});
 }
 
 // Collects the tensors of one round length and launches them.
@@ -926,7 +974,7 @@ struct Group {
             }
             L.long_slots = cap.long_slots;
             L.stream_cap_words = static_cast<uint32_t>(cap.words());
-            const int rc = launch_tasks<kLong, 2>(L, cap.words(), stores, stream, rec);
+            const int rc = launch_tasks<kLong, 2>(L, cap.words(), cap.max_stream, stores, stream, rec);
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;
@@ -959,15 +1007,16 @@ struct Group {
         for (int at = 0; at < n; at += static_cast<int>(L.n_tasks)) {
             L.n_tasks = static_cast<uint32_t>(n - at < each ? n - at : each);
             uint32_t blocks = 0;
-            uint64_t out_bytes = 0;
+            uint64_t out_bytes = 0, n_streams = 0;
             for (uint32_t k = 0; k < L.n_tasks; ++k) {
                 L.task[k] = packed[at + static_cast<int>(k)];
                 const Shape &s = shape[L.task[k].high >> 12 & (kMaxShapes - 1u)];
                 const uint32_t b = (s.n_streams + 1u) / 2u;
                 blocks = b > blocks ? b : blocks;
                 out_bytes += 2 * s.n_values;
+                n_streams += s.n_streams;
             }
-            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, stores, stream, rec});
+            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, n_streams, cap_of_all.max_stream, stores, stream, rec});
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;

@@ -492,6 +492,27 @@ def test_more_tensors_of_long_codes_than_one_launch_takes():
         assert np.array_equal(g, w), i
 
 
+@pytest.mark.parametrize("lengths", [[9216 * 4096], [9216 * 4096 + 1], [14_000_003] * 3, [38_000_001, 5, 70_000], [5_000_011] * 8,
+                                     [660_007] * 60], ids=["at the line", "above it", "three", "numbered", "eight", "shared"])
+def test_launches_of_many_streams_with_streaming_stores(lengths):
+    """more than 9216 streams of 4096 values: one tensor, row launches of few and of many, a numbered one and a shared one"""
+    w = synth.special_tensor("gauss", max(lengths), seed=5)
+    tensors = [[w[7 * i: 7 * i + n] if 7 * i + n <= w.size else w[:n]] for i, n in enumerate(lengths)]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, 8, zm.STORES_STREAMING)
+    assert len(shapes) == 1 and shapes[0].streaming_stores == 1
+    for a, g in zip(flat, got):
+        assert np.array_equal(g, a)
+
+
+def test_a_launch_of_many_streams_holds_tensors_of_every_kind():
+    """raw chunks, cut-off streams and streams shorter than a group beside whole ones, in one launch of more than 9216 streams"""
+    tensors = [synth.special_tensor("gauss", 40_000_003, 5)] + [synth.special_tensor(kind, n, n) for kind in ("uniform_u16", "rare_last", "all_equal")
+                                                               for n in (1, 9, 511, 4095, 4097, 50_001)]
+    blobs = [zm.compress(w, 16384, 4096 if i % 2 == 0 else 512, 8)[0] for i, w in enumerate(tensors)]
+    for w, g in zip(tensors, gpu_decode_tensors(blobs, stores=zm.STORES_STREAMING)):
+        assert np.array_equal(g, w)
+
+
 @pytest.mark.parametrize("n", [(18 << 20) - 1, 18 << 20, (18 << 20) + 1])
 def test_outputs_at_the_line_between_the_store_kinds(n):
     """36 MiB in one launch"""
