@@ -787,10 +787,10 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // three rows and lose in that one); from 64 MB on both are within 2 % of each other.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
-// Launches of more streams than this, of one group of tiles each, take kStreamingMany.  Its kernel has 78 registers and six waves
-// per SIMD where kStreaming has 70 and seven, which long launches have no use for (7168 streams then are at work at a time)
-// and short ones have.  Experts of 2048 x 1408 x 3 (2112 streams each), us with kStreaming / kStreamingMany, nothing cached:
-//   1: 7.62 / 7.68   2: 13.07 / 13.12   4: 22.94 / 22.94   5: 27.29 / 26.92   8: 41.17 / 40.98   10: 48.40 / 47.96
+// Launches of more streams than this, of one group of tiles each, take kStreamingMany.  Its kernel has 74 registers and six waves
+// per SIMD where that of kStreaming has 70 and seven: 6144 and 7168 streams at work at a time, of which short launches prefer
+// the larger and long ones, bound by bandwidth, the smaller number.  Experts of 2048 x 1408 x 3 (2112 streams each), us with kStreaming / kStreamingMany, nothing cached:
+//   1: 7.62 / 7.68   2: 13.07 / 13.12   4: 22.94 / 22.94   5: 27.29 / 26.91   8: 41.08 / 40.85   10: 48.36 / 47.99
 // all cached, 4: 19.07 / 19.24; streams of 1024 values, 4: 19.26 / 20.36; of 16384 values, 8: 54.48 / 54.61.
 constexpr uint64_t kManyStreams = 9216;
 
