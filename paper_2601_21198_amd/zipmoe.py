@@ -370,9 +370,10 @@ class ExpertLayer:
         ids = (ctypes.c_int32 * len(expert_ids))(*[int(e) for e in expert_ids])
         t = self.tensors_per_expert
         bases = [b.data_ptr() for b in out_buffers]
-        offsets = [2 * starts[m] for m in range(t)] if bases else []      # one for every tensor of an expert, or an IndexError
+        # one for every tensor of an expert, or an IndexError (a list, what alloc_outputs returns, is read at once)
+        offsets = [2 * s for s in (starts[:t] if type(starts) is list and len(starts) >= t else [starts[m] for m in range(t if bases else 0)])]
         outs = (ctypes.c_void_p * (len(expert_ids) * t))(*[base + o for base in bases for o in offsets])
-        f = lib().zm_decode_experts_stores
+        f = (_lib or lib()).zm_decode_experts_stores
         args = (self._ptr_blobs, self._ptr_tables, self._ptr_infos, self.n_experts, t, ids, len(expert_ids), outs, stores)
 
         def call(stream: int = 0):
