@@ -377,9 +377,9 @@ int zm_cache_image_bytes(const zm_cache_config *config, const zm_tensor_info *in
 /* Packs what the cache ever copies of one expert -- the SM sections of its
  * tensors, then their E-chunk regions, laid out as in a pool slot -- into
  * `image` (HOST memory of zm_cache_image_bytes bytes, pinned for asynchronous
- * copies).  With such images a fetch moves an expert's missing parts with one
- * copy (both parts) or one per part instead of one per tensor and part; each
- * host-to-device copy has a fixed cost of some 10 us.  host_blobs: as for
+ * transfers).  With such images a fetch moves an expert's missing parts as one
+ * piece (both parts) or one per part instead of one per tensor and part; where
+ * pieces are copied, each costs some 10 us beside its bytes.  host_blobs: as for
  * zm_cache_create.  ZM_E_ARG, ZM_E_SIZE. */
 int zm_cache_pack_expert(const zm_cache_config *config, const zm_tensor_info *infos, const void *const *host_blobs,
                          int expert, void *image, size_t image_bytes);
