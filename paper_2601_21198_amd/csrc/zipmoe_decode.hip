@@ -37,6 +37,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <type_traits>
 
 #include "zipmoe.h"
 
@@ -57,18 +58,31 @@ struct Task {
     const uint8_t *echunks;   // E-chunk region (what the blob holds from e_offset on)
     const uint64_t *table;    // chunk table (entries of 8 + 4*(streams_per_chunk+1) bytes, rounded up to 8); offsets count from the start of the blob
     uint16_t *out;
-    uint64_t n_values;
     uint64_t e_offset;        // blob offset of the E-chunk region
     uint64_t e_size;          // bytes in the E-chunk region
     uint32_t stream_values;
     uint32_t streams_per_chunk;
+    uint32_t per_chunk;       // reciprocal of streams_per_chunk, see chunk_of
     uint32_t n_streams;
-    uint32_t code;            // longest code length | lane quantum << 8
+    uint32_t last_values;     // values of the last stream
+    uint32_t code;            // longest code length | shift of the reciprocal << 4 | lane quantum << 9
+    __host__ __device__ uint64_t n_values() const { return static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values; }
 };
+__host__ __device__ constexpr uint32_t max_len_of(uint32_t code) { return code & 15u; }
+__host__ __device__ constexpr uint32_t quantum_of(uint32_t code) { return code >> 9; }
+
+// The chunk that stream g lies in, g / streams_per_chunk: with 2^k the next power of two from the divisor on, r = ceil(2^(31+k) / divisor)
+// is below 2^32 and exact for every g < 2^31.  (The compiler's division by a value it does not know goes through the
+// floating-point reciprocal, 30 instructions in front of a wave's first read.)
+__device__ __forceinline__ uint32_t chunk_of(uint32_t g, uint32_t per_chunk, uint32_t code)
+{
+    return __umulhi(2u * g, per_chunk) >> (code >> 4 & 31u);
+}
 
 // Kernel arguments of a launch of up to N tensors.  The runtime copies all of them, used or not, into the device's
-// memory for every launch, so a launch of few tensors takes the small kind: one matrix of 256 x 512 called again and again
-// 7.2 us with 4 KB, 6.9 with 0.5, waited for every time 21.6 and 16.5; three of 2048 x 1408 8.7 and 8.5.
+// memory for every launch, so a launch of few tensors takes a smaller kind: one matrix of 256 x 512 called again and again
+// 7.2 us with 4 KB, 6.9 with 0.5, waited for every time 21.6 and 16.5; three of 2048 x 1408 8.7 and 8.5.  (Those that are whole blobs
+// cut alike a smaller one still, Few.)
 // grid: x = workgroup inside the tensor, y = tensor.  kFlat, for tensors of very different lengths: x counts through
 // the workgroups of all tensors, first_block[k] being the first one of tensor k.  (A kind of its own: a flag among the
 // arguments would be one more read that every wave waits for.)
@@ -86,9 +100,9 @@ static_assert(kMaxTasks <= 64, "a wave finds its tensor with one value per lane"
 
 // What the tensors of one shape share, and what is left of a tensor: 16 bytes, so that a launch takes five times as many.
 struct Shape {
-    uint64_t n_values, sm_offset, e_offset;
+    uint64_t sm_offset, e_offset;
     uint32_t lut_offset, table_offset;
-    uint32_t stream_values, streams_per_chunk, n_streams, code;
+    uint32_t stream_values, streams_per_chunk, per_chunk, n_streams, last_values, code;
 };
 struct Packed {
     uint32_t blob;       // bits 4..35 of the blob's address
@@ -110,6 +124,23 @@ struct PackedLaunch {
     Shape shape[kMaxShapes];
 };
 static_assert(sizeof(PackedLaunch) <= 4096, "kernel arguments must stay under 4 KiB");
+
+// Up to six blobs cut alike, in 112 bytes, because the host takes longer for a launch with more: 2.75 us up to 112 B, 3.45 from 116 B on,
+// 4.2 with 4 KB (a kernel that does nothing).  Prepared calls from Python, in turn in one process: one tensor 3.8 -> 3.55 us, three 4.1 ->
+// 3.65, six 4.2 -> 3.75 against a Launch<6>.  Unpacking them costs a wave a few scalar instructions: one matrix of 256 x 512 3.88 -> 3.92 us
+// on the GPU.  (With the first 56 bytes preloaded into scalar registers, so that a wave's first read is the chunk table's, launches
+// of many short waves were slower than with reads: 4096 streams of 512 values 3.65 -> 3.75 us.)
+struct Few {
+    // [0] stream_values / 512 | longest code length << 7 | log2 of streams_per_chunk << 11 | lane quantum << 16 | long_slots << 24
+    // [1] n_streams  [2] last_values | lut_offset << 16  [3] table_offset  [4] sm_offset / 256  [5] e_offset / 256
+    uint32_t lead[6];
+    const uint8_t *low;            // the lowest blob
+    uint32_t to[kFewTasks];        // from there to tensor k's, / 256
+    uint16_t *out;                 // the lowest output
+    uint32_t to_out[kFewTasks];    // from there to tensor k's, / 16
+    uint32_t e_units[kFewTasks];   // bytes in the E-chunk region / 256
+};
+static_assert(sizeof(Few) == 112 && offsetof(Few, out) == 56);
 
 // The tensor that a workgroup works on and the workgroup's number inside the tensor.
 template <int N, bool kFlat>
@@ -134,7 +165,7 @@ __device__ __forceinline__ Task task_of(const PackedLaunch &P, uint32_t, uint32_
     const uint8_t *blob = reinterpret_cast<const uint8_t *>(static_cast<uint64_t>(p.blob) << 4 | static_cast<uint64_t>(p.high & 0xfffu) << 36);
     uint16_t *out = reinterpret_cast<uint16_t *>(static_cast<uint64_t>(p.out) << 4 | static_cast<uint64_t>(p.high >> 20) << 36);
     return Task{blob + s.lut_offset, blob + s.sm_offset, blob + s.e_offset, reinterpret_cast<const uint64_t *>(blob + s.table_offset), out,
-                s.n_values, s.e_offset, static_cast<uint64_t>(p.e_units) * 256u, s.stream_values, s.streams_per_chunk, s.n_streams, s.code};
+                s.e_offset, static_cast<uint64_t>(p.e_units) * 256u, s.stream_values, s.streams_per_chunk, s.per_chunk, s.n_streams, s.last_values, s.code};
 }
 
 // LDS words of a table of long codes with `slots` shared beginnings (LongTable), a multiple of four
@@ -144,6 +175,15 @@ __host__ __device__ constexpr uint32_t long_table_words(uint32_t slots)
 }
 
 constexpr uint32_t kLaneBytes = 64;   // a stream opens with one length byte per lane
+
+// LDS words a wave reserves for one stream of the launch's longest kind: the length bytes, the code bits
+// of a lane bounded by the longest code, the rounding of every lane to the quantum, the padding to 16 bytes,
+// and two words a lane may read past its last one.
+template <class Words>
+__host__ __device__ constexpr Words stream_cap_words(Words stream_values, uint32_t max_len_bound, uint32_t quantum)
+{
+    return (kLaneBytes + 8u * (stream_values / 64u * max_len_bound + quantum) + 16u + 8u + 15u) / 16u * 4u;
+}
 
 // Exclusive prefix sum of x over the 64 lanes of the wave (a6), by data-parallel primitives: an inclusive
 // scan inside each row of 16 lanes (shifts by 1, 2, 4, 8), then lane 15 of row 0 and 2 is added to the next
@@ -506,9 +546,14 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
     }
 }
 
-// kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is written
-template <bool kLong, int kWaves, Stores kStores, class Args>
-__global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
+// What no kernel writes, read through the scalar cache where the address is the same for all lanes.
+template <class T>
+using Constant = __attribute__((address_space(4))) T;
+
+// The stream of one wave.  kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is
+// written; cap_words: LDS words reserved per wave for its stream; long_slots: as in Launch
+template <bool kLong, int kWaves, Stores kStores>
+__device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint32_t cap_words, uint32_t long_slots)
 {
     // The decode table of the workgroup's tensor, at a fixed LDS address: one 16-bit read gives a code's length and its
     // symbol.  (Two byte tables, one read each, were 2-4 % slower: twice the LDS instructions, whose random accesses
@@ -520,61 +565,66 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-    uint32_t block;
-    const Task t = task_of(P, lane, block);
-    uint32_t *words = dynamic_lds + (kLong ? long_table_words(P.long_slots) : 0u) + wave * P.stream_cap_words;
-    const uint32_t W = t.stream_values;
-    const uint32_t max_len = t.code & 0xffu, quantum = t.code >> 8;
-    const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;     // bytes of a chunk-table entry
-
     const uint32_t g = block * kWaves + wave;
-    bool active = g < t.n_streams;
+    if (g >= t.n_streams) return;
+    uint32_t *words = dynamic_lds + (kLong ? long_table_words(long_slots) : 0u) + wave * cap_words;
+    const uint32_t W = t.stream_values;
+    const uint32_t max_len = max_len_of(t.code), quantum = quantum_of(t.code);
+    const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;     // bytes of a chunk-table entry
     const uint64_t v0 = static_cast<uint64_t>(g) * W;              // first value of the stream in the tensor
-    uint32_t sn = 0, mode = ZM_MODE_RAW, tiles = 0;
-    const uint8_t *raw = nullptr;
-    if (active) {
-        const uint64_t rest = t.n_values - v0;
-        sn = rest < W ? static_cast<uint32_t>(rest) : W;
-        tiles = (sn + kTile - 1) / kTile;
-    }
+    const uint32_t sn = g + 1u < t.n_streams ? W : t.last_values, tiles = (sn + kTile - 1) / kTile;
     const int32_t mine = static_cast<int32_t>(sn) - static_cast<int32_t>(lane * 8u);   // values left from this lane's first one
 
+    // one read of the chunk's table entry gives the chunk's place and mode and this stream's extent
+    const uint32_t c = chunk_of(g, t.per_chunk, t.code), s = g - c * t.streams_per_chunk;
+    const Constant<uint8_t> *entry = (const Constant<uint8_t> *)(reinterpret_cast<const uint8_t *>(t.table) + static_cast<uint64_t>(c) * stride);
+    const uint64_t ent = *(const Constant<uint64_t> *)entry;
+    const uint32_t o0 = ((const Constant<uint32_t> *)(entry + 8))[s], o1 = ((const Constant<uint32_t> *)(entry + 8))[s + 1u];
+
+    // The decode table is asked for meanwhile: behind the sign-mantissa bytes it would be served behind them, and decoding
+    // waits for it.
+    const uint16_t *const lut = reinterpret_cast<const uint16_t *>(t.lut);
+    const uint32_t mask = (1u << max_len) - 1u;
+    uint2 lut4;                      // entries 4 * lane .. + 3, of codes shorter than eight bits replicated over the index bits above
+    uint32_t lut_tail = 0;           // long codes: see below
+    if constexpr (kLong) {
+        lut4 = reinterpret_cast<const uint2 *>(lut)[lane];
+    } else {
+        lut4 = make_uint2(*reinterpret_cast<const uint32_t *>(lut + (4u * lane & mask)), *reinterpret_cast<const uint32_t *>(lut + (4u * lane + 2u & mask)));
+    }
+    asm volatile("" :: "s"(ent), "s"(o0), "s"(o1));        // with one wait: the compiler would read o0 and o1 where they are used
+
+    bool active = true;
+    const uint8_t *raw = nullptr;
     uint4 held_a = make_uint4(0u, 0u, 0u, 0u), held_b = held_a;   // first 2 KiB of the stream
     uint32_t n_held = 0;
     bool dense = false;          // long codes: four symbols of a lane are likely to have more bits than a window
-    if (active) {
-        const uint32_t c = g / t.streams_per_chunk, s = g % t.streams_per_chunk;
-        // one read of the chunk's table entry gives the chunk's place and mode and this stream's extent
-        const uint8_t *entry = reinterpret_cast<const uint8_t *>(t.table) + static_cast<uint64_t>(c) * stride;
-        const uint64_t ent = *reinterpret_cast<const uint64_t *>(entry);
-        const uint32_t o0 = reinterpret_cast<const uint32_t *>(entry + 8)[s];
-        const uint32_t o1 = reinterpret_cast<const uint32_t *>(entry + 8)[s + 1];
-        const uint64_t at = (ent & ~15ull) - t.e_offset;            // offset inside the E-chunk region
-        mode = static_cast<uint32_t>(ent & 15ull);
-        if ((ent & ~15ull) < t.e_offset) {
+    const uint64_t at = (ent & ~15ull) - t.e_offset;            // offset inside the E-chunk region
+    const uint32_t mode = static_cast<uint32_t>(ent & 15ull);
+    if ((ent & ~15ull) < t.e_offset) {
+        active = false;
+    } else if (mode == ZM_MODE_CODED) {
+        // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
+        // sign-mantissa bytes because decoding can not start without them; the first 2 KiB (two
+        // vectors per lane, more than a typical stream) wait in registers until the other requests
+        // are out, longer streams are copied here.
+        if (o1 < o0 + kLaneBytes || at + o1 > t.e_size) {
             active = false;
-        } else if (mode == ZM_MODE_CODED) {
-            // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
-            // sign-mantissa bytes because decoding can not start without them; the first 2 KiB (two
-            // vectors per lane, more than a typical stream) wait in registers until the other requests
-            // are out, longer streams are copied here.
-            if (o1 < o0 + kLaneBytes || at + o1 > t.e_size) {
-                active = false;
-            } else {
-                const uint32_t nvec = min((o1 - o0) >> 4, P.stream_cap_words >> 2);
-                if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
-                const uint4 *src = reinterpret_cast<const uint4 *>(t.echunks + at + o0);
-                uint4 *dst = reinterpret_cast<uint4 *>(words);
-                n_held = min(nvec, 128u);
-                if (lane < n_held) held_a = src[lane];
-                if (lane + 64 < n_held) held_b = src[lane + 64];
-                for (uint32_t i = 128 + lane; i < nvec; i += 64) dst[i] = src[i];
-            }
         } else {
-            raw = t.echunks + at + static_cast<uint64_t>(s) * W;
-            if (mode != ZM_MODE_RAW || at + static_cast<uint64_t>(s) * W + ((sn + 15u) & ~15u) > t.e_size) active = false;
+            const uint32_t nvec = min((o1 - o0) >> 4, cap_words >> 2);
+            if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
+            const uint4 *src = reinterpret_cast<const uint4 *>(t.echunks + at + o0);
+            uint4 *dst = reinterpret_cast<uint4 *>(words);
+            n_held = min(nvec, 128u);
+            if (lane < n_held) held_a = src[lane];
+            if (lane + 64 < n_held) held_b = src[lane + 64];
+            for (uint32_t i = 128 + lane; i < nvec; i += 64) dst[i] = src[i];
         }
+    } else {
+        raw = t.echunks + at + static_cast<uint64_t>(s) * W;
+        if (mode != ZM_MODE_RAW || at + static_cast<uint64_t>(s) * W + ((sn + 15u) & ~15u) > t.e_size) active = false;
     }
+    if constexpr (kLong) lut_tail = lut[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
     // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
     // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
     // With device-scope stores the first kAhead pairs are asked for here and pair i + kAhead when pair i is done:
@@ -608,34 +658,24 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     LongTable table{0u, 0};
     bool narrow = false;         // long codes: the table has no room for all shared beginnings
     {
-        const uint16_t *src = reinterpret_cast<const uint16_t *>(t.lut);
-        const uint32_t mask = (1u << max_len) - 1u;
         const uint32_t i = 4u * lane;
+        const uint2 e = lut4;
         if constexpr (!kLong) {
-            uint2 e;                     // entries 4 * lane .. + 3, replicated over the index bits above the longest code
-            if (max_len == 8u) {
-                e = reinterpret_cast<const uint2 *>(src)[lane];
-            } else {
-                e = make_uint2(src[i & mask] | static_cast<uint32_t>(src[(i + 1) & mask]) << 16,
-                               src[(i + 2) & mask] | static_cast<uint32_t>(src[(i + 3) & mask]) << 16);
-            }
             reinterpret_cast<uint2 *>(tab)[lane] = make_uint2(__builtin_amdgcn_perm(e.x, e.x, 0x02030001u), __builtin_amdgcn_perm(e.y, e.y, 0x02030001u));
         } else {
             // The blob's table is indexed with a code's first bit lowest, so the number v of LongTable has to be reversed;
             // its first 256 entries are those of the eight-bit beginnings, with a length above eight at shared ones.
-            // The last 64 values of v belong to long codes if any are; they are asked for before it is known how many
+            // The last 64 values of v belong to long codes if any are (lut_tail); they are asked for before it is known how many
             // more there are, which on Gaussian weights is none.
             const uint32_t more = max_len - 8u;
-            const uint2 e = reinterpret_cast<const uint2 *>(src)[lane];
-            const uint32_t tail = src[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
             uint32_t n_shared = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t v = (k & 2 ? e.y : e.x) >> (16 * (k & 1)) & 0xffffu;
                 n_shared += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64((v >> 8) > 8u)));
             }
-            narrow = n_shared > P.long_slots;
-            n_shared = min(n_shared, P.long_slots);
+            narrow = n_shared > long_slots;
+            n_shared = min(n_shared, long_slots);
             const uint32_t whole_codes = kTableEntries - n_shared, late = n_shared << more;
             table.shift = 32u - max_len;
             table.skip = static_cast<int32_t>((whole_codes << more) - whole_codes);
@@ -645,9 +685,9 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
                 const uint32_t at = __builtin_bitreverse32(i + k) >> 24;
                 if (at < whole_codes) tab[at] = swap_entry(v);
             }
-            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = swap_entry(tail);
+            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = swap_entry(lut_tail);
             for (uint32_t k = lane; k + 64u < late; k += 64u) {
-                const uint32_t v = src[__builtin_bitreverse32((whole_codes << more) + k) >> (32u - max_len)];
+                const uint32_t v = lut[__builtin_bitreverse32((whole_codes << more) + k) >> (32u - max_len)];
                 tab[whole_codes + k] = swap_entry(v);
             }
         }
@@ -678,15 +718,15 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     if constexpr (kLong) {
         if (__builtin_expect(narrow, 0)) {
             Decoder<true, true> dec;
-            dec.words = words; dec.last_word = P.stream_cap_words - 1u;
+            dec.words = words; dec.last_word = cap_words - 1u;
             dec.table = table;
             dec.start(first, first + bits);
-            decode_any_stream(dec, reinterpret_cast<const uint16_t *>(t.lut), out, sm, 0u, tiles, mine, up, down);
+            decode_any_stream(dec, lut, out, sm, 0u, tiles, mine, up, down);
             return;
         }
     }
     Decoder<kLong> dec;
-    dec.words = words; dec.last_word = P.stream_cap_words - 1u;
+    dec.words = words; dec.last_word = cap_words - 1u;
     dec.table = table;
     dec.start(first, first + bits);
     uint32_t done = 0;
@@ -701,6 +741,38 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     decode_any_stream(dec, tab, out, sm, done, tiles, mine, up, down);
 }
 
+
+template <bool kLong, int kWaves, Stores kStores, class Args>
+__global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
+{
+    uint32_t block;
+    const Task t = task_of(P, threadIdx.x & 63u, block);
+    const uint32_t cap_words = P.stream_cap_words, long_slots = kLong ? P.long_slots : 0u;
+    // All of the arguments with one wait: the compiler would read each where it is first used, one wait after another.  One
+    // expert of 2048 x 1408 x 3 6.28 -> 6.09 us, one matrix of 1024 x 2048 in streams of 512 values 3.66 -> 3.45 (with the
+    // chunk-table entry read at once, the look-up table asked for before the stream, and no division).
+    asm volatile("" :: "s"(t.lut), "s"(t.sm), "s"(t.echunks), "s"(t.table), "s"(t.out), "s"(t.e_offset), "s"(t.e_size), "s"(t.stream_values),
+                       "s"(t.streams_per_chunk), "s"(t.per_chunk), "s"(t.n_streams), "s"(t.last_values), "s"(t.code), "s"(cap_words), "s"(long_slots));
+    decode_block<kLong, kWaves, kStores>(t, block, cap_words, long_slots);
+}
+
+template <bool kLong, int kWaves, Stores kStores>
+__global__ void __launch_bounds__(64 * kWaves) zm_decode_few_kernel(const Few P)
+{
+    const uint32_t k = blockIdx.y;
+    const uint32_t code = P.lead[0], n_streams = P.lead[1], last_lut = P.lead[2], table_offset = P.lead[3], sm_units = P.lead[4], e_at = P.lead[5];
+    const uint8_t *low = P.low;
+    const uint32_t to = P.to[k], to_out = P.to_out[k], e_units = P.e_units[k];
+    uint16_t *out = P.out;
+    asm volatile("" :: "s"(code), "s"(n_streams), "s"(last_lut), "s"(table_offset), "s"(sm_units), "s"(e_at), "s"(low), "s"(to), "s"(to_out), "s"(e_units), "s"(out));
+    const uint8_t *blob = low + static_cast<uint64_t>(to) * 256u;
+    const uint32_t W = (code & 127u) * kTile, max_len = code >> 7 & 15u, shift = code >> 11 & 31u, quantum = code >> 16 & 255u, long_slots = code >> 24;
+    const uint64_t e_offset = static_cast<uint64_t>(e_at) * 256u;
+    const Task t{blob + (last_lut >> 16), blob + static_cast<uint64_t>(sm_units) * 256u, blob + e_offset, reinterpret_cast<const uint64_t *>(blob + table_offset),
+                 out + static_cast<uint64_t>(to_out) * 8u, e_offset, static_cast<uint64_t>(e_units) * 256u, W, 1u << shift, 1u << 31, n_streams,
+                 last_lut & 0xffffu, max_len | shift << 4 | quantum << 9};
+    decode_block<kLong, kWaves, kStores>(t, blockIdx.x, stream_cap_words(W, kLong ? ZM_MAX_CODE_LEN : 8u, quantum), long_slots);
+}
 
 // Stand-alone tensor recovery (Sec. 3.3): one tile of 512 values per wave; lane j merges values
 // 8j..8j+7 -- a 64-bit load from each input, one 128-bit store, all contiguous across the wave.
@@ -756,16 +828,6 @@ __global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restri
     }
 }
 
-// LDS words a wave reserves for one stream of the launch's longest kind: the length bytes, the code bits
-// of a lane bounded by the longest code, the rounding of every lane to the quantum, the padding to 16 bytes,
-// and two words a lane may read past its last one.
-inline size_t stream_cap_words(uint32_t stream_values, uint32_t max_len_bound, uint32_t quantum)
-{
-    const size_t syms = static_cast<size_t>(stream_values / kTile) * 8;
-    const size_t bytes = kLaneBytes + (64 * (syms * max_len_bound + quantum) + 7) / 8 + 16 + 8;
-    return ((bytes + 15) & ~static_cast<size_t>(15)) / 4;
-}
-
 // Streams share a workgroup's LDS up to this size; one that is longer by itself is refused.  A table of long codes
 // (0.5 to 4.3 KB) comes on top, so that the line does not depend on the tensor's symbols.
 constexpr size_t kLdsLimit = 64 * 1024;
@@ -819,7 +881,9 @@ template <bool kLong, int kWaves, Stores kStores, class Args>
 int launch_kernel(void *args, const Plan &p)
 {
     void *argv[] = {args};
-    const void *fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, Args>);
+    const void *fn;
+    if constexpr (std::is_same<Args, Few>::value) fn = reinterpret_cast<const void *>(&zm_decode_few_kernel<kLong, kWaves, kStores>);
+    else fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, Args>);
     // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
     return hipLaunchKernel(fn, p.grid, dim3(64 * kWaves), argv, p.lds, p.stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
@@ -869,7 +933,7 @@ int launch_tasks(Launch<N, true> &L, size_t cap, uint32_t max_stream, int stores
         L.first_block[k] = static_cast<uint32_t>(total);
         blocks = b > blocks ? b : blocks;
         total += b;
-        out_bytes += 2 * L.task[k].n_values;
+        out_bytes += 2 * L.task[k].n_values();
         n_streams += L.task[k].n_streams;
     }
     if (!blocks) return ZM_OK;
@@ -898,7 +962,7 @@ struct Group {
 
     static bool same(const Shape &a, const Shape &b)
     {
-        return a.n_values == b.n_values && a.sm_offset == b.sm_offset && a.e_offset == b.e_offset && a.lut_offset == b.lut_offset &&
+        return a.last_values == b.last_values && a.per_chunk == b.per_chunk && a.sm_offset == b.sm_offset && a.e_offset == b.e_offset && a.lut_offset == b.lut_offset &&
                a.table_offset == b.table_offset && a.stream_values == b.stream_values && a.streams_per_chunk == b.streams_per_chunk &&
                a.n_streams == b.n_streams && a.code == b.code;
     }
@@ -911,9 +975,9 @@ struct Group {
             const uint32_t slots = (ti.n_present < kTableEntries ? ti.n_present : kTableEntries) / 2;
             long_slots = long_slots > slots ? long_slots : slots;
             max_stream = max_stream > t.stream_values ? max_stream : t.stream_values;
-            max_quantum = max_quantum > (t.code >> 8) ? max_quantum : (t.code >> 8);
+            max_quantum = max_quantum > quantum_of(t.code) ? max_quantum : quantum_of(t.code);
         }
-        size_t words() const { return stream_cap_words(max_stream, kLenBound, max_quantum); }
+        size_t words() const { return stream_cap_words<size_t>(max_stream, kLenBound, max_quantum); }
     };
     Cap cap_of_all;
 
@@ -931,16 +995,20 @@ struct Group {
 
     static constexpr uint32_t kUnpackable = ~0u;      // no device address has all of bits 36..47 set
 
+    // Whether the tensor's parts lie as in a blob at address b.
+    static bool whole_blob(const Task &t, const zm_tensor_info &ti, uint64_t b)
+    {
+        return reinterpret_cast<uint64_t>(t.sm) == b + ti.sm_offset && reinterpret_cast<uint64_t>(t.echunks) == b + ti.e_offset &&
+               reinterpret_cast<uint64_t>(t.table) == b + ti.table_offset && !(t.e_size & 255) && t.e_size >> 8 <= UINT32_MAX;
+    }
+
     Packed pack(const Task &t, const zm_tensor_info &ti)
     {
         const Packed no{0, kUnpackable, 0, 0};
-        const uint8_t *blob = t.lut - ti.lut_offset;
-        const uint64_t b = reinterpret_cast<uint64_t>(blob), o = reinterpret_cast<uint64_t>(t.out);
-        if (ti.lut_offset > UINT32_MAX || ti.table_offset > UINT32_MAX || t.sm != blob + ti.sm_offset || t.echunks != blob + ti.e_offset ||
-            reinterpret_cast<const uint8_t *>(t.table) != blob + ti.table_offset || (b & 15) || b >> 48 || o >> 48 || (t.e_size & 255) ||
-            t.e_size >> 8 > UINT32_MAX) return no;
-        const Shape s{t.n_values, ti.sm_offset, ti.e_offset, static_cast<uint32_t>(ti.lut_offset), static_cast<uint32_t>(ti.table_offset),
-                      t.stream_values, t.streams_per_chunk, t.n_streams, t.code};
+        const uint64_t b = reinterpret_cast<uint64_t>(t.lut) - ti.lut_offset, o = reinterpret_cast<uint64_t>(t.out);
+        if (ti.lut_offset > UINT32_MAX || ti.table_offset > UINT32_MAX || !whole_blob(t, ti, b) || (b & 15) || b >> 48 || o >> 48) return no;
+        const Shape s{ti.sm_offset, ti.e_offset, static_cast<uint32_t>(ti.lut_offset), static_cast<uint32_t>(ti.table_offset),
+                      t.stream_values, t.streams_per_chunk, t.per_chunk, t.n_streams, t.last_values, t.code};
         uint32_t k;
         for (k = 0; k < n_shapes; ++k) if (same(shape[k], s)) break;
         if (k == n_shapes) {
@@ -956,9 +1024,62 @@ struct Group {
     template <typename Next>
     int launch(Next next, int stores, hipStream_t stream, Recorder *rec)
     {
-        if (n <= kFewTasks) return launch_wide<kFewTasks>(next, stores, stream, rec);
+        if (n <= kFewTasks) {
+            int rc;
+            return launch_few(next, stores, stream, rec, rc) ? rc : launch_wide<kFewTasks>(next, stores, stream, rec);
+        }
         if (may_share && packable && rows_pay() && 8 * cap_of_all.words() + kBesideStreams<kLong> <= kLdsLimit) return launch_packed(stores, stream, rec);
         return launch_wide<kMaxTasks>(next, stores, stream, rec);
+    }
+
+    // Where the tensors fit a Few: launches them, and sets rc.
+    template <typename Next>
+    bool launch_few(Next next, int stores, hipStream_t stream, Recorder *rec, int &rc)
+    {
+        Task t[kFewTasks];
+        uint64_t blob[kFewTasks], low = UINT64_MAX, low_out = UINT64_MAX;
+        const zm_tensor_info *ti = nullptr;
+        Cap cap;
+        for (int k = 0; k < n; ++k) {
+            const zm_tensor_info &tk = next(t[k]);
+            cap.see(t[k], tk);
+            blob[k] = reinterpret_cast<uint64_t>(t[k].lut) - tk.lut_offset;
+            const uint64_t out = reinterpret_cast<uint64_t>(t[k].out);
+            if (blob[k] & 255 || !whole_blob(t[k], tk, blob[k])) return false;
+            if (k && !(t[k].last_values == t[0].last_values && t[k].n_streams == t[0].n_streams && t[k].stream_values == t[0].stream_values &&
+                       t[k].streams_per_chunk == t[0].streams_per_chunk && t[k].code == t[0].code && tk.lut_offset == ti->lut_offset &&
+                       tk.table_offset == ti->table_offset && tk.sm_offset == ti->sm_offset && tk.e_offset == ti->e_offset)) return false;
+            ti = &tk;
+            low = low < blob[k] ? low : blob[k];
+            low_out = low_out < out ? low_out : out;
+        }
+        const uint32_t shift = t[0].code >> 4 & 31u, quantum = quantum_of(t[0].code), W = t[0].stream_values;
+        if (t[0].streams_per_chunk != 1u << shift || quantum > 255 || W / kTile > 127 || ti->lut_offset > 0xffff || ti->table_offset > UINT32_MAX ||
+            (ti->sm_offset | ti->e_offset) & 255 || ti->e_offset >> 8 > UINT32_MAX) return false;
+        Few F;
+        const uint32_t lead[6] = {W / kTile | max_len_of(t[0].code) << 7 | shift << 11 | quantum << 16 | (kLong ? cap.long_slots : 0u) << 24, t[0].n_streams,
+                                  t[0].last_values | static_cast<uint32_t>(ti->lut_offset) << 16, static_cast<uint32_t>(ti->table_offset),
+                                  static_cast<uint32_t>(ti->sm_offset >> 8), static_cast<uint32_t>(ti->e_offset >> 8)};
+        for (int i = 0; i < 6; ++i) F.lead[i] = lead[i];
+        F.low = reinterpret_cast<const uint8_t *>(low);
+        F.out = reinterpret_cast<uint16_t *>(low_out);
+        for (int k = 0; k < kFewTasks; ++k) {
+            const int j = k < n ? k : 0;
+            const uint64_t to = (blob[j] - low) >> 8, to_out = (reinterpret_cast<uint64_t>(t[j].out) - low_out) >> 4;
+            if (to > UINT32_MAX || to_out > UINT32_MAX) return false;
+            F.to[k] = static_cast<uint32_t>(to);
+            F.to_out[k] = static_cast<uint32_t>(to_out);
+            F.e_units[k] = static_cast<uint32_t>(t[j].e_size >> 8);
+        }
+        const size_t words = cap.words(), table = kLong ? 4 * long_table_words(cap.long_slots) : 0;
+        const uint64_t n_all = n, out_bytes = 2 * n_all * t[0].n_values(), n_streams = n_all * t[0].n_streams;
+        auto plan = [&](uint32_t waves) {
+            return Plan{dim3((t[0].n_streams + waves - 1) / waves, static_cast<uint32_t>(n)), static_cast<uint32_t>(n), 4 * waves * words + table, out_bytes, n_streams, W, stores, stream, rec};
+        };
+        if (8 * words + kBesideStreams<kLong> <= kLdsLimit) rc = launch_args<kLong, 2, Few>(&F, plan(2));
+        else if (4 * words + kBesideStreams<kLong> <= kLdsLimit) rc = launch_args<kLong, 1, Few>(&F, plan(1));
+        else rc = ZM_E_ARG;                     // stream too long to stage in LDS
+        return true;
     }
 
     template <int N, typename Next>
@@ -1013,7 +1134,7 @@ struct Group {
                 const Shape &s = shape[L.task[k].high >> 12 & (kMaxShapes - 1u)];
                 const uint32_t b = (s.n_streams + 1u) / 2u;
                 blocks = b > blocks ? b : blocks;
-                out_bytes += 2 * s.n_values;
+                out_bytes += 2 * (static_cast<uint64_t>(s.n_streams - 1u) * s.stream_values + s.last_values);
                 n_streams += s.n_streams;
             }
             const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, n_streams, cap_of_all.max_stream, stores, stream, rec});
@@ -1045,13 +1166,16 @@ int make_task(const zm_tensor_parts &pt, const zm_tensor_info &ti, void *out, Ta
     t.echunks = static_cast<const uint8_t *>(pt.echunks);
     t.table = static_cast<const uint64_t *>(pt.chunk_offsets);
     t.out = static_cast<uint16_t *>(out);
-    t.n_values = ti.n_values;
     t.e_offset = ti.e_offset;
     t.e_size = ti.blob_size - ti.e_offset;
     t.stream_values = ti.stream_values;
     t.streams_per_chunk = ti.chunk_values / ti.stream_values;
     t.n_streams = static_cast<uint32_t>(n_streams);
-    t.code = ti.max_len | ti.lane_quantum << 8;
+    t.last_values = static_cast<uint32_t>(ti.n_values - (n_streams - 1) * ti.stream_values);
+    uint32_t shift = 0;
+    while (1ull << shift < t.streams_per_chunk) ++shift;
+    t.per_chunk = static_cast<uint32_t>(((1ull << (31 + shift)) + t.streams_per_chunk - 1) / t.streams_per_chunk);
+    t.code = ti.max_len | shift << 4 | ti.lane_quantum << 9;
     return ZM_OK;
 }
 
@@ -1085,7 +1209,7 @@ int decode_call(int n_tensors, Describe describe, Info info, int stores, hipStre
         const int rc = describe(i, t, skip, ti);
         if (rc != ZM_OK) return rc;
         if (skip) continue;
-        if ((t.code & 0xffu) <= 8) short_codes.count(t, *ti);
+        if (max_len_of(t.code) <= 8) short_codes.count(t, *ti);
         else long_codes.count(t, *ti);
     }
     // the tensors of one group, in the call's order
@@ -1094,7 +1218,7 @@ int decode_call(int n_tensors, Describe describe, Info info, int stores, hipStre
             for (;;) {
                 bool skip; const zm_tensor_info *ti;
                 describe(i++, t, skip, ti);
-                if (!skip && ((t.code & 0xffu) <= 8) == want_short) return *ti;
+                if (!skip && (max_len_of(t.code) <= 8) == want_short) return *ti;
             }
         };
     };

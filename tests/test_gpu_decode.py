@@ -606,3 +606,59 @@ def test_long_codes_do_not_depend_on_the_count_of_symbols_in_a_description(monke
         assert np.array_equal(gpu_decode_tensors([b], stores=zm.STORES_STREAMING)[0], w)
     for w, g in zip(tensors, gpu_decode_tensors(blobs)):
         assert np.array_equal(g, w)
+
+
+def decode_at(blobs, ids, stores, shift, gap, backwards):
+    """Decodes blobs[i] for i in ids from one arena in which every blob starts `shift` bytes past a multiple of 256 and `gap` bytes
+    past the last, with outputs in the order of ids or backwards."""
+    import torch
+    at, starts = 0, []
+    for b in blobs:
+        starts.append(-(-at // 256) * 256 + shift)
+        at = starts[-1] + b.size + gap
+    arena = torch.zeros(at, dtype=torch.uint8, device="cuda")
+    infos = (zm.TensorInfo * len(blobs))()
+    blob_ptrs, table_ptrs = (ctypes.c_void_p * len(blobs))(), (ctypes.c_void_p * len(blobs))()
+    for k, b in enumerate(blobs):
+        arena[starts[k]: starts[k] + b.size].copy_(torch.from_numpy(np.ascontiguousarray(b)))
+        infos[k] = zm.blob_info(b[:384])
+        blob_ptrs[k] = arena.data_ptr() + starts[k]
+        table_ptrs[k] = blob_ptrs[k] + infos[k].table_offset
+    order = list(range(len(ids)))[::-1] if backwards else list(range(len(ids)))
+    rooms, end = [0] * len(ids), GUARD
+    for j in order:
+        rooms[j] = end
+        end += -(-int(infos[ids[j]].n_values) // 8) * 8 + GUARD
+    out = torch.full((end,), GUARD_WORD, dtype=torch.int16, device="cuda")
+    ptrs = (ctypes.c_void_p * len(ids))(*[out.data_ptr() + 2 * r for r in rooms])
+    cast = lambda a, t=ctypes.c_void_p: ctypes.cast(a, ctypes.POINTER(t))
+    rc = zm.lib().zm_decode_experts_stores(cast(blob_ptrs), cast(table_ptrs), cast(infos, zm.TensorInfo), len(blobs), 1,
+                                           (ctypes.c_int32 * len(ids))(*ids), len(ids), cast(ptrs), stores,
+                                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == zm.OK
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().view(np.uint16)
+    untouched = np.ones(end, bool)
+    for j, e in enumerate(ids):
+        untouched[rooms[j]: rooms[j] + int(infos[e].n_values)] = False
+    assert np.all(got[untouched] == GUARD_WORD)
+    return [got[rooms[j]: rooms[j] + int(infos[e].n_values)] for j, e in enumerate(ids)]
+
+
+@pytest.mark.parametrize("C,W,max_len", [(16384, 4096, 8), (12288, 4096, 8), (2560, 512, 8), (4096, 1024, 3), (1 << 17, 512, 8), (16384, 16384, 12),
+                                         (32768, 32768, 12), (65536, 4096, 11)])
+@pytest.mark.parametrize("count,shift,backwards", [(1, 0, False), (2, 16, False), (3, 0, True), (6, 0, False), (6, 208, True), (7, 0, False)])
+def test_calls_of_few_tensors(C, W, max_len, count, shift, backwards):
+    # up to six blobs cut alike travel in their own kind of arguments: those, and what does not fit it (chunks of other than 2^k
+    # streams, addresses that are no multiple of 256, seven tensors, one of another length or codebook)
+    n = 2 * C + C // 2 + 777
+    kinds = ["two_exponents" if max_len < 8 else "gauss" if max_len == 8 else "wide"] * count
+    tensors = [synth.special_tensor(kind, n, seed=50 + i) for i, kind in enumerate(kinds)]
+    tensors.append(synth.special_tensor("gauss", n - 1, seed=7))
+    tensors.append(synth.special_tensor("all_equal", n, seed=8))
+    blobs = [zm.compress(w, C, W, max_len if i < count else max(max_len, 8))[0] for i, w in enumerate(tensors)]
+    refs = [zo.decode(b) for b in blobs]
+    for ids in (list(range(count)), list(range(count))[::-1], list(range(count - 1)) + [count], list(range(count - 1)) + [count + 1], [0] * count):
+        for stores in (zm.STORES_CACHED, zm.STORES_STREAMING):
+            for e, g in zip(ids, decode_at(blobs, ids, stores, shift, 4096, backwards)):
+                assert np.array_equal(g, refs[e]) and np.array_equal(g, tensors[e])
