@@ -505,11 +505,8 @@ def main() -> int:
     t_per = layers[0].tensors_per_expert
     sel = [layers[0].infos[int(e) * t_per + m] for e in routes[0][0] for m in range(t_per)]
     shapes = zm.decode_launch_shapes(sel, zm.STORES_STREAMING)
-    # launches of more than 9216 streams of 4096 values, codes of at most 8 bits, have a streaming kernel of their own
-    many = sum(-(-int(i.n_values) // int(i.stream_values)) for i in sel) > 9216 and all(i.stream_values == 4096 for i in sel)
     kernel_names = ["zm_decode_kernel<%s,%d,%s>" % ("true" if sh.round_symbols == 2 else "false", sh.waves_per_workgroup,
-                                                     "kThrough or kOrdinary" if not sh.streaming_stores else
-                                                     "kStreamingMany" if many and sh.round_symbols == 4 else "kStreaming")
+                                                     "kStreaming" if sh.streaming_stores else "kThrough or kOrdinary")
                     for sh in shapes]
 
     result = {

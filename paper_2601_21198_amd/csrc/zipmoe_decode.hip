@@ -17,8 +17,7 @@
 //   1. one read of the chunk's table entry locates the stream; its bytes (64 lane-length bytes, then the 64
 //      lane bitstreams back to back) are requested with 128-bit loads (a4) -- first, because decoding can not
 //      start without them -- and go to LDS;
-//   2. the sign-mantissa bytes of the stream's tiles are requested: all eight of a group with non-temporal
-//      stores, the first four otherwise (the others as tiles are finished);
+//   2. the sign-mantissa bytes of the stream's first tiles are requested, the others as tiles are finished;
 //   3. the decode table goes to LDS (a3) as 16-bit entries, code length in the low byte and symbol in the high byte:
 //      256 entries for codes of at most eight bits; longer codes take 16 more for each beginning that they share;
 //   4. a wavefront prefix sum over the 64 lane-length bytes gives every lane the first and the last bit of
@@ -215,8 +214,7 @@ __device__ __forceinline__ void recover4(uint32_t e4, uint32_t sm4, uint32_t &w0
 //   kThrough    device-scope stores: the L2 caches keep the line and pass it on to the last-level cache at once
 //   kStreaming  non-temporal: the output is larger than the last-level cache, or the caller said that its buffers are
 //               not cache-resident
-//   kStreamingMany  the same in launches of many streams of one group of tiles, with per-lane addresses
-enum Stores { kOrdinary, kThrough, kStreaming, kStreamingMany };
+enum Stores { kOrdinary, kThrough, kStreaming };
 
 // Where they go: the first n_values of stream_base, lane j's eight words of tile k at k * kTile + 8 * j.  Buffer stores,
 // because 128-bit device-scope stores exist as these only; the descriptor covers the wave's words and nothing else.
@@ -264,14 +262,6 @@ __device__ __forceinline__ void store_some(uint16_t *p, uint4 w, uint32_t left)
     for (uint32_t q = 0; q < 8; ++q)
         if (q < left) p[q] = static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1)));
 }
-
-template <>
-struct Sink<kStreamingMany> {
-    uint16_t *lane_words;
-    __device__ __forceinline__ Sink(uint16_t *stream_base, uint32_t, uint32_t lane) : lane_words(stream_base + 8u * lane) {}
-    __device__ __forceinline__ void store(uint32_t tile, uint4 w) const { store_streaming(lane_words + tile * kTile, w); }
-    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w, uint32_t left) const { store_some(lane_words + tile * kTile, w, left); }
-};
 
 __device__ __forceinline__ uint4 recover8(uint2 e, uint2 sm)
 {
@@ -426,25 +416,17 @@ struct Decoder {
 // One byte per value of a stream (sign-mantissa bytes, or a raw chunk's exponent bytes), read as 64 bits per lane and
 // tile.  The descriptor covers the stream's bytes, rounded up to whole groups of eight (the section is padded): a lane
 // or a tile past them reads zeros and touches no memory.
-template <Stores kStores>
 struct ByteSource {
     __amdgpu_buffer_rsrc_t bytes;
     uint32_t lane_offset;
-    const uint8_t *lane_bytes;
     __device__ __forceinline__ ByteSource(const uint8_t *stream_base, uint32_t n_values, uint32_t lane)
         : bytes(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(stream_base), 0, static_cast<int>((n_values + 7u) & ~7u), kRawBuffer)),
-          lane_offset(lane * 8u), lane_bytes(stream_base + 8u * lane) {}
+          lane_offset(lane * 8u) {}
     __device__ __forceinline__ uint2 load(uint32_t tile) const
     {
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(bytes, static_cast<int>(lane_offset + tile * kTile), 0, 0);
         return make_uint2(v.x, v.y);
-    }
-    // of a tile that lies in the stream
-    __device__ __forceinline__ uint2 load_inside(uint32_t tile) const
-    {
-        if constexpr (kStores == kStreamingMany) return *reinterpret_cast<const uint2 *>(lane_bytes + tile * kTile);
-        else return load(tile);
     }
 };
 
@@ -463,46 +445,63 @@ __device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t t
 // the caller, the others of the first kPairs pairs are asked for when pair p - kAhead is done.
 constexpr int kPairs = kGroup / 2;
 
-// Streams of whole tiles, a multiple of eight of them.  kOneGroup: exactly eight, the common case, straight-line code.
-// In longer ones the next group's bytes are asked for when a group is done: they come while its first pair is decoded.
-// (Asking for them pair by pair, two or four pairs ahead, was 10 % slower: a wave waits for each such load behind its
-// own stores.)
-// Returns the first pair that is not done: with long codes, a pair in which a lane's four symbols had more bits than a
-// window is left alone, with the decoder as it was in front of it.
-template <bool kLong, int kAhead, bool kOneGroup, Stores kStores>
-__device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource<kStores> &sm,
-                                                  uint32_t tiles, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
+// Pairs first .. first + kPairs - 1.  Returns how many are done: with long codes, a pair in which a lane's four symbols had more
+// bits than a window is left alone, with the decoder as it was in front of it.
+template <bool kLong, int kAhead, Stores kStores>
+__device__ __forceinline__ uint32_t decode_group(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+                                                 uint32_t first, uint32_t tiles, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
-    for (uint32_t first = 0;;) {
 #pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-            const uint32_t lo = first + i, hi = tiles - 1u - lo;
-            const Decoder<kLong> before = dec;
-            uint32_t most = 0;
-            // a tile's eight symbols come in two quads: the upward chain gives values 0..3 first, the
-            // downward chain values 4..7 first
-            const uint2 a = dec.quad(tab, most), b = dec.quad(tab, most);
-            if constexpr (kLong) {
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(most > 32u) != 0, 0)) {
-                    dec = before;
-                    return lo;
-                }
-            }
-            out.store(lo, recover8(make_uint2(a.x, b.x), up[i]));
-            out.store(hi, recover8(make_uint2(b.y, a.y), down[i]));
-            if (i + kAhead < kPairs) {
-                up[i + kAhead] = sm.load_inside(lo + kAhead);
-                down[i + kAhead] = sm.load_inside(hi - kAhead);
+    for (int i = 0; i < kPairs; ++i) {
+        const uint32_t lo = first + i, hi = tiles - 1u - lo;
+        const Decoder<kLong> before = dec;
+        uint32_t most = 0;
+        // a tile's eight symbols come in two quads: the upward chain gives values 0..3 first, the
+        // downward chain values 4..7 first
+        const uint2 a = dec.quad(tab, most), b = dec.quad(tab, most);
+        if constexpr (kLong) {
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(most > 32u) != 0, 0)) {
+                dec = before;
+                return static_cast<uint32_t>(i);
             }
         }
-        first += kPairs;
-        if (kOneGroup || 2u * first >= tiles) return first;
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-            up[i] = sm.load_inside(first + i);
-            down[i] = sm.load_inside(tiles - 1u - first - i);
+        out.store(lo, recover8(make_uint2(a.x, b.x), up[i]));
+        out.store(hi, recover8(make_uint2(b.y, a.y), down[i]));
+        if (i + kAhead < kPairs) {
+            up[i + kAhead] = sm.load(lo + kAhead);
+            down[i + kAhead] = sm.load(hi - kAhead);
         }
     }
+    return kPairs;
+}
+
+// Streams of whole tiles, a multiple of eight of them: returns the pairs that are done.  The next group's bytes are asked for when a
+// group is begun, into registers of their own: they come while it is decoded, and as they are asked for in front of its stores, the
+// wait for them is not a wait for these.  The last group asks for tiles that read as zero and touch no memory, and groups take turns
+// with the registers, so that the same requests follow a group's bytes on every way to their use: where the compiler can not
+// count them, or has to move the bytes, it waits for more than is needed.
+template <bool kLong, Stores kStores>
+__device__ __forceinline__ uint32_t decode_groups(Decoder<kLong> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
+                                                  uint32_t tiles, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
+{
+    constexpr uint32_t kOutside = 1u << 20;        // tiles; no stream has as many
+    uint2 other_up[kPairs], other_down[kPairs];
+    uint32_t done = 0;
+    // the next group, with the one after it asked for; false: nothing is left to do here
+    auto group = [&](uint2 (&u)[kPairs], uint2 (&d)[kPairs], uint2 (&next_u)[kPairs], uint2 (&next_d)[kPairs]) {
+        const uint32_t next = done + kPairs, skip = 2u * next >= tiles ? kOutside : 0u;
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            next_u[i] = sm.load(next + i + skip);
+            next_d[i] = sm.load(tiles - 1u - next - i + skip);
+        }
+        const uint32_t more = decode_group<kLong, kPairs>(dec, tab, out, sm, done, tiles, u, d);
+        done += more;
+        return more == kPairs && 2u * done < tiles;
+    };
+    if (group(up, down, other_up, other_down))
+        while (group(other_up, other_down, up, down) && group(up, down, other_up, other_down)) {}
+    return done;
 }
 
 // Any stream, from pair `lo` on: short ones, last ones, ones dense in long codes.  With an odd number of tiles the last
@@ -510,7 +509,7 @@ __device__ __forceinline__ uint32_t decode_stream(Decoder<kLong> &dec, const uin
 // caller has asked for two pairs (up[0], up[1]); kept rolled, since the unrolled loop with its partial tiles costs the
 // whole kernel 20 registers.
 template <bool kLong, bool kFromBlob, Stores kStores>
-__device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource<kStores> &sm,
+__device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec, const uint16_t *tab, const Sink<kStores> &out, const ByteSource &sm,
                                                   uint32_t lo, uint32_t tiles, int32_t mine, uint2 (&up)[kPairs], uint2 (&down)[kPairs])
 {
 #pragma unroll 1
@@ -534,7 +533,7 @@ __device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec
 // A chunk that is stored raw: its exponent bytes lie in memory as they are.  Four tiles are asked for before the first
 // is merged.
 template <Stores kStores>
-__device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const ByteSource<kStores> &raw, const ByteSource<kStores> &sm,
+__device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const ByteSource &raw, const ByteSource &sm,
                                                  uint32_t tiles, int32_t mine)
 {
     for (uint32_t first = 0; first < tiles; first += kPairs) {
@@ -550,9 +549,33 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
 template <class T>
 using Constant = __attribute__((address_space(4))) T;
 
+// What a launch's streams are, and how many waves of it a SIMD holds at most (the registers would admit seven or eight; the
+// compiler is told, and reserves what keeps the others out).  A launch that finds places for all of its waves is the faster the more
+// it has; one that does not is bound by the memory, which serves fewer waves, with fewer places open at a time, faster.
+//   kShortStreams  streams of less than one group of tiles: bound by their waves' latencies, so as many as go.  Eight experts of
+//                  1024 x 2048 x 3 in streams of 512 values, us at seven / eight waves: 31.6 / 30.3, long codes at five / eight 48.1 / 38.7
+//   kFitting       of one group, short codes, in launches of up to kManyStreams.  Four experts (6144 streams), all cached, at three / five /
+//                  seven waves: 14.9 / 14.4 / 13.5; up to two experts no difference
+//   kMany          of one group, in launches of more.  Six waves: what layers of large matrices take best, two of 4096 x 14336 x 3 at
+//                  three / five / six / seven: 196 / 192.2 / 191.5 / 191.1, 16 of 4096 x 4096 x 3 451 / 449 / 444 / 445.  Long codes four:
+//                  eight / 16 / 48 experts of 1024 x 2048 x 3 at three 27.1 / 61.5 / 171, four 27.3 / 61.2 / 178, five 27.7 / 62.7 / 181, eight
+//                  29.2 / - / -; default stores 37.9 / 68.3, 35.9 / 64.8, 36.0 / 66.0
+//   kManyTensors   the same where the launch has many tensors (kFewPerTensor), short codes: three.  Experts of 1024 x 2048 x 3 at three / six
+//                  waves: 16 59.4 / 61.2, 24 83.9 / 85.7, 48 163.9 / 167.6; 48 of 512 x 1024 x 3 42.9 / 44.9; ten of 2048 x 1408 x 3 49.1 / 50.1
+//   kDeep          longer streams: three.  In streams of 8192 values four / eight / 16 experts of 1024 x 2048 x 3 at three 15.1 / 26.9 / 61.8, at
+//                  four 16.2 / 26.9 / 62.1, uncapped 16.2 / 28.4 / 63.6; of longer ones LDS holds fewer
+enum Kind { kShortStreams, kFitting, kMany, kManyTensors, kDeep };
+constexpr int most_waves(Kind kind, bool long_codes)
+{
+    return kind == kShortStreams ? 8 : kind == kFitting ? 7 : kind == kMany ? (long_codes ? 4 : 6) : 3;
+}
+// Streams that are at work at a time with seven waves per SIMD; streams per tensor, on average, up to which a launch has many tensors
+// (at 4096 streams per tensor three waves are slower than six, at 704 faster).
+constexpr uint64_t kManyStreams = 7168, kFewPerTensor = 1024;
+
 // The stream of one wave.  kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is
 // written; cap_words: LDS words reserved per wave for its stream; long_slots: as in Launch
-template <bool kLong, int kWaves, Stores kStores>
+template <bool kLong, int kWaves, Stores kStores, Kind kKind>
 __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint32_t cap_words, uint32_t long_slots)
 {
     // The decode table of the workgroup's tensor, at a fixed LDS address: one 16-bit read gives a code's length and its
@@ -596,7 +619,13 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
 
     bool active = true;
     const uint8_t *raw = nullptr;
-    uint4 held_a = make_uint4(0u, 0u, 0u, 0u), held_b = held_a;   // first 2 KiB of the stream
+    // The stream's first vectors, lane + 64 k, wait in registers until the other requests are out: 2 KiB, more than a typical
+    // stream of 4096 values, or 12, as much as one of 32768.  (What is copied in the loop below waits for every vector anew: streams
+    // of 32768 values, two / eight experts of 1024 x 2048 x 3, 20.7 / 45.5 us with 2 KiB, 17.8 / 37.8 with 12 and the next group of
+    // tiles asked for early, of 16384 values 13.2 / 32.8 and 12.1 / 32.1.)
+    constexpr uint32_t kHeld = kKind == kDeep ? 12 : 2;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 held[kHeld];
     uint32_t n_held = 0;
     bool dense = false;          // long codes: four symbols of a lane are likely to have more bits than a window
     const uint64_t at = (ent & ~15ull) - t.e_offset;            // offset inside the E-chunk region
@@ -605,20 +634,19 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
         active = false;
     } else if (mode == ZM_MODE_CODED) {
         // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
-        // sign-mantissa bytes because decoding can not start without them; the first 2 KiB (two
-        // vectors per lane, more than a typical stream) wait in registers until the other requests
-        // are out, longer streams are copied here.
+        // sign-mantissa bytes because decoding can not start without them.  What is not held is copied here.
         if (o1 < o0 + kLaneBytes || at + o1 > t.e_size) {
             active = false;
         } else {
             const uint32_t nvec = min((o1 - o0) >> 4, cap_words >> 2);
             if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
-            const uint4 *src = reinterpret_cast<const uint4 *>(t.echunks + at + o0);
-            uint4 *dst = reinterpret_cast<uint4 *>(words);
-            n_held = min(nvec, 128u);
-            if (lane < n_held) held_a = src[lane];
-            if (lane + 64 < n_held) held_b = src[lane + 64];
-            for (uint32_t i = 128 + lane; i < nvec; i += 64) dst[i] = src[i];
+            const u32x4 *src = reinterpret_cast<const u32x4 *>(t.echunks + at + o0);
+            u32x4 *dst = reinterpret_cast<u32x4 *>(words);
+            n_held = min(nvec, 64u * kHeld);
+#pragma unroll
+            for (uint32_t k = 0; k < kHeld; ++k)
+                if (lane + 64u * k < n_held) held[k] = src[lane + 64u * k];
+            for (uint32_t i = 64u * kHeld + lane; i < nvec; i += 64) dst[i] = src[i];
         }
     } else {
         raw = t.echunks + at + static_cast<uint64_t>(s) * W;
@@ -627,37 +655,25 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     if constexpr (kLong) lut_tail = lut[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
     // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
     // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
-    // With device-scope stores the first kAhead pairs are asked for here and pair i + kAhead when pair i is done:
-    // the requests of the thousands of waves that start together are spread out and everyone's first tiles
-    // arrive sooner.  A wave waits for such a later load behind its own earlier stores, though, and non-temporal
-    // stores take long to be acknowledged: with them all eight tiles of a group are asked for up front.  So they are
-    // in streams of several groups, of which fewer start together.
-    constexpr int kAhead = kStores == kStreaming || kStores == kStreamingMany ? kPairs : 2;
+    // The first kAhead pairs are asked for here and pair i + kAhead when pair i is done: the requests of the
+    // thousands of waves that start together are spread out and everyone's first tiles arrive sooner.  Four, three and two ahead, us:
+    // four experts of 2048 x 1408 x 3 with streaming stores 18.98 / 18.91 / 18.86, with ordinary ones 23.84 / 23.35 / 22.23,
+    // 16 of 1024 x 2048 x 3 streaming 57.9 / 56.0 / 55.6; one ahead is behind two there (59.2), but ahead with the four waves of
+    // long codes: eight experts 35.6 -> 33.7.  In streams of several groups, of which fewer start together, a whole group.
+    constexpr int kAhead = kKind == kDeep ? kPairs : kLong && kKind != kShortStreams ? 1 : 2;
     const bool coded = mode == ZM_MODE_CODED;
-    const bool whole = sn % (kGroup * kTile) == 0;
+    const bool straight = kKind != kShortStreams && sn % (kGroup * kTile) == 0 && !dense;     // whole groups of tiles, decoded without a look at their ends
     uint2 up[kPairs], down[kPairs];
-    const ByteSource<kStores> sm(t.sm + v0, sn, lane);
-    if (kStores == kStreamingMany && coded && active && whole) {
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-            up[i] = sm.load_inside(i);
-            down[i] = sm.load_inside(tiles - 1u - i);
-        }
-    } else if (coded && active) {
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-            if (i < 2 || (whole && (i < kAhead || tiles > kGroup))) {
-                up[i] = sm.load(i);
-                down[i] = sm.load(tiles - 1u - i);
-            }
-        }
-    }
-
+    const ByteSource sm(t.sm + v0, sn, lane), first_sm(t.sm + v0, coded && active ? sn : 0u, lane);
+    auto ask = [&](int i) {        // tiles that the stream does not have read as zero and touch no memory
+        up[i] = first_sm.load(i);
+        down[i] = first_sm.load(tiles - 1u - i);
+    };
     // a3: decode table -> LDS with the two bytes of an entry swapped (length low).  Every wave of the workgroup writes the
     // same bytes (LDS word writes are atomic), so a wave may read as soon as its own writes are done: no workgroup barrier.
     LongTable table{0u, 0};
     bool narrow = false;         // long codes: the table has no room for all shared beginnings
-    {
+    auto stage = [&] {
         const uint32_t i = 4u * lane;
         const uint2 e = lut4;
         if constexpr (!kLong) {
@@ -691,12 +707,22 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
                 tab[whole_codes + k] = swap_entry(v);
             }
         }
-    }
-
-    if (n_held) {
-        uint4 *dst = reinterpret_cast<uint4 *>(words);
-        if (lane < n_held) dst[lane] = held_a;
-        if (lane + 64 < n_held) dst[lane + 64] = held_b;
+        u32x4 *dst = reinterpret_cast<u32x4 *>(words);
+#pragma unroll
+        for (uint32_t k = 0; k < kHeld; ++k)
+            if (lane + 64u * k < n_held) dst[lane + 64u * k] = held[k];
+    };
+    // The requests that follow a stream's are known to be so many when it is copied: no branch lies in between.  Where the
+    // compiler can not count them it waits for all of them, and decoding does not start before the sign-mantissa bytes have come.
+    // (One expert of 1024 x 2048 x 3, streaming stores 5.40 -> 5.18 us, eight 26.8 -> 26.55, one matrix of 256 x 512 3.92 -> 3.80.)
+    ask(0);
+    if (kAhead == 2 || !straight) {
+        ask(1);
+        stage();
+    } else {
+#pragma unroll
+        for (int i = 1; i < kAhead; ++i) ask(i);
+        stage();
     }
     // LDS written by some lanes of this wave is read by others: order the LDS accesses only
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
@@ -707,7 +733,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     const Sink<kStores> out(t.out + v0, sn, lane);
 
     if (!coded) {
-        merge_raw_stream(out, ByteSource<kStores>(raw, sn, lane), sm, tiles, mine);
+        merge_raw_stream(out, ByteSource(raw, sn, lane), sm, tiles, mine);
         return;
     }
     // a6: this lane's bitstream has 8 * tiles + quantum * (its length byte) bits and starts where
@@ -721,6 +747,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
             dec.words = words; dec.last_word = cap_words - 1u;
             dec.table = table;
             dec.start(first, first + bits);
+            if (kAhead < 2) ask(1);
             decode_any_stream(dec, lut, out, sm, 0u, tiles, mine, up, down);
             return;
         }
@@ -730,10 +757,9 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     dec.table = table;
     dec.start(first, first + bits);
     uint32_t done = 0;
-    if (whole && !dense) {
-        // kStreamingMany: streams have no more than one group
-        done = kStores == kStreamingMany || tiles == kGroup ? decode_stream<kLong, kAhead, true>(dec, tab, out, sm, tiles, up, down)
-                                                            : decode_stream<kLong, kPairs, false>(dec, tab, out, sm, tiles, up, down);
+    if (straight) {
+        if constexpr (kKind == kDeep) done = decode_groups(dec, tab, out, sm, tiles, up, down);
+        else done = decode_group<kLong, kAhead>(dec, tab, out, sm, 0u, tiles, up, down);
         if (!kLong || 2u * done >= tiles) return;
         up[0] = sm.load(done); down[0] = sm.load(tiles - 1u - done);
         up[1] = sm.load(done + 1u); down[1] = sm.load(tiles - 2u - done);
@@ -742,8 +768,8 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
 }
 
 
-template <bool kLong, int kWaves, Stores kStores, class Args>
-__global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
+template <bool kLong, int kWaves, Stores kStores, Kind kKind, class Args>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, most_waves(kKind, kLong)))) zm_decode_kernel(const Args P)
 {
     uint32_t block;
     const Task t = task_of(P, threadIdx.x & 63u, block);
@@ -753,11 +779,11 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_kernel(const Args P)
     // chunk-table entry read at once, the look-up table asked for before the stream, and no division).
     asm volatile("" :: "s"(t.lut), "s"(t.sm), "s"(t.echunks), "s"(t.table), "s"(t.out), "s"(t.e_offset), "s"(t.e_size), "s"(t.stream_values),
                        "s"(t.streams_per_chunk), "s"(t.per_chunk), "s"(t.n_streams), "s"(t.last_values), "s"(t.code), "s"(cap_words), "s"(long_slots));
-    decode_block<kLong, kWaves, kStores>(t, block, cap_words, long_slots);
+    decode_block<kLong, kWaves, kStores, kKind>(t, block, cap_words, long_slots);
 }
 
-template <bool kLong, int kWaves, Stores kStores>
-__global__ void __launch_bounds__(64 * kWaves) zm_decode_few_kernel(const Few P)
+template <bool kLong, int kWaves, Stores kStores, Kind kKind>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, most_waves(kKind, kLong)))) zm_decode_few_kernel(const Few P)
 {
     const uint32_t k = blockIdx.y;
     const uint32_t code = P.lead[0], n_streams = P.lead[1], last_lut = P.lead[2], table_offset = P.lead[3], sm_units = P.lead[4], e_at = P.lead[5];
@@ -771,7 +797,7 @@ __global__ void __launch_bounds__(64 * kWaves) zm_decode_few_kernel(const Few P)
     const Task t{blob + (last_lut >> 16), blob + static_cast<uint64_t>(sm_units) * 256u, blob + e_offset, reinterpret_cast<const uint64_t *>(blob + table_offset),
                  out + static_cast<uint64_t>(to_out) * 8u, e_offset, static_cast<uint64_t>(e_units) * 256u, W, 1u << shift, 1u << 31, n_streams,
                  last_lut & 0xffffu, max_len | shift << 4 | quantum << 9};
-    decode_block<kLong, kWaves, kStores>(t, blockIdx.x, stream_cap_words(W, kLong ? ZM_MAX_CODE_LEN : 8u, quantum), long_slots);
+    decode_block<kLong, kWaves, kStores, kKind>(t, blockIdx.x, stream_cap_words(W, kLong ? ZM_MAX_CODE_LEN : 8u, quantum), long_slots);
 }
 
 // Stand-alone tensor recovery (Sec. 3.3): one tile of 512 values per wave; lane j merges values
@@ -849,13 +875,6 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // three rows and lose in that one); from 64 MB on both are within 2 % of each other.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
-// Launches of more streams than this, of one group of tiles each, take kStreamingMany.  Its kernel has 74 registers and six waves
-// per SIMD where that of kStreaming has 70 and seven: 6144 and 7168 streams at work at a time, of which short launches prefer
-// the larger and long ones, bound by bandwidth, the smaller number.  Experts of 2048 x 1408 x 3 (2112 streams each), us with kStreaming / kStreamingMany, nothing cached:
-//   1: 7.62 / 7.68   2: 13.07 / 13.12   4: 22.94 / 22.94   5: 27.29 / 26.91   8: 41.08 / 40.85   10: 48.36 / 47.99
-// all cached, 4: 19.07 / 19.24; streams of 1024 values, 4: 19.26 / 20.36; of 16384 values, 8: 54.48 / 54.61.
-constexpr uint64_t kManyStreams = 9216;
-
 // Where the shapes of a call's launches go when they are asked for instead of launched.
 struct Recorder {
     zm_launch_shape *out;
@@ -877,15 +896,25 @@ struct Plan {
 };
 
 // args: an Args, or something that begins like one
-template <bool kLong, int kWaves, Stores kStores, class Args>
+template <bool kLong, int kWaves, Stores kStores, Kind kKind, class Args>
 int launch_kernel(void *args, const Plan &p)
 {
     void *argv[] = {args};
     const void *fn;
-    if constexpr (std::is_same<Args, Few>::value) fn = reinterpret_cast<const void *>(&zm_decode_few_kernel<kLong, kWaves, kStores>);
-    else fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, Args>);
+    if constexpr (std::is_same<Args, Few>::value) fn = reinterpret_cast<const void *>(&zm_decode_few_kernel<kLong, kWaves, kStores, kKind>);
+    else fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, kKind, Args>);
     // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
     return hipLaunchKernel(fn, p.grid, dim3(64 * kWaves), argv, p.lds, p.stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+}
+
+template <bool kLong, int kWaves, Kind kKind, class Args>
+int launch_stores(void *args, const Plan &p, Stores kind)
+{
+    switch (kind) {
+    case kStreaming: return launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p);
+    case kThrough: return launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
+    default: return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
+    }
 }
 
 template <bool kLong, int kWaves, class Args>
@@ -899,11 +928,17 @@ int launch_args(void *args, const Plan &p)
         ++p.rec->n;
         return ZM_OK;
     }
-    if constexpr (!kLong && kWaves == 2) {
-        if (streaming && p.n_streams > kManyStreams && p.max_stream == kGroup * kTile) return launch_kernel<kLong, kWaves, kStreamingMany, Args>(args, p);
+    const Stores kind = streaming ? kStreaming : p.out_bytes <= kThroughBytes ? kThrough : kOrdinary;
+    if constexpr (kWaves == 2) {
+        if (p.max_stream < kGroup * kTile) return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
+        if (p.max_stream == kGroup * kTile) {
+            if constexpr (kLong) return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
+            else if (p.n_streams <= kManyStreams) return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
+            else if (p.n_streams > kFewPerTensor * p.n_tasks) return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
+            else return launch_stores<kLong, kWaves, kManyTensors, Args>(args, p, kind);
+        }
     }
-    if (streaming) return launch_kernel<kLong, kWaves, kStreaming, Args>(args, p);
-    return p.out_bytes <= kThroughBytes ? launch_kernel<kLong, kWaves, kThrough, Args>(args, p) : launch_kernel<kLong, kWaves, kOrdinary, Args>(args, p);
+    return launch_stores<kLong, kWaves, kDeep, Args>(args, p, kind);
 }
 
 // Whether a launch numbers its workgroups through all tensors instead of giving every tensor as many as the largest has.

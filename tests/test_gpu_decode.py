@@ -662,3 +662,34 @@ def test_calls_of_few_tensors(C, W, max_len, count, shift, backwards):
         for stores in (zm.STORES_CACHED, zm.STORES_STREAMING):
             for e, g in zip(ids, decode_at(blobs, ids, stores, shift, 4096, backwards)):
                 assert np.array_equal(g, refs[e]) and np.array_equal(g, tensors[e])
+
+
+@pytest.mark.parametrize("W", [8192, 20480, 24576, 32768])
+@pytest.mark.parametrize("bits", [1, 2, 3, 5, 7])
+def test_long_streams_of_every_density(W, bits):
+    # streams of several groups of tiles that take between a kilobyte and thrice what a wave holds in registers, whole, cut off in
+    # front of a group's end and within a tile; every exponent's code has `bits` bits, or (long codes) around twice as many
+    rng = np.random.default_rng(W + bits)
+    blobs, tensors = [], []
+    for n in (3 * W, 2 * W + W // 2, W + 4096, 2 * W - 4095, W + 8 * 512 + 3):
+        e = 100 + rng.permutation(np.arange(n, dtype=np.uint32) % (1 << bits)).astype(np.uint16)
+        tensors.append((e << 7) | rng.integers(0, 128, n, dtype=np.uint16))
+        blobs.append(zm.compress(tensors[-1], 2 * W, W, 8)[0])
+        tensors.append(bursts(n, 60, 300, 20000 >> bits, bits))
+        blobs.append(zm.compress(tensors[-1], W, W, 12)[0])
+    for stores in (zm.STORES_CACHED, zm.STORES_STREAMING):
+        for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
+            assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
+
+
+@pytest.mark.parametrize("streams,count", [(7168, 1), (7169, 1), (1024, 7), (1024, 8), (1025, 8), (512, 14), (512, 15), (180, 48)])
+@pytest.mark.parametrize("stores,max_len", [(zm.STORES_CACHED, 8), (zm.STORES_STREAMING, 8), (zm.STORES_STREAMING, 12)])
+def test_launches_around_the_lines_between_wave_counts(streams, count, stores, max_len):
+    """as many streams as find a place at once and more, in one tensor and in many"""
+    n = streams * 4096 - 5
+    w = synth.special_tensor("gauss" if max_len == 8 else "wide", n + 64, seed=streams)
+    tensors = [[w[k % 8: k % 8 + n]] for k in range(count)]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, max_len, stores)
+    assert len(shapes) == 1
+    for a, g in zip(flat, got):
+        assert np.array_equal(g, a)
