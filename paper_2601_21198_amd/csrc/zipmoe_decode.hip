@@ -556,22 +556,19 @@ using Constant = __attribute__((address_space(4))) T;
 //                  1024 x 2048 x 3 in streams of 512 values, us at seven / eight waves: 31.6 / 30.3, long codes at five / eight 48.1 / 38.7
 //   kFitting       of one group, short codes, in launches of up to kManyStreams.  Four experts (6144 streams), all cached, at three / five /
 //                  seven waves: 14.9 / 14.4 / 13.5; up to two experts no difference
-//   kMany          of one group, in launches of more.  Six waves: what layers of large matrices take best, two of 4096 x 14336 x 3 at
-//                  three / five / six / seven: 196 / 192.2 / 191.5 / 191.1, 16 of 4096 x 4096 x 3 451 / 449 / 444 / 445.  Long codes four:
-//                  eight / 16 / 48 experts of 1024 x 2048 x 3 at three 27.1 / 61.5 / 171, four 27.3 / 61.2 / 178, five 27.7 / 62.7 / 181, eight
-//                  29.2 / - / -; default stores 37.9 / 68.3, 35.9 / 64.8, 36.0 / 66.0
-//   kManyTensors   the same where the launch has many tensors (kFewPerTensor), short codes: three.  Experts of 1024 x 2048 x 3 at three / six
-//                  waves: 16 59.4 / 61.2, 24 83.9 / 85.7, 48 163.9 / 167.6; 48 of 512 x 1024 x 3 42.9 / 44.9; ten of 2048 x 1408 x 3 49.1 / 50.1
+//   kMany          of one group, in launches of more: three waves, long codes four.  us, nothing cached, at three / four / six: one layer of
+//                  4096 x 4096 x 3 with streaming stores 29.7 / 30.2 / 30.8, two 55.4 / 56.1 / 57.1, two of 14336 x 4096 x 3 185.4 / 189.1 /
+//                  190.7, with device-scope stores one of 4096 x 4096 x 3 31.1 / 31.0 / 31.5, two 57.3 / 58.2 / 59.1, 48 of 512 x 1024 x 3
+//                  44.8 / 45.1 / 45.8 (five).  Long codes, eight / 16 experts of 1024 x 2048 x 3 at three 35.2 / 64.9, four 33.9 / 62.2,
+//                  five 34.2 / 63.3, seven 34.9 / 64.5
 //   kDeep          longer streams: three.  In streams of 8192 values four / eight / 16 experts of 1024 x 2048 x 3 at three 15.1 / 26.9 / 61.8, at
 //                  four 16.2 / 26.9 / 62.1, uncapped 16.2 / 28.4 / 63.6; of longer ones LDS holds fewer
-enum Kind { kShortStreams, kFitting, kMany, kManyTensors, kDeep };
+enum Kind { kShortStreams, kFitting, kMany, kDeep };
 constexpr int most_waves(Kind kind, bool long_codes)
 {
-    return kind == kShortStreams ? 8 : kind == kFitting ? 7 : kind == kMany ? (long_codes ? 4 : 6) : 3;
+    return kind == kShortStreams ? 8 : kind == kFitting ? 7 : kind == kMany && long_codes ? 4 : 3;
 }
-// Streams that are at work at a time with seven waves per SIMD; streams per tensor, on average, up to which a launch has many tensors
-// (at 4096 streams per tensor three waves are slower than six, at 704 faster).
-constexpr uint64_t kManyStreams = 7168, kFewPerTensor = 1024;
+constexpr uint64_t kManyStreams = 7168;      // that many are at work at a time with seven waves per SIMD
 
 // The stream of one wave.  kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is
 // written; cap_words: LDS words reserved per wave for its stream; long_slots: as in Launch
@@ -863,16 +860,16 @@ template <bool kLong>
 constexpr size_t kStaticLds = kLong ? 16 : 2 * kTableEntries;
 constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cache
 // What a launch leaves dirty in the L2 caches (eight of 4 MiB) is written back when it ends; device-scope stores spread that
-// over the launch, which pays while it is a large part of what the launch writes.  Experts of 1024 x 2048 x 3 (12.6 MB of bf16),
-// us per call with ordinary / device-scope stores:
-//                                        one           two           three           four
-//   inputs and outputs cached            6.2 /  4.9    9.0 /  6.5    11.1 /  8.9     13.3 / 12.1
-//   three sets in turn, all cached       6.6 /  5.1    9.2 /  8.0    11.2 / 10.7     13.3 / 14.5
-//   inputs from HBM, outputs cached      7.4 /  6.7   10.2 /  8.9    12.8 / 11.8     15.7 / 15.0
-//   neither cached                       7.9 /  7.2   11.2 / 10.2    14.7 / 14.1     18.0 / 17.6
-// A kernel that reads the words afterwards takes no longer.  The line was found by trying: it lies where three sets in turn
-// stop gaining (38 MB, three such experts: between 5 % slower and 6 % faster, depending on the shape; four gain in the other
-// three rows and lose in that one); from 64 MB on both are within 2 % of each other.
+// over the launch.  Experts of 1024 x 2048 x 3 (12 MiB each), us per call with ordinary / device-scope stores, short codes unless it says long:
+//   out, MiB                              48            72            96            96, long      192           288
+//   one set, all cached                   13.6 / 11.9   21.4 / 20.1   27.4 / 25.8   29.0 / 27.1   60.7 / 57.9   88.3 / 84.8
+//   inputs from HBM, one output set       15.3 / 15.2   23.0 / 21.4   28.9 / 26.9   30.8 / 29.5   59.6 / 58.3   86.5 / 84.7
+//   neither cached                        18.0 / 17.5   25.7 / 24.9   32.5 / 31.4   34.7 / 34.1   59.5 / 58.1   86.4 / 84.4
+//   the same and a kernel that reads      26.1 / 25.2   36.9 / 35.5   46.9 / 45.6   49.1 / 47.8   92.3 / 90.9   143.9 / 141.3
+// Device-scope stores are ahead in every row, and from streams of 512 to 16384 values, but for one place: launches of short codes that find
+// places for all of their waves (kFitting, up to 56 MiB) and take turns with two or three sets that stay cached.  There, from 38 MiB on (two
+// sets in turn, MiB: 36 11.2 / 11.2, 38 11.4 / 12.4, 48 13.6 / 14.5, 52 15.3 / 15.6, 54 15.8 / 16.0), fewer waves help neither (three / four /
+// five / six at 48 MiB: 14.0 / 14.4 / 14.7 / 14.5), and these keep ordinary stores.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
 // Where the shapes of a call's launches go when they are asked for instead of launched.
@@ -910,11 +907,10 @@ int launch_kernel(void *args, const Plan &p)
 template <bool kLong, int kWaves, Kind kKind, class Args>
 int launch_stores(void *args, const Plan &p, Stores kind)
 {
-    switch (kind) {
-    case kStreaming: return launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p);
-    case kThrough: return launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
-    default: return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
-    }
+    if constexpr (kKind == kFitting)
+        if (kind == kThrough && p.out_bytes > kThroughBytes) return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
+    return kind == kStreaming ? launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p)
+                              : launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
 }
 
 template <bool kLong, int kWaves, class Args>
@@ -928,14 +924,12 @@ int launch_args(void *args, const Plan &p)
         ++p.rec->n;
         return ZM_OK;
     }
-    const Stores kind = streaming ? kStreaming : p.out_bytes <= kThroughBytes ? kThrough : kOrdinary;
+    const Stores kind = streaming ? kStreaming : kThrough;
     if constexpr (kWaves == 2) {
         if (p.max_stream < kGroup * kTile) return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
         if (p.max_stream == kGroup * kTile) {
             if constexpr (kLong) return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
-            else if (p.n_streams <= kManyStreams) return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
-            else if (p.n_streams > kFewPerTensor * p.n_tasks) return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
-            else return launch_stores<kLong, kWaves, kManyTensors, Args>(args, p, kind);
+            else return p.n_streams <= kManyStreams ? launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind) : launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
         }
     }
     return launch_stores<kLong, kWaves, kDeep, Args>(args, p, kind);

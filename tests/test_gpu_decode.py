@@ -504,6 +504,19 @@ def test_launches_of_many_streams_with_streaming_stores(lengths):
         assert np.array_equal(g, a)
 
 
+@pytest.mark.parametrize("max_len", [8, 12])
+@pytest.mark.parametrize("lengths", [[7168 * 4096], [7168 * 4096 + 1], [11_000_003] * 3, [31_000_001, 5, 70_000], [660_007] * 60],
+                         ids=["at the line", "above it", "three", "numbered", "shared"])
+def test_launches_of_many_streams_that_stay_cached(lengths, max_len):
+    """up to 7168 streams of 4096 values and more of them, with stores that leave their lines cached"""
+    w = synth.special_tensor("gauss" if max_len == 8 else "wide", max(lengths), seed=6)
+    tensors = [[w[7 * i: 7 * i + n] if 7 * i + n <= w.size else w[:n]] for i, n in enumerate(lengths)]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, max_len, zm.STORES_CACHED)
+    assert sum(s.tensors for s in shapes) == len(lengths) and all(s.streaming_stores == 0 for s in shapes)
+    for a, g in zip(flat, got):
+        assert np.array_equal(g, a)
+
+
 def test_a_launch_of_many_streams_holds_tensors_of_every_kind():
     """raw chunks, cut-off streams and streams shorter than a group beside whole ones, in one launch of more than 9216 streams"""
     tensors = [synth.special_tensor("gauss", 40_000_003, 5)] + [synth.special_tensor(kind, n, n) for kind in ("uniform_u16", "rare_last", "all_equal")
