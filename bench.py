@@ -173,8 +173,8 @@ def bench_split(args, wl, workers: int, steps: int, warmup: int) -> int:
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": measured_traffic("split-" + args.workload),
                      # the library stores non-temporally when a launch moves more than 128 MiB (4 bytes per value)
-                     "kernel": "zm_recover_kernel<%s>" % ("kStreaming" if 4 * max(h[2] for h in dev) > (128 << 20) else
-                                                           "kThrough" if max(h[2] for h in dev) > (5 << 20) else "kOrdinary"),
+                     "kernel": "zm_recover_kernel<%s>" % ("kStreaming, 4, 1" if 4 * max(h[2] for h in dev) > (128 << 20) else
+                                                           "kThrough, 4, 4" if max(h[2] for h in dev) > (4 << 20) else "kThrough, 1, 4"),
                      "us_per_launch": round(kernel_s * 1e6, 2), "algorithmic_bytes_per_launch": alg},
         "host_decode": {"value": round(2.0 * n_total / host_dt / 1e9, 3), "unit": "GB/s of bf16", "threads": workers,
                         "note": "zm_decode_exponents_host over the same tensors, one after the other"},

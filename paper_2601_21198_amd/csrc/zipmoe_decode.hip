@@ -246,23 +246,6 @@ struct Sink {
     }
 };
 
-// Non-temporal, at an address that is a multiple of 16: four adjacent word stores, which the compiler merges into one.
-__device__ __forceinline__ void store_streaming(uint16_t *p, uint4 w)
-{
-    uint32_t *q = reinterpret_cast<uint32_t *>(__builtin_assume_aligned(p, 16));
-    __builtin_nontemporal_store(w.x, q); __builtin_nontemporal_store(w.y, q + 1);
-    __builtin_nontemporal_store(w.z, q + 2); __builtin_nontemporal_store(w.w, q + 3);
-}
-
-// The first `left` < 8 values of w.
-__device__ __forceinline__ void store_some(uint16_t *p, uint4 w, uint32_t left)
-{
-    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (uint32_t q = 0; q < 8; ++q)
-        if (q < left) p[q] = static_cast<uint16_t>(ws[q >> 1] >> (16 * (q & 1)));
-}
-
 __device__ __forceinline__ uint4 recover8(uint2 e, uint2 sm)
 {
     uint4 w;
@@ -797,58 +780,54 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
     decode_block<kLong, kWaves, kStores, kKind>(t, blockIdx.x, stream_cap_words(W, kLong ? ZM_MAX_CODE_LEN : 8u, quantum), long_slots);
 }
 
-// Stand-alone tensor recovery (Sec. 3.3): one tile of 512 values per wave; lane j merges values
-// 8j..8j+7 -- a 64-bit load from each input, one 128-bit store, all contiguous across the wave.
-constexpr int kRecoverTilesPerWave = 1;   // measured on 58.7 M-value tensors: 1 tile 68.9 %, 2: 68.3 %, 4: 67.4 %, 8: 65.7 % of 8 TB/s
-
-// Device-scope stores go through a descriptor of the wave's words; the others keep per-lane addresses: tensors of 4.2 M / 5.2 M /
-// 58.7 M values 3.31 / 3.77 / 41.00 us, through a descriptor and with an early exit 3.33 / 3.81 / 41.13.
-template <Stores kStores>
-__global__ void __launch_bounds__(256) zm_recover_kernel(const uint8_t *__restrict__ e, const uint8_t *__restrict__ sm,
-                                                         uint16_t *__restrict__ out, uint64_t n)
+// Stand-alone tensor recovery (Sec. 3.3): lane j merges values 8j..8j+7 of its wave's tiles -- per tile a 64-bit load from each
+// input and one 128-bit store, all contiguous across the wave.  Bound by the memory.  A wave asks for all of its tiles before it merges
+// the first; one, two, four and eight of them, us with buffers that are not cached: 58.7 M values (non-temporal stores, one wave per workgroup,
+// four per SIMD) 42.0 (four waves per workgroup) / 39.5 / 39.6 / 40.7, 37.7 M 26.2 / 25.5 / 24.8 / 25.1.  Four waves per workgroup take 39.7 with
+// four tiles; six or eight per SIMD 39.8.  With device-scope stores and four waves per workgroup, not cached 25 M 20.9 / 20.0 / 20.1 / -, 6.3 M 6.85 /
+// 6.6 / 6.55 / -, three sets that stay cached 6.3 M 5.0 / 4.3 / 4.1 / -, 4.2 M 2.6 / 2.7 / 2.8 / -, 1 M 1.66 / 1.69 / 1.76 / -: small tensors
+// need the waves.
+template <Stores kStores, int kTiles, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, kStores == kStreaming ? 4 : 8)))
+zm_recover_kernel(const uint8_t *__restrict__ e, const uint8_t *__restrict__ sm, uint16_t *__restrict__ out, uint64_t n)
 {
-    constexpr uint32_t kWaveValues = kRecoverTilesPerWave * kTile;
+    constexpr uint32_t kWaveValues = kTiles * kTile;
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = kStores == kThrough ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
-    const uint64_t first = (static_cast<uint64_t>(blockIdx.x) * 4u + wave) * kWaveValues;
-    if (kStores == kThrough && first >= n) return;
-    const uint64_t base = first + lane * 8u;
-    const uint64_t rest = first < n ? n - first : 0u;
-    const Sink<kStores> sink(out + first, rest < kWaveValues ? static_cast<uint32_t>(rest) : kWaveValues, lane);      // kThrough only
-    uint2 ev[kRecoverTilesPerWave], sv[kRecoverTilesPerWave];
+    // the first workgroup takes the tensor's end, whose last wave takes longer than the others
+    const uint64_t block = blockIdx.x ? blockIdx.x - 1u : (n - 1u) / (kWaves * kWaveValues);
+    const uint64_t first = (block * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kWaveValues;
+    if (first >= n) return;
+    const uint32_t have = n - first < kWaveValues ? static_cast<uint32_t>(n - first) : kWaveValues;
+    const Sink<kStores> sink(out + first, have, lane);
+    if (have == kWaveValues) {
+        const ByteSource es(e + first, have, lane), ss(sm + first, have, lane);
+        uint2 ev[kTiles], sv[kTiles];
 #pragma unroll
-    for (int k = 0; k < kRecoverTilesPerWave; ++k) {
-        const uint64_t i = base + static_cast<uint64_t>(k) * kTile;
-        ev[k] = sv[k] = make_uint2(0u, 0u);
-        if (i + 8 <= n) {
-            ev[k] = *reinterpret_cast<const uint2 *>(e + i);
-            sv[k] = *reinterpret_cast<const uint2 *>(sm + i);
-        } else if (i < n) {                       // the tensor's last, partial group of eight
-            uint32_t eb[2] = {0u, 0u}, sb[2] = {0u, 0u};
-            for (uint32_t q = 0; q < n - i; ++q) {
-                eb[q >> 2] |= static_cast<uint32_t>(e[i + q]) << (8 * (q & 3));
-                sb[q >> 2] |= static_cast<uint32_t>(sm[i + q]) << (8 * (q & 3));
-            }
-            ev[k] = make_uint2(eb[0], eb[1]); sv[k] = make_uint2(sb[0], sb[1]);
+        for (int k = 0; k < kTiles; ++k) { ev[k] = es.load(k); sv[k] = ss.load(k); }
+#pragma unroll
+        for (int k = 0; k < kTiles; ++k) sink.store(static_cast<uint32_t>(k), recover8(ev[k], sv[k]));
+        return;
+    }
+    // The tensor's last wave: whole groups of eight are read as above, past them nothing; the one lane that owns a part of a group reads
+    // it byte by byte.  All at once: tile by tile this wave alone took a microsecond (7.0 M values, cached, 4.6 us).
+    const ByteSource es(e + first, have & ~7u, lane), ss(sm + first, have & ~7u, lane);
+    uint2 ev[kTiles], sv[kTiles];
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) { ev[k] = es.load(k); sv[k] = ss.load(k); }
+    if ((have & 7u) && lane == (have >> 3 & 63u)) {
+        const uint32_t group = have & ~7u, left = have & 7u;
+        uint32_t eb[2] = {0u, 0u}, sb[2] = {0u, 0u};
+#pragma unroll
+        for (uint32_t q = 0; q < 7; ++q) {
+            const uint64_t i = first + group + (q < left ? q : 0u);       // past the end: the group's first byte again
+            eb[q >> 2] |= static_cast<uint32_t>(e[i]) << (8 * (q & 3));
+            sb[q >> 2] |= static_cast<uint32_t>(sm[i]) << (8 * (q & 3));
         }
+        sink.store_partial(have / kTile, recover8(make_uint2(eb[0], eb[1]), make_uint2(sb[0], sb[1])), left);
     }
 #pragma unroll
-    for (int k = 0; k < kRecoverTilesPerWave; ++k) {
-        const uint64_t i = base + static_cast<uint64_t>(k) * kTile;
-        const uint4 w = recover8(ev[k], sv[k]);
-        if constexpr (kStores == kThrough) {
-            if (i + 8 <= n) sink.store(static_cast<uint32_t>(k), w);
-            else if (i < n) sink.store_partial(static_cast<uint32_t>(k), w, static_cast<uint32_t>(n - i));
-        } else if (i + 8 <= n) {
-            if constexpr (kStores == kStreaming) {
-                store_streaming(out + i, w);
-            } else {
-                *reinterpret_cast<uint4 *>(out + i) = w;
-            }
-        } else if (i < n) {
-            store_some(out + i, w, static_cast<uint32_t>(n - i));
-        }
-    }
+    for (int k = 0; k < kTiles; ++k)
+        if (k * kTile + lane * 8u + 8u <= have) sink.store(static_cast<uint32_t>(k), recover8(ev[k], sv[k]));
 }
 
 // Streams share a workgroup's LDS up to this size; one that is longer by itself is refused.  A table of long codes
@@ -1332,22 +1311,23 @@ extern "C" int zm_recover(const void *exponents, const void *sign_mantissa, size
     if (!exponents || !sign_mantissa || !out_bf16) return ZM_E_ARG;
     if ((reinterpret_cast<uintptr_t>(exponents) & 7) || (reinterpret_cast<uintptr_t>(sign_mantissa) & 7) ||
         (reinterpret_cast<uintptr_t>(out_bf16) & 15)) return ZM_E_ARG;
-    const uint64_t per_block = 4ull * kRecoverTilesPerWave * kTile;
-    const uint64_t blocks = (n_values + per_block - 1) / per_block;
-    if (blocks > 0x7FFFFFFFull) return ZM_E_ARG;
+    constexpr uint64_t kSmallTensor = 4ull << 20;
+    constexpr int kRecoverTiles = 4;
     const uint8_t *e = static_cast<const uint8_t *>(exponents), *sm = static_cast<const uint8_t *>(sign_mantissa);
     uint16_t *out = static_cast<uint16_t *>(out_bf16);
     uint64_t n = n_values;
-    void *args[] = {&e, &sm, &out, &n};
     // A launch that moves more than half of the last-level cache (four bytes per value) writes with non-temporal
-    // stores: measured on 58.7 M-value tensors 71.6 against 68.9 % of the HBM roofline.  Smaller ones write with device-scope
-    // stores, us per call against ordinary ones, three sets in turn / outputs not cached: 8.4 M values 6.2 / 8.3 against
-    // 6.3 / 8.3, 16.8 M 10.7 / 13.9 against 10.9 / 14.2, 25 M 19.0 / 19.3 against 19.6 / 20.2.  Up to kOrdinaryValues the
-    // ordinary ones are ahead where the outputs are not cached: 2.9 M values 4.1 against 4.2, 4.2 M 4.9 against 5.1.
-    constexpr uint64_t kOrdinaryValues = 5ull << 20;
-    const void *fn = 4 * n > kLastLevelCacheBytes / 2 ? reinterpret_cast<const void *>(&zm_recover_kernel<kStreaming>)
-                     : n > kOrdinaryValues            ? reinterpret_cast<const void *>(&zm_recover_kernel<kThrough>)
-                                                      : reinterpret_cast<const void *>(&zm_recover_kernel<kOrdinary>);
-    return hipLaunchKernel(fn, dim3(static_cast<uint32_t>(blocks)), dim3(256),
+    // stores: measured on 58.7 M-value tensors 40.5 against 42.0 us with one tile per wave.  Smaller ones write with device-scope
+    // stores, us against ordinary ones with one tile, three sets in turn / not cached: 25 M values 20.3 / 20.9 against
+    // 21.3 / 21.9, 6.3 M 5.0 / 6.85 against 5.65 / 7.2, 4.2 M 2.6 / 5.1 against 3.3 / 4.9, 1 M 1.66 / 2.13 against 1.90 / 2.23.
+    const bool streaming = 4 * n > kLastLevelCacheBytes / 2, small = n <= kSmallTensor;
+    const uint64_t per_block = small ? 4 * kTile : streaming ? kRecoverTiles * kTile : 4 * kRecoverTiles * kTile;
+    const uint64_t blocks = (n + per_block - 1) / per_block;
+    if (blocks > 0x7FFFFFFFull) return ZM_E_ARG;
+    void *args[] = {&e, &sm, &out, &n};
+    const void *fn = streaming ? reinterpret_cast<const void *>(&zm_recover_kernel<kStreaming, kRecoverTiles, 1>)
+                     : small   ? reinterpret_cast<const void *>(&zm_recover_kernel<kThrough, 1, 4>)
+                               : reinterpret_cast<const void *>(&zm_recover_kernel<kThrough, kRecoverTiles, 4>);
+    return hipLaunchKernel(fn, dim3(static_cast<uint32_t>(blocks)), dim3(streaming ? 64 : 256),
                            args, 0, static_cast<hipStream_t>(stream)) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }

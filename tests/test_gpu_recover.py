@@ -49,6 +49,16 @@ def test_recover_at_the_line_between_the_store_kinds(n):
     assert np.array_equal(gpu_recover(e, sm), zo.merge(e, sm))
 
 
+@pytest.mark.parametrize("n", [(4 << 20) - 1, 4 << 20, (4 << 20) + 1, (4 << 20) + 2048 + 7, (4 << 20) + 4 * 2048 - 1, (4 << 20) + 5 * 2048 + 513,
+                               32 << 20, (32 << 20) + 1, (32 << 20) + 2047, (32 << 20) + 2048, (32 << 20) + 1536 + 8])
+def test_recover_where_waves_take_four_tiles(n):
+    """the lines between the three kernels, last waves that are whole, that hold one value and that end inside a tile"""
+    rng = np.random.default_rng(n)
+    e = rng.integers(0, 256, n, dtype=np.uint8)
+    sm = rng.integers(0, 256, n, dtype=np.uint8)
+    assert np.array_equal(gpu_recover(e, sm), zo.merge(e, sm))
+
+
 def test_recover_all_pairs():
     e = np.repeat(np.arange(256, dtype=np.uint8), 256)
     sm = np.tile(np.arange(256, dtype=np.uint8), 256)
