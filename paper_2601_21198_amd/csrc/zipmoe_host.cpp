@@ -13,6 +13,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <atomic>
+#include <memory>
 #include <new>
 #include <thread>
 #include <vector>
@@ -150,21 +151,86 @@ inline void put_four(BitSink &to, const uint32_t entry[256], const uint8_t *e)
 struct Packer {
     uint32_t up[256], down[256];      // code with its first bit lowest / highest, | length << 16
     std::vector<uint8_t> half;
+    // The same for two symbols at a time, | length << 24 | kAbsent where the book lacks one of them (with a length that keeps a lane's
+    // bits no fewer than its symbols), indexed by the two bytes as they lie in memory.  Only rows lowest..highest, of the second symbol, are
+    // filled.  One look-up and one merge for two symbols instead of two and two, and eight symbols for one put: 704 streams of 4096 values
+    // 3.1 -> 2.0 ms, with 0.045 for the tables; zm_encode of 2.9 M values 5.1 -> 2.5 ms, of 32 K 65 -> 48 us (one core at 2.7 GHz).
+    static constexpr uint32_t kAbsent = 1u << 31;
+    std::unique_ptr<uint32_t[]> up_pairs, down_pairs;
+    uint32_t lowest = 255, highest = 0;
 
-    Packer(const Book &b, uint32_t stream_values) : half(stream_values / kLanes * ZM_MAX_CODE_LEN / 16 + 16)
+    Packer(const Book &b, uint32_t stream_values, size_t n_values) : half(stream_values / kLanes * ZM_MAX_CODE_LEN / 16 + 16)
     {
-        for (int s = 0; s < 256; ++s) {
+        for (uint32_t s = 0; s < 256; ++s) {
             up[s] = b.wire[s] | static_cast<uint32_t>(b.len[s]) << 16;
             down[s] = b.canon[s] | static_cast<uint32_t>(b.len[s]) << 16;
+            if (!b.len[s]) continue;
+            lowest = std::min(lowest, s);
+            highest = std::max(highest, s);
+        }
+        // filling a table's entry takes about as long as the pairs save on one value
+        if (lowest > highest || 2 * 256 * static_cast<size_t>(highest - lowest + 1) > n_values) return;
+        up_pairs.reset(new uint32_t[256 * 256]);
+        down_pairs.reset(new uint32_t[256 * 256]);
+        for (uint32_t second = lowest; second <= highest; ++second) {
+            uint32_t *u = &up_pairs[256 * second], *d = &down_pairs[256 * second];
+            const uint32_t l2 = b.len[second];
+            for (uint32_t s = 0; s < 256; ++s) u[s] = d[s] = kAbsent | 2u << 24;
+            for (uint32_t s = lowest; l2 && s <= highest; ++s) {
+                const uint32_t l = b.len[s];
+                if (!l) continue;
+                u[s] = b.wire[s] | static_cast<uint32_t>(b.wire[second]) << l | (l + l2) << 24;
+                d[s] = b.canon[s] | static_cast<uint32_t>(b.canon[second]) << l | (l + l2) << 24;
+            }
         }
     }
+
+    // Whether the table of pairs may be looked up with the symbols of e.
+    bool covers(const uint8_t *e, size_t n) const
+    {
+        uint8_t low = 255, high = 0;
+        for (size_t i = 0; i < n; ++i) { low = std::min(low, e[i]); high = std::max(high, e[i]); }
+        return low >= lowest && high <= highest;
+    }
 };
+
+// The codes of four symbols from the table of pairs, and their bits in `count`; seen: the entries so far.
+inline uint64_t four_codes(const uint32_t *pairs, uint32_t four, uint32_t &count, uint32_t &seen)
+{
+    const uint32_t a = pairs[four & 0xffffu], b = pairs[four >> 16];
+    const uint32_t la = a >> 24 & 31u;
+    seen |= a | b;
+    count = la + (b >> 24 & 31u);
+    return (a & 0xffffffu) | static_cast<uint64_t>(b & 0xffffffu) << la;
+}
+
+inline void put_four(BitSink &to, const uint32_t *pairs, const uint8_t *e, uint32_t &seen)
+{
+    uint32_t n;
+    const uint64_t codes = four_codes(pairs, load_le<uint32_t>(e), n, seen);
+    to.put(codes, n);
+}
+
+// Eight symbols at once: a put waits for the one before it, and that chain is what packing takes.
+inline void put_eight(BitSink &to, const uint32_t *pairs, const uint8_t *e, uint32_t &seen)
+{
+    uint32_t n, m;
+    const uint64_t first = four_codes(pairs, load_le<uint32_t>(e), n, seen), second = four_codes(pairs, load_le<uint32_t>(e + 4), m, seen);
+    if (__builtin_expect(n + m <= 56, 1)) {
+        to.put(first | second << n, n + m);
+    } else {
+        to.put(first, n);
+        to.put(second, m);
+    }
+}
 
 // Packs the exponents of one stream of `tiles` tiles (padded to whole tiles): 64 length bytes, then the lanes' bitstreams
 // back to back (LSB first), zero bits to a multiple of 16 bytes.  A lane's bitstream holds the codes of its first half
 // of symbols from its first bit upwards and those of its second half, last symbol first, from its last bit downwards;
-// the unused bits sit in the middle.  Returns the bytes written; eight more may be overwritten.
-size_t pack_stream(const uint8_t *e, uint32_t tiles, Packer &book, uint32_t quantum, uint8_t *out)
+// the unused bits sit in the middle.  Returns the bytes written; eight more may be overwritten.  kPairs: through the tables of pairs, which
+// cover e; seen: see four_codes.
+template <bool kPairs>
+size_t pack_stream(const uint8_t *e, uint32_t tiles, Packer &book, uint32_t quantum, uint8_t *out, uint32_t &seen)
 {
     const uint32_t syms = tiles * kRun;                 // per lane
     BitSink to{out + kLanes};
@@ -175,23 +241,39 @@ size_t pack_stream(const uint8_t *e, uint32_t tiles, Packer &book, uint32_t quan
         // in ascending bit order: the first half's codes, first bit lowest; the zero bits in the middle; the
         // second half's codes from the half's first symbol (read last) to the lane's last symbol (read first),
         // each with its first bit highest.  A half is a whole number of fours.
-        for (uint32_t j = 0; j < syms / 2; j += 4) put_four(to, book.up, first + j / kRun * kTile + j % kRun);
         BitSink late{book.half.data()};
-        for (uint32_t j = syms / 2; j < syms; j += 4) put_four(late, book.down, first + j / kRun * kTile + j % kRun);
+        auto place = [&](uint32_t j) { return first + j / kRun * kTile + j % kRun; };
+        uint32_t j = 0;
+        if constexpr (kPairs) {
+            if (tiles % 2 == 0) {                       // both halves are whole runs
+                for (; j < syms / 2; j += kRun) {
+                    put_eight(to, book.up_pairs.get(), place(j), seen);
+                    put_eight(late, book.down_pairs.get(), place(syms / 2 + j), seen);
+                }
+            }
+        }
+        for (; j < syms / 2; j += 4) {
+            if constexpr (kPairs) {
+                put_four(to, book.up_pairs.get(), place(j), seen);
+                put_four(late, book.down_pairs.get(), place(syms / 2 + j), seen);
+            } else {
+                put_four(to, book.up, place(j));
+                put_four(late, book.down, place(syms / 2 + j));
+            }
+        }
         const uint32_t late_bits = static_cast<uint32_t>(late.p - book.half.data()) * 8 + late.fill;
         const uint32_t used = static_cast<uint32_t>(to.p - start) * 8 + to.fill - start_fill + late_bits;
         const uint32_t units = (used - syms + quantum - 1) / quantum;
         out[lane] = static_cast<uint8_t>(units);
-        for (uint32_t fillers = syms + quantum * units - used; fillers; ) {
-            const uint32_t k = std::min(fillers, 32u);
-            to.put(0, k);
-            fillers -= k;
-        }
+        // without a branch where one round does, as nearly always: the counts differ from lane to lane
+        uint32_t fillers = syms + quantum * units - used;
+        for (; fillers > 56; fillers -= 56) to.put(0, 56);
+        to.put(0, fillers);
         store_le<uint64_t>(late.p, late.acc);
         const uint8_t *from = book.half.data();
         uint32_t left = late_bits;
-        for (; left > 32; left -= 32, from += 4) to.put(load_le<uint32_t>(from), 32);
-        to.put(load_le<uint32_t>(from) & (0xffffffffu >> (32 - left)), left);     // every half has at least one symbol: left >= 1
+        for (; left > 56; left -= 56, from += 7) to.put(load_le<uint64_t>(from) & ((1ull << 56) - 1), 56);
+        to.put(load_le<uint64_t>(from) & ((1ull << left) - 1), left);             // at most 56
     }
     if (to.fill) to.put(0, 8 - to.fill);
     const size_t used = static_cast<size_t>(to.p - out), total = align_up(used, 16);
@@ -458,7 +540,7 @@ int zm_encode(const uint16_t *bf16, size_t n_values, uint32_t chunk_values, uint
         const size_t longest = static_cast<size_t>(align_up(std::min<uint64_t>(chunk_values, std::max<uint64_t>(n_values, 1)), kTile));
         std::vector<uint8_t> expo(longest);
         std::vector<uint8_t> coded(std::min<size_t>(max_streams, (longest + stream_values - 1) / stream_values) * stream_byte_bound(stream_values) + 8);
-        Packer packer(book, stream_values);
+        Packer packer(book, stream_values, n_values);
         uint64_t pos = e_off;
         for (size_t c = 0; c < chunks; ++c) {
             const size_t first = c * static_cast<size_t>(chunk_values);
@@ -471,20 +553,30 @@ int zm_encode(const uint16_t *bf16, size_t n_values, uint32_t chunk_values, uint
                 expo[i] = static_cast<uint8_t>(w >> 7);
                 sm[first + i] = static_cast<uint8_t>(((w >> 8) & 0x80) | (w & 0x7F));
             }
-            uint8_t seen[256] = {};
-            for (size_t i = 0; i < cn; ++i) seen[expo[i]] = 1;
-            for (int s = 0; s < 256; ++s) if (seen[s] && !book.len[s]) return ZM_E_ARG;
+            auto all_present = [&] {
+                uint8_t seen[256] = {};
+                for (size_t i = 0; i < cn; ++i) seen[expo[i]] = 1;
+                for (int s = 0; s < 256; ++s) if (seen[s] && !book.len[s]) return false;
+                return true;
+            };
+            const bool pairs = packer.up_pairs != nullptr;
+            if (pairs ? !packer.covers(expo.data(), cn) : !all_present()) return ZM_E_ARG;
             // positions past the end of the last tile hold the pad symbol
             std::memset(expo.data() + cn, static_cast<int>(book.pad), align_up(cn, kTile) - cn);
             uint8_t *entry = blob + table_off + static_cast<uint64_t>(stride) * c;      // zero so far
             size_t at = 0;                                                               // bytes
             bool smaller = true;
+            uint32_t seen = 0;
             for (uint32_t s = 0; s < streams; ++s) {
                 store_le<uint32_t>(entry + 8 + 4 * s, static_cast<uint32_t>(at));
                 const uint32_t sn = std::min(stream_values, cn - s * stream_values);
-                at += pack_stream(&expo[static_cast<size_t>(s) * stream_values], (sn + kTile - 1) / kTile, packer, quantum, &coded[at]);
+                const uint8_t *e = &expo[static_cast<size_t>(s) * stream_values];
+                const uint32_t tiles = (sn + kTile - 1) / kTile;
+                at += pairs ? pack_stream<true>(e, tiles, packer, quantum, &coded[at], seen) : pack_stream<false>(e, tiles, packer, quantum, &coded[at], seen);
                 if (at >= raw_bytes) { smaller = false; break; }
             }
+            // the table of pairs tells of symbols that the book lacks, as far as they were packed
+            if ((seen & Packer::kAbsent) || (pairs && !smaller && !all_present())) return ZM_E_ARG;
             uint64_t mode;
             if (smaller) {
                 store_le<uint32_t>(entry + 8 + 4 * streams, static_cast<uint32_t>(at));

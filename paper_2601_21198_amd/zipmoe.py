@@ -233,7 +233,8 @@ def encode(bf16, chunk_values: int, stream_values: int, code_len) -> Tuple[np.nd
     _check(lib().zm_encode(_ptr(w, ctypes.c_uint16), w.size, chunk_values, stream_values, _ptr(cl, ctypes.c_uint8),
                            _ptr(blob, ctypes.c_uint8), cap, ctypes.byref(size),
                            _ptr(offs, ctypes.c_uint64), offs.size, ctypes.byref(n_chunks)), "zm_encode")
-    return blob[: size.value].copy(), offs[: (n_chunks.value + 1) * words_per_entry].reshape(-1, words_per_entry).copy()
+    blob.resize(size.value, refcheck=False)           # gives back the rest in place; a copy takes 0.3 ms for 3.9 MB
+    return blob, offs[: (n_chunks.value + 1) * words_per_entry].reshape(-1, words_per_entry).copy()
 
 
 def compress(bf16, chunk_values: int, stream_values: int = 4096, max_len: int = 8) -> Tuple[np.ndarray, np.ndarray]:

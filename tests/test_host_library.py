@@ -88,6 +88,34 @@ def test_workload_tensors_match_reference():
         assert np.array_equal(zo.decode(blob), w.reshape(-1))
 
 
+@pytest.mark.parametrize("kind,max_len", [("gauss", 8), ("wide", 12), ("many_long", 12), ("all_equal", 8), ("two_exponents", 8), ("uniform_u16", 8)])
+@pytest.mark.parametrize("C,W", [(4096, 512), (3072, 1536), (16384, 4096), (32768, 32768)])
+def test_encode_through_the_table_of_symbol_pairs(kind, max_len, C, W):
+    """lengths around the one from which on symbols are packed in pairs, eight and four at a time, with codes of up to 96 bits for eight"""
+    for n in (511, 512 * 17, 512 * 24 + 7, 150_001):
+        w = synth.special_tensor(kind, n, seed=n)
+        lengths = zm.build_codebook(zm.exponent_histogram(w), max_len)
+        assert np.array_equal(zm.encode(w, C, W, lengths)[0], zo.encode(w, C, W, lengths))
+
+
+@pytest.mark.parametrize("symbol", [0, 90, 121, 255])
+@pytest.mark.parametrize("at", [0, 16384 * 2 + 5, 99_999])
+@pytest.mark.parametrize("raw", [False, True])
+def test_encode_refuses_a_symbol_without_a_code_in_a_long_tensor(symbol, at, raw):
+    rng = np.random.default_rng(3)
+    e = np.where(rng.random(100_000) < 0.5, 120, 100 + 4 * rng.integers(0, 10, 100_000)).astype(np.uint16)     # 121 lies between symbols
+    w = (e << 7) | rng.integers(0, 128, e.size, dtype=np.uint16)
+    hist = zm.exponent_histogram(w)
+    if raw:                                       # codes so long that every chunk is stored raw
+        hist[100:140:4] = [1, 1, 2, 4, 8, 16, 32, 64, 128, 256]
+        w[:] = (w & 127) | (100 << 7)
+    lengths = zm.build_codebook(hist, 12)
+    assert zm.encode(w, 16384, 4096, lengths)[0].size > 0
+    w[at] = symbol << 7
+    with pytest.raises(zm.ZipMoEError):
+        zm.encode(w, 16384, 4096, lengths)
+
+
 def test_encode_rejects_bad_arguments():
     w = synth.special_tensor("gauss", 5000, 0)
     lengths = zm.build_codebook(zm.exponent_histogram(w), 8)
