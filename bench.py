@@ -29,8 +29,8 @@ HBM_PEAK_GBPS = 8000.0        # MI355X published peak HBM3E bandwidth
 # copy of known size; the summaries are under profiles/).  Valid only for the kernel source they were taken
 # with: the entry is reported only while the source's hash still matches, else "traffic" is null.
 MEASURED_TRAFFIC = {
-    "kernel_sha256_16": "19113a8c478145c5",
-    "bytes_per_launch": {"cfg5": 117.17e6, "cfg3": 170.42e6, "cfg4": 1195.81e6, "split-cfg4": 234.95e6},
+    "kernel_sha256_16": "2fe9e91f255c58f6",
+    "bytes_per_launch": {"cfg5": 117.15e6, "cfg3": 170.4e6, "cfg4": 1195.72e6, "split-cfg4": 234.93e6},
 }
 
 
