@@ -1161,7 +1161,7 @@ int make_task(const zm_tensor_parts &pt, const zm_tensor_info &ti, void *out, Ta
     if ((reinterpret_cast<uintptr_t>(pt.table) & 15) || (reinterpret_cast<uintptr_t>(pt.chunk_offsets) & 7) ||
         (reinterpret_cast<uintptr_t>(pt.sm) & 15) || (reinterpret_cast<uintptr_t>(pt.echunks) & 15) ||
         (reinterpret_cast<uintptr_t>(out) & 15)) return ZM_E_ARG;
-    if (ti.stream_values == 0 || ti.stream_values % kTile || ti.chunk_values % ti.stream_values) return ZM_E_ARG;
+    if (ti.stream_values == 0 || ti.stream_values % kTile || ti.chunk_values == 0 || ti.chunk_values % ti.stream_values) return ZM_E_ARG;
     if (ti.max_len < 1 || ti.max_len > ZM_MAX_CODE_LEN) return ZM_E_ARG;
     const uint32_t span = (ti.max_len - 1) * (ti.stream_values / 64);
     if (ti.lane_quantum != (span + 254) / 255 + (span == 0)) return ZM_E_ARG;

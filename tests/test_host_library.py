@@ -307,6 +307,17 @@ def test_launch_shapes_follow_code_length_stream_length_and_output_size():
     assert [s.streaming_stores for s in zm.decode_launch_shapes([big], zm.STORES_CACHED)] == [0]
 
 
+@pytest.mark.parametrize("count", [1, 7, 60])
+def test_a_description_without_chunk_values_is_refused(count):
+    """zero chunk values pass the other checks of a description: they are a multiple of the stream's, with an entry of 16 bytes"""
+    info = zm.blob_info(zm.compress(synth.special_tensor("gauss", 70000, 3), 16384, 4096)[0])
+    bad = zm.TensorInfo.from_buffer_copy(info)
+    bad.chunk_values, bad.table_stride = 0, 16
+    with pytest.raises(zm.ZipMoEError) as refused:
+        zm.decode_launch_shapes([info] * (count - 1) + [bad])
+    assert refused.value.status == zm.E_ARG
+
+
 def test_cache_configuration_is_checked_on_the_host():
     w = synth.special_tensor("gauss", 5000, 0)
     blob, _ = zm.compress(w, 4096, 4096)
