@@ -1165,10 +1165,11 @@ int make_task(const zm_tensor_parts &pt, const zm_tensor_info &ti, void *out, Ta
     if (ti.max_len < 1 || ti.max_len > ZM_MAX_CODE_LEN) return ZM_E_ARG;
     const uint32_t span = (ti.max_len - 1) * (ti.stream_values / 64);
     if (ti.lane_quantum != (span + 254) / 255 + (span == 0)) return ZM_E_ARG;
-    if (ti.e_offset > ti.blob_size || ti.sm_offset + ((ti.n_values + 255) & ~255ull) > ti.e_offset) return ZM_E_ARG;
-    if (ti.table_stride != ((8u + 4u * (ti.chunk_values / ti.stream_values + 1u) + 7u) & ~7u)) return ZM_E_ARG;
-    const uint64_t n_streams = (ti.n_values + ti.stream_values - 1) / ti.stream_values;
+    // no sum here may wrap past 2^64
+    const uint64_t n_streams = (ti.n_values - 1) / ti.stream_values + 1;
     if (n_streams > 0x7FFFFFFFull) return ZM_E_ARG;
+    if (ti.e_offset > ti.blob_size || ti.sm_offset > ti.e_offset || ((ti.n_values + 255) & ~255ull) > ti.e_offset - ti.sm_offset) return ZM_E_ARG;
+    if (ti.table_stride != ((8u + 4u * (ti.chunk_values / ti.stream_values + 1u) + 7u) & ~7u)) return ZM_E_ARG;
     t.lut = static_cast<const uint8_t *>(pt.table);
     t.sm = static_cast<const uint8_t *>(pt.sm);
     t.echunks = static_cast<const uint8_t *>(pt.echunks);

@@ -318,6 +318,21 @@ def test_a_description_without_chunk_values_is_refused(count):
     assert refused.value.status == zm.E_ARG
 
 
+@pytest.mark.parametrize("n_values,sm_offset,e_offset", [
+    ((1 << 64) - 1, None, None), ((1 << 64) - 4095, None, None), ((1 << 64) - 4096, None, None), ((1 << 64) - 255, None, (1 << 64) - 1),
+    (1 << 20, (1 << 64) - (1 << 20), None), (70000, (1 << 64) - 256, None), ((4096 << 31) - 4095, None, 1 << 63)])
+@pytest.mark.parametrize("count", [1, 7])
+def test_counts_and_places_at_the_end_of_their_type_are_refused(n_values, sm_offset, e_offset, count):
+    """sums that would wrap past 2^64 pass no check, and no launch of no workgroups comes of them"""
+    info = zm.blob_info(zm.compress(synth.special_tensor("gauss", 70000, 3), 16384, 4096)[0])
+    bad = zm.TensorInfo.from_buffer_copy(info)
+    bad.n_values, bad.sm_offset, bad.e_offset = n_values, sm_offset or info.sm_offset, e_offset or info.e_offset
+    bad.blob_size = max(bad.blob_size, bad.e_offset)
+    with pytest.raises(zm.ZipMoEError) as refused:
+        zm.decode_launch_shapes([info] * (count - 1) + [bad])
+    assert refused.value.status == zm.E_ARG
+
+
 def test_cache_configuration_is_checked_on_the_host():
     w = synth.special_tensor("gauss", 5000, 0)
     blob, _ = zm.compress(w, 4096, 4096)
