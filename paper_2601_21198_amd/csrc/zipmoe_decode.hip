@@ -39,8 +39,11 @@
 #include <type_traits>
 
 #include "zipmoe.h"
+#include "zipmoe_extent.h"
 
 namespace {
+
+using zipmoe::kLaneBytes;
 
 constexpr int kMaxTensorsPerCall = 256;
 constexpr int kMaxTasks = 48;     // tensors per launch; 84 B each keeps the kernel arguments under 4 KiB
@@ -172,8 +175,6 @@ __host__ __device__ constexpr uint32_t long_table_words(uint32_t slots)
 {
     return (256u + ((1u << (ZM_MAX_CODE_LEN - 8)) - 1u) * slots + 7u) / 8u * 4u;
 }
-
-constexpr uint32_t kLaneBytes = 64;   // a stream opens with one length byte per lane
 
 // LDS words a wave reserves for one stream of the launch's longest kind: the length bytes, the code bits
 // of a lane bounded by the longest code, the rounding of every lane to the quantum, the padding to 16 bytes,
@@ -608,16 +609,13 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     u32x4 held[kHeld];
     uint32_t n_held = 0;
     bool dense = false;          // long codes: four symbols of a lane are likely to have more bits than a window
-    const uint64_t at = (ent & ~15ull) - t.e_offset;            // offset inside the E-chunk region
+    const uint64_t chunk = ent & ~15ull, at = chunk - t.e_offset;            // offsets inside the blob and the E-chunk region
     const uint32_t mode = static_cast<uint32_t>(ent & 15ull);
-    if ((ent & ~15ull) < t.e_offset) {
-        active = false;
-    } else if (mode == ZM_MODE_CODED) {
+    if (mode == ZM_MODE_CODED) {
         // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
         // sign-mantissa bytes because decoding can not start without them.  What is not held is copied here.
-        if (o1 < o0 + kLaneBytes || at + o1 > t.e_size) {
-            active = false;
-        } else {
+        active = zipmoe::stream_inside(chunk, o0, o1, t.e_offset, t.e_size);
+        if (active) {
             const uint32_t nvec = min((o1 - o0) >> 4, cap_words >> 2);
             if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
             const u32x4 *src = reinterpret_cast<const u32x4 *>(t.echunks + at + o0);
@@ -630,7 +628,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
         }
     } else {
         raw = t.echunks + at + static_cast<uint64_t>(s) * W;
-        if (mode != ZM_MODE_RAW || at + static_cast<uint64_t>(s) * W + ((sn + 15u) & ~15u) > t.e_size) active = false;
+        active = mode == ZM_MODE_RAW && zipmoe::raw_stream_inside(chunk, static_cast<uint64_t>(s) * W, (sn + 15u) & ~15u, t.e_offset, t.e_size);
     }
     if constexpr (kLong) lut_tail = lut[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
     // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
