@@ -40,17 +40,16 @@
 
 #include "zipmoe.h"
 #include "zipmoe_extent.h"
+#include "zipmoe_kinds.h"
 
 namespace {
 
-using zipmoe::kLaneBytes;
+using namespace zipmoe;
 
 constexpr int kMaxTensorsPerCall = 256;
 constexpr int kMaxTasks = 48;     // tensors per launch; 84 B each keeps the kernel arguments under 4 KiB
 constexpr int kFewTasks = 6;      // tensors of a launch with small arguments: two experts of three matrices
-constexpr uint32_t kTile = 512;
 constexpr int kRawBuffer = 0x00027000;   // last word of a descriptor of untyped memory
-constexpr int kGroup = 8;         // tiles whose sign-mantissa loads are in flight together
 
 // One tensor to decode.  Its parts may live in separate allocations (a cache may keep only some of them
 // resident), so each has a pointer of its own.
@@ -68,7 +67,6 @@ struct Task {
     uint32_t n_streams;
     uint32_t last_values;     // values of the last stream
     uint32_t code;            // longest code length | shift of the reciprocal << 4 | lane quantum << 9
-    __host__ __device__ uint64_t n_values() const { return static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values; }
 };
 __host__ __device__ constexpr uint32_t max_len_of(uint32_t code) { return code & 15u; }
 __host__ __device__ constexpr uint32_t quantum_of(uint32_t code) { return code >> 9; }
@@ -209,13 +207,6 @@ __device__ __forceinline__ void recover4(uint32_t e4, uint32_t sm4, uint32_t &w0
     w01 = __builtin_amdgcn_perm(hi4, lo4, 0x05010400u);
     w23 = __builtin_amdgcn_perm(hi4, lo4, 0x07030602u);
 }
-
-// How a wave writes its bf16 words.
-//   kOrdinary   the lines stay dirty in the L2 caches; what is left of them is written back when the kernel ends
-//   kThrough    device-scope stores: the L2 caches keep the line and pass it on to the last-level cache at once
-//   kStreaming  non-temporal: the output is larger than the last-level cache, or the caller said that its buffers are
-//               not cache-resident
-enum Stores { kOrdinary, kThrough, kStreaming };
 
 // Where they go: the first n_values of stream_base, lane j's eight words of tile k at k * kTile + 8 * j.  Buffer stores,
 // because 128-bit device-scope stores exist as these only; the descriptor covers the wave's words and nothing else.
@@ -427,7 +418,6 @@ __device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t t
 // Decodes a coded stream from both ends: pair p is tile p (upward chain) and tile tiles - 1 - p (downward chain), and
 // up[p % kPairs] / down[p % kPairs] receive their sign-mantissa bytes.  The first kAhead pairs' have been asked for by
 // the caller, the others of the first kPairs pairs are asked for when pair p - kAhead is done.
-constexpr int kPairs = kGroup / 2;
 
 // Pairs first .. first + kPairs - 1.  Returns how many are done: with long codes, a pair in which a lane's four symbols had more
 // bits than a window is left alone, with the decoder as it was in front of it.
@@ -533,27 +523,6 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
 template <class T>
 using Constant = __attribute__((address_space(4))) T;
 
-// What a launch's streams are, and how many waves of it a SIMD holds at most (the registers would admit seven or eight; the
-// compiler is told, and reserves what keeps the others out).  A launch that finds places for all of its waves is the faster the more
-// it has; one that does not is bound by the memory, which serves fewer waves, with fewer places open at a time, faster.
-//   kShortStreams  streams of less than one group of tiles: bound by their waves' latencies, so as many as go.  Eight experts of
-//                  1024 x 2048 x 3 in streams of 512 values, us at seven / eight waves: 31.6 / 30.3, long codes at five / eight 48.1 / 38.7
-//   kFitting       of one group, short codes, in launches of up to kManyStreams.  Four experts (6144 streams), all cached, at three / five /
-//                  seven waves: 14.9 / 14.4 / 13.5; up to two experts no difference
-//   kMany          of one group, in launches of more: three waves, long codes four.  us, nothing cached, at three / four / six: one layer of
-//                  4096 x 4096 x 3 with streaming stores 29.7 / 30.2 / 30.8, two 55.4 / 56.1 / 57.1, two of 14336 x 4096 x 3 185.4 / 189.1 /
-//                  190.7, with device-scope stores one of 4096 x 4096 x 3 31.1 / 31.0 / 31.5, two 57.3 / 58.2 / 59.1, 48 of 512 x 1024 x 3
-//                  44.8 / 45.1 / 45.8 (five).  Long codes, eight / 16 experts of 1024 x 2048 x 3 at three 35.2 / 64.9, four 33.9 / 62.2,
-//                  five 34.2 / 63.3, seven 34.9 / 64.5
-//   kDeep          longer streams: three.  In streams of 8192 values four / eight / 16 experts of 1024 x 2048 x 3 at three 15.1 / 26.9 / 61.8, at
-//                  four 16.2 / 26.9 / 62.1, uncapped 16.2 / 28.4 / 63.6; of longer ones LDS holds fewer
-enum Kind { kShortStreams, kFitting, kMany, kDeep };
-constexpr int most_waves(Kind kind, bool long_codes)
-{
-    return kind == kShortStreams ? 8 : kind == kFitting ? 7 : kind == kMany && long_codes ? 4 : 3;
-}
-constexpr uint64_t kManyStreams = 7168;      // that many are at work at a time with seven waves per SIMD
-
 // The stream of one wave.  kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is
 // written; cap_words: LDS words reserved per wave for its stream; long_slots: as in Launch
 template <bool kLong, int kWaves, Stores kStores, Kind kKind>
@@ -614,7 +583,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     if (mode == ZM_MODE_CODED) {
         // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
         // sign-mantissa bytes because decoding can not start without them.  What is not held is copied here.
-        active = zipmoe::stream_inside(chunk, o0, o1, t.e_offset, t.e_size);
+        active = stream_inside(chunk, o0, o1, t.e_offset, t.e_size);
         if (active) {
             const uint32_t nvec = min((o1 - o0) >> 4, cap_words >> 2);
             if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
@@ -628,19 +597,15 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
         }
     } else {
         raw = t.echunks + at + static_cast<uint64_t>(s) * W;
-        active = mode == ZM_MODE_RAW && zipmoe::raw_stream_inside(chunk, static_cast<uint64_t>(s) * W, (sn + 15u) & ~15u, t.e_offset, t.e_size);
+        active = mode == ZM_MODE_RAW && raw_stream_inside(chunk, static_cast<uint64_t>(s) * W, (sn + 15u) & ~15u, t.e_offset, t.e_size);
     }
     if constexpr (kLong) lut_tail = lut[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
     // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
     // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
-    // The first kAhead pairs are asked for here and pair i + kAhead when pair i is done: the requests of the
-    // thousands of waves that start together are spread out and everyone's first tiles arrive sooner.  Four, three and two ahead, us:
-    // four experts of 2048 x 1408 x 3 with streaming stores 18.98 / 18.91 / 18.86, with ordinary ones 23.84 / 23.35 / 22.23,
-    // 16 of 1024 x 2048 x 3 streaming 57.9 / 56.0 / 55.6; one ahead is behind two there (59.2), but ahead with the four waves of
-    // long codes: eight experts 35.6 -> 33.7.  In streams of several groups, of which fewer start together, a whole group.
-    constexpr int kAhead = kKind == kDeep ? kPairs : kLong && kKind != kShortStreams ? 1 : 2;
+    constexpr int kAhead = pairs_ahead(kKind, kLong, kStores);
+    constexpr bool kGroups = kKind == kDeep;          // there may be streams of several groups
     const bool coded = mode == ZM_MODE_CODED;
-    const bool straight = kKind != kShortStreams && sn % (kGroup * kTile) == 0 && !dense;     // whole groups of tiles, decoded without a look at their ends
+    const bool straight = kKind != kShortStreams && (kGroups ? sn % kGroupValues == 0 : sn == kGroupValues) && !dense;     // whole groups of tiles, decoded without a look at their ends
     uint2 up[kPairs], down[kPairs];
     const ByteSource sm(t.sm + v0, sn, lane), first_sm(t.sm + v0, coded && active ? sn : 0u, lane);
     auto ask = [&](int i) {        // tiles that the stream does not have read as zero and touch no memory
@@ -736,7 +701,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     dec.start(first, first + bits);
     uint32_t done = 0;
     if (straight) {
-        if constexpr (kKind == kDeep) done = decode_groups(dec, tab, out, sm, tiles, up, down);
+        if constexpr (kGroups) done = decode_groups(dec, tab, out, sm, tiles, up, down);
         else done = decode_group<kLong, kAhead>(dec, tab, out, sm, 0u, tiles, up, down);
         if (!kLong || 2u * done >= tiles) return;
         up[0] = sm.load(done); down[0] = sm.load(tiles - 1u - done);
@@ -844,7 +809,7 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 //   neither cached                        18.0 / 17.5   25.7 / 24.9   32.5 / 31.4   34.7 / 34.1   59.5 / 58.1   86.4 / 84.4
 //   the same and a kernel that reads      26.1 / 25.2   36.9 / 35.5   46.9 / 45.6   49.1 / 47.8   92.3 / 90.9   143.9 / 141.3
 // Device-scope stores are ahead in every row, and from streams of 512 to 16384 values, but for one place: launches of short codes that find
-// places for all of their waves (kFitting, up to 56 MiB) and take turns with two or three sets that stay cached.  There, from 38 MiB on (two
+// places for all of their waves (up to 56 MiB) and take turns with two or three sets that stay cached.  There, from 38 MiB on (two
 // sets in turn, MiB: 36 11.2 / 11.2, 38 11.4 / 12.4, 48 13.6 / 14.5, 52 15.3 / 15.6, 54 15.8 / 16.0), fewer waves help neither (three / four /
 // five / six at 48 MiB: 14.0 / 14.4 / 14.7 / 14.5), and these keep ordinary stores.
 constexpr uint64_t kThroughBytes = 36ull << 20;
@@ -861,9 +826,7 @@ struct Plan {
     dim3 grid;
     uint32_t n_tasks;
     size_t lds;              // dynamic part: the streams
-    uint64_t out_bytes;
-    uint64_t n_streams;
-    uint32_t max_stream;     // values of the longest one
+    Streams streams;
     int stores;
     hipStream_t stream;
     Recorder *rec;
@@ -885,7 +848,8 @@ template <bool kLong, int kWaves, Kind kKind, class Args>
 int launch_stores(void *args, const Plan &p, Stores kind)
 {
     if constexpr (kKind == kFitting)
-        if (kind == kThrough && p.out_bytes > kThroughBytes) return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
+        if (kind == kThrough && p.streams.out_bytes() > kThroughBytes && p.streams.longest == kGroupValues && p.streams.n <= kManyStreams)
+            return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
     return kind == kStreaming ? launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p)
                               : launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
 }
@@ -893,7 +857,7 @@ int launch_stores(void *args, const Plan &p, Stores kind)
 template <bool kLong, int kWaves, class Args>
 int launch_args(void *args, const Plan &p)
 {
-    const bool streaming = p.stores == ZM_STORES_STREAMING || (p.stores == ZM_STORES_AUTO && p.out_bytes > kLastLevelCacheBytes);
+    const bool streaming = p.stores == ZM_STORES_STREAMING || (p.stores == ZM_STORES_AUTO && p.streams.out_bytes() > kLastLevelCacheBytes);
     if (p.rec) {
         if (p.rec->n < p.rec->cap)
             p.rec->out[p.rec->n] = zm_launch_shape{kLong ? 2u : 4u, static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, p.grid.x,
@@ -903,10 +867,13 @@ int launch_args(void *args, const Plan &p)
     }
     const Stores kind = streaming ? kStreaming : kThrough;
     if constexpr (kWaves == 2) {
-        if (p.max_stream < kGroup * kTile) return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
-        if (p.max_stream == kGroup * kTile) {
-            if constexpr (kLong) return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
-            else return p.n_streams <= kManyStreams ? launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind) : launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
+        switch (kind_of(kLong, p.streams, kind)) {
+        case kShortStreams: return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
+        case kFitting:
+            if constexpr (!kLong) return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
+            break;
+        case kMany: return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
+        case kDeep: break;
         }
     }
     return launch_stores<kLong, kWaves, kDeep, Args>(args, p, kind);
@@ -925,22 +892,22 @@ bool number_through(uint64_t useful, uint64_t started)
 }
 
 template <bool kLong, int kWaves, int N>
-int launch_tasks(Launch<N, true> &L, size_t cap, uint32_t max_stream, int stores, hipStream_t stream, Recorder *rec)
+int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream, Recorder *rec)
 {
     const size_t streams = 4 * kWaves * cap, lds = streams + (kLong ? 4 * long_table_words(L.long_slots) : 0);   // dynamic part
     if (streams + kBesideStreams<kLong> > kLdsLimit) {
-        if constexpr (kWaves > 1) return launch_tasks<kLong, kWaves / 2>(L, cap, max_stream, stores, stream, rec);
+        if constexpr (kWaves > 1) return launch_tasks<kLong, kWaves / 2>(L, cap, stores, stream, rec);
         else return ZM_E_ARG;                   // stream too long to stage in LDS
     }
     uint32_t blocks = 0;            // of the largest tensor
-    uint64_t total = 0, out_bytes = 0, n_streams = 0;
+    uint64_t total = 0;
+    Streams streams_of;
     for (uint32_t k = 0; k < L.n_tasks; ++k) {
         const uint32_t b = (L.task[k].n_streams + kWaves - 1) / kWaves;
         L.first_block[k] = static_cast<uint32_t>(total);
         blocks = b > blocks ? b : blocks;
         total += b;
-        out_bytes += 2 * L.task[k].n_values();
-        n_streams += L.task[k].n_streams;
+        streams_of.add(L.task[k].stream_values, L.task[k].n_streams, L.task[k].last_values);
     }
     if (!blocks) return ZM_OK;
     // without the workgroup numbers the arguments are the same up to the end of the tasks
@@ -949,8 +916,8 @@ int launch_tasks(Launch<N, true> &L, size_t cap, uint32_t max_stream, int stores
     static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
     // a launch admits 2^32 - 1 threads in x
     if (total <= UINT32_MAX / (64u * kWaves) && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
-        return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, out_bytes, n_streams, max_stream, stores, stream, rec});
-    return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, out_bytes, n_streams, max_stream, stores, stream, rec});
+        return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, streams_of, stores, stream, rec});
+    return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, streams_of, stores, stream, rec});
 }
 
 // Collects the tensors of one round length and launches them.
@@ -1078,9 +1045,10 @@ struct Group {
             F.e_units[k] = static_cast<uint32_t>(t[j].e_size >> 8);
         }
         const size_t words = cap.words(), table = kLong ? 4 * long_table_words(cap.long_slots) : 0;
-        const uint64_t n_all = n, out_bytes = 2 * n_all * t[0].n_values(), n_streams = n_all * t[0].n_streams;
+        Streams streams_of;
+        for (int k = 0; k < n; ++k) streams_of.add(W, t[k].n_streams, t[k].last_values);
         auto plan = [&](uint32_t waves) {
-            return Plan{dim3((t[0].n_streams + waves - 1) / waves, static_cast<uint32_t>(n)), static_cast<uint32_t>(n), 4 * waves * words + table, out_bytes, n_streams, W, stores, stream, rec};
+            return Plan{dim3((t[0].n_streams + waves - 1) / waves, static_cast<uint32_t>(n)), static_cast<uint32_t>(n), 4 * waves * words + table, streams_of, stores, stream, rec};
         };
         if (8 * words + kBesideStreams<kLong> <= kLdsLimit) rc = launch_args<kLong, 2, Few>(&F, plan(2));
         else if (4 * words + kBesideStreams<kLong> <= kLdsLimit) rc = launch_args<kLong, 1, Few>(&F, plan(1));
@@ -1101,7 +1069,7 @@ struct Group {
             }
             L.long_slots = cap.long_slots;
             L.stream_cap_words = static_cast<uint32_t>(cap.words());
-            const int rc = launch_tasks<kLong, 2>(L, cap.words(), cap.max_stream, stores, stream, rec);
+            const int rc = launch_tasks<kLong, 2>(L, cap.words(), stores, stream, rec);
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;
@@ -1134,16 +1102,15 @@ struct Group {
         for (int at = 0; at < n; at += static_cast<int>(L.n_tasks)) {
             L.n_tasks = static_cast<uint32_t>(n - at < each ? n - at : each);
             uint32_t blocks = 0;
-            uint64_t out_bytes = 0, n_streams = 0;
+            Streams streams_of;
             for (uint32_t k = 0; k < L.n_tasks; ++k) {
                 L.task[k] = packed[at + static_cast<int>(k)];
                 const Shape &s = shape[L.task[k].high >> 12 & (kMaxShapes - 1u)];
                 const uint32_t b = (s.n_streams + 1u) / 2u;
                 blocks = b > blocks ? b : blocks;
-                out_bytes += 2 * (static_cast<uint64_t>(s.n_streams - 1u) * s.stream_values + s.last_values);
-                n_streams += s.n_streams;
+                streams_of.add(s.stream_values, s.n_streams, s.last_values);
             }
-            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), out_bytes, n_streams, cap_of_all.max_stream, stores, stream, rec});
+            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), streams_of, stores, stream, rec});
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;

@@ -1,0 +1,87 @@
+// Which kernel decodes a launch: what its streams are, how many waves of it a SIMD holds at most and how early a wave asks for its
+// sign-mantissa bytes.  Plain C++: the rule is host code, its answers are template arguments of the kernels.
+//
+// A launch that finds places for all of its waves is the faster the more it has; one that does not is bound by the memory, which serves fewer
+// waves, with fewer places open at a time, faster -- if they decode straight through.  Streams that do not (shorter than a group of tiles, no
+// whole groups) wait for each tile and need the waves.  Figures are us, GPU time by graph replay, of experts of 1024 x 2048 x 3
+// with inputs and outputs that are not cached unless they say otherwise; nt: non-temporal stores, dev: device-scope stores.
+#pragma once
+#include <cstdint>
+
+namespace zipmoe {
+
+constexpr uint32_t kTile = 512;
+constexpr int kGroup = 8;                 // tiles of a stream that are decoded straight through; tile i and tile 7 - i are a pair
+constexpr int kPairs = kGroup / 2;
+constexpr uint32_t kGroupValues = kGroup * kTile;
+constexpr uint64_t kSimds = 1024;         // 256 CUs of four
+constexpr uint64_t kManyStreams = 7 * kSimds;      // that many are at work at a time with seven waves per SIMD
+
+// How a wave writes its bf16 words.
+//   kOrdinary   the lines stay dirty in the L2 caches; what is left of them is written back when the kernel ends
+//   kThrough    device-scope stores: the L2 caches keep the line and pass it on to the last-level cache at once
+//   kStreaming  non-temporal: the output is larger than the last-level cache, or the caller said that its buffers are
+//               not cache-resident
+enum Stores { kOrdinary, kThrough, kStreaming };
+
+//   kShortStreams  streams shorter than a group: bound by their waves' latencies, so as many as go
+//   kFitting       of one group, short codes, in launches of up to kManyStreams; streams of no whole groups whatever their number
+//   kMany          of one group, in launches of more
+//   kDeep          of several whole groups
+enum Kind { kShortStreams, kFitting, kMany, kDeep };
+
+// What a launch decodes.
+struct Streams {
+    uint64_t n = 0;
+    uint64_t in_groups = 0;                      // of tensors whose streams are several whole groups of tiles
+    uint64_t values = 0;
+    uint32_t longest = 0;                        // values of the longest stream
+    void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values)
+    {
+        n += n_streams;
+        in_groups += stream_values > kGroupValues && stream_values % kGroupValues == 0 ? n_streams : 0u;
+        values += static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values;
+        longest = longest > stream_values ? longest : stream_values;
+    }
+    uint64_t out_bytes() const { return 2 * values; }
+};
+
+// stores: kThrough or kStreaming.
+//   no whole groups, longer than one: 6144 values, four experts nt 20.9 with three waves, 18.3 with seven, dev 23.9 / 20.2; long codes as short streams.
+inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
+{
+    (void)stores;
+    if (s.in_groups || s.longest > 2 * kGroupValues) return kDeep;
+    if (s.longest < kGroupValues) return kShortStreams;
+    if (s.longest > kGroupValues) return long_codes ? kShortStreams : kFitting;
+    return long_codes || s.n > kManyStreams ? kMany : kFitting;
+}
+
+// Waves that a SIMD holds at most (the registers would admit six to eight; the compiler is told, and reserves what keeps the others out.
+// Keeping them out by LDS instead is not as good: four experts with long codes nt 20.0 against 19.2).
+//   kShortStreams  eight experts in streams of 512 values at seven / eight waves: 31.6 / 30.3, long codes at five / eight 48.1 / 38.7
+//   kFitting       four experts (6144 streams), all cached, at three / five / seven waves: 14.9 / 14.4 / 13.5.
+//   kMany          three; at three / four / six: one layer of 4096 x 4096 x 3 nt 29.7 / 30.2 / 30.8, two 55.4 / 56.1 / 57.1, two of
+//                  14336 x 4096 x 3 185.4 / 189.1 / 190.7, dev one of 4096 x 4096 x 3 31.1 / 31.0 / 31.5, two 57.3 / 58.2 / 59.1, 48 of 512 x 1024 x 3
+//                  44.8 / 45.1 / 45.8 (five).  Long codes, one pair ahead, eight / 16 experts at three 35.2 / 64.9, four 33.9 / 62.2, five 34.2 / 63.3
+//   kDeep          three.  8192 values, four / eight / 16 experts at three 15.1 / 26.9 / 61.8, at four 16.2 / 26.9 / 62.1, uncapped 16.2 / 28.4 /
+//                  63.6; of longer ones LDS holds fewer
+constexpr int most_waves(Kind kind, bool long_codes)
+{
+    return kind == kShortStreams ? 8 : kind == kFitting ? 7 : kind == kMany ? (long_codes ? 4 : 3) : 3;
+}
+
+// Pairs of tiles of a group whose sign-mantissa bytes a wave asks for before it decodes the first; pair i + that many is asked for when pair i is
+// done.  All up front, the thousands of waves that start together queue behind each other's late tiles; few, a wave waits for a load
+// behind its own stores.
+//   short codes    two: four experts of 2048 x 1408 x 3 nt with four / three / two ahead 18.98 / 18.91 / 18.86, 16 experts 57.9 / 56.0 / 55.6 (one 59.2).
+//   long codes     one: eight experts dev two / one 35.6 / 33.7
+constexpr int pairs_ahead(Kind kind, bool long_codes, Stores stores)
+{
+    if (kind == kShortStreams) return 2;         // never straight through
+    if (kind == kDeep) return kPairs;
+    (void)stores;
+    return long_codes ? 1 : 2;
+}
+
+}  // namespace zipmoe

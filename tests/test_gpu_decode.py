@@ -706,3 +706,18 @@ def test_launches_around_the_lines_between_wave_counts(streams, count, stores, m
     assert len(shapes) == 1
     for a, g in zip(flat, got):
         assert np.array_equal(g, a)
+
+
+@pytest.mark.parametrize("max_len", [8, 12])
+@pytest.mark.parametrize("W", [4608, 6144, 7680, 10240, 14336])
+def test_streams_of_no_whole_groups(W, max_len):
+    """longer than a group of tiles and no multiple of it, with last streams that are whole groups all the same or end inside a tile"""
+    lengths = [3 * W, 2 * W + 4096, 5 * W + 8192 if W > 8192 else 5 * W + 512, W + 1, 2 * W - 511, 4096, 40 * W - 5]
+    tensors = [synth.special_tensor("gauss" if max_len == 8 else "wide", n, seed=n) for n in lengths]
+    tensors.append(bursts(3 * W, 60, 300, 5000, W))
+    blobs = [zm.compress(w, 2 * W, W, max_len)[0] for w in tensors]
+    for stores in (zm.STORES_CACHED, zm.STORES_STREAMING):
+        for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
+            assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
+        for i in range(3):
+            assert np.array_equal(gpu_decode_tensors(blobs[i: i + 1], stores=stores)[0], tensors[i])

@@ -1,0 +1,48 @@
+"""Which kernel a launch takes (zipmoe_kinds.h, built as host code): at the lines between the kinds, and for what a line could miss."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "zipmoe_kinds.h"
+// long_codes streaming {stream_values n_streams last_values e_size}...
+int main(int argc, char **argv)
+{
+    static const char *const names[] = {"short", "fitting", "many", "deep"};
+    zipmoe::Streams s;
+    for (int i = 3; i + 3 < argc; i += 4)
+        s.add(std::strtoul(argv[i], nullptr, 10), std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10));
+    const bool long_codes = argv[1][0] == '1';
+    const zipmoe::Stores stores = argv[2][0] == '1' ? zipmoe::kStreaming : zipmoe::kThrough;
+    const zipmoe::Kind k = zipmoe::kind_of(long_codes, s, stores);
+    std::printf("%s %d %d\n", names[k], zipmoe::most_waves(k, long_codes), zipmoe::pairs_ahead(k, long_codes, stores));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def kind_of(tmp_path_factory):
+    at = tmp_path_factory.mktemp("kinds")
+    (at / "kinds.cpp").write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2601_21198_amd", "csrc"), str(at / "kinds.cpp"), "-o", str(at / "kinds")])
+
+    def ask(tensors, long_codes=False, streaming=False, bits=3):
+        """tensors: (stream_values, streams), whole streams of `bits` bits of code a value; bits = 8: stored raw"""
+        args = [str(x) for w, n in tensors for x in (w, n, w, w * n * bits // 8 + (256 if bits == 8 else 0))]
+        name, waves, ahead = subprocess.check_output([str(at / "kinds"), str(int(long_codes)), str(int(streaming)), *args], text=True).split()
+        return name, int(waves), int(ahead)
+    return ask
+
+
+@pytest.mark.parametrize("streaming", [False, True])
+@pytest.mark.parametrize("w", [4608, 5632, 6144, 7680])
+@pytest.mark.parametrize("n", [100, 2000, 20000])
+def test_streams_of_no_whole_groups_keep_their_waves(kind_of, w, n, streaming):
+    """they never decode straight through, so that the three waves of long streams starve them"""
+    assert kind_of([(w, n)], streaming=streaming)[:2] == ("fitting", 7)
+    assert kind_of([(w, n)], long_codes=True, streaming=streaming)[1] >= 5
+    assert kind_of([(8192, n)], streaming=streaming) == ("deep", 3, 4)
