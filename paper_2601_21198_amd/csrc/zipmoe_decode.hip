@@ -907,7 +907,7 @@ int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream,
         L.first_block[k] = static_cast<uint32_t>(total);
         blocks = b > blocks ? b : blocks;
         total += b;
-        streams_of.add(L.task[k].stream_values, L.task[k].n_streams, L.task[k].last_values);
+        streams_of.add(L.task[k].stream_values, L.task[k].n_streams, L.task[k].last_values, L.task[k].e_size);
     }
     if (!blocks) return ZM_OK;
     // without the workgroup numbers the arguments are the same up to the end of the tasks
@@ -1046,7 +1046,7 @@ struct Group {
         }
         const size_t words = cap.words(), table = kLong ? 4 * long_table_words(cap.long_slots) : 0;
         Streams streams_of;
-        for (int k = 0; k < n; ++k) streams_of.add(W, t[k].n_streams, t[k].last_values);
+        for (int k = 0; k < n; ++k) streams_of.add(W, t[k].n_streams, t[k].last_values, t[k].e_size);
         auto plan = [&](uint32_t waves) {
             return Plan{dim3((t[0].n_streams + waves - 1) / waves, static_cast<uint32_t>(n)), static_cast<uint32_t>(n), 4 * waves * words + table, streams_of, stores, stream, rec};
         };
@@ -1108,7 +1108,7 @@ struct Group {
                 const Shape &s = shape[L.task[k].high >> 12 & (kMaxShapes - 1u)];
                 const uint32_t b = (s.n_streams + 1u) / 2u;
                 blocks = b > blocks ? b : blocks;
-                streams_of.add(s.stream_values, s.n_streams, s.last_values);
+                streams_of.add(s.stream_values, s.n_streams, s.last_values, static_cast<uint64_t>(L.task[k].e_units) * 256u);
             }
             const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), streams_of, stores, stream, rec});
             if (rc != ZM_OK) return rc;

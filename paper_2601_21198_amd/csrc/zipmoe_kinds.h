@@ -3,7 +3,7 @@
 //
 // A launch that finds places for all of its waves is the faster the more it has; one that does not is bound by the memory, which serves fewer
 // waves, with fewer places open at a time, faster -- if they decode straight through.  Streams that do not (shorter than a group of tiles, no
-// whole groups) wait for each tile and need the waves.  Figures are us, GPU time by graph replay, of experts of 1024 x 2048 x 3
+// whole groups, raw) wait for each tile and need the waves.  Figures are us, GPU time by graph replay, of experts of 1024 x 2048 x 3
 // with inputs and outputs that are not cached unless they say otherwise; nt: non-temporal stores, dev: device-scope stores.
 #pragma once
 #include <cstdint>
@@ -25,7 +25,7 @@ constexpr uint64_t kManyStreams = 7 * kSimds;      // that many are at work at a
 enum Stores { kOrdinary, kThrough, kStreaming };
 
 //   kShortStreams  streams shorter than a group: bound by their waves' latencies, so as many as go
-//   kFitting       of one group, short codes, in launches of up to kManyStreams; streams of no whole groups whatever their number
+//   kFitting       of one group, short codes, in launches of up to kManyStreams; streams of no whole groups and raw ones whatever their number
 //   kMany          of one group, in launches of more
 //   kDeep          of several whole groups
 enum Kind { kShortStreams, kFitting, kMany, kDeep };
@@ -34,13 +34,15 @@ enum Kind { kShortStreams, kFitting, kMany, kDeep };
 struct Streams {
     uint64_t n = 0;
     uint64_t in_groups = 0;                      // of tensors whose streams are several whole groups of tiles
-    uint64_t values = 0;
+    uint64_t values = 0, raw_values = 0;         // values, and those of tensors that are stored raw
     uint32_t longest = 0;                        // values of the longest stream
-    void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values)
+    void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values, uint64_t e_size)
     {
+        const uint64_t n_values = static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values;
         n += n_streams;
         in_groups += stream_values > kGroupValues && stream_values % kGroupValues == 0 ? n_streams : 0u;
-        values += static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values;
+        values += n_values;
+        raw_values += e_size >= n_values ? n_values : 0u;        // a coded chunk is smaller than a raw one
         longest = longest > stream_values ? longest : stream_values;
     }
     uint64_t out_bytes() const { return 2 * values; }
@@ -48,13 +50,15 @@ struct Streams {
 
 // stores: kThrough or kStreaming.
 //   no whole groups, longer than one: 6144 values, four experts nt 20.9 with three waves, 18.3 with seven, dev 23.9 / 20.2; long codes as short streams.
+//   raw: every chunk of a tensor's, eight experts nt 37.0 with three waves, 34.8 with seven, dev 40.1 / 37.2.  (Dense codes are not raw: eight experts with
+//     codes of seven bits dev 37.3 with three, 39.3 with seven.)
 inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
 {
     (void)stores;
     if (s.in_groups || s.longest > 2 * kGroupValues) return kDeep;
     if (s.longest < kGroupValues) return kShortStreams;
     if (s.longest > kGroupValues) return long_codes ? kShortStreams : kFitting;
-    return long_codes || s.n > kManyStreams ? kMany : kFitting;
+    return long_codes || (s.n > kManyStreams && 2 * s.raw_values <= s.values) ? kMany : kFitting;
 }
 
 // Waves that a SIMD holds at most (the registers would admit six to eight; the compiler is told, and reserves what keeps the others out.

@@ -15,7 +15,7 @@ int main(int argc, char **argv)
     static const char *const names[] = {"short", "fitting", "many", "deep"};
     zipmoe::Streams s;
     for (int i = 3; i + 3 < argc; i += 4)
-        s.add(std::strtoul(argv[i], nullptr, 10), std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10));
+        s.add(std::strtoul(argv[i], nullptr, 10), std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10), std::strtoull(argv[i + 3], nullptr, 10));
     const bool long_codes = argv[1][0] == '1';
     const zipmoe::Stores stores = argv[2][0] == '1' ? zipmoe::kStreaming : zipmoe::kThrough;
     const zipmoe::Kind k = zipmoe::kind_of(long_codes, s, stores);
@@ -46,3 +46,10 @@ def test_streams_of_no_whole_groups_keep_their_waves(kind_of, w, n, streaming):
     assert kind_of([(w, n)], streaming=streaming)[:2] == ("fitting", 7)
     assert kind_of([(w, n)], long_codes=True, streaming=streaming)[1] >= 5
     assert kind_of([(8192, n)], streaming=streaming) == ("deep", 3, 4)
+
+
+@pytest.mark.parametrize("streaming", [False, True])
+def test_raw_launches_keep_their_waves(kind_of, streaming):
+    assert kind_of([(4096, 12288)], streaming=streaming)[:2] == ("many", 3)
+    assert kind_of([(4096, 12288)], streaming=streaming, bits=7)[:2] == ("many", 3)       # dense codes are no raw chunks
+    assert kind_of([(4096, 12288)], streaming=streaming, bits=8)[:2] == ("fitting", 7)
