@@ -847,7 +847,7 @@ int launch_kernel(void *args, const Plan &p)
 template <bool kLong, int kWaves, Kind kKind, class Args>
 int launch_stores(void *args, const Plan &p, Stores kind)
 {
-    if constexpr (kKind == kFitting)
+    if constexpr (kKind == kFitting && !kLong)
         if (kind == kThrough && p.streams.out_bytes() > kThroughBytes && p.streams.longest == kGroupValues && p.streams.n <= kManyStreams)
             return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
     return kind == kStreaming ? launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p)
@@ -869,9 +869,7 @@ int launch_args(void *args, const Plan &p)
     if constexpr (kWaves == 2) {
         switch (kind_of(kLong, p.streams, kind)) {
         case kShortStreams: return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
-        case kFitting:
-            if constexpr (!kLong) return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
-            break;
+        case kFitting: return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
         case kMany: return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
         case kDeep: break;
         }

@@ -25,7 +25,7 @@ constexpr uint64_t kManyStreams = 7 * kSimds;      // that many are at work at a
 enum Stores { kOrdinary, kThrough, kStreaming };
 
 //   kShortStreams  streams shorter than a group: bound by their waves' latencies, so as many as go
-//   kFitting       of one group, short codes, in launches of up to kManyStreams; streams of no whole groups and raw ones whatever their number
+//   kFitting       of one group, in launches that find places for all of their waves, or nearly; streams of no whole groups and raw ones whatever their number
 //   kMany          of one group, in launches of more
 //   kDeep          of several whole groups
 enum Kind { kShortStreams, kFitting, kMany, kDeep };
@@ -49,42 +49,46 @@ struct Streams {
 };
 
 // stores: kThrough or kStreaming.
-//   no whole groups, longer than one: 6144 values, four experts nt 20.9 with three waves, 18.3 with seven, dev 23.9 / 20.2; long codes as short streams.
+//   no whole groups, longer than one: 6144 values, four experts nt 20.9 with three waves, 18.3 with seven, dev 23.9 / 20.2; long codes, 4608 values,
+//     eight experts dev 43.6 with three, 38.6 with five.
+//   kShortStreams: all of short codes.  Long codes: 2048 values, eight experts nt
+//     38.9 with eight, 36.2 with five, but two (6144 streams, which find places) 9.1 / 9.9, all cached; 1024 values, eight dev 39.3 / 41.6.
 //   raw: every chunk of a tensor's, eight experts nt 37.0 with three waves, 34.8 with seven, dev 40.1 / 37.2.  (Dense codes are not raw: eight experts with
 //     codes of seven bits dev 37.3 with three, 39.3 with seven.)
 inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
 {
-    (void)stores;
+    const bool streaming = stores == kStreaming;
     if (s.in_groups || s.longest > 2 * kGroupValues) return kDeep;
-    if (s.longest < kGroupValues) return kShortStreams;
-    if (s.longest > kGroupValues) return long_codes ? kShortStreams : kFitting;
-    return long_codes || (s.n > kManyStreams && 2 * s.raw_values <= s.values) ? kMany : kFitting;
+    if (s.longest <= 1024u || (s.longest < kGroupValues && (!long_codes || s.n <= 8 * kSimds))) return kShortStreams;
+    return s.longest == kGroupValues && s.n > (long_codes && !streaming ? 5 * kSimds : kManyStreams) && 2 * s.raw_values <= s.values ? kMany : kFitting;
 }
 
 // Waves that a SIMD holds at most (the registers would admit six to eight; the compiler is told, and reserves what keeps the others out.
 // Keeping them out by LDS instead is not as good: four experts with long codes nt 20.0 against 19.2).
 //   kShortStreams  eight experts in streams of 512 values at seven / eight waves: 31.6 / 30.3, long codes at five / eight 48.1 / 38.7
-//   kFitting       four experts (6144 streams), all cached, at three / five / seven waves: 14.9 / 14.4 / 13.5.
+//   kFitting       four experts (6144 streams), all cached, at three / five / seven waves: 14.9 / 14.4 / 13.5.  Long codes at four / five: three experts
+//                  (4608) dev, three sets cached 12.9 / 11.6, four (6144) nt 19.9 / 19.3, dev 20.0 / 20.7
 //   kMany          three; at three / four / six: one layer of 4096 x 4096 x 3 nt 29.7 / 30.2 / 30.8, two 55.4 / 56.1 / 57.1, two of
 //                  14336 x 4096 x 3 185.4 / 189.1 / 190.7, dev one of 4096 x 4096 x 3 31.1 / 31.0 / 31.5, two 57.3 / 58.2 / 59.1, 48 of 512 x 1024 x 3
-//                  44.8 / 45.1 / 45.8 (five).  Long codes, one pair ahead, eight / 16 experts at three 35.2 / 64.9, four 33.9 / 62.2, five 34.2 / 63.3
+//                  44.8 / 45.1 / 45.8 (five).  Long codes four: eight experts nt at four / five / eight 31.8 / 32.8 / 34.6, dev 34.4 / 34.6 / 35.5
 //   kDeep          three.  8192 values, four / eight / 16 experts at three 15.1 / 26.9 / 61.8, at four 16.2 / 26.9 / 62.1, uncapped 16.2 / 28.4 /
 //                  63.6; of longer ones LDS holds fewer
 constexpr int most_waves(Kind kind, bool long_codes)
 {
-    return kind == kShortStreams ? 8 : kind == kFitting ? 7 : kind == kMany ? (long_codes ? 4 : 3) : 3;
+    return kind == kShortStreams ? 8 : kind == kFitting ? (long_codes ? 5 : 7) : kind == kMany ? (long_codes ? 4 : 3) : 3;
 }
 
 // Pairs of tiles of a group whose sign-mantissa bytes a wave asks for before it decodes the first; pair i + that many is asked for when pair i is
 // done.  All up front, the thousands of waves that start together queue behind each other's late tiles; few, a wave waits for a load
 // behind its own stores.
 //   short codes    two: four experts of 2048 x 1408 x 3 nt with four / three / two ahead 18.98 / 18.91 / 18.86, 16 experts 57.9 / 56.0 / 55.6 (one 59.2).
-//   long codes     one: eight experts dev two / one 35.6 / 33.7
+//   long codes     nt four: one / four: two experts 10.8 / 10.3, eight 34.3 / 31.8, four of 2048 x 1408 x 3 25.0 / 24.4, 16 60.1 / 60.7, two of
+//                  14336 x 4096 x 3 193.7 / 198.3.  dev one: one / four: two experts 11.8 / 13.9, eight 34.4 / 35.2
 constexpr int pairs_ahead(Kind kind, bool long_codes, Stores stores)
 {
     if (kind == kShortStreams) return 2;         // never straight through
     if (kind == kDeep) return kPairs;
-    (void)stores;
+    if (stores == kStreaming) return long_codes ? kPairs : 2;
     return long_codes ? 1 : 2;
 }
 

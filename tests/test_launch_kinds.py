@@ -53,3 +53,16 @@ def test_raw_launches_keep_their_waves(kind_of, streaming):
     assert kind_of([(4096, 12288)], streaming=streaming)[:2] == ("many", 3)
     assert kind_of([(4096, 12288)], streaming=streaming, bits=7)[:2] == ("many", 3)       # dense codes are no raw chunks
     assert kind_of([(4096, 12288)], streaming=streaming, bits=8)[:2] == ("fitting", 7)
+
+
+def test_long_codes_find_places_or_are_served_straight_through(kind_of):
+    assert kind_of([(4096, 4608)], long_codes=True, streaming=True) == ("fitting", 5, 4)
+    assert kind_of([(4096, 4608)], long_codes=True) == ("fitting", 5, 1)
+    assert kind_of([(4096, 7168)], long_codes=True, streaming=True) == ("fitting", 5, 4)
+    assert kind_of([(4096, 7169)], long_codes=True, streaming=True) == ("many", 4, 4)
+    assert kind_of([(4096, 5120)], long_codes=True) == ("fitting", 5, 1)
+    assert kind_of([(4096, 5121)], long_codes=True) == ("many", 4, 1)
+    for w in (1536, 2048, 3584):
+        assert kind_of([(w, 8192)], long_codes=True) == ("short", 8, 2)
+        assert kind_of([(w, 8193)], long_codes=True)[:2] == ("fitting", 5)
+    assert kind_of([(1024, 50000)], long_codes=True) == ("short", 8, 2)
