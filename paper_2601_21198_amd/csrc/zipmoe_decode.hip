@@ -570,10 +570,10 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     bool active = true;
     const uint8_t *raw = nullptr;
     // The stream's first vectors, lane + 64 k, wait in registers until the other requests are out: 2 KiB, more than a typical
-    // stream of 4096 values, or 12, as much as one of 32768.  (What is copied in the loop below waits for every vector anew: streams
+    // stream of 4096 values, 4, or 12, as much as one of 32768.  (What is copied in the loop below waits for every vector anew: streams
     // of 32768 values, two / eight experts of 1024 x 2048 x 3, 20.7 / 45.5 us with 2 KiB, 17.8 / 37.8 with 12 and the next group of
     // tiles asked for early, of 16384 values 13.2 / 32.8 and 12.1 / 32.1.)
-    constexpr uint32_t kHeld = kKind == kDeep ? 12 : 2;
+    constexpr uint32_t kHeld = kKind == kDeep ? 12 : kKind == kMixed ? 4 : 2;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4 held[kHeld];
     uint32_t n_held = 0;
@@ -603,9 +603,10 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
     // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
     constexpr int kAhead = pairs_ahead(kKind, kLong, kStores);
-    constexpr bool kGroups = kKind == kDeep;          // there may be streams of several groups
+    constexpr bool kGroups = kKind == kDeep || kKind == kMixed;          // there may be streams of several groups
     const bool coded = mode == ZM_MODE_CODED;
     const bool straight = kKind != kShortStreams && (kGroups ? sn % kGroupValues == 0 : sn == kGroupValues) && !dense;     // whole groups of tiles, decoded without a look at their ends
+    const bool groups = kGroups && straight && (kKind == kDeep || tiles > kGroup);                     // all of them are asked for group by group
     uint2 up[kPairs], down[kPairs];
     const ByteSource sm(t.sm + v0, sn, lane), first_sm(t.sm + v0, coded && active ? sn : 0u, lane);
     auto ask = [&](int i) {        // tiles that the stream does not have read as zero and touch no memory
@@ -659,7 +660,11 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     // compiler can not count them it waits for all of them, and decoding does not start before the sign-mantissa bytes have come.
     // (One expert of 1024 x 2048 x 3, streaming stores 5.40 -> 5.18 us, eight 26.8 -> 26.55, one matrix of 256 x 512 3.92 -> 3.80.)
     ask(0);
-    if (kAhead == 2 || !straight) {
+    if (groups) {
+#pragma unroll
+        for (int i = 1; i < kPairs; ++i) ask(i);
+        stage();
+    } else if (kAhead == 2 || !straight) {
         ask(1);
         stage();
     } else {
@@ -701,7 +706,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     dec.start(first, first + bits);
     uint32_t done = 0;
     if (straight) {
-        if constexpr (kGroups) done = decode_groups(dec, tab, out, sm, tiles, up, down);
+        if (groups) done = decode_groups(dec, tab, out, sm, tiles, up, down);
         else done = decode_group<kLong, kAhead>(dec, tab, out, sm, 0u, tiles, up, down);
         if (!kLong || 2u * done >= tiles) return;
         up[0] = sm.load(done); down[0] = sm.load(tiles - 1u - done);
@@ -848,7 +853,7 @@ template <bool kLong, int kWaves, Kind kKind, class Args>
 int launch_stores(void *args, const Plan &p, Stores kind)
 {
     if constexpr (kKind == kFitting && !kLong)
-        if (kind == kThrough && p.streams.out_bytes() > kThroughBytes && p.streams.longest == kGroupValues && p.streams.n <= kManyStreams)
+        if (kind == kThrough && p.streams.out_bytes() > kThroughBytes && p.streams.one_group == p.streams.n && p.streams.n <= kManyStreams)
             return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
     return kind == kStreaming ? launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p)
                               : launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
@@ -871,6 +876,9 @@ int launch_args(void *args, const Plan &p)
         case kShortStreams: return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
         case kFitting: return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
         case kMany: return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
+        case kMixed:
+            if constexpr (!kLong) return launch_stores<kLong, kWaves, kMixed, Args>(args, p, kind);
+            break;
         case kDeep: break;
         }
     }

@@ -27,19 +27,21 @@ enum Stores { kOrdinary, kThrough, kStreaming };
 //   kShortStreams  streams shorter than a group: bound by their waves' latencies, so as many as go
 //   kFitting       of one group, in launches that find places for all of their waves, or nearly; streams of no whole groups and raw ones whatever their number
 //   kMany          of one group, in launches of more
+//   kMixed         of one group and of other lengths in one launch; long ones of no whole groups
 //   kDeep          of several whole groups
-enum Kind { kShortStreams, kFitting, kMany, kDeep };
+enum Kind { kShortStreams, kFitting, kMany, kMixed, kDeep };
 
 // What a launch decodes.
 struct Streams {
     uint64_t n = 0;
-    uint64_t in_groups = 0;                      // of tensors whose streams are several whole groups of tiles
+    uint64_t one_group = 0, in_groups = 0;       // of tensors whose streams are one whole group of tiles, and several
     uint64_t values = 0, raw_values = 0;         // values, and those of tensors that are stored raw
     uint32_t longest = 0;                        // values of the longest stream
     void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values, uint64_t e_size)
     {
         const uint64_t n_values = static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values;
         n += n_streams;
+        one_group += stream_values == kGroupValues ? n_streams : 0u;
         in_groups += stream_values > kGroupValues && stream_values % kGroupValues == 0 ? n_streams : 0u;
         values += n_values;
         raw_values += e_size >= n_values ? n_values : 0u;        // a coded chunk is smaller than a raw one
@@ -49,18 +51,27 @@ struct Streams {
 };
 
 // stores: kThrough or kStreaming.
+//   kDeep / kMixed, longer streams.  A launch of nothing but whole groups: three waves (most_waves).  With 23 tensors in streams of 4096 values, one
+//     of 8192 ran dev 35.2 with three waves and all pairs ahead, 31.8 as kMixed (nt 29.9 / 28.9); with 23 of 1024 values 53.1 / 39.2.  nt keeps kDeep
+//     from half the streams on: of eight tensors of 8192 and four of 4096, 17.4 against 19.1 (dev 21.9 / 21.5).  Whole groups need it, the
+//     others are held by LDS at four waves or less: of 10240 values 16 experts nt 70.0 as kDeep, 65.5 as kMixed, dev 73.4 / 68.7.  Long codes have
+//     no kMixed: as kDeep they are ahead there (10240 values, eight experts dev 44.6, 47.1 as kFitting).
 //   no whole groups, longer than one: 6144 values, four experts nt 20.9 with three waves, 18.3 with seven, dev 23.9 / 20.2; long codes, 4608 values,
 //     eight experts dev 43.6 with three, 38.6 with five.
 //   kShortStreams: all of short codes.  Long codes: 2048 values, eight experts nt
 //     38.9 with eight, 36.2 with five, but two (6144 streams, which find places) 9.1 / 9.9, all cached; 1024 values, eight dev 39.3 / 41.6.
+//   kMixed, streams of one group and others: 23 tensors of 4096 values and one of 1024 nt 32.4 with three waves, 32.6 with seven, 30.6 as kMixed, dev 34.6 /
+//     33.6 / 32.5.  Where the others are more it is kFitting: one of 4096 and 23 of 1024 nt 33.5 as kMixed, 31.8 as kFitting, dev 36.1 / 33.6.
 //   raw: every chunk of a tensor's, eight experts nt 37.0 with three waves, 34.8 with seven, dev 40.1 / 37.2.  (Dense codes are not raw: eight experts with
 //     codes of seven bits dev 37.3 with three, 39.3 with seven.)
 inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
 {
     const bool streaming = stores == kStreaming;
-    if (s.in_groups || s.longest > 2 * kGroupValues) return kDeep;
+    if (s.in_groups || s.longest > 2 * kGroupValues)
+        return long_codes || s.in_groups == s.n || (streaming && 2 * s.in_groups >= s.n) ? kDeep : kMixed;
     if (s.longest <= 1024u || (s.longest < kGroupValues && (!long_codes || s.n <= 8 * kSimds))) return kShortStreams;
-    return s.longest == kGroupValues && s.n > (long_codes && !streaming ? 5 * kSimds : kManyStreams) && 2 * s.raw_values <= s.values ? kMany : kFitting;
+    if (s.one_group < s.n) return !long_codes && 2 * s.one_group >= s.n ? kMixed : kFitting;
+    return s.n > (long_codes && !streaming ? 5 * kSimds : kManyStreams) && 2 * s.raw_values <= s.values ? kMany : kFitting;
 }
 
 // Waves that a SIMD holds at most (the registers would admit six to eight; the compiler is told, and reserves what keeps the others out.
@@ -71,24 +82,26 @@ inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
 //   kMany          three; at three / four / six: one layer of 4096 x 4096 x 3 nt 29.7 / 30.2 / 30.8, two 55.4 / 56.1 / 57.1, two of
 //                  14336 x 4096 x 3 185.4 / 189.1 / 190.7, dev one of 4096 x 4096 x 3 31.1 / 31.0 / 31.5, two 57.3 / 58.2 / 59.1, 48 of 512 x 1024 x 3
 //                  44.8 / 45.1 / 45.8 (five).  Long codes four: eight experts nt at four / five / eight 31.8 / 32.8 / 34.6, dev 34.4 / 34.6 / 35.5
+//   kMixed         six, of what LDS admits: 11 tensors of 4096 values and one of 1024 dev 18.9 at four, 18.6 at six, one of 8192 and 11 of 1024 23.1 / 21.3
 //   kDeep          three.  8192 values, four / eight / 16 experts at three 15.1 / 26.9 / 61.8, at four 16.2 / 26.9 / 62.1, uncapped 16.2 / 28.4 /
 //                  63.6; of longer ones LDS holds fewer
 constexpr int most_waves(Kind kind, bool long_codes)
 {
-    return kind == kShortStreams ? 8 : kind == kFitting ? (long_codes ? 5 : 7) : kind == kMany ? (long_codes ? 4 : 3) : 3;
+    return kind == kShortStreams ? 8 : kind == kFitting ? (long_codes ? 5 : 7) : kind == kMany ? (long_codes ? 4 : 3) : kind == kMixed ? 6 : 3;
 }
 
 // Pairs of tiles of a group whose sign-mantissa bytes a wave asks for before it decodes the first; pair i + that many is asked for when pair i is
 // done.  All up front, the thousands of waves that start together queue behind each other's late tiles; few, a wave waits for a load
 // behind its own stores.
 //   short codes    two: four experts of 2048 x 1408 x 3 nt with four / three / two ahead 18.98 / 18.91 / 18.86, 16 experts 57.9 / 56.0 / 55.6 (one 59.2).
+//                  kMixed nt four: 23 tensors of 4096 values and one of 1024 two / four 32.2 / 30.6
 //   long codes     nt four: one / four: two experts 10.8 / 10.3, eight 34.3 / 31.8, four of 2048 x 1408 x 3 25.0 / 24.4, 16 60.1 / 60.7, two of
 //                  14336 x 4096 x 3 193.7 / 198.3.  dev one: one / four: two experts 11.8 / 13.9, eight 34.4 / 35.2
 constexpr int pairs_ahead(Kind kind, bool long_codes, Stores stores)
 {
     if (kind == kShortStreams) return 2;         // never straight through
     if (kind == kDeep) return kPairs;
-    if (stores == kStreaming) return long_codes ? kPairs : 2;
+    if (stores == kStreaming) return long_codes || kind == kMixed ? kPairs : 2;
     return long_codes ? 1 : 2;
 }
 

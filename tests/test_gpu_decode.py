@@ -721,3 +721,22 @@ def test_streams_of_no_whole_groups(W, max_len):
             assert np.array_equal(g, w) and np.array_equal(g, zo.decode(b))
         for i in range(3):
             assert np.array_equal(gpu_decode_tensors(blobs[i: i + 1], stores=stores)[0], tensors[i])
+
+
+@pytest.mark.parametrize("streams", [[8192, 4096, 4096, 4096], [8192, 8192, 8192, 4096], [8192, 1024, 1024, 512], [16384, 4096, 1024, 4096],
+                                     [4096, 4096, 4096, 1024], [4096, 1024, 512, 1024], [6144, 4096, 4096, 12288], [10240, 4096, 8192, 10240]])
+@pytest.mark.parametrize("count", [5, 12, 60])
+@pytest.mark.parametrize("max_len", [8, 12])
+def test_launches_of_several_stream_lengths(streams, count, max_len):
+    """one launch decodes streams of one group of tiles, of several, of none, of each length in the majority: up to six tensors, more, and many that
+    share a launch; every fourth one is cut off inside a tile"""
+    n = (1 << 16) + 12288
+    tensors, blobs = [], []
+    for i in range(count):
+        kind = "gauss" if max_len == 8 else ("wide", "gauss")[i % 2]
+        tensors.append(synth.special_tensor(kind, n - 5 * (i % 4 == 3 and count < 60), seed=i % 5))
+        blobs.append(zm.compress(tensors[-1], 2 * streams[i % 4], streams[i % 4], max_len)[0])
+    for stores in (zm.STORES_CACHED, zm.STORES_STREAMING):
+        for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
+            assert np.array_equal(g, w)
+    assert np.array_equal(gpu_decode_tensors(blobs[:1], stores=zm.STORES_CACHED)[0], zo.decode(blobs[0]))

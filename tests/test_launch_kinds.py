@@ -12,7 +12,7 @@ PROGRAM = r"""
 // long_codes streaming {stream_values n_streams last_values e_size}...
 int main(int argc, char **argv)
 {
-    static const char *const names[] = {"short", "fitting", "many", "deep"};
+    static const char *const names[] = {"short", "fitting", "many", "mixed", "deep"};
     zipmoe::Streams s;
     for (int i = 3; i + 3 < argc; i += 4)
         s.add(std::strtoul(argv[i], nullptr, 10), std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10), std::strtoull(argv[i + 3], nullptr, 10));
@@ -66,3 +66,21 @@ def test_long_codes_find_places_or_are_served_straight_through(kind_of):
         assert kind_of([(w, 8192)], long_codes=True) == ("short", 8, 2)
         assert kind_of([(w, 8193)], long_codes=True)[:2] == ("fitting", 5)
     assert kind_of([(1024, 50000)], long_codes=True) == ("short", 8, 2)
+
+
+@pytest.mark.parametrize("streaming", [False, True])
+def test_launches_of_several_stream_lengths(kind_of, streaming):
+    # whole groups of one and of several
+    assert kind_of([(8192, 256)] + [(4096, 512)] * 23, streaming=streaming) == ("mixed", 6, 4 if streaming else 2)
+    assert kind_of([(8192, 256)] + [(1024, 2048)] * 23, streaming=streaming)[0] == "mixed"
+    assert kind_of([(8192, 256)] * 8 + [(4096, 512)] * 4, streaming=streaming)[0] == ("deep" if streaming else "mixed")
+    assert kind_of([(8192, 256)] * 7 + [(4096, 512)] * 4, streaming=streaming)[0] == "mixed"
+    assert kind_of([(8192, 256), (16384, 128)], streaming=streaming)[0] == "deep"
+    # one group and shorter ones: the more frequent decide
+    assert kind_of([(4096, 512)] * 23 + [(1024, 2048)], streaming=streaming)[0] == "mixed"
+    assert kind_of([(4096, 512)] + [(1024, 2048)] * 23, streaming=streaming)[:2] == ("fitting", 7)
+    assert kind_of([(6144, 342)] * 8 + [(4096, 512)] * 5, streaming=streaming)[0] == "fitting"
+    assert kind_of([(10240, 20000)], streaming=streaming)[0] == "mixed"
+    # long codes have no kind of their own for these
+    assert kind_of([(8192, 256)] + [(4096, 512)] * 23, long_codes=True, streaming=streaming)[0] == "deep"
+    assert kind_of([(4096, 512)] * 23 + [(1024, 2048)], long_codes=True, streaming=streaming)[0] == "fitting"
