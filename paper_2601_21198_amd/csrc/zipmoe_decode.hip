@@ -855,8 +855,9 @@ int launch_stores(void *args, const Plan &p, Stores kind)
     if constexpr (kKind == kFitting && !kLong)
         if (kind == kThrough && p.streams.out_bytes() > kThroughBytes && p.streams.one_group == p.streams.n && p.streams.n <= kManyStreams)
             return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
-    return kind == kStreaming ? launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p)
-                              : launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
+    if constexpr (kKind != kSparse)
+        if (kind == kStreaming) return launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p);
+    return launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
 }
 
 template <bool kLong, int kWaves, class Args>
@@ -874,6 +875,7 @@ int launch_args(void *args, const Plan &p)
     if constexpr (kWaves == 2) {
         switch (kind_of(kLong, p.streams, kind)) {
         case kShortStreams: return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
+        case kSparse: return launch_stores<kLong, kWaves, kSparse, Args>(args, p, kind);
         case kFitting: return launch_stores<kLong, kWaves, kFitting, Args>(args, p, kind);
         case kMany: return launch_stores<kLong, kWaves, kMany, Args>(args, p, kind);
         case kMixed:

@@ -25,11 +25,12 @@ constexpr uint64_t kManyStreams = 7 * kSimds;      // that many are at work at a
 enum Stores { kOrdinary, kThrough, kStreaming };
 
 //   kShortStreams  streams shorter than a group: bound by their waves' latencies, so as many as go
+//   kSparse        of one group, so few that a wave has its SIMD (nearly) to itself, dev
 //   kFitting       of one group, in launches that find places for all of their waves, or nearly; streams of no whole groups and raw ones whatever their number
 //   kMany          of one group, in launches of more
 //   kMixed         of one group and of other lengths in one launch; long ones of no whole groups
 //   kDeep          of several whole groups
-enum Kind { kShortStreams, kFitting, kMany, kMixed, kDeep };
+enum Kind { kShortStreams, kSparse, kFitting, kMany, kMixed, kDeep };
 
 // What a launch decodes.
 struct Streams {
@@ -62,6 +63,7 @@ struct Streams {
 //     38.9 with eight, 36.2 with five, but two (6144 streams, which find places) 9.1 / 9.9, all cached; 1024 values, eight dev 39.3 / 41.6.
 //   kMixed, streams of one group and others: 23 tensors of 4096 values and one of 1024 nt 32.4 with three waves, 32.6 with seven, 30.6 as kMixed, dev 34.6 /
 //     33.6 / 32.5.  Where the others are more it is kFitting: one of 4096 and 23 of 1024 nt 33.5 as kMixed, 31.8 as kFitting, dev 36.1 / 33.6.
+//   kSparse: see pairs_ahead.
 //   raw: every chunk of a tensor's, eight experts nt 37.0 with three waves, 34.8 with seven, dev 40.1 / 37.2.  (Dense codes are not raw: eight experts with
 //     codes of seven bits dev 37.3 with three, 39.3 with seven.)
 inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
@@ -71,6 +73,7 @@ inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
         return long_codes || s.in_groups == s.n || (streaming && 2 * s.in_groups >= s.n) ? kDeep : kMixed;
     if (s.longest <= 1024u || (s.longest < kGroupValues && (!long_codes || s.n <= 8 * kSimds))) return kShortStreams;
     if (s.one_group < s.n) return !long_codes && 2 * s.one_group >= s.n ? kMixed : kFitting;
+    if (!streaming && s.n <= (long_codes ? kSimds : 3 * kSimds)) return kSparse;
     return s.n > (long_codes && !streaming ? 5 * kSimds : kManyStreams) && 2 * s.raw_values <= s.values ? kMany : kFitting;
 }
 
@@ -87,22 +90,24 @@ inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
 //                  63.6; of longer ones LDS holds fewer
 constexpr int most_waves(Kind kind, bool long_codes)
 {
-    return kind == kShortStreams ? 8 : kind == kFitting ? (long_codes ? 5 : 7) : kind == kMany ? (long_codes ? 4 : 3) : kind == kMixed ? 6 : 3;
+    return kind == kShortStreams ? 8 : kind == kSparse || kind == kFitting ? (long_codes ? 5 : 7) : kind == kMany ? (long_codes ? 4 : 3) : kind == kMixed ? 6 : 3;
 }
 
 // Pairs of tiles of a group whose sign-mantissa bytes a wave asks for before it decodes the first; pair i + that many is asked for when pair i is
 // done.  All up front, the thousands of waves that start together queue behind each other's late tiles; few, a wave waits for a load
 // behind its own stores.
 //   short codes    two: four experts of 2048 x 1408 x 3 nt with four / three / two ahead 18.98 / 18.91 / 18.86, 16 experts 57.9 / 56.0 / 55.6 (one 59.2).
-//                  kMixed nt four: 23 tensors of 4096 values and one of 1024 two / four 32.2 / 30.6
+//                  kFitting dev one: two experts of 2048 x 1408 x 3 (4224 streams), three sets cached, two / one 11.1 / 10.2, three 11.2 / 10.9; up to
+//                  three waves per SIMD two: one expert 7.0 / 7.7.  kMixed nt four: 23 tensors of 4096 values and one of 1024 two / four 32.2 / 30.6
 //   long codes     nt four: one / four: two experts 10.8 / 10.3, eight 34.3 / 31.8, four of 2048 x 1408 x 3 25.0 / 24.4, 16 60.1 / 60.7, two of
-//                  14336 x 4096 x 3 193.7 / 198.3.  dev one: one / four: two experts 11.8 / 13.9, eight 34.4 / 35.2
+//                  14336 x 4096 x 3 193.7 / 198.3.  dev one: one / four: two experts 11.8 / 13.9, eight 34.4 / 35.2; up to one wave per SIMD four: 12
+//                  tensors of 300001 values (888 streams) 7.7 / 6.8, one expert (1536) 8.8 / 9.0
 constexpr int pairs_ahead(Kind kind, bool long_codes, Stores stores)
 {
     if (kind == kShortStreams) return 2;         // never straight through
     if (kind == kDeep) return kPairs;
     if (stores == kStreaming) return long_codes || kind == kMixed ? kPairs : 2;
-    return long_codes ? 1 : 2;
+    return kind == kSparse ? (long_codes ? kPairs : 2) : long_codes || kind == kFitting ? 1 : 2;
 }
 
 }  // namespace zipmoe

@@ -740,3 +740,16 @@ def test_launches_of_several_stream_lengths(streams, count, max_len):
         for w, b, g in zip(tensors, blobs, gpu_decode_tensors(blobs, stores=stores)):
             assert np.array_equal(g, w)
     assert np.array_equal(gpu_decode_tensors(blobs[:1], stores=zm.STORES_CACHED)[0], zo.decode(blobs[0]))
+
+
+@pytest.mark.parametrize("streams,count", [(3072, 1), (3073, 1), (512, 6), (513, 6), (256, 12), (257, 12), (64, 48), (65, 48), (1024, 1), (1025, 1), (128, 8), (129, 8)])
+@pytest.mark.parametrize("max_len", [8, 12])
+def test_launches_around_the_lines_of_few_streams(streams, count, max_len):
+    """with stores that leave their lines cached, as many streams as ask for their bytes early and one more"""
+    n = streams * 4096 - 5
+    w = synth.special_tensor("gauss" if max_len == 8 else "wide", n + 64, seed=streams)
+    tensors = [[w[k % 8: k % 8 + n]] for k in range(count)]
+    flat, _, got, shapes = layer_calls(tensors, 16384, 4096, max_len, zm.STORES_CACHED)
+    assert len(shapes) == 1
+    for a, g in zip(flat, got):
+        assert np.array_equal(g, a)

@@ -12,7 +12,7 @@ PROGRAM = r"""
 // long_codes streaming {stream_values n_streams last_values e_size}...
 int main(int argc, char **argv)
 {
-    static const char *const names[] = {"short", "fitting", "many", "mixed", "deep"};
+    static const char *const names[] = {"short", "sparse", "fitting", "many", "mixed", "deep"};
     zipmoe::Streams s;
     for (int i = 3; i + 3 < argc; i += 4)
         s.add(std::strtoul(argv[i], nullptr, 10), std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10), std::strtoull(argv[i + 3], nullptr, 10));
@@ -84,3 +84,12 @@ def test_launches_of_several_stream_lengths(kind_of, streaming):
     # long codes have no kind of their own for these
     assert kind_of([(8192, 256)] + [(4096, 512)] * 23, long_codes=True, streaming=streaming)[0] == "deep"
     assert kind_of([(4096, 512)] * 23 + [(1024, 2048)], long_codes=True, streaming=streaming)[0] == "fitting"
+
+
+def test_few_streams_ask_early_more_ask_late(kind_of):
+    assert kind_of([(4096, 1024)] * 3) == ("sparse", 7, 2)
+    assert kind_of([(4096, 3073)]) == ("fitting", 7, 1)
+    assert kind_of([(4096, 3072)], streaming=True) == ("fitting", 7, 2) == kind_of([(4096, 3073)], streaming=True)
+    assert kind_of([(4096, 1024)], long_codes=True) == ("sparse", 5, 4)
+    assert kind_of([(4096, 1025)], long_codes=True) == ("fitting", 5, 1)
+    assert kind_of([(4096, 7169)]) == ("many", 3, 2)
