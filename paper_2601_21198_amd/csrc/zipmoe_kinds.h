@@ -59,7 +59,7 @@ struct Streams {
 //     no kMixed: as kDeep they are ahead there (10240 values, eight experts dev 44.6, 47.1 as kFitting).
 //   no whole groups, longer than one: 6144 values, four experts nt 20.9 with three waves, 18.3 with seven, dev 23.9 / 20.2; long codes, 4608 values,
 //     eight experts dev 43.6 with three, 38.6 with five.
-//   kShortStreams: all of short codes.  Long codes: 2048 values, eight experts nt
+//   kShortStreams: 3072 values, eight experts nt 33.8 with eight waves, 33.2 with seven.  Long codes: 2048 values, eight experts nt
 //     38.9 with eight, 36.2 with five, but two (6144 streams, which find places) 9.1 / 9.9, all cached; 1024 values, eight dev 39.3 / 41.6.
 //   kMixed, streams of one group and others: 23 tensors of 4096 values and one of 1024 nt 32.4 with three waves, 32.6 with seven, 30.6 as kMixed, dev 34.6 /
 //     33.6 / 32.5.  Where the others are more it is kFitting: one of 4096 and 23 of 1024 nt 33.5 as kMixed, 31.8 as kFitting, dev 36.1 / 33.6.
@@ -71,7 +71,7 @@ inline Kind kind_of(bool long_codes, const Streams &s, Stores stores)
     const bool streaming = stores == kStreaming;
     if (s.in_groups || s.longest > 2 * kGroupValues)
         return long_codes || s.in_groups == s.n || (streaming && 2 * s.in_groups >= s.n) ? kDeep : kMixed;
-    if (s.longest <= 1024u || (s.longest < kGroupValues && (!long_codes || s.n <= 8 * kSimds))) return kShortStreams;
+    if (s.longest <= 1024u || (s.longest < kGroupValues && (long_codes ? s.n <= 8 * kSimds : s.longest <= 2048u))) return kShortStreams;
     if (s.one_group < s.n) return !long_codes && 2 * s.one_group >= s.n ? kMixed : kFitting;
     if (!streaming && s.n <= (long_codes ? kSimds : 3 * kSimds)) return kSparse;
     return s.n > (long_codes && !streaming ? 5 * kSimds : kManyStreams) && 2 * s.raw_values <= s.values ? kMany : kFitting;

@@ -93,3 +93,10 @@ def test_few_streams_ask_early_more_ask_late(kind_of):
     assert kind_of([(4096, 1024)], long_codes=True) == ("sparse", 5, 4)
     assert kind_of([(4096, 1025)], long_codes=True) == ("fitting", 5, 1)
     assert kind_of([(4096, 7169)]) == ("many", 3, 2)
+
+
+@pytest.mark.parametrize("streaming", [False, True])
+def test_nearly_whole_groups_run_seven_waves(kind_of, streaming):
+    assert kind_of([(2048, 30000)], streaming=streaming) == ("short", 8, 2)
+    for w in (2560, 3584):
+        assert kind_of([(w, 20000)], streaming=streaming)[:2] == ("fitting", 7)
