@@ -1296,15 +1296,22 @@ extern "C" int zm_recover(const void *exponents, const void *sign_mantissa, size
     if (!exponents || !sign_mantissa || !out_bf16) return ZM_E_ARG;
     if ((reinterpret_cast<uintptr_t>(exponents) & 7) || (reinterpret_cast<uintptr_t>(sign_mantissa) & 7) ||
         (reinterpret_cast<uintptr_t>(out_bf16) & 15)) return ZM_E_ARG;
-    constexpr uint64_t kSmallTensor = 4ull << 20;
+    constexpr uint64_t kSmallTensor = 5ull << 20;
     constexpr int kRecoverTiles = 4;
     const uint8_t *e = static_cast<const uint8_t *>(exponents), *sm = static_cast<const uint8_t *>(sign_mantissa);
     uint16_t *out = static_cast<uint16_t *>(out_bf16);
     uint64_t n = n_values;
     // A launch that moves more than half of the last-level cache (four bytes per value) writes with non-temporal
     // stores: measured on 58.7 M-value tensors 40.5 against 42.0 us with one tile per wave.  Smaller ones write with device-scope
-    // stores, us against ordinary ones with one tile, three sets in turn / not cached: 25 M values 20.3 / 20.9 against
-    // 21.3 / 21.9, 6.3 M 5.0 / 6.85 against 5.65 / 7.2, 4.2 M 2.6 / 5.1 against 3.3 / 4.9, 1 M 1.66 / 2.13 against 1.90 / 2.23.
+    // stores.  us, ordinary / device-scope (one tile):
+    //   values                                                    1.0 M        1.6 M        2.1 M        2.9 M        4.2 M        5.0 M
+    //   exponents just copied from the host, nothing else cached   3.63 / 3.58  4.01 / 3.91  4.48 / 4.16  4.93 / 4.63  5.80 / 5.57  7.08 / 6.69
+    //   values                                                    1.0 M        1.6 M        2.4 M        3.0 M        4.2 M        4.6 M
+    //   three sets in turn                                         2.04 / 1.96  2.18 / 2.19  2.47 / 2.31  2.79 / 2.51  3.36 / 2.76  4.26 / 3.22
+    //   nothing cached, graph replay                               2.47 / 2.59  3.21 / 3.45  3.84 / 3.95  4.26 / 4.42  4.86 / 4.98  5.84 / 5.94
+    // The first row, taken from the profiler's trace, is what recovery is for: exponent bytes that the host has decompressed arrive by a copy, which
+    // leaves them in the last-level cache.  The last is the one in which ordinary stores are ahead.  One tile against four: 4.6 M three sets
+    // 3.22 / 3.22, one set 2.86 / 3.15, not cached 5.94 / 6.09, 5.2 M 3.15 / 3.28 (one set), 6.40 / 6.35; 6.0 M three sets 4.43 / 4.20.
     const bool streaming = 4 * n > kLastLevelCacheBytes / 2, small = n <= kSmallTensor;
     const uint64_t per_block = small ? 4 * kTile : streaming ? kRecoverTiles * kTile : 4 * kRecoverTiles * kTile;
     const uint64_t blocks = (n + per_block - 1) / per_block;
