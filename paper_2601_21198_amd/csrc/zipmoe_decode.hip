@@ -1116,18 +1116,27 @@ struct Group {
         PackedLaunch L;
         L.stream_cap_words = static_cast<uint32_t>(cap);
         L.long_slots = cap_of_all.long_slots;
-        for (uint32_t k = 0; k < n_shapes; ++k) L.shape[k] = shape[k];
+        uint64_t n_values[kMaxShapes];
+        for (uint32_t k = 0; k < n_shapes; ++k) {
+            L.shape[k] = shape[k];
+            n_values[k] = Streams::values_of(shape[k].stream_values, shape[k].n_streams, shape[k].last_values);
+        }
         const int launches = launches_of(kMaxPacked), each = (n + launches - 1) / launches;
         for (int at = 0; at < n; at += static_cast<int>(L.n_tasks)) {
             L.n_tasks = static_cast<uint32_t>(n - at < each ? n - at : each);
-            uint32_t blocks = 0;
-            Streams streams_of;
+            uint32_t blocks = 0, count[kMaxShapes] = {}, raw[kMaxShapes] = {};
             for (uint32_t k = 0; k < L.n_tasks; ++k) {
                 L.task[k] = packed[at + static_cast<int>(k)];
-                const Shape &s = shape[L.task[k].high >> 12 & (kMaxShapes - 1u)];
-                const uint32_t b = (s.n_streams + 1u) / 2u;
+                const uint32_t of = L.task[k].high >> 12 & (kMaxShapes - 1u);
+                ++count[of];
+                raw[of] += Streams::is_raw(static_cast<uint64_t>(L.task[k].e_units) * 256u, n_values[of]);
+            }
+            Streams streams_of;
+            for (uint32_t k = 0; k < n_shapes; ++k) {
+                if (!count[k]) continue;
+                const uint32_t b = (shape[k].n_streams + 1u) / 2u;
                 blocks = b > blocks ? b : blocks;
-                streams_of.add(s.stream_values, s.n_streams, s.last_values, static_cast<uint64_t>(L.task[k].e_units) * 256u);
+                streams_of.add(shape[k].stream_values, shape[k].n_streams, n_values[k], count[k], raw[k]);
             }
             const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), streams_of, stores, stream, rec});
             if (rc != ZM_OK) return rc;
@@ -1165,9 +1174,10 @@ int make_task(const zm_tensor_parts &pt, const zm_tensor_info &ti, void *out, Ta
     t.streams_per_chunk = ti.chunk_values / ti.stream_values;
     t.n_streams = static_cast<uint32_t>(n_streams);
     t.last_values = static_cast<uint32_t>(ti.n_values - (n_streams - 1) * ti.stream_values);
-    uint32_t shift = 0;
-    while (1ull << shift < t.streams_per_chunk) ++shift;
-    t.per_chunk = static_cast<uint32_t>(((1ull << (31 + shift)) + t.streams_per_chunk - 1) / t.streams_per_chunk);
+    // a power of two, the usual case, takes no division: this runs twice per tensor of a call
+    const uint32_t shift = t.streams_per_chunk > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(t.streams_per_chunk - 1)) : 0u;
+    t.per_chunk = t.streams_per_chunk == 1u << shift ? 1u << 31
+                                                     : static_cast<uint32_t>(((1ull << (31 + shift)) + t.streams_per_chunk - 1) / t.streams_per_chunk);
     t.code = ti.max_len | shift << 4 | ti.lane_quantum << 9;
     return ZM_OK;
 }

@@ -38,16 +38,27 @@ struct Streams {
     uint64_t one_group = 0, in_groups = 0;       // of tensors whose streams are one whole group of tiles, and several
     uint64_t values = 0, raw_values = 0;         // values, and those of tensors that are stored raw
     uint32_t longest = 0;                        // values of the longest stream
-    void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values, uint64_t e_size)
+    // tensors cut alike, `raw` of them stored raw
+    void add(uint32_t stream_values, uint32_t n_streams, uint64_t n_values, uint32_t tensors, uint32_t raw)
     {
-        const uint64_t n_values = static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values;
-        n += n_streams;
-        one_group += stream_values == kGroupValues ? n_streams : 0u;
-        in_groups += stream_values > kGroupValues && stream_values % kGroupValues == 0 ? n_streams : 0u;
-        values += n_values;
-        raw_values += e_size >= n_values ? n_values : 0u;        // a coded chunk is smaller than a raw one
+        const uint64_t streams = static_cast<uint64_t>(tensors) * n_streams;
+        n += streams;
+        one_group += stream_values == kGroupValues ? streams : 0u;
+        in_groups += stream_values > kGroupValues && stream_values % kGroupValues == 0 ? streams : 0u;
+        values += tensors * n_values;
+        raw_values += raw * n_values;
         longest = longest > stream_values ? longest : stream_values;
     }
+    void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values, uint64_t e_size)
+    {
+        const uint64_t n_values = values_of(stream_values, n_streams, last_values);
+        add(stream_values, n_streams, n_values, 1u, is_raw(e_size, n_values));
+    }
+    static constexpr uint64_t values_of(uint32_t stream_values, uint32_t n_streams, uint32_t last_values)
+    {
+        return static_cast<uint64_t>(n_streams - 1u) * stream_values + last_values;
+    }
+    static constexpr bool is_raw(uint64_t e_size, uint64_t n_values) { return e_size >= n_values; }        // a coded chunk is smaller than a raw one
     uint64_t out_bytes() const { return 2 * values; }
 };
 
