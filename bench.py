@@ -26,24 +26,44 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBPS = 8000.0        # MI355X published peak HBM3E bandwidth
 
 # HBM bytes per launch of the decode kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by a plain
-# copy of known size; the summaries are under profiles/).  Valid only for the kernel source they were taken
-# with: the entry is reported only while the source's hash still matches, else "traffic" is null.
+# copy of known size; the summaries are under profiles/).  Valid only for the kernel sources they were taken
+# with, and for streams of 4096 values, codes of up to 8 bits and streaming stores: else "traffic" is null.
+KERNEL_SOURCES = ("zipmoe_decode.hip", "zipmoe_kinds.h", "zipmoe_extent.h")
 MEASURED_TRAFFIC = {
     "kernel_sha256_16": "2fe9e91f255c58f6",
     "bytes_per_launch": {"cfg5": 117.15e6, "cfg3": 170.4e6, "cfg4": 1195.72e6, "split-cfg4": 234.93e6},
 }
 
 
-def measured_traffic(workload: str):
+def kernel_sha256_16() -> str:
     import hashlib
-    src = os.path.join(ROOT, "paper_2601_21198_amd", "csrc", "zipmoe_decode.hip")
-    try:
-        digest = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    except OSError:
-        return None
-    if digest != MEASURED_TRAFFIC["kernel_sha256_16"]:
+    digest = hashlib.sha256()
+    for name in KERNEL_SOURCES:
+        digest.update(open(os.path.join(ROOT, "paper_2601_21198_amd", "csrc", name), "rb").read())
+    return digest.hexdigest()[:16]
+
+
+def measured_traffic(workload: str, stream_values: int = 4096, max_len: int = 8):
+    if (stream_values, max_len) != (4096, 8) or kernel_sha256_16() != MEASURED_TRAFFIC["kernel_sha256_16"]:
         return None
     return MEASURED_TRAFFIC["bytes_per_launch"].get(workload)
+
+
+def kernel_names(infos, shapes):
+    """The kernels that one call of these tensors launches with streaming stores: what zm_decode_launch_shapes tells, the kind of arguments (up to six
+    tensors cut alike have their own) and, for streams of 4096 values, the kind that their number decides."""
+    names = []
+    for sh in shapes:
+        long_codes = sh.round_symbols == 2
+        group = [i for i in infos if (i.max_len > 8) == long_codes]
+        cut = {(i.n_values, i.chunk_values, i.stream_values, i.max_len, i.sm_offset, i.e_offset) for i in group}
+        few = len(group) <= 6 and len(cut) == 1
+        kind = ""
+        if len(shapes) == 1 and all(i.stream_values == 4096 for i in group):
+            kind = ", kMany" if sum(-(-int(i.n_values) // 4096) for i in group) > 7168 else ", kFitting"
+        names.append("zm_decode_%skernel<%s, %d, %s%s>" % ("few_" if few else "", "true" if long_codes else "false", sh.waves_per_workgroup,
+                                                           "kStreaming" if sh.streaming_stores else "kThrough", kind))
+    return names
 
 
 def log(msg: str) -> None:
@@ -174,7 +194,7 @@ def bench_split(args, wl, workers: int, steps: int, warmup: int) -> int:
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": measured_traffic("split-" + args.workload),
                      # the library stores non-temporally when a launch moves more than 128 MiB (4 bytes per value)
                      "kernel": "zm_recover_kernel<%s>" % ("kStreaming, 4, 1" if 4 * max(h[2] for h in dev) > (128 << 20) else
-                                                           "kThrough, 4, 4" if max(h[2] for h in dev) > (4 << 20) else "kThrough, 1, 4"),
+                                                           "kThrough, 4, 4" if max(h[2] for h in dev) > (5 << 20) else "kThrough, 1, 4"),
                      "us_per_launch": round(kernel_s * 1e6, 2), "algorithmic_bytes_per_launch": alg},
         "host_decode": {"value": round(2.0 * n_total / host_dt / 1e9, 3), "unit": "GB/s of bf16", "threads": workers,
                         "note": "zm_decode_exponents_host over the same tensors, one after the other"},
@@ -505,10 +525,6 @@ def main() -> int:
     t_per = layers[0].tensors_per_expert
     sel = [layers[0].infos[int(e) * t_per + m] for e in routes[0][0] for m in range(t_per)]
     shapes = zm.decode_launch_shapes(sel, zm.STORES_STREAMING)
-    kernel_names = ["zm_decode_kernel<%s,%d,%s>" % ("true" if sh.round_symbols == 2 else "false", sh.waves_per_workgroup,
-                                                     "kStreaming" if sh.streaming_stores else "kThrough or kOrdinary")
-                    for sh in shapes]
-
     result = {
         "metric": "decompressed bf16 GB/s per GPU; % of HBM roofline (bytes read+written)",
         "value": round(value, 2),
@@ -542,8 +558,8 @@ def main() -> int:
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBPS, 4),
-            "traffic": measured_traffic(args.workload),
-            "kernel": ", ".join(kernel_names),
+            "traffic": measured_traffic(args.workload, args.stream_values, args.max_len),
+            "kernel": ", ".join(kernel_names(sel, shapes)),
             "us_per_launch": round(kernel_s * 1e6, 2),
             "us_per_launch_is": "HIP-event time of the timed region / launches (launch gaps included)",
             "algorithmic_bytes_per_launch": alg_bytes / launches,
