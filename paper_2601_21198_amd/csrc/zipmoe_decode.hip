@@ -14,10 +14,10 @@
 //           both contiguous across the wave (512 B and 1 KiB per instruction)
 //
 // Per wave
-//   1. one read of the chunk's table entry locates the stream; its bytes (64 lane-length bytes, then the 64
-//      lane bitstreams back to back) are requested with 128-bit loads (a4) -- first, because decoding can not
-//      start without them -- and go to LDS;
-//   2. the sign-mantissa bytes of the stream's first tiles are requested, the others as tiles are finished;
+//   1. one read of the chunk's table entry locates the stream, and the decode table is requested meanwhile; the stream's bytes (64
+//      lane-length bytes, then the 64 lane bitstreams back to back) are requested with 128-bit loads (a4), because
+//      decoding can not start without them, and go to LDS;
+//   2. the sign-mantissa bytes of the stream's first tiles are requested behind them, the others as tiles are finished;
 //   3. the decode table goes to LDS (a3) as 16-bit entries, code length in the low byte and symbol in the high byte:
 //      256 entries for codes of at most eight bits; longer codes take 16 more for each beginning that they share;
 //   4. a wavefront prefix sum over the 64 lane-length bytes gives every lane the first and the last bit of
@@ -226,9 +226,9 @@ struct Sink {
         __builtin_amdgcn_raw_buffer_store_b128((u32x4){w.x, w.y, w.z, w.w}, words, static_cast<int>(lane_offset + tile * (2u * kTile)), 0, kFlags);
     }
 
-    // for a lane that owns `left` < 8 values of the tile: one word at a time, and those past the end of the
+    // for a lane that owns fewer than eight values of the tile: one word at a time, and those past the end of the
     // stream are past the end of the descriptor too, which drops them
-    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w, uint32_t) const
+    __device__ __forceinline__ void store_partial(uint32_t tile, uint4 w) const
     {
         const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
@@ -412,7 +412,7 @@ __device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t t
     const int32_t left = mine - static_cast<int32_t>(tile * kTile);
     const uint4 w = recover8(e, sm);
     if (left >= 8) out.store(tile, w);
-    else if (left > 0) out.store_partial(tile, w, static_cast<uint32_t>(left));
+    else if (left > 0) out.store_partial(tile, w);
 }
 
 // Decodes a coded stream from both ends: pair p is tile p (upward chain) and tile tiles - 1 - p (downward chain), and
@@ -802,7 +802,7 @@ zm_recover_kernel(const uint8_t *__restrict__ e, const uint8_t *__restrict__ sm,
             eb[q >> 2] |= static_cast<uint32_t>(e[i]) << (8 * (q & 3));
             sb[q >> 2] |= static_cast<uint32_t>(sm[i]) << (8 * (q & 3));
         }
-        sink.store_partial(have / kTile, recover8(make_uint2(eb[0], eb[1]), make_uint2(sb[0], sb[1])), left);
+        sink.store_partial(have / kTile, recover8(make_uint2(eb[0], eb[1]), make_uint2(sb[0], sb[1])));
     }
 #pragma unroll
     for (int k = 0; k < kTiles; ++k)

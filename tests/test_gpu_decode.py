@@ -475,7 +475,7 @@ def test_raw_and_long_streams_in_groups_of_tiles(n, W):
 @pytest.mark.parametrize("layouts,stores,max_len,launches", [(4, zm.STORES_CACHED, 8, [60]), (4, zm.STORES_STREAMING, 8, [60]), (4, zm.STORES_CACHED, 12, [60]),
                                                              (4, zm.STORES_STREAMING, 12, [60]), (5, zm.STORES_CACHED, 8, [48, 12])])
 def test_many_tensors_share_a_launch_with_every_kind_of_store(layouts, stores, max_len, launches):
-    """more than the 36 MiB up to which device-scope stores are used; and more layouts than a shared launch has room for"""
+    """more than 36 MiB in a launch, where ordinary stores take over from device-scope ones; and more layouts than a shared launch has room for"""
     tensors = [[synth.special_tensor("gauss" if max_len == 8 else "wide", 340_000 + 4099 * (i % layouts), seed=i % 4)] for i in range(60)]
     flat, _, got, shapes = layer_calls(tensors, 16384, 4096, max_len, stores)
     assert sum(2 * w.size for w in flat[:48]) <= 36 << 20 < sum(2 * w.size for w in flat)
@@ -492,10 +492,10 @@ def test_more_tensors_of_long_codes_than_one_launch_takes():
         assert np.array_equal(g, w), i
 
 
-@pytest.mark.parametrize("lengths", [[9216 * 4096], [9216 * 4096 + 1], [14_000_003] * 3, [38_000_001, 5, 70_000], [5_000_011] * 8,
+@pytest.mark.parametrize("lengths", [[7168 * 4096], [7168 * 4096 + 1], [14_000_003] * 3, [38_000_001, 5, 70_000], [5_000_011] * 8,
                                      [660_007] * 60], ids=["at the line", "above it", "three", "numbered", "eight", "shared"])
 def test_launches_of_many_streams_with_streaming_stores(lengths):
-    """more than 9216 streams of 4096 values: one tensor, row launches of few and of many, a numbered one and a shared one"""
+    """up to 7168 streams of 4096 values and more of them: one tensor, row launches of few and of many, a numbered one and a shared one"""
     w = synth.special_tensor("gauss", max(lengths), seed=5)
     tensors = [[w[7 * i: 7 * i + n] if 7 * i + n <= w.size else w[:n]] for i, n in enumerate(lengths)]
     flat, _, got, shapes = layer_calls(tensors, 16384, 4096, 8, zm.STORES_STREAMING)
@@ -518,7 +518,7 @@ def test_launches_of_many_streams_that_stay_cached(lengths, max_len):
 
 
 def test_a_launch_of_many_streams_holds_tensors_of_every_kind():
-    """raw chunks, cut-off streams and streams shorter than a group beside whole ones, in one launch of more than 9216 streams"""
+    """raw chunks, cut-off streams and streams shorter than a group beside whole ones, in one launch of more than 7168 streams"""
     tensors = [synth.special_tensor("gauss", 40_000_003, 5)] + [synth.special_tensor(kind, n, n) for kind in ("uniform_u16", "rare_last", "all_equal")
                                                                for n in (1, 9, 511, 4095, 4097, 50_001)]
     blobs = [zm.compress(w, 16384, 4096 if i % 2 == 0 else 512, 8)[0] for i, w in enumerate(tensors)]
@@ -535,7 +535,7 @@ def test_outputs_at_the_line_between_the_store_kinds(n):
 
 
 def test_outputs_between_the_store_kinds():
-    """a call that writes more than the 36 MiB that device-scope stores are used for, and less than the last-level cache"""
+    """a launch of up to 7168 streams that writes more than 36 MiB, where it takes ordinary stores, and less than the last-level cache"""
     w = synth.special_tensor("gauss", (20 << 20) + 777, seed=9)
     blob, _ = zm.compress(w, 16384, 4096)
     assert np.array_equal(gpu_decode_tensors([blob])[0], w)

@@ -42,14 +42,14 @@ def test_recover_launch_larger_than_half_the_last_level_cache():
 
 
 @pytest.mark.parametrize("n", [(5 << 20) - 1, 5 << 20, (5 << 20) + 1, (6 << 20) + 509])
-def test_recover_at_the_line_between_the_store_kinds(n):
+def test_recover_at_the_line_between_one_tile_and_four(n):
     rng = np.random.default_rng(n)
     e = rng.integers(0, 256, n, dtype=np.uint8)
     sm = rng.integers(0, 256, n, dtype=np.uint8)
     assert np.array_equal(gpu_recover(e, sm), zo.merge(e, sm))
 
 
-@pytest.mark.parametrize("n", [(4 << 20) - 1, 4 << 20, (4 << 20) + 1, (4 << 20) + 2048 + 7, (4 << 20) + 4 * 2048 - 1, (4 << 20) + 5 * 2048 + 513,
+@pytest.mark.parametrize("n", [(4 << 20) - 1, 4 << 20, (4 << 20) + 1, (5 << 20) + 2048 + 7, (5 << 20) + 4 * 2048 - 1, (5 << 20) + 5 * 2048 + 513,
                                32 << 20, (32 << 20) + 1, (32 << 20) + 2047, (32 << 20) + 2048, (32 << 20) + 1536 + 8])
 def test_recover_where_waves_take_four_tiles(n):
     """the lines between the three kernels, last waves that are whole, that hold one value and that end inside a tile"""
