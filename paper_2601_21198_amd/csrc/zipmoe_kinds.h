@@ -109,7 +109,8 @@ constexpr int most_waves(Kind kind, bool long_codes)
 // behind its own stores.
 //   short codes    two: four experts of 2048 x 1408 x 3 nt with four / three / two ahead 18.98 / 18.91 / 18.86, 16 experts 57.9 / 56.0 / 55.6 (one 59.2).
 //                  kFitting dev one: two experts of 2048 x 1408 x 3 (4224 streams), three sets cached, two / one 11.1 / 10.2, three 11.2 / 10.9; up to
-//                  three waves per SIMD two: one expert 7.0 / 7.7.  kMixed nt four: 23 tensors of 4096 values and one of 1024 two / four 32.2 / 30.6
+//                  three waves per SIMD two: one expert 7.0 / 7.7; with ordinary stores no difference (four experts 18.1 / 18.0): two.  kMixed nt
+//                  four: 23 tensors of 4096 values and one of 1024 two / four 32.2 / 30.6
 //   long codes     nt four: one / four: two experts 10.8 / 10.3, eight 34.3 / 31.8, four of 2048 x 1408 x 3 25.0 / 24.4, 16 60.1 / 60.7, two of
 //                  14336 x 4096 x 3 193.7 / 198.3.  dev one: one / four: two experts 11.8 / 13.9, eight 34.4 / 35.2; up to one wave per SIMD four: 12
 //                  tensors of 300001 values (888 streams) 7.7 / 6.8, one expert (1536) 8.8 / 9.0
@@ -118,7 +119,7 @@ constexpr int pairs_ahead(Kind kind, bool long_codes, Stores stores)
     if (kind == kShortStreams) return 2;         // never straight through
     if (kind == kDeep) return kPairs;
     if (stores == kStreaming) return long_codes || kind == kMixed ? kPairs : 2;
-    return kind == kSparse ? (long_codes ? kPairs : 2) : long_codes || kind == kFitting ? 1 : 2;
+    return kind == kSparse ? (long_codes ? kPairs : 2) : long_codes || (kind == kFitting && stores == kThrough) ? 1 : 2;
 }
 
 }  // namespace zipmoe
