@@ -753,3 +753,28 @@ def test_launches_around_the_lines_of_few_streams(streams, count, max_len):
     assert len(shapes) == 1
     for a, g in zip(flat, got):
         assert np.array_equal(g, a)
+
+
+@pytest.mark.parametrize("W,max_len", [(512, 8), (4096, 8), (4096, 12), (16384, 8)])
+@pytest.mark.parametrize("damage", ["start", "chunk behind", "chunk in front", "raw"])
+def test_streams_that_a_table_places_outside_are_left_alone(W, max_len, damage):
+    """entries of one chunk whose places wrap in 32 or 64 bits: its streams write nothing (the words before stay), the others are decoded"""
+    import torch
+    C, n = 2 * W, 7 * W + 5
+    w = synth.special_tensor("gauss" if max_len == 8 else "wide", n, seed=W)
+    blob = zm.compress(w, C, W, max_len)[0].copy()
+    assert chunk_modes(blob)[1] == 0
+    info = zm.blob_info(blob)
+    entry = info.table_offset + info.table_stride * 1
+    places = {"start": (entry + 12, "<u4", (1 << 32) - 16), "chunk behind": (entry, "<u8", (1 << 64) - 16), "chunk in front": (entry, "<u8", 0),
+              "raw": (entry, "<u8", (1 << 64) - 16 | 1)}
+    at, kind, value = places[damage]
+    blob[at: at + int(kind[2])] = np.array([value], kind).view(np.uint8)
+    layer = zm.ExpertLayer([[blob]], validate=False)
+    bufs, starts, _ = layer.alloc_outputs(1)
+    bufs[0].fill_(GUARD_WORD)
+    layer.decode([0], bufs, starts, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = bufs[0].cpu().numpy().view(np.uint16)
+    assert np.all(got[C: 2 * C] == GUARD_WORD)
+    assert np.array_equal(got[:C], w[:C]) and np.array_equal(got[2 * C: n], w[2 * C:])
