@@ -271,8 +271,26 @@ struct LongTable {
     }
 };
 
-// Symbol low, length high, as blobs have it, to length low, symbol high.
-__device__ __forceinline__ uint16_t swap_entry(uint32_t v) { return static_cast<uint16_t>(__builtin_amdgcn_perm(0u, v, 0x0c0c0001u)); }
+// A shift reads five bits of its amount, so an entry is one as it stands.  Written out: the compiler would put the `and` that the
+// language asks for back in front of the next look-up, and a field extract behind it.
+__device__ __forceinline__ uint32_t shifted_down(uint32_t x, uint32_t by) { uint32_t r; asm("v_lshrrev_b32_e32 %0, %1, %2" : "=v"(r) : "v"(by), "v"(x)); return r; }
+__device__ __forceinline__ uint32_t shifted_up(uint32_t x, uint32_t by) { uint32_t r; asm("v_lshlrev_b32_e32 %0, %1, %2" : "=v"(r) : "v"(by), "v"(x)); return r; }
+// All ones where bit kBit of x is set, else zero (likewise: as a condition it takes a comparison more).
+template <int kBit>
+__device__ __forceinline__ uint32_t spread(uint32_t x) { uint32_t r; asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(r) : "v"(x), "n"(kBit)); return r; }
+
+// Bits of `mask` from a, the others from b: one instruction.
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
+
+// An entry of the LDS table: the code's length in its low bits, the symbol in bits 7..14, where a bf16 word has its exponent.  So the
+// entry is the shift to the next code as it stands (shifts read five bits), a sum of four has the bits used in its low seven, and two
+// entries side by side take the sign-mantissa bytes in place of all other bits (merge2).  Made from two entries of a blob, symbol in the low
+// byte and length in the high one; bit 15 holds anything.
+constexpr uint32_t kExponentBits = 0x7f807f80u;
+__device__ __forceinline__ uint32_t entry_pair(uint32_t v) { return pick(kExponentBits, v << 7, v >> 8); }
+
+// Two bf16 words from two entries and their two sign-mantissa bytes, twice each: s eeeeeee e mmmmmmm.
+__device__ __forceinline__ uint32_t merge2(uint32_t entries, uint32_t sm_twice) { return pick(kExponentBits, entries, sm_twice); }
 
 // Lock-step decoder state of one lane (a5): two chains, one reading the lane's bitstream upwards from its
 // first bit (the first half of the lane's symbols, in order), one reading it downwards from its last bit (the
@@ -287,10 +305,11 @@ struct Decoder {
     const uint32_t *words;        // the stream as staged in LDS (length bytes included)
     uint32_t last_word;           // highest index a read may use
     LongTable table;              // kLong only
-    // upward chain: words q and q+1 of the bitstream, bits of lo already used (< 32 at the start of a round), index of word q+2
+    // Upward chain: words q and q+1 of the bitstream, bits of lo already used (< 32 at the start of a round), index of word q+2.
+    // Downward chain, short codes: the same of the bitstream from its end, every word reversed, so that it reads upwards as well.
+    // Long codes: dhi is the word that holds the bits just below the read position, of which its low dpos bits (0..31) are still
+    // unread, dlo the word below it, dnext the index of the word below that.
     uint32_t lo = 0, hi = 0, pos = 0, next = 0;
-    // downward chain: dhi is the word that holds the bits just below the read position, of which its low dpos
-    // bits (0..31) are still unread, dlo the word below it, dnext the index of the word below that
     uint32_t dlo = 0, dhi = 0, dpos = 0, dnext = 0;
 
     // first_bit, end_bit: where this lane's bitstream starts and ends, counted from the first payload bit
@@ -301,92 +320,115 @@ struct Decoder {
         lo = words[min(q, last_word)];
         hi = words[min(q + 1u, last_word)];
         next = q + 2u;
-        const uint32_t w = min(kLaneBytes / 4 + (end_bit >> 5), last_word);     // >= 16, so the indices below stay >= 14
-        dpos = end_bit & 31u;
-        dhi = words[w];
-        dlo = words[w - 1u];
+        const uint32_t end = kLong ? end_bit : end_bit - 1u;                    // a bitstream has at least eight bits
+        const uint32_t w = min(kLaneBytes / 4 + (end >> 5), last_word);         // >= 16, so the indices below stay >= 14
+        const uint32_t top = words[w], below = words[w - 1u];
         dnext = w - 2u;
+        if constexpr (kLong) {
+            dpos = end & 31u;
+            dhi = top;
+            dlo = below;
+        } else {
+            dpos = ~end & 31u;
+            dlo = __builtin_bitreverse32(top);
+            dhi = __builtin_bitreverse32(below);
+        }
     }
 
-    // The entry (length | symbol << 8) of the code that starts `used & 31` bits into a window whose first bit is its
-    // lowest (short codes) or its highest (long codes).
-    __device__ __forceinline__ uint32_t look(const uint16_t *tab, uint32_t win, uint32_t used) const
+    // The entry of the code at the beginning of a window: its lowest bits (short codes) or its highest (long codes).
+    __device__ __forceinline__ uint32_t look(const uint16_t *tab, uint32_t win) const
     {
-        if constexpr (kFromBlob) return swap_entry(tab[__builtin_bitreverse32(win << (used & 31u) >> table.shift) >> table.shift]);
-        else if constexpr (kLong) return tab[table.index(win << (used & 31u))];
-        else return tab[__builtin_amdgcn_ubfe(win, used, 8)];
+        if constexpr (kFromBlob) return entry_pair(tab[__builtin_bitreverse32(win >> table.shift) >> table.shift]);
+        else if constexpr (kLong) return tab[table.index(win)];
+        else return tab[win & 0xffu];
     }
 
     // One round: R symbols of each chain.  up / down receive the R entries in the order read; the result is the larger
     // of the two chains' bits used, of which no more than 32 are real.
+    // A chain's step is a look-up, a shift of the window by the entry, and the next address: two instructions between one read
+    // and the next, the rest is off the chain.  Where a launch is bound by its waves' chains, us: one matrix of 256 x 512 4.00 -> 3.86, one
+    // expert of 2048 x 1408 x 3, cached, 6.23 -> 5.98, two in streams of 16384 values 13.1 -> 12.5, of 32768 18.1 -> 17.2, against bits
+    // used that were summed up and codes extracted from an unmoved window (three instructions; a round with its merging and stores 56
+    // vector instructions instead of 44).
     template <int R>
     __device__ __forceinline__ uint32_t round(const uint16_t *tab, uint32_t (&up)[R], uint32_t (&down)[R])
     {
         // the words the chains take if the round crosses a word boundary: asked for now, used after the round
         const uint32_t fresh = words[min(next, last_word)];
-        const uint32_t dfresh = words[min(dnext, last_word)];
-        // R symbols out of one 32-bit window per chain.  acc sums the entries: its low byte is the bit offset of
-        // the next code in the window, the bytes above hold a sum of symbols that nothing reads.  Short codes: the field
-        // extract takes the low five bits of acc as its offset; when they wrap (32 bits used) no further code is
-        // extracted.  One chain's window is reversed, so that the next bit of both is the lowest or the highest.
+        uint32_t dfresh = words[min(dnext, last_word)];
         uint32_t win = __builtin_amdgcn_alignbit(hi, lo, pos), dwin = __builtin_amdgcn_alignbit(dhi, dlo, dpos);
         if constexpr (kLong) win = __builtin_bitreverse32(win);
-        else dwin = __builtin_bitreverse32(dwin);
-        uint32_t acc = 0, dacc = 0;
+        uint32_t used = 0, dused = 0;                 // in the low seven bits; those above hold sums of symbols
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const uint32_t v = look(tab, win, acc), dv = look(tab, dwin, dacc);
+            const uint32_t v = look(tab, win), dv = look(tab, dwin);
             up[k] = v;
             down[k] = dv;
-            acc += v;
-            dacc += dv;
+            if (k + 1 < R) {
+                win = kLong ? shifted_up(win, v) : shifted_down(win, v);
+                dwin = kLong ? shifted_up(dwin, dv) : shifted_down(dwin, dv);
+            }
+            used += v;
+            dused += dv;
         }
-        // written without branches so that a whole tile pair is one basic block
-        const uint32_t used = acc & 0xffu, dused = dacc & 0xffu;
+        // written without branches so that a whole tile pair is one basic block: the masks are all ones where the chain has used
+        // up its first word
         pos += used;
-        const bool take = pos >= 32u;
-        lo = take ? hi : lo;
-        hi = take ? fresh : hi;
-        next += take ? 1u : 0u;
+        const uint32_t take = spread<5>(pos);
         pos &= 31u;
-        const int32_t left = static_cast<int32_t>(dpos) - static_cast<int32_t>(dused);    // -32..31
-        const bool dtake = left < 0;
-        dhi = dtake ? dlo : dhi;
-        dlo = dtake ? dfresh : dlo;
-        dnext -= dtake ? 1u : 0u;
-        dpos = static_cast<uint32_t>(left) & 31u;
-        return max(used, dused);
+        lo = pick(take, hi, lo);
+        hi = pick(take, fresh, hi);
+        next -= take;
+        if constexpr (kLong) {
+            dpos -= dused;                            // -48..31 in the low seven bits
+            const uint32_t dtake = spread<6>(dpos);
+            dpos &= 31u;
+            dhi = pick(dtake, dlo, dhi);
+            dlo = pick(dtake, dfresh, dlo);
+            dnext += dtake;
+        } else {
+            dpos += dused;
+            const uint32_t dtake = spread<5>(dpos);
+            dpos &= 31u;
+            dlo = pick(dtake, dhi, dlo);
+            dhi = pick(dtake, __builtin_bitreverse32(dfresh), dhi);
+            dnext += dtake;
+        }
+        return kLong ? max(used & 127u, dused & 127u) : 0u;
     }
 
-    // Four symbols of each chain: .x = the upward chain's, .y = the downward chain's, both packed in value order
-    // (byte 0 = the symbol with the lowest index), i.e. half a tile's exponent bytes for this lane each.  most: the
-    // largest number of bits that a round has used.
-    __device__ __forceinline__ uint2 quad(const uint16_t *tab, uint32_t &most)
+    // Four symbols of each chain, as entries, two per register in value order: half a tile's of this lane each.  most: the
+    // largest number of bits that a round has used (long codes only).
+    struct Quad { uint2 up, down; };
+    __device__ __forceinline__ Quad quad(const uint16_t *tab, uint32_t &most)
     {
         uint32_t up[4], down[4];
         most = max(most, round(tab, up, down));
-        return make_uint2(pack(up[0], up[1], up[2], up[3]), pack(down[3], down[2], down[1], down[0]));
+        return Quad{make_uint2(pack(up[0], up[1]), pack(up[2], up[3])), make_uint2(pack(down[3], down[2]), pack(down[1], down[0]))};
     }
 
-    __device__ __forceinline__ uint2 safe_quad(const uint16_t *tab)
+    __device__ __forceinline__ Quad safe_quad(const uint16_t *tab)
     {
         if constexpr (kLong) {
             uint32_t ua[2], da[2], ub[2], db[2];
             round(tab, ua, da);
             round(tab, ub, db);
-            return make_uint2(pack(ua[0], ua[1], ub[0], ub[1]), pack(db[1], db[0], da[1], da[0]));
+            return Quad{make_uint2(pack(ua[0], ua[1]), pack(ub[0], ub[1])), make_uint2(pack(db[1], db[0]), pack(da[1], da[0]))};
         } else {
             uint32_t most = 0;
             return quad(tab, most);
         }
     }
 
-    // byte 1 (the symbol) of four entries, packed with byte permutes (0x0c selects a zero byte)
-    static __device__ __forceinline__ uint32_t pack(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
-    {
-        return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0501u), __builtin_amdgcn_perm(b, a, 0x0c0c0501u), 0x05040100u);
-    }
+    static __device__ __forceinline__ uint32_t pack(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 };
+
+// One lane's eight bf16 words of a tile from its entries, values 0..3 and 4..7, and its sign-mantissa bytes.
+__device__ __forceinline__ uint4 merge8(uint2 e03, uint2 e47, uint2 sm)
+{
+    return make_uint4(merge2(e03.x, __builtin_amdgcn_perm(sm.x, sm.x, 0x01010000u)), merge2(e03.y, __builtin_amdgcn_perm(sm.x, sm.x, 0x03030202u)),
+                      merge2(e47.x, __builtin_amdgcn_perm(sm.y, sm.y, 0x01010000u)), merge2(e47.y, __builtin_amdgcn_perm(sm.y, sm.y, 0x03030202u)));
+}
 
 // One byte per value of a stream (sign-mantissa bytes, or a raw chunk's exponent bytes), read as 64 bits per lane and
 // tile.  The descriptor covers the stream's bytes, rounded up to whole groups of eight (the section is padded): a lane
@@ -405,12 +447,11 @@ struct ByteSource {
     }
 };
 
-// Merges and stores one lane's eight values of a tile, or those that it has.
+// Stores one lane's eight values of a tile, or those that it has.
 template <Stores kStores>
-__device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t tile, uint2 e, uint2 sm, int32_t mine)
+__device__ __forceinline__ void finish_tile(const Sink<kStores> &out, uint32_t tile, uint4 w, int32_t mine)
 {
     const int32_t left = mine - static_cast<int32_t>(tile * kTile);
-    const uint4 w = recover8(e, sm);
     if (left >= 8) out.store(tile, w);
     else if (left > 0) out.store_partial(tile, w);
 }
@@ -432,15 +473,15 @@ __device__ __forceinline__ uint32_t decode_group(Decoder<kLong> &dec, const uint
         uint32_t most = 0;
         // a tile's eight symbols come in two quads: the upward chain gives values 0..3 first, the
         // downward chain values 4..7 first
-        const uint2 a = dec.quad(tab, most), b = dec.quad(tab, most);
+        const auto a = dec.quad(tab, most), b = dec.quad(tab, most);
         if constexpr (kLong) {
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(most > 32u) != 0, 0)) {
                 dec = before;
                 return static_cast<uint32_t>(i);
             }
         }
-        out.store(lo, recover8(make_uint2(a.x, b.x), up[i]));
-        out.store(hi, recover8(make_uint2(b.y, a.y), down[i]));
+        out.store(lo, merge8(a.up, b.up, up[i]));
+        out.store(hi, merge8(b.down, a.down, down[i]));
         if (i + kAhead < kPairs) {
             up[i + kAhead] = sm.load(lo + kAhead);
             down[i + kAhead] = sm.load(hi - kAhead);
@@ -489,14 +530,14 @@ __device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec
 #pragma unroll 1
     for (;; ++lo) {
         const uint32_t hi = tiles - 1u - lo;
-        const uint2 a = dec.safe_quad(tab);
+        const auto a = dec.safe_quad(tab);
         if (lo == hi) {
-            finish_tile(out, lo, make_uint2(a.x, a.y), up[0], mine);
+            finish_tile(out, lo, merge8(a.up, a.down, up[0]), mine);
             return;
         }
-        const uint2 b = dec.safe_quad(tab);
-        finish_tile(out, lo, make_uint2(a.x, b.x), up[0], mine);
-        finish_tile(out, hi, make_uint2(b.y, a.y), down[0], mine);
+        const auto b = dec.safe_quad(tab);
+        finish_tile(out, lo, merge8(a.up, b.up, up[0]), mine);
+        finish_tile(out, hi, merge8(b.down, a.down, down[0]), mine);
         if (lo + 1u >= hi) return;
         up[0] = up[1]; down[0] = down[1];
         up[1] = sm.load(lo + 2u);
@@ -515,7 +556,7 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
 #pragma unroll
         for (int k = 0; k < kPairs; ++k) { e[k] = raw.load(first + k); s[k] = sm.load(first + k); }
 #pragma unroll
-        for (int k = 0; k < kPairs; ++k) finish_tile(out, first + k, e[k], s[k], mine);
+        for (int k = 0; k < kPairs; ++k) finish_tile(out, first + k, recover8(e[k], s[k]), mine);
     }
 }
 
@@ -627,7 +668,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
         const uint32_t i = 4u * lane;
         const uint2 e = lut4;
         if constexpr (!kLong) {
-            reinterpret_cast<uint2 *>(tab)[lane] = make_uint2(__builtin_amdgcn_perm(e.x, e.x, 0x02030001u), __builtin_amdgcn_perm(e.y, e.y, 0x02030001u));
+            reinterpret_cast<uint2 *>(tab)[lane] = make_uint2(entry_pair(e.x), entry_pair(e.y));
         } else {
             // The blob's table is indexed with a code's first bit lowest, so the number v of LongTable has to be reversed;
             // its first 256 entries are those of the eight-bit beginnings, with a length above eight at shared ones.
@@ -649,12 +690,12 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
             for (int k = 0; k < 4; ++k) {
                 const uint32_t v = (k & 2 ? e.y : e.x) >> (16 * (k & 1)) & 0xffffu;
                 const uint32_t at = __builtin_bitreverse32(i + k) >> 24;
-                if (at < whole_codes) tab[at] = swap_entry(v);
+                if (at < whole_codes) tab[at] = static_cast<uint16_t>(entry_pair(v));
             }
-            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = swap_entry(lut_tail);
+            if (lane + late >= 64u) tab[whole_codes + late - 64u + lane] = static_cast<uint16_t>(entry_pair(lut_tail));
             for (uint32_t k = lane; k + 64u < late; k += 64u) {
                 const uint32_t v = lut[__builtin_bitreverse32((whole_codes << more) + k) >> (32u - max_len)];
-                tab[whole_codes + k] = swap_entry(v);
+                tab[whole_codes + k] = static_cast<uint16_t>(entry_pair(v));
             }
         }
         u32x4 *dst = reinterpret_cast<u32x4 *>(words);
