@@ -564,107 +564,45 @@ __device__ __forceinline__ void merge_raw_stream(const Sink<kStores> &out, const
 template <class T>
 using Constant = __attribute__((address_space(4))) T;
 
-// The stream of one wave.  kLong: codes of more than eight bits; kWaves: waves (streams) per workgroup; kStores: how the output is
-// written; cap_words: LDS words reserved per wave for its stream; long_slots: as in Launch
-template <bool kLong, int kWaves, Stores kStores, Kind kKind>
-__device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint32_t cap_words, uint32_t long_slots)
+// LDS written by some lanes of this wave is read by others: order the LDS accesses only
+__device__ __forceinline__ void order_lds()
 {
-    // The decode table of the workgroup's tensor, at a fixed LDS address: one 16-bit read gives a code's length and its
-    // symbol.  (Two byte tables, one read each, were 2-4 % slower: twice the LDS instructions, whose random accesses
-    // collide on banks.)  That of long codes lies in front of the streams, as long as the launch's widest tensor needs.
-    __shared__ __align__(16) uint16_t short_tab[kLong ? 8 : kTableEntries];
-    extern __shared__ __align__(16) uint32_t dynamic_lds[];
-    uint16_t *const tab = kLong ? reinterpret_cast<uint16_t *>(dynamic_lds) : short_tab;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-    const uint32_t g = block * kWaves + wave;
-    if (g >= t.n_streams) return;
-    uint32_t *words = dynamic_lds + (kLong ? long_table_words(long_slots) : 0u) + wave * cap_words;
-    const uint32_t W = t.stream_values;
-    const uint32_t max_len = max_len_of(t.code), quantum = quantum_of(t.code);
-    const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;     // bytes of a chunk-table entry
-    const uint64_t v0 = static_cast<uint64_t>(g) * W;              // first value of the stream in the tensor
-    const uint32_t sn = g + 1u < t.n_streams ? W : t.last_values, tiles = (sn + kTile - 1) / kTile;
-    const int32_t mine = static_cast<int32_t>(sn) - static_cast<int32_t>(lane * 8u);   // values left from this lane's first one
-
-    // one read of the chunk's table entry gives the chunk's place and mode and this stream's extent
-    const uint32_t c = chunk_of(g, t.per_chunk, t.code), s = g - c * t.streams_per_chunk;
-    const Constant<uint8_t> *entry = (const Constant<uint8_t> *)(reinterpret_cast<const uint8_t *>(t.table) + static_cast<uint64_t>(c) * stride);
-    const uint64_t ent = *(const Constant<uint64_t> *)entry;
-    const uint32_t o0 = ((const Constant<uint32_t> *)(entry + 8))[s], o1 = ((const Constant<uint32_t> *)(entry + 8))[s + 1u];
-
-    // The decode table is asked for meanwhile: behind the sign-mantissa bytes it would be served behind them, and decoding
-    // waits for it.
-    const uint16_t *const lut = reinterpret_cast<const uint16_t *>(t.lut);
-    const uint32_t mask = (1u << max_len) - 1u;
+// a3: a tensor's decode table -> LDS, in entries of the decoder's form.  Every wave of the workgroup writes the
+// same bytes (LDS word writes are atomic), so a wave may read as soon as its own writes are done: no workgroup barrier.
+template <bool kLong>
+struct TableStage {
+    const uint16_t *lut;             // the blob's table
+    uint32_t max_len;
     uint2 lut4;                      // entries 4 * lane .. + 3, of codes shorter than eight bits replicated over the index bits above
-    uint32_t lut_tail = 0;           // long codes: see below
-    if constexpr (kLong) {
-        lut4 = reinterpret_cast<const uint2 *>(lut)[lane];
-    } else {
-        lut4 = make_uint2(*reinterpret_cast<const uint32_t *>(lut + (4u * lane & mask)), *reinterpret_cast<const uint32_t *>(lut + (4u * lane + 2u & mask)));
-    }
-    asm volatile("" :: "s"(ent), "s"(o0), "s"(o1));        // with one wait: the compiler would read o0 and o1 where they are used
+    uint32_t lut_tail = 0;           // long codes: see put
 
-    bool active = true;
-    const uint8_t *raw = nullptr;
-    // The stream's first vectors, lane + 64 k, wait in registers until the other requests are out: 2 KiB, more than a typical
-    // stream of 4096 values, 4, or 12, as much as one of 32768.  (What is copied in the loop below waits for every vector anew: streams
-    // of 32768 values, two / eight experts of 1024 x 2048 x 3, 20.7 / 45.5 us with 2 KiB, 17.8 / 37.8 with 12 and the next group of
-    // tiles asked for early, of 16384 values 13.2 / 32.8 and 12.1 / 32.1.)  What lies past 4 KiB is left out in one step: one tensor of 32760
-    // values in streams of 8192 8.33 -> 7.93 us, four experts of three tensors of 70001 6.14 -> 5.78.
-    constexpr uint32_t kHeld = kKind == kDeep ? 12 : kKind == kMixed ? 4 : 2, kFirst = kHeld < 4 ? kHeld : 4;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 held[kHeld];
-    uint32_t n_held = 0;
-    bool dense = false;          // long codes: four symbols of a lane are likely to have more bits than a window
-    const uint64_t chunk = ent & ~15ull, at = chunk - t.e_offset;            // offsets inside the blob and the E-chunk region
-    const uint32_t mode = static_cast<uint32_t>(ent & 15ull);
-    if (mode == ZM_MODE_CODED) {
-        // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
-        // sign-mantissa bytes because decoding can not start without them.  What is not held is copied here.
-        active = stream_inside(chunk, o0, o1, t.e_offset, t.e_size);
-        if (active) {
-            const uint32_t nvec = min((o1 - o0) >> 4, cap_words >> 2);
-            if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
-            const u32x4 *src = reinterpret_cast<const u32x4 *>(t.echunks + at + o0);
-            u32x4 *dst = reinterpret_cast<u32x4 *>(words);
-            n_held = min(nvec, 64u * kHeld);
-#pragma unroll
-            for (uint32_t k = 0; k < kFirst; ++k)
-                if (lane + 64u * k < n_held) held[k] = src[lane + 64u * k];
-            if (kFirst < kHeld && n_held > 64u * kFirst) {
-#pragma unroll
-                for (uint32_t k = kFirst; k < kHeld; ++k)
-                    if (lane + 64u * k < n_held) held[k] = src[lane + 64u * k];
-            }
-            for (uint32_t i = 64u * kHeld + lane; i < nvec; i += 64) dst[i] = src[i];
+    __device__ __forceinline__ void ask(const Task &t, uint32_t lane)
+    {
+        lut = reinterpret_cast<const uint16_t *>(t.lut);
+        max_len = max_len_of(t.code);
+        if constexpr (kLong) {
+            lut4 = reinterpret_cast<const uint2 *>(lut)[lane];
+        } else {
+            const uint32_t mask = (1u << max_len) - 1u;
+            lut4 = make_uint2(*reinterpret_cast<const uint32_t *>(lut + (4u * lane & mask)), *reinterpret_cast<const uint32_t *>(lut + (4u * lane + 2u & mask)));
         }
-    } else {
-        raw = t.echunks + at + static_cast<uint64_t>(s) * W;
-        active = mode == ZM_MODE_RAW && raw_stream_inside(chunk, static_cast<uint64_t>(s) * W, (sn + 15u) & ~15u, t.e_offset, t.e_size);
     }
-    if constexpr (kLong) lut_tail = lut[__builtin_bitreverse32(mask - 63u + lane) >> (32u - max_len)];
-    // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
-    // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
-    constexpr int kAhead = pairs_ahead(kKind, kLong, kStores);
-    constexpr bool kGroups = kKind == kDeep || kKind == kMixed;          // there may be streams of several groups
-    const bool coded = mode == ZM_MODE_CODED;
-    const bool straight = kKind != kShortStreams && (kGroups ? sn % kGroupValues == 0 : sn == kGroupValues) && !dense;     // whole groups of tiles, decoded without a look at their ends
-    const bool groups = kGroups && straight && (kKind == kDeep || tiles > kGroup);                     // all of them are asked for group by group
-    uint2 up[kPairs], down[kPairs];
-    const ByteSource sm(t.sm + v0, sn, lane), first_sm(t.sm + v0, coded && active ? sn : 0u, lane);
-    auto ask = [&](int i) {        // tiles that the stream does not have read as zero and touch no memory
-        up[i] = first_sm.load(i);
-        down[i] = first_sm.load(tiles - 1u - i);
-    };
-    // a3: decode table -> LDS with the two bytes of an entry swapped (length low).  Every wave of the workgroup writes the
-    // same bytes (LDS word writes are atomic), so a wave may read as soon as its own writes are done: no workgroup barrier.
-    LongTable table{0u, 0};
-    bool narrow = false;         // long codes: the table has no room for all shared beginnings
-    auto stage = [&] {
+
+    __device__ __forceinline__ void ask_tail(uint32_t lane)
+    {
+        if constexpr (kLong) lut_tail = lut[__builtin_bitreverse32((1u << max_len) - 64u + lane) >> (32u - max_len)];
+    }
+
+    // narrow: the table has no room for all shared beginnings
+    __device__ __forceinline__ void put(uint16_t *tab, uint32_t lane, uint32_t long_slots, LongTable &table, bool &narrow) const
+    {
         const uint32_t i = 4u * lane;
         const uint2 e = lut4;
         if constexpr (!kLong) {
@@ -698,6 +636,89 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
                 tab[whole_codes + k] = static_cast<uint16_t>(entry_pair(v));
             }
         }
+    }
+};
+
+// Stream g of a tensor, by one wave.  kLong: codes of more than eight bits; kStores: how the output is written; tab: LDS for the decode
+// table; words: LDS for the stream, cap_words of it; long_slots: as in Launch
+template <bool kLong, Stores kStores, Kind kKind>
+__device__ __forceinline__ void decode_stream(const Task &t, uint32_t g, uint16_t *tab, uint32_t *words, uint32_t cap_words, uint32_t long_slots)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t W = t.stream_values;
+    const uint32_t quantum = quantum_of(t.code);
+    const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;     // bytes of a chunk-table entry
+    const uint64_t v0 = static_cast<uint64_t>(g) * W;              // first value of the stream in the tensor
+    const uint32_t sn = g + 1u < t.n_streams ? W : t.last_values, tiles = (sn + kTile - 1) / kTile;
+    const int32_t mine = static_cast<int32_t>(sn) - static_cast<int32_t>(lane * 8u);   // values left from this lane's first one
+
+    // one read of the chunk's table entry gives the chunk's place and mode and this stream's extent
+    const uint32_t c = chunk_of(g, t.per_chunk, t.code), s = g - c * t.streams_per_chunk;
+    const Constant<uint8_t> *entry = (const Constant<uint8_t> *)(reinterpret_cast<const uint8_t *>(t.table) + static_cast<uint64_t>(c) * stride);
+    const uint64_t ent = *(const Constant<uint64_t> *)entry;
+    const uint32_t o0 = ((const Constant<uint32_t> *)(entry + 8))[s], o1 = ((const Constant<uint32_t> *)(entry + 8))[s + 1u];
+
+    // The decode table is asked for meanwhile: behind the sign-mantissa bytes it would be served behind them, and decoding
+    // waits for it.
+    TableStage<kLong> stage_table;
+    stage_table.ask(t, lane);
+    asm volatile("" :: "s"(ent), "s"(o0), "s"(o1));        // with one wait: the compiler would read o0 and o1 where they are used
+
+    bool active = true;
+    const uint8_t *raw = nullptr;
+    // The stream's first vectors, lane + 64 k, wait in registers until the other requests are out: 2 KiB, more than a typical
+    // stream of 4096 values, 4, or 12, as much as one of 32768.  (What is copied in the loop below waits for every vector anew: streams
+    // of 32768 values, two / eight experts of 1024 x 2048 x 3, 20.7 / 45.5 us with 2 KiB, 17.8 / 37.8 with 12 and the next group of
+    // tiles asked for early, of 16384 values 13.2 / 32.8 and 12.1 / 32.1.)  What lies past 4 KiB is left out in one step: one tensor of 32760
+    // values in streams of 8192 8.33 -> 7.93 us, four experts of three tensors of 70001 6.14 -> 5.78.
+    constexpr uint32_t kHeld = kKind == kDeep ? 12 : kKind == kMixed ? 4 : 2, kFirst = kHeld < 4 ? kHeld : 4;
+    u32x4 held[kHeld];
+    uint32_t n_held = 0;
+    bool dense = false;          // long codes: four symbols of a lane are likely to have more bits than a window
+    const uint64_t chunk = ent & ~15ull, at = chunk - t.e_offset;            // offsets inside the blob and the E-chunk region
+    const uint32_t mode = static_cast<uint32_t>(ent & 15ull);
+    if (mode == ZM_MODE_CODED) {
+        // a4: the stream's bytes, 128 bits per lane per load.  They are requested before the (larger)
+        // sign-mantissa bytes because decoding can not start without them.  What is not held is copied here.
+        active = stream_inside(chunk, o0, o1, t.e_offset, t.e_size);
+        if (active) {
+            const uint32_t nvec = min((o1 - o0) >> 4, cap_words >> 2);
+            if constexpr (kLong) dense = 2u * (o1 - o0) > sn;          // more than four bits a value
+            const u32x4 *src = reinterpret_cast<const u32x4 *>(t.echunks + at + o0);
+            u32x4 *dst = reinterpret_cast<u32x4 *>(words);
+            n_held = min(nvec, 64u * kHeld);
+#pragma unroll
+            for (uint32_t k = 0; k < kFirst; ++k)
+                if (lane + 64u * k < n_held) held[k] = src[lane + 64u * k];
+            if (kFirst < kHeld && n_held > 64u * kFirst) {
+#pragma unroll
+                for (uint32_t k = kFirst; k < kHeld; ++k)
+                    if (lane + 64u * k < n_held) held[k] = src[lane + 64u * k];
+            }
+            for (uint32_t i = 64u * kHeld + lane; i < nvec; i += 64) dst[i] = src[i];
+        }
+    } else {
+        raw = t.echunks + at + static_cast<uint64_t>(s) * W;
+        active = mode == ZM_MODE_RAW && raw_stream_inside(chunk, static_cast<uint64_t>(s) * W, (sn + 15u) & ~15u, t.e_offset, t.e_size);
+    }
+    stage_table.ask_tail(lane);
+    // Next in the request order: the sign-mantissa bytes of the first tiles.  They stay in flight while the
+    // stream is staged and decoding starts.  up[i] / down[i] hold those of a pair of tiles, one from either end.
+    constexpr int kAhead = pairs_ahead(kKind, kLong, kStores);
+    constexpr bool kGroups = kKind == kDeep || kKind == kMixed;          // there may be streams of several groups
+    const bool coded = mode == ZM_MODE_CODED;
+    const bool straight = kKind != kShortStreams && (kGroups ? sn % kGroupValues == 0 : sn == kGroupValues) && !dense;     // whole groups of tiles, decoded without a look at their ends
+    const bool groups = kGroups && straight && (kKind == kDeep || tiles > kGroup);                     // all of them are asked for group by group
+    uint2 up[kPairs], down[kPairs];
+    const ByteSource sm(t.sm + v0, sn, lane), first_sm(t.sm + v0, coded && active ? sn : 0u, lane);
+    auto ask = [&](int i) {        // tiles that the stream does not have read as zero and touch no memory
+        up[i] = first_sm.load(i);
+        down[i] = first_sm.load(tiles - 1u - i);
+    };
+    LongTable table{0u, 0};
+    bool narrow = false;         // long codes: the table has no room for all shared beginnings
+    auto stage = [&] {
+        stage_table.put(tab, lane, long_slots, table, narrow);
         u32x4 *dst = reinterpret_cast<u32x4 *>(words);
 #pragma unroll
         for (uint32_t k = 0; k < kFirst; ++k)
@@ -724,10 +745,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
         for (int i = 1; i < kAhead; ++i) ask(i);
         stage();
     }
-    // LDS written by some lanes of this wave is read by others: order the LDS accesses only
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    order_lds();
     if (!active) return;
 
     const Sink<kStores> out(t.out + v0, sn, lane);
@@ -748,7 +766,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
             dec.table = table;
             dec.start(first, first + bits);
             if (kAhead < 2) ask(1);
-            decode_any_stream(dec, lut, out, sm, 0u, tiles, mine, up, down);
+            decode_any_stream(dec, stage_table.lut, out, sm, 0u, tiles, mine, up, down);
             return;
         }
     }
@@ -767,9 +785,138 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     decode_any_stream(dec, tab, out, sm, done, tiles, mine, up, down);
 }
 
+// kBundle consecutive streams of a tensor, eight tiles together, by one wave: where streams are short, a wave's life is mostly the chain of
+// dependent reads in front of a few look-ups, and this puts eight tiles behind one chain and interleaves the look-ups of two streams.  Lane k
+// reads the chunk-table entry of stream k; the streams follow one another in memory and are fetched as one piece.  That is for whole coded streams;
+// others (raw ones, what a damaged table has) are decoded one after another, and so is the rest of a tensor that is no whole bundle, by a wave each.
+template <bool kLong, Stores kStores, Kind kKind, int kBundle>
+__device__ __forceinline__ void decode_bundle(const Task &t, uint32_t wave_of_tensor, uint16_t *tab, uint32_t *words, uint32_t cap_words, uint32_t long_slots)
+{
+    constexpr uint32_t kTilesEach = kGroup / kBundle, kValues = kTilesEach * kTile;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t bundles = whole_bundles(t.n_streams, t.last_values, kBundle);
+    const uint32_t alone = wave_of_tensor - min(wave_of_tensor, bundles), g0 = (wave_of_tensor - alone) * kBundle + alone;
+    if (g0 >= t.n_streams) return;
+    uint32_t one_by_one = 1u;        // streams to be decoded by themselves, bit k is stream g0 + k
+    if (wave_of_tensor < bundles) {
+        const uint32_t stride = (8u + 4u * (t.streams_per_chunk + 1u) + 7u) & ~7u;
+        const uint64_t v0 = static_cast<uint64_t>(g0) * kValues;
+        const uint32_t quantum = quantum_of(t.code);
 
-template <bool kLong, int kWaves, Stores kStores, Kind kKind, class Args>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, most_waves(kKind, kLong)))) zm_decode_kernel(const Args P)
+        const uint32_t k_of = lane & (kBundle - 1u), g = g0 + k_of;
+        const uint32_t c = chunk_of(g, t.per_chunk, t.code), s = g - c * t.streams_per_chunk;
+        const uint8_t *entry = reinterpret_cast<const uint8_t *>(t.table) + static_cast<uint64_t>(c) * stride;
+        const uint64_t ent = *reinterpret_cast<const uint64_t *>(entry);
+        const uint32_t o0 = reinterpret_cast<const uint32_t *>(entry + 8)[s], o1 = reinterpret_cast<const uint32_t *>(entry + 8)[s + 1u];
+        TableStage<kLong> stage_table;
+        stage_table.ask(t, lane);
+
+        const uint64_t chunk = ent & ~15ull, from = reinterpret_cast<uint64_t>(t.echunks) + (chunk - t.e_offset) + o0;
+        const uint32_t bytes = o1 - o0;
+        const uint64_t from0 = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(from >> 32), 0))) << 32 |
+                               static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(from), 0));
+        const uint32_t rel = static_cast<uint32_t>(from - from0), end = rel + bytes;
+        const uint32_t before = __builtin_amdgcn_update_dpp(0u, end, 0x111, 0xf, 0xf, false);       // row_shr:1
+        const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(end), kBundle - 1));
+        constexpr uint32_t kHeld = 4;
+        const bool simple = (ent & 15ull) == ZM_MODE_CODED && stream_inside(chunk, o0, o1, t.e_offset, t.e_size) && !((from | bytes) & 15u) && from - from0 <= 1024u * kHeld &&
+                            (k_of == 0 || rel == before) && end <= min(1024u * kHeld, 4u * kBundle * cap_words) && !(kLong && 2u * bytes > kValues);
+        one_by_one = (1u << kBundle) - 1u;
+        if (__builtin_amdgcn_ballot_w64(simple) == ~0ull) {
+            u32x4 held[kHeld];
+            const __amdgpu_buffer_rsrc_t piece = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(from0), 0, static_cast<int>(total), kRawBuffer);
+#pragma unroll
+            for (uint32_t k = 0; k < kHeld; ++k) held[k] = __builtin_amdgcn_raw_buffer_load_b128(piece, static_cast<int>(16u * lane + 1024u * k), 0, 0);
+            stage_table.ask_tail(lane);
+            // sign-mantissa bytes, in the order of use: two streams take turns, each from both ends
+            const ByteSource sm(t.sm + v0, kGroupValues, lane);
+            auto tile_of = [](uint32_t i) {
+                if (kTilesEach == 1) return i;
+                const uint32_t pair = i / (2u * kTilesEach), p = i % (2u * kTilesEach) / 4u, which = i & 3u;
+                return (2u * pair + which / 2u) * kTilesEach + (which & 1u ? kTilesEach - 1u - p : p);
+            };
+            constexpr uint32_t kAhead = bundle_ahead(kKind, kStores);
+            uint2 byte8[kGroup];
+#pragma unroll
+            for (uint32_t i = 0; i < kAhead; ++i) byte8[i] = sm.load(tile_of(i));
+            LongTable table{0u, 0};
+            bool narrow = false;
+            stage_table.put(tab, lane, long_slots, table, narrow);
+#pragma unroll
+            for (uint32_t k = 0; k < kHeld; ++k)
+                if (16u * lane + 1024u * k < total) reinterpret_cast<u32x4 *>(words)[lane + 64u * k] = held[k];
+            order_lds();
+            if (!narrow) {
+                const Sink<kStores> out(t.out + v0, kGroupValues, lane);
+                one_by_one = 0;
+#pragma unroll
+                for (int k = 0; k < kBundle; k += 2) {
+                    const uint32_t at0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rel), k)) / 4u, at1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rel), k + 1)) / 4u;
+                    const uint32_t *const w0 = words + at0, *const w1 = words + at1;
+                    // two streams' prefix sums in one: 64 lanes of at most 8 * 4 + 2 * 255 bits
+                    const uint32_t bits0 = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(w0)[lane], bits1 = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(w1)[lane];
+                    const uint32_t first = wave_exclusive_sum(bits0 | bits1 << 16);
+                    Decoder<kLong> d0, d1;
+                    d0.words = w0; d1.words = w1;
+                    d0.last_word = kBundle * cap_words - 1u - at0;
+                    d1.last_word = kBundle * cap_words - 1u - at1;
+                    d0.table = d1.table = table;
+                    d0.start(first & 0xffffu, (first & 0xffffu) + bits0);
+                    d1.start(first >> 16, (first >> 16) + bits1);
+                    uint32_t most0 = 0, most1 = 0;
+                    const uint32_t done = k * kTilesEach;          // tiles
+                    auto more = [&](uint32_t i) { if (i + kAhead < kGroup) byte8[i + kAhead] = sm.load(tile_of(i + kAhead)); };
+                    if constexpr (kTilesEach == 1) {
+                        const auto a0 = d0.quad(tab, most0), a1 = d1.quad(tab, most1);
+                        out.store(done, merge8(a0.up, a0.down, byte8[done]));
+                        out.store(done + 1u, merge8(a1.up, a1.down, byte8[done + 1u]));
+                        more(done); more(done + 1u);
+                    } else {
+#pragma unroll
+                        for (uint32_t p = 0; p < kTilesEach / 2u; ++p) {
+                            const auto a0 = d0.quad(tab, most0), a1 = d1.quad(tab, most1), b0 = d0.quad(tab, most0), b1 = d1.quad(tab, most1);
+                            const uint32_t i = done + 4u * p;
+                            out.store(tile_of(i), merge8(a0.up, b0.up, byte8[i]));
+                            out.store(tile_of(i + 1u), merge8(b0.down, a0.down, byte8[i + 1u]));
+                            out.store(tile_of(i + 2u), merge8(a1.up, b1.up, byte8[i + 2u]));
+                            out.store(tile_of(i + 3u), merge8(b1.down, a1.down, byte8[i + 3u]));
+                            more(i); more(i + 1u); more(i + 2u); more(i + 3u);
+                        }
+                    }
+                    // long codes: a stream in which some lane's four symbols had more bits than a window is done again
+                    if constexpr (kLong)
+                        one_by_one |= (__builtin_amdgcn_ballot_w64(most0 > 32u) ? 1u << k : 0u) | (__builtin_amdgcn_ballot_w64(most1 > 32u) ? 2u << k : 0u);
+                }
+            }
+        }
+    }
+    while (one_by_one) {
+        const uint32_t k = static_cast<uint32_t>(__builtin_ctz(one_by_one));
+        one_by_one &= one_by_one - 1u;
+        decode_stream<kLong, kStores, kShortStreams>(t, g0 + k, tab, words, cap_words, long_slots);
+    }
+}
+
+// What a wave decodes: a stream, or kBundle of them.  kWaves: waves per workgroup; cap_words: LDS words reserved for a stream
+template <bool kLong, int kWaves, Stores kStores, Kind kKind, int kBundle>
+__device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint32_t cap_words, uint32_t long_slots)
+{
+    // The decode table of the workgroup's tensor, at a fixed LDS address: one 16-bit read gives a code's length and its
+    // symbol.  (Two byte tables, one read each, were 2-4 % slower: twice the LDS instructions, whose random accesses
+    // collide on banks.)  That of long codes lies in front of the streams, as long as the launch's widest tensor needs.
+    __shared__ __align__(16) uint16_t short_tab[kLong ? 8 : kTableEntries];
+    extern __shared__ __align__(16) uint32_t dynamic_lds[];
+    uint16_t *const tab = kLong ? reinterpret_cast<uint16_t *>(dynamic_lds) : short_tab;
+
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t g = block * kWaves + wave;
+    uint32_t *words = dynamic_lds + (kLong ? long_table_words(long_slots) : 0u) + wave * cap_words * kBundle;
+    if constexpr (kBundle > 1) decode_bundle<kLong, kStores, kKind, kBundle>(t, g, tab, words, cap_words, long_slots);
+    else if (g < t.n_streams) decode_stream<kLong, kStores, kKind>(t, g, tab, words, cap_words, long_slots);
+}
+
+template <bool kLong, int kWaves, Stores kStores, Kind kKind, int kBundle, class Args>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, kBundle > 1 ? bundle_waves(kKind, kLong) : most_waves(kKind, kLong)))) zm_decode_kernel(const Args P)
 {
     uint32_t block;
     const Task t = task_of(P, threadIdx.x & 63u, block);
@@ -779,11 +926,11 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
     // chunk-table entry read at once, the look-up table asked for before the stream, and no division).
     asm volatile("" :: "s"(t.lut), "s"(t.sm), "s"(t.echunks), "s"(t.table), "s"(t.out), "s"(t.e_offset), "s"(t.e_size), "s"(t.stream_values),
                        "s"(t.streams_per_chunk), "s"(t.per_chunk), "s"(t.n_streams), "s"(t.last_values), "s"(t.code), "s"(cap_words), "s"(long_slots));
-    decode_block<kLong, kWaves, kStores, kKind>(t, block, cap_words, long_slots);
+    decode_block<kLong, kWaves, kStores, kKind, kBundle>(t, block, cap_words, long_slots);
 }
 
-template <bool kLong, int kWaves, Stores kStores, Kind kKind>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, most_waves(kKind, kLong)))) zm_decode_few_kernel(const Few P)
+template <bool kLong, int kWaves, Stores kStores, Kind kKind, int kBundle>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, kBundle > 1 ? bundle_waves(kKind, kLong) : most_waves(kKind, kLong)))) zm_decode_few_kernel(const Few P)
 {
     const uint32_t k = blockIdx.y;
     const uint32_t code = P.lead[0], n_streams = P.lead[1], last_lut = P.lead[2], table_offset = P.lead[3], sm_units = P.lead[4], e_at = P.lead[5];
@@ -797,7 +944,7 @@ __global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_e
     const Task t{blob + (last_lut >> 16), blob + static_cast<uint64_t>(sm_units) * 256u, blob + e_offset, reinterpret_cast<const uint64_t *>(blob + table_offset),
                  out + static_cast<uint64_t>(to_out) * 8u, e_offset, static_cast<uint64_t>(e_units) * 256u, W, 1u << shift, 1u << 31, n_streams,
                  last_lut & 0xffffu, max_len | shift << 4 | quantum << 9};
-    decode_block<kLong, kWaves, kStores, kKind>(t, blockIdx.x, stream_cap_words(W, kLong ? ZM_MAX_CODE_LEN : 8u, quantum), long_slots);
+    decode_block<kLong, kWaves, kStores, kKind, kBundle>(t, blockIdx.x, stream_cap_words(W, kLong ? ZM_MAX_CODE_LEN : 8u, quantum), long_slots);
 }
 
 // Stand-alone tensor recovery (Sec. 3.3): lane j merges values 8j..8j+7 of its wave's tiles -- per tile a 64-bit load from each
@@ -871,6 +1018,12 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // five / six at 48 MiB: 14.0 / 14.4 / 14.7 / 14.5), and these keep ordinary stores.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
+// How a launch writes, for the caller's policy.
+Stores stores_of(int policy, const Streams &s)
+{
+    return policy == ZM_STORES_STREAMING || (policy == ZM_STORES_AUTO && s.out_bytes() > kLastLevelCacheBytes) ? kStreaming : kThrough;
+}
+
 // Where the shapes of a call's launches go when they are asked for instead of launched.
 struct Recorder {
     zm_launch_shape *out;
@@ -880,6 +1033,7 @@ struct Recorder {
 
 // What a launch needs to know beside its kernel arguments.
 struct Plan {
+    Bundle bundle;
     dim3 grid;
     uint32_t n_tasks;
     size_t lds;              // dynamic part: the streams
@@ -890,41 +1044,57 @@ struct Plan {
 };
 
 // args: an Args, or something that begins like one
-template <bool kLong, int kWaves, Stores kStores, Kind kKind, class Args>
+template <bool kLong, int kWaves, Stores kStores, Kind kKind, int kBundle, class Args>
 int launch_kernel(void *args, const Plan &p)
 {
     void *argv[] = {args};
     const void *fn;
-    if constexpr (std::is_same<Args, Few>::value) fn = reinterpret_cast<const void *>(&zm_decode_few_kernel<kLong, kWaves, kStores, kKind>);
-    else fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, kKind, Args>);
+    if constexpr (std::is_same<Args, Few>::value) fn = reinterpret_cast<const void *>(&zm_decode_few_kernel<kLong, kWaves, kStores, kKind, kBundle>);
+    else fn = reinterpret_cast<const void *>(&zm_decode_kernel<kLong, kWaves, kStores, kKind, kBundle, Args>);
     // the launch's own status: an error left behind by an earlier, unrelated call is not this call's
     return hipLaunchKernel(fn, p.grid, dim3(64 * kWaves), argv, p.lds, p.stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
 }
 
-template <bool kLong, int kWaves, Kind kKind, class Args>
+template <bool kLong, int kWaves, Kind kKind, class Args, int kBundle = 1>
 int launch_stores(void *args, const Plan &p, Stores kind)
 {
-    if constexpr (kKind == kFitting && !kLong)
+    if constexpr (kKind == kFitting && !kLong && kBundle == 1)
         if (kind == kThrough && p.streams.out_bytes() > kThroughBytes && p.streams.one_group == p.streams.n && p.streams.n <= kManyStreams)
-            return launch_kernel<kLong, kWaves, kOrdinary, kKind, Args>(args, p);
+            return launch_kernel<kLong, kWaves, kOrdinary, kKind, 1, Args>(args, p);
     if constexpr (kKind != kSparse)
-        if (kind == kStreaming) return launch_kernel<kLong, kWaves, kStreaming, kKind, Args>(args, p);
-    return launch_kernel<kLong, kWaves, kThrough, kKind, Args>(args, p);
+        if (kind == kStreaming) return launch_kernel<kLong, kWaves, kStreaming, kKind, kBundle, Args>(args, p);
+    return launch_kernel<kLong, kWaves, kThrough, kKind, kBundle, Args>(args, p);
+}
+
+// What bundle_of answers.
+template <bool kLong, class Args>
+int launch_bundles(void *args, const Plan &p, Stores kind)
+{
+    const bool many = p.bundle.kind == kMany;
+    if (p.bundle.streams == 8u) return launch_stores<kLong, 2, kLong ? kMany : kFitting, Args, 8>(args, p, kind);
+    if (p.bundle.streams == 4u) {
+        if constexpr (kLong)
+            if (many) return launch_stores<kLong, 2, kMany, Args, 4>(args, p, kind);
+        return launch_stores<kLong, 2, kFitting, Args, 4>(args, p, kind);
+    }
+    if (!many) return launch_stores<kLong, 2, kFitting, Args, 2>(args, p, kind);
+    if constexpr (kLong) return launch_stores<kLong, 2, kMany, Args, 2>(args, p, kind);
+    else return launch_kernel<kLong, 2, kThrough, kMany, 2, Args>(args, p);
 }
 
 template <bool kLong, int kWaves, class Args>
 int launch_args(void *args, const Plan &p)
 {
-    const bool streaming = p.stores == ZM_STORES_STREAMING || (p.stores == ZM_STORES_AUTO && p.streams.out_bytes() > kLastLevelCacheBytes);
+    const Stores kind = stores_of(p.stores, p.streams);
     if (p.rec) {
         if (p.rec->n < p.rec->cap)
-            p.rec->out[p.rec->n] = zm_launch_shape{kLong ? 2u : 4u, static_cast<uint32_t>(kWaves), streaming ? 1u : 0u, p.grid.x,
+            p.rec->out[p.rec->n] = zm_launch_shape{kLong ? 2u : 4u, static_cast<uint32_t>(kWaves), kind == kStreaming ? 1u : 0u, p.grid.x,
                                                    p.n_tasks, static_cast<uint32_t>(p.lds + kStaticLds<kLong>)};
         ++p.rec->n;
         return ZM_OK;
     }
-    const Stores kind = streaming ? kStreaming : kThrough;
     if constexpr (kWaves == 2) {
+        if (p.bundle.streams > 1) return launch_bundles<kLong, Args>(args, p, kind);
         switch (kind_of(kLong, p.streams, kind)) {
         case kShortStreams: return launch_stores<kLong, kWaves, kShortStreams, Args>(args, p, kind);
         case kSparse: return launch_stores<kLong, kWaves, kSparse, Args>(args, p, kind);
@@ -954,20 +1124,22 @@ bool number_through(uint64_t useful, uint64_t started)
 template <bool kLong, int kWaves, int N>
 int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream, Recorder *rec)
 {
-    const size_t streams = 4 * kWaves * cap, lds = streams + (kLong ? 4 * long_table_words(L.long_slots) : 0);   // dynamic part
+    const size_t streams = 4 * kWaves * cap, table = kLong ? 4 * long_table_words(L.long_slots) : 0;
     if (streams + kBesideStreams<kLong> > kLdsLimit) {
         if constexpr (kWaves > 1) return launch_tasks<kLong, kWaves / 2>(L, cap, stores, stream, rec);
         else return ZM_E_ARG;                   // stream too long to stage in LDS
     }
+    Streams streams_of;
+    for (uint32_t k = 0; k < L.n_tasks; ++k) streams_of.add(L.task[k].stream_values, L.task[k].n_streams, L.task[k].last_values, L.task[k].e_size);
+    const Bundle bundle = kWaves == 2 ? bundle_of(kLong, streams_of, stores_of(stores, streams_of)) : Bundle{1u, kShortStreams};
+    const size_t lds = streams * bundle.streams + table;       // dynamic part
     uint32_t blocks = 0;            // of the largest tensor
     uint64_t total = 0;
-    Streams streams_of;
     for (uint32_t k = 0; k < L.n_tasks; ++k) {
-        const uint32_t b = (L.task[k].n_streams + kWaves - 1) / kWaves;
+        const uint32_t b = (waves_of(L.task[k].n_streams, L.task[k].last_values, bundle.streams) + kWaves - 1) / kWaves;
         L.first_block[k] = static_cast<uint32_t>(total);
         blocks = b > blocks ? b : blocks;
         total += b;
-        streams_of.add(L.task[k].stream_values, L.task[k].n_streams, L.task[k].last_values, L.task[k].e_size);
     }
     if (!blocks) return ZM_OK;
     // without the workgroup numbers the arguments are the same up to the end of the tasks
@@ -976,8 +1148,8 @@ int launch_tasks(Launch<N, true> &L, size_t cap, int stores, hipStream_t stream,
     static_assert(offsetof(Through, task) == offsetof(Rows, task) && sizeof(Rows) <= sizeof(Through));
     // a launch admits 2^32 - 1 threads in x
     if (total <= UINT32_MAX / (64u * kWaves) && number_through(total, static_cast<uint64_t>(blocks) * L.n_tasks))
-        return launch_args<kLong, kWaves, Through>(&L, Plan{dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, streams_of, stores, stream, rec});
-    return launch_args<kLong, kWaves, Rows>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, lds, streams_of, stores, stream, rec});
+        return launch_args<kLong, kWaves, Through>(&L, Plan{bundle, dim3(static_cast<uint32_t>(total)), L.n_tasks, lds, streams_of, stores, stream, rec});
+    return launch_args<kLong, kWaves, Rows>(&L, Plan{bundle, dim3(blocks, L.n_tasks), L.n_tasks, lds, streams_of, stores, stream, rec});
 }
 
 // Collects the tensors of one round length and launches them.
@@ -1108,7 +1280,8 @@ struct Group {
         Streams streams_of;
         for (int k = 0; k < n; ++k) streams_of.add(W, t[k].n_streams, t[k].last_values, t[k].e_size);
         auto plan = [&](uint32_t waves) {
-            return Plan{dim3((t[0].n_streams + waves - 1) / waves, static_cast<uint32_t>(n)), static_cast<uint32_t>(n), 4 * waves * words + table, streams_of, stores, stream, rec};
+            const Bundle bundle = waves == 2 ? bundle_of(kLong, streams_of, stores_of(stores, streams_of)) : Bundle{1u, kShortStreams};
+            return Plan{bundle, dim3((waves_of(t[0].n_streams, t[0].last_values, bundle.streams) + waves - 1) / waves, static_cast<uint32_t>(n)), static_cast<uint32_t>(n), 4 * waves * bundle.streams * words + table, streams_of, stores, stream, rec};
         };
         if (8 * words + kBesideStreams<kLong> <= kLdsLimit) rc = launch_args<kLong, 2, Few>(&F, plan(2));
         else if (4 * words + kBesideStreams<kLong> <= kLdsLimit) rc = launch_args<kLong, 1, Few>(&F, plan(1));
@@ -1166,20 +1339,24 @@ struct Group {
         for (int at = 0; at < n; at += static_cast<int>(L.n_tasks)) {
             L.n_tasks = static_cast<uint32_t>(n - at < each ? n - at : each);
             uint32_t blocks = 0, count[kMaxShapes] = {}, raw[kMaxShapes] = {};
+            uint64_t e_bytes[kMaxShapes] = {};
             for (uint32_t k = 0; k < L.n_tasks; ++k) {
                 L.task[k] = packed[at + static_cast<int>(k)];
                 const uint32_t of = L.task[k].high >> 12 & (kMaxShapes - 1u);
+                const uint64_t e_size = static_cast<uint64_t>(L.task[k].e_units) * 256u;
                 ++count[of];
-                raw[of] += Streams::is_raw(static_cast<uint64_t>(L.task[k].e_units) * 256u, n_values[of]);
+                raw[of] += Streams::is_raw(e_size, n_values[of]);
+                e_bytes[of] += e_size;
             }
             Streams streams_of;
+            for (uint32_t k = 0; k < n_shapes; ++k)
+                if (count[k]) streams_of.add(shape[k].stream_values, shape[k].n_streams, n_values[k], count[k], raw[k], e_bytes[k]);
+            const Bundle bundle = bundle_of(kLong, streams_of, stores_of(stores, streams_of));
             for (uint32_t k = 0; k < n_shapes; ++k) {
-                if (!count[k]) continue;
-                const uint32_t b = (shape[k].n_streams + 1u) / 2u;
-                blocks = b > blocks ? b : blocks;
-                streams_of.add(shape[k].stream_values, shape[k].n_streams, n_values[k], count[k], raw[k]);
+                const uint32_t b = (waves_of(shape[k].n_streams, shape[k].last_values, bundle.streams) + 1u) / 2u;
+                if (count[k]) blocks = b > blocks ? b : blocks;
             }
-            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{dim3(blocks, L.n_tasks), L.n_tasks, 8 * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), streams_of, stores, stream, rec});
+            const int rc = launch_args<kLong, 2, PackedLaunch>(&L, Plan{bundle, dim3(blocks, L.n_tasks), L.n_tasks, 8 * bundle.streams * cap + (kLong ? 4 * long_table_words(L.long_slots) : 0), streams_of, stores, stream, rec});
             if (rc != ZM_OK) return rc;
         }
         return ZM_OK;

@@ -37,9 +37,10 @@ struct Streams {
     uint64_t n = 0;
     uint64_t one_group = 0, in_groups = 0;       // of tensors whose streams are one whole group of tiles, and several
     uint64_t values = 0, raw_values = 0;         // values, and those of tensors that are stored raw
-    uint32_t longest = 0;                        // values of the longest stream
+    uint64_t e_bytes = 0;                        // in the E-chunk regions
+    uint32_t longest = 0, shortest = ~0u;        // values of the longest and the shortest kind of stream
     // tensors cut alike, `raw` of them stored raw
-    void add(uint32_t stream_values, uint32_t n_streams, uint64_t n_values, uint32_t tensors, uint32_t raw)
+    void add(uint32_t stream_values, uint32_t n_streams, uint64_t n_values, uint32_t tensors, uint32_t raw, uint64_t e_size)
     {
         const uint64_t streams = static_cast<uint64_t>(tensors) * n_streams;
         n += streams;
@@ -47,12 +48,14 @@ struct Streams {
         in_groups += stream_values > kGroupValues && stream_values % kGroupValues == 0 ? streams : 0u;
         values += tensors * n_values;
         raw_values += raw * n_values;
+        e_bytes += e_size;
         longest = longest > stream_values ? longest : stream_values;
+        shortest = shortest < stream_values ? shortest : stream_values;
     }
     void add(uint32_t stream_values, uint32_t n_streams, uint32_t last_values, uint64_t e_size)
     {
         const uint64_t n_values = values_of(stream_values, n_streams, last_values);
-        add(stream_values, n_streams, n_values, 1u, is_raw(e_size, n_values));
+        add(stream_values, n_streams, n_values, 1u, is_raw(e_size, n_values), e_size);
     }
     static constexpr uint64_t values_of(uint32_t stream_values, uint32_t n_streams, uint32_t last_values)
     {
@@ -122,4 +125,71 @@ constexpr int pairs_ahead(Kind kind, bool long_codes, Stores stores)
     return kind == kSparse ? (long_codes ? kPairs : 2) : long_codes || (kind == kFitting && stores == kThrough) ? 1 : 2;
 }
 
+// Streams of 512, 1024 and 2048 values, all of a launch cut alike: whether a wave takes eight tiles of them, and the kind of kernel that does it
+// (kFitting or kMany; streams == 1: it does not).
+struct Bundle {
+    uint32_t streams;
+    Kind kind;
+};
+
+// us, three tensors, a wave per stream / bundles as kFitting / as kMany; cached: three sets in turn, device-scope stores; else nothing cached.
+//   short codes, streams        cached                 dev                    nt
+//     512:   8000                4.9 /  5.0 /  4.9      6.3 /  6.6 /  6.6      6.2 /  6.3 /  6.4
+//            9000                5.4 /  5.2 /  5.2      7.0 /  6.9 /  6.9      6.7 /  6.6 /  6.6
+//           24000               10.3 /  8.4 /  8.2     12.9 / 10.5 / 10.5     12.5 /  9.6 / 10.0
+//           98304               45.1 / 34.3            45.0 / 34.4            42.5 / 32.4
+//    1024:   8000                6.1 /  6.2 /  6.2      8.4 /  8.6 /  8.6      8.3 /  7.2 /  8.5
+//           12000                8.6 /  8.2 /  8.2     10.6 / 10.1 / 10.0     10.6 /  9.1 / 10.0
+//           18000               11.6 / 11.8 / 11.8     14.5 / 15.2 / 15.3     13.9 / 13.9 / 14.7
+//           50000               32.0 / 34.2 / 33.9     32.1 / 34.3 / 34.1     31.5 / 32.4 / 33.1
+//    2048:   4500                6.7 /  7.0 /  7.0      9.7 /  9.2 /  9.2      7.8 /  7.9 /  9.3
+//            6000                8.1 /  8.2 /  8.2     11.1 / 10.0 /  9.9      9.8 /  9.0 /  9.9
+//            8000               10.4 /  9.8 / 11.2     14.1 / 12.8 / 13.7     11.9 / 10.6 / 12.3
+//           12000               14.4 / 15.0 / 14.2     18.9 / 18.4 / 17.8     17.3 / 17.6 / 17.1
+//           24000               32.0 / 31.9 / 31.1     32.0 / 31.9 / 31.1     30.5 / 31.0 / 30.6
+//   long codes
+//     512:   8000                5.9 /  5.9 /  5.9      7.3 /  7.1 /  7.1      6.9 /  7.1 /  7.0
+//           24000               12.7 /  9.5 /  9.0     14.8 / 11.3 / 11.0     14.1 / 11.7 / 10.7
+//    1024:   6000                6.2 /  6.6 /  6.6      7.8 /  8.1 /  8.1      7.4 /  7.6 /  8.0
+//            8000                7.4 /  6.9 /  6.9     10.0 /  8.8 /  8.8      9.4 /  8.0 /  8.8
+//           16000               11.9 / 10.0 / 11.2     14.9 / 13.7 / 14.5     13.4 / 12.1 / 12.8
+//           24000               16.1 / 15.2 / 14.9     19.8 / 19.4 / 18.5     19.3 / 19.2 / 18.0
+//    2048:   3000                6.7 /  7.1 /  7.0      8.9 /  8.8 /  8.8      7.6 /  7.9 /  8.4
+//            4500                7.9 /  8.2 /  8.1     11.4 / 10.0 /  9.9     10.1 /  9.2 /  9.8
+//            8000               11.1 / 10.3 / 11.8     16.0 / 14.1 / 14.7     13.0 / 12.1 / 12.9
+//           24000               36.7 / 33.6 / 32.7     36.3 / 33.4 / 32.4     33.2 / 32.3 / 31.7
+// So waves of one stream stay where all of them find places, and for short codes in large launches where they are bound by the memory
+// already; device-scope stores of few streams that stay cached decide where the lines lie, though cold ones would gain earlier.  Raw streams are not bundled, nor dense ones of more than a kilobyte, nor what has no room for its streams at all.
+inline Bundle bundle_of(bool long_codes, const Streams &s, Stores stores)
+{
+    const Bundle none{1u, kShortStreams};
+    if (s.shortest != s.longest || 2 * s.raw_values > s.values || s.e_bytes > 1024 * s.n || s.e_bytes < 80 * s.n) return none;
+    const bool streaming = stores == kStreaming;
+    switch (s.longest) {
+    case 512u: return s.n > 8 * kSimds ? Bundle{8u, long_codes ? kMany : kFitting} : none;
+    case 1024u:
+        if (s.n <= (long_codes ? 7 : streaming ? 8 : 10) * kSimds) return none;
+        return s.n <= 16 * kSimds ? Bundle{4u, kFitting} : long_codes ? Bundle{4u, kMany} : none;
+    case 2048u:
+        if (s.n <= (!streaming ? 6 : long_codes ? 4 : 5) * kSimds) return none;
+        return s.n <= 9 * kSimds ? Bundle{2u, kFitting} : long_codes || !streaming ? Bundle{2u, kMany} : none;
+    default: return none;
+    }
+}
+
+constexpr int bundle_waves(Kind kind, bool long_codes) { return kind == kMany ? 3 : long_codes ? 5 : 6; }
+// Tiles whose sign-mantissa bytes are asked for before the first is decoded.  Bundles of short codes as kFitting, nt, with eight / four: 12000 streams of 1024
+// values 9.1 / 10.0 us; dev 10.5 / 10.1.
+constexpr uint32_t bundle_ahead(Kind kind, Stores stores) { return kind == kFitting && stores == kStreaming ? 8u : 4u; }
+
+// Whole bundles of a tensor: none holds a stream that is cut off.
+constexpr uint32_t whole_bundles(uint32_t n_streams, uint32_t last_values, uint32_t bundle)
+{
+    return (n_streams - (last_values % (kGroupValues / bundle) ? 1u : 0u)) / bundle;
+}
+// Waves that a tensor takes: one for every whole bundle, and for every stream behind them.
+constexpr uint32_t waves_of(uint32_t n_streams, uint32_t last_values, uint32_t bundle)
+{
+    return bundle == 1u ? n_streams : n_streams - whole_bundles(n_streams, last_values, bundle) * (bundle - 1u);
+}
 }  // namespace zipmoe

@@ -778,3 +778,55 @@ def test_streams_that_a_table_places_outside_are_left_alone(W, max_len, damage):
     got = bufs[0].cpu().numpy().view(np.uint16)
     assert np.all(got[C: 2 * C] == GUARD_WORD)
     assert np.array_equal(got[:C], w[:C]) and np.array_equal(got[2 * C: n], w[2 * C:])
+
+
+def bundle_tensor(n, W, max_len, seed):
+    """Gaussian weights with streams that a bundle can not take: a stretch that is stored raw, one that is dense in rare exponents, and lanes whose
+    symbols all have the longest codes"""
+    rng = np.random.default_rng(seed)
+    w = synth.special_tensor("gauss", n, seed).copy()
+
+    def rare(at, count):
+        at = max(0, min(at, n - count))
+        w[at: at + count] = (rng.integers(0x90, 0xa8, count).astype(np.uint16) << 7) | (w[at: at + count] & 0x807F)
+
+    for k in range(5):
+        rare((n * (k + 1) // 7) // 8 * 8, 8)
+    rare(n // 3 // W * W + W // 2, min(W // 2, n // 64))
+    if n > 256 * W:
+        rare(n // 2 // (4 * W) * 4 * W, 4 * W)
+    return w
+
+
+@pytest.mark.parametrize("count,ragged,stores", [(1, False, zm.STORES_CACHED), (7, True, zm.STORES_STREAMING), (60, False, zm.STORES_CACHED)])
+@pytest.mark.parametrize("W,max_len,streams", [(512, 8, 8192), (512, 8, 8193), (512, 12, 8193), (1024, 8, 10241), (1024, 8, 16385), (1024, 12, 7169), (1024, 12, 16385),
+                                               (2048, 8, 6145), (2048, 8, 9217), (2048, 12, 6145), (2048, 12, 9217)])
+def test_waves_that_take_several_short_streams(W, max_len, streams, count, ragged, stores):
+    """at the lines from which on they do: tensors of no whole bundle and a cut-off last stream, with streams in between that go one by one; whole
+    blobs alike, tensors of very different lengths, many in a launch; and what a damaged chunk table places outside stays as it was"""
+    import torch
+    lengths = [max(1, (streams // (2 ** k if k else 1)) // 2) for k in range(count)] if ragged else [-(-streams // count)] * count
+    lengths[0] += max(0, streams - sum(lengths))
+    tensors = [[bundle_tensor(s * W - (5 if k % 2 or count == 1 else 0), W, max_len, seed=k % 3)] for k, s in enumerate(lengths)]
+    flat, blobs, got, shapes = layer_calls(tensors, 4 * W, W, max_len, stores)
+    assert {int(zm.blob_info(b).max_len > 8) for b in blobs} == {int(max_len > 8)} and len(shapes) == (1 if count < 60 else len(shapes))
+    assert count == 60 or set(chunk_modes(blobs[0])) == {0, 1}
+    for a, g in zip(flat, got):
+        assert np.array_equal(g, a)
+    assert np.array_equal(got[-1], zo.decode(blobs[-1]))
+    if count > 1:
+        return
+    blob, (w,) = blobs[0].copy(), flat
+    info = zm.blob_info(blob)
+    at = info.table_offset + info.table_stride * 5
+    assert chunk_modes(blob)[5] == 0
+    blob[at + 12: at + 16] = np.array([(1 << 32) - 16], "<u4").view(np.uint8)         # the first two streams of chunk 5
+    layer = zm.ExpertLayer([[blob]], validate=False)
+    bufs, starts, _ = layer.alloc_outputs(1)
+    bufs[0].fill_(GUARD_WORD)
+    layer.decode([0], bufs, starts, torch.cuda.current_stream().cuda_stream, stores)
+    torch.cuda.synchronize()
+    back, lost = bufs[0].cpu().numpy().view(np.uint16)[: w.size], slice(20 * W, 22 * W)
+    assert np.all(back[lost] == GUARD_WORD)
+    back[lost] = w[lost]
+    assert np.array_equal(back, w)
