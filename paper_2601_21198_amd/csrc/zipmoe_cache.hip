@@ -15,10 +15,11 @@
 //             unless it is in F, C or S; E-chunks unless it is in F, C or E;
 //             decompression unless it is in F.
 //
-// On MI355X the tier below HBM is (pinned) host memory.  Copies run on a stream
-// of their own and overlap the decode of the experts that need none; the decode
-// itself is zm_decode_tensors.  Where the host memory is mapped for the device, as
-// pinned memory is, one kernel fetches all missing parts of a call.
+// On MI355X the tier below HBM is (pinned) host memory; the decode itself is
+// zm_decode_tensors.  Where the host memory is mapped for the device, as pinned
+// memory is, one kernel fetches all missing parts of a call, on the caller's stream
+// in front of one decode launch.  Copies of other memory, and fetches beside which
+// there is much to decode, run on a stream of their own.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -128,14 +129,25 @@ __global__ void __launch_bounds__(256) zm_cache_fetch_kernel(const Parts P)
     }
 }
 
-int fetch_parts(Parts &parts, hipStream_t stream)
+int fetch_parts(const Part *part, size_t n, hipStream_t stream)
 {
-    if (parts.n_parts == 0) return ZM_OK;
-    void *args[] = {&parts};
-    const hipError_t rc = hipLaunchKernel(reinterpret_cast<const void *>(&zm_cache_fetch_kernel), dim3(kFetchBlocks), dim3(256), args, 0, stream);
-    parts.n_parts = 0;
-    return rc == hipSuccess ? ZM_OK : ZM_E_HIP;
+    for (size_t at = 0; at < n; at += kMaxParts) {
+        Parts parts;
+        parts.n_parts = static_cast<uint32_t>(std::min<size_t>(n - at, kMaxParts));
+        std::copy(part + at, part + at + parts.n_parts, parts.part);
+        void *args[] = {&parts};
+        if (hipLaunchKernel(reinterpret_cast<const void *>(&zm_cache_fetch_kernel), dim3(kFetchBlocks), dim3(256), args, 0, stream) != hipSuccess) return ZM_E_HIP;
+    }
+    return ZM_OK;
 }
+
+// bf16 bytes of the experts that need no copy from which on they are decoded beside the fetch, whose kernel then has a stream of its own.  Handing over to
+// that stream and back costs 10 to 15 us on the GPU; the decode, while the host link is busy, takes up to four times as long as by itself.  us per
+// fetch, beside / behind each other, one expert of 1024 x 2048 x 3 missing:
+//   MiB decoded beside    0.75 (128 x 512)    3 (256 x 1024)    12            24            48              84              144
+//                         21.4 /  9.9         43.2 / 30.0       51.7 / 47.0   94.1 / 87.4   179.6 / 170.3   180.2 / 179.4   180.5 / 197.8
+// experts of 4096 x 4096 x 3: 96 MiB 650.8 / 646.5, 288 MiB 1243 / 1286.
+constexpr uint64_t kDecodeBeside = 64ull << 20;
 
 // Host memory that a kernel may read, asked for range by range: what has been found mapped stays known until the object
 // goes, which is to be within one call, since the caller may unmap and map his memory between calls.
@@ -204,6 +216,9 @@ struct zm_cache {
     // work lists of a fetch (sized at creation for max_selected experts; a fetch is not re-entrant anyway)
     struct Plan { int expert, found, target, slot; };
     std::vector<Plan> plan;
+    struct Move { uint8_t *dst; const uint8_t *src; size_t bytes; };
+    std::vector<Part> fetched;                 // parts that the kernel reads from the host
+    std::vector<Move> moved;                   // and parts that change pool
     std::vector<zm_tensor_parts> parts_now, parts_later;
     std::vector<zm_tensor_info> infos_now, infos_later;
     std::vector<void *> out_now, out_later;
@@ -288,6 +303,7 @@ int zm_cache_create(const zm_cache_config *config, const void *const *host_blobs
         c->count.assign(config->n_experts, 0);
         const size_t most = static_cast<size_t>(config->max_selected) * config->tensors_per_expert;
         c->plan.resize(config->max_selected);
+        c->fetched.reserve(2 * most); c->moved.reserve(2 * most);
         c->parts_now.resize(most); c->parts_later.resize(most);
         c->infos_now.resize(most); c->infos_later.resize(most);
         c->out_now.resize(most); c->out_later.resize(most);
@@ -321,6 +337,8 @@ int zm_cache_create(const zm_cache_config *config, const void *const *host_blobs
 void zm_cache_destroy(zm_cache *c)
 {
     if (!c) return;
+    // what was fetched on a caller's stream is waited for through its event
+    if (c->copy_stream && c->ev_copied && hipStreamWaitEvent(c->copy_stream, c->ev_copied, 0) != hipSuccess) (void)hipGetLastError();
     if (c->copy_stream) { (void)hipStreamSynchronize(c->copy_stream); (void)hipStreamDestroy(c->copy_stream); }
     if (c->ev_start) (void)hipEventDestroy(c->ev_start);
     if (c->ev_copied) (void)hipEventDestroy(c->ev_copied);
@@ -360,21 +378,20 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
                    ? ZM_OK : ZM_E_HIP;
     };
     // a part that comes from the host: `bytes` of it at `offset` of image or blob number `i`
-    Parts parts;
-    parts.n_parts = 0;
+    c->fetched.clear();
+    c->moved.clear();
     Mapped mapped;
     auto from_host = [&](uint8_t *dst, const std::vector<const uint8_t *> &host, size_t i, size_t offset, size_t bytes) -> int {
-        if (begin_copies() != ZM_OK) return ZM_E_HIP;
         const uint8_t *src = host[i] + offset;
         // the kernel moves whole vectors only
         if (((reinterpret_cast<uintptr_t>(src) | bytes) & 15) || !mapped.covers(src, bytes))
-            return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
-        parts.part[parts.n_parts++] = Part{reinterpret_cast<const u32x4 *>(src), reinterpret_cast<u32x4 *>(dst), bytes / 16};
-        return parts.n_parts == kMaxParts ? fetch_parts(parts, c->copy_stream) : ZM_OK;
+            return begin_copies() == ZM_OK && hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+        c->fetched.push_back(Part{reinterpret_cast<const u32x4 *>(src), reinterpret_cast<u32x4 *>(dst), bytes / 16});
+        return ZM_OK;
     };
-    auto on_device = [&](uint8_t *dst, const uint8_t *src, size_t bytes) -> int {
-        if (begin_copies() != ZM_OK) return ZM_E_HIP;
-        return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->copy_stream) == hipSuccess ? ZM_OK : ZM_E_HIP;
+    auto on_device = [&](uint8_t *dst, const uint8_t *src, size_t bytes) {
+        c->moved.push_back(zm_cache::Move{dst, src, bytes});
+        return ZM_OK;
     };
 
     for (int j = 0; j < n_selected; ++j) ++c->count[expert_ids[j]];
@@ -424,6 +441,7 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
     zm_tensor_info *infos_now = c->infos_now.data(), *infos_later = c->infos_later.data();
     void **out_now = c->out_now.data(), **out_later = c->out_later.data();
     int n_now = 0, n_later = 0;
+    uint64_t values_now = 0;
     for (int j = 0; j < n_selected; ++j) {
         const Plan &pl = plan[j];
         const int e = pl.expert;
@@ -491,16 +509,29 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
             pt.echunks = e_dst ? e_dst : e_src;
             out = keep_full ? keep_full + c->lay.full_off[m] : tr_full + c->lay.full_off[m];
             if (copied) { parts_later[n_later] = pt; infos_later[n_later] = ti; out_later[n_later++] = out; }
-            else { parts_now[n_now] = pt; infos_now[n_now] = ti; out_now[n_now++] = out; }
+            else { parts_now[n_now] = pt; infos_now[n_now] = ti; out_now[n_now++] = out; values_now += ti.n_values; }
         }
     }
-    // experts whose parts are all resident decode while the copies for the others are in flight
-    int rc = fetch_parts(parts, c->copy_stream);
-    if (rc == ZM_OK) rc = zm_decode_tensors(parts_now, infos_now, n_now, out_now, stream);
-    if (rc == ZM_OK && any_copy) {
-        if (hipEventRecord(c->ev_copied, c->copy_stream) != hipSuccess ||
-            hipStreamWaitEvent(main_stream, c->ev_copied, 0) != hipSuccess) rc = ZM_E_HIP;
-        else rc = zm_decode_tensors(parts_later, infos_later, n_later, out_later, stream);
+    // Where the kernel fetches all that is missing, everything follows on the caller's stream, with one decode launch.  Where something has to be copied,
+    // or there is much to decode meanwhile, copies have a stream of their own.
+    int rc = ZM_OK;
+    const bool any = any_copy || !c->fetched.empty() || !c->moved.empty();
+    if (any && 2 * values_now > kDecodeBeside) rc = begin_copies();
+    hipStream_t copies = any_copy ? c->copy_stream : main_stream;
+    for (const zm_cache::Move &m : c->moved)
+        if (rc == ZM_OK && hipMemcpyAsync(m.dst, m.src, m.bytes, hipMemcpyDeviceToDevice, copies) != hipSuccess) rc = ZM_E_HIP;
+    if (rc == ZM_OK) rc = fetch_parts(c->fetched.data(), c->fetched.size(), copies);
+    if (any_copy) {
+        if (rc == ZM_OK) rc = zm_decode_tensors(parts_now, infos_now, n_now, out_now, stream);
+        if (rc == ZM_OK && (hipEventRecord(c->ev_copied, c->copy_stream) != hipSuccess || hipStreamWaitEvent(main_stream, c->ev_copied, 0) != hipSuccess)) rc = ZM_E_HIP;
+        if (rc == ZM_OK) rc = zm_decode_tensors(parts_later, infos_later, n_later, out_later, stream);
+    } else {
+        std::copy(parts_later, parts_later + n_later, parts_now + n_now);
+        std::copy(infos_later, infos_later + n_later, infos_now + n_now);
+        std::copy(out_later, out_later + n_later, out_now + n_now);
+        if (rc == ZM_OK) rc = zm_decode_tensors(parts_now, infos_now, n_now + n_later, out_now, stream);
+        // zm_cache_destroy waits for it: until then the kernel may read the host's memory
+        if (rc == ZM_OK && any && hipEventRecord(c->ev_copied, main_stream) != hipSuccess) rc = ZM_E_HIP;
     }
     if (rc != ZM_OK) c->broken = true;
     return rc;

@@ -204,3 +204,26 @@ def test_a_fetch_can_be_captured_and_replayed(monkeypatch, packed, pinned):
             for m, n in enumerate(shapes):
                 assert np.array_equal(read_back(cache, ptrs[j][m], n), tensors[e][m]), (e, m)
     cache.close()
+
+
+def test_fetches_beside_and_in_front_of_the_decode():
+    """with 64 MiB or more to decode meanwhile a fetch has a stream of its own, else it lies in front of the decode; in turn, with nothing but the stream
+    between them, parts that change pool included, and the cache destroyed while the last fetch may be on its way"""
+    import torch
+    n = 6 << 20
+    tensors, blobs = make_layer(8, (n,), seed=5)
+    cache = zm.ExpertCache(blobs, (0, 6, 1, 0), 0, max_selected=7)
+    stream = torch.cuda.current_stream().cuda_stream
+    saved = []
+    for ids in ([0, 1, 2, 3, 4, 5], [0, 1, 2, 3, 4, 5], [0, 1, 2, 3, 4, 5, 6], [0, 1, 7], [0, 1, 2, 3, 4, 5, 7], [6, 5], [6], [6, 0, 1, 2, 3, 4, 7], [7, 0]):
+        ptrs, _ = cache.fetch(ids, stream)
+        for j, e in enumerate(ids):
+            off = ptrs[j][0] - cache.arena.data_ptr()
+            saved.append((e, cache.arena[off: off + 2 * n].clone()))
+    arena, host = cache.arena, cache.host                # outlive the cache
+    cache.close()
+    torch.cuda.synchronize()
+    want = [torch.from_numpy(t[0].view(np.uint8)).cuda() for t in tensors]
+    for e, got in saved:
+        assert torch.equal(got, want[e]), e
+    del arena, host
