@@ -1,4 +1,4 @@
-"""ctypes binding of libzipmoe (include/zipmoe.h): argument marshalling only.
+"""Binding of libzipmoe (include/zipmoe.h): argument marshalling only, by ctypes and, for the hot calls, by an extension module.
 
 Every step of the decode path runs in the library's HIP kernels; PyTorch is used
 by callers for device memory and streams.  The library must have been built
@@ -13,7 +13,7 @@ from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
 
-from .build import LIB_PATH
+from .build import LIB_PATH, NATIVE_PATH
 
 OK, E_ARG, E_SIZE, E_FORMAT, E_HIP, E_NOMEM = 0, -1, -2, -3, -4, -5
 MAX_CODE_LEN = 12
@@ -100,13 +100,18 @@ class ZipMoEError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
+_native = None                          # the extension module, and the addresses of the functions that it calls
+_fn = {}
 
 
 def lib() -> ctypes.CDLL:
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2601_21198_amd.build`")
+        if not os.path.exists(NATIVE_PATH):
+            raise ImportError(f"{NATIVE_PATH} is not built; run `python -m paper_2601_21198_amd.build`")
+        from . import _native as native
         L = ctypes.CDLL(LIB_PATH)
         c = ctypes
         u8p, u16p, u64p = c.POINTER(c.c_uint8), c.POINTER(c.c_uint16), c.POINTER(c.c_uint64)
@@ -167,6 +172,9 @@ def lib() -> ctypes.CDLL:
         for name in EXPORTS:
             if name not in ("zm_strerror", "zm_encode_bound", "zm_cache_destroy", "zm_layer_destroy"):
                 getattr(L, name).restype = c.c_int
+        for name in ("zm_decode_experts_stores", "zm_layer_decode", "zm_recover"):
+            _fn[name] = c.cast(getattr(L, name), c.c_void_p).value
+        _native = native
         _lib = L
     return _lib
 
@@ -279,7 +287,13 @@ def decode_exponents_host(blob, chunk_begin: int = 0, chunk_end: Optional[int] =
 
 def recover(exponents_ptr: int, sign_mantissa_ptr: int, n_values: int, out_ptr: int, stream: int = 0) -> None:
     """zm_recover on device pointers."""
-    _check(lib().zm_recover(ctypes.c_void_p(exponents_ptr), ctypes.c_void_p(sign_mantissa_ptr), n_values,
+    L = _lib or lib()
+    rc = _native.recover(_fn["zm_recover"], exponents_ptr, sign_mantissa_ptr, n_values, out_ptr, stream)
+    if rc == OK:
+        return
+    if rc is not None:
+        raise ZipMoEError(rc, "zm_recover")
+    _check(L.zm_recover(ctypes.c_void_p(exponents_ptr), ctypes.c_void_p(sign_mantissa_ptr), n_values,
                             ctypes.c_void_p(out_ptr), ctypes.c_void_p(stream)), "zm_recover")
 
 
@@ -309,6 +323,10 @@ def decode_host_tensors(host_blobs, infos, n_tensors: int, out_bf16, stream: int
     """zm_decode_host_tensors with ready-made ctypes arrays."""
     _check(lib().zm_decode_host_tensors(host_blobs, infos, n_tensors, out_bf16, ctypes.c_void_p(stream)),
            "zm_decode_host_tensors")
+
+
+def _raise_decode(rc: int) -> None:
+    raise ZipMoEError(rc, "zm_decode_experts_stores")
 
 
 class ExpertLayer:
@@ -350,6 +368,9 @@ class ExpertLayer:
         self._ptr_blobs = ctypes.cast(self.blob_ptrs, ctypes.POINTER(ctypes.c_void_p))
         self._ptr_tables = ctypes.cast(self.table_ptrs, ctypes.POINTER(ctypes.c_void_p))
         self._ptr_infos = ctypes.cast(self.infos, ctypes.POINTER(TensorInfo))
+        self._arrays = (_fn["zm_decode_experts_stores"], ctypes.addressof(self.blob_ptrs), ctypes.addressof(self.table_ptrs),
+                        ctypes.addressof(self.infos), self.n_experts, self.tensors_per_expert)
+        self._decode = _native.Target(*self._arrays).decode
 
     def expert_values(self, expert: int) -> List[int]:
         t = self.tensors_per_expert
@@ -374,6 +395,9 @@ class ExpertLayer:
         # one for every tensor of an expert, or an IndexError (a list, what alloc_outputs returns, is read at once)
         offsets = [2 * s for s in (starts[:t] if type(starts) is list and len(starts) >= t else [starts[m] for m in range(t if bases else 0)])]
         outs = (ctypes.c_void_p * (len(expert_ids) * t))(*[base + o for base in bases for o in offsets])
+        if type(stores) is int and -(1 << 31) <= stores < 1 << 31:
+            return _native.Prepared(*self._arrays, ctypes.addressof(ids), len(expert_ids), ctypes.addressof(outs), stores,
+                                    (ids, outs, out_buffers), (self.blob_ptrs, self.table_ptrs, self.infos), _raise_decode)
         f = (_lib or lib()).zm_decode_experts_stores
         args = (self._ptr_blobs, self._ptr_tables, self._ptr_infos, self.n_experts, t, ids, len(expert_ids), outs, stores)
 
@@ -385,6 +409,11 @@ class ExpertLayer:
         return call
 
     def decode(self, expert_ids, out_buffers, starts, stream: int = 0, stores: int = STORES_AUTO) -> None:
+        rc = self._decode(expert_ids, out_buffers, starts, stream, stores)
+        if rc == OK:
+            return
+        if rc is not None:
+            _raise_decode(rc)
         self.make_call(expert_ids, out_buffers, starts, stores)(stream)
 
 
@@ -415,6 +444,12 @@ class Layer:
 
     def decode(self, expert_ids, out_ptrs, stream: int = 0, stores: int = STORES_AUTO) -> None:
         """out_ptrs: device addresses, one per selected expert and tensor (expert-major)."""
+        if self._handle:
+            rc = _native.layer_decode(_fn["zm_layer_decode"], self._handle.value, expert_ids, out_ptrs, stream, stores)
+            if rc == OK:
+                return
+            if rc is not None:
+                raise ZipMoEError(rc, "zm_layer_decode")
         ids = (ctypes.c_int32 * len(expert_ids))(*[int(e) for e in expert_ids])
         outs = (ctypes.c_void_p * len(out_ptrs))(*[int(p) for p in out_ptrs])
         _check(lib().zm_layer_decode(self._handle, ids, len(expert_ids), outs, stores, ctypes.c_void_p(stream)), "zm_layer_decode")

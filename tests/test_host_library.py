@@ -531,3 +531,48 @@ def test_one_launch_of_many_tensors_only_where_their_lengths_agree(big, small, c
 
     shapes = zm.decode_launch_shapes([tensor(big)] + [tensor(small)] * count)
     assert [(s.tensors, s.workgroups) for s in shapes] == launches
+
+
+def test_calls_of_unusual_types_are_what_they_are_for_usual_ones():
+    """the extension module takes lists of ints and objects with data_ptr, ctypes the rest: same statuses, same errors.  (A layer in host memory; what is
+    asked for is refused before anything is launched.)"""
+    import torch
+    blobs = [[zm.compress(synth.special_tensor("gauss", 600, m), 4096, 4096)[0] for m in range(3)] for _ in range(2)]
+    layer = zm.ExpertLayer(blobs, device="cpu")
+    bufs, starts, _ = layer.alloc_outputs(2)
+    ids = {"list": [0, 2], "tuple": (0, 2), "numpy": np.array([0, 2]), "numpy ints": [np.int64(0), np.int32(2)], "negative": [-1, 0], "wraps": [(1 << 32) + 2, 0]}
+    for what, i in ids.items():
+        for stream in (0, None):
+            with pytest.raises(zm.ZipMoEError) as e:
+                layer.decode(i, bufs, starts, stream)
+            assert e.value.status == zm.E_ARG, what
+            with pytest.raises(zm.ZipMoEError) as e:
+                layer.make_call(i, bufs, starts)(stream)
+            assert e.value.status == zm.E_ARG, what
+    for s in (starts, tuple(starts), dict(enumerate(starts))):
+        with pytest.raises(zm.ZipMoEError):
+            layer.decode([0, 2], bufs, s)
+        with pytest.raises(zm.ZipMoEError):                       # a store policy that there is not, an output that is missing
+            layer.decode([0, 1], bufs, s, stores=7)
+        with pytest.raises(zm.ZipMoEError):
+            layer.decode([0, 1], bufs[:1], s)
+    for call in (lambda: layer.decode([0], bufs, starts), lambda: layer.decode([0, 1], bufs, starts[:2]), lambda: layer.make_call([0], bufs, starts)):
+        with pytest.raises(IndexError):
+            call()
+    with pytest.raises(AttributeError):
+        layer.decode([0, 1], [1, 2], starts)
+    for bad in ([0.5], "x"):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            layer.make_call([0, 2], bufs, starts)(bad)
+    assert layer.decode([], [], starts) is None and layer.make_call([], [], starts)() is None and layer.make_call([], [], starts)(stream=0) is None
+    call = layer.make_call([0, 2], bufs, starts)
+    call.keepalive[0][1] = 7                                      # the arrays that a call hands over are those that it shows
+    with pytest.raises(zm.ZipMoEError):
+        call()
+    call.note = "kept"
+    assert call.note == "kept" and call.keepalive[2] is bufs
+    for args in ((0, 8, 5, 16), (8, 0, 5, 16), (8, 8, 5, 0), (8, 8, 5, 8), (4, 8, 5, 16)):
+        with pytest.raises(zm.ZipMoEError) as e:
+            zm.recover(*args)
+        assert e.value.status == zm.E_ARG
+    assert zm.recover(0, 0, 0, 0) is None
