@@ -1018,10 +1018,20 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // five / six at 48 MiB: 14.0 / 14.4 / 14.7 / 14.5), and these keep ordinary stores.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
+// From three quarters of the last-level cache on non-temporal stores are ahead whatever the caller does: outputs so large leave the cache before
+// they are read or written again, and push out what is read meanwhile.  us device-scope / non-temporal, experts of 1024 x 2048 x 3 (long codes):
+//   out, MiB                              156                          192                          228                          252
+//   one set                               42.9 / 40.6  (51.6 / 41.7)   52.4 / 49.7  (61.4 / 50.6)   66.3 / 58.7  (72.5 / 60.0)   74.1 / 64.7  (79.4 / 65.9)
+//   inputs from HBM, one output set       41.3 / 46.1  (45.0 / 51.0)   55.8 / 55.5  (60.3 / 61.2)   67.3 / 65.5  (74.0 / 73.0)   74.0 / 72.4  (80.1 / 79.8)
+//   neither cached                        48.1 / 46.1  (51.4 / 50.8)   57.6 / 55.6  (62.3 / 60.8)   67.4 / 65.7  (73.7 / 72.7)   73.7 / 72.0  (80.3 / 79.8)
+//   the same and a product that reads     156.1 / 156.1                190.6 / 190.6                216.8 / 216.9                248.7 / 248.1
+// Experts of 512 x 1024 x 3: one set 159 MiB 44.0 / 41.8, 192 55.3 / 49.9; inputs from HBM 42.0 / 47.8, 58.3 / 56.7.
+constexpr uint64_t kStreamingBytes = kLastLevelCacheBytes / 4 * 3;
+
 // How a launch writes, for the caller's policy.
 Stores stores_of(int policy, const Streams &s)
 {
-    return policy == ZM_STORES_STREAMING || (policy == ZM_STORES_AUTO && s.out_bytes() > kLastLevelCacheBytes) ? kStreaming : kThrough;
+    return policy == ZM_STORES_STREAMING || (policy == ZM_STORES_AUTO && s.out_bytes() >= kStreamingBytes) ? kStreaming : kThrough;
 }
 
 // Where the shapes of a call's launches go when they are asked for instead of launched.

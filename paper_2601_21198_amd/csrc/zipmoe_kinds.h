@@ -20,7 +20,7 @@ constexpr uint64_t kManyStreams = 7 * kSimds;      // that many are at work at a
 // How a wave writes its bf16 words.
 //   kOrdinary   the lines stay dirty in the L2 caches; what is left of them is written back when the kernel ends
 //   kThrough    device-scope stores: the L2 caches keep the line and pass it on to the last-level cache at once
-//   kStreaming  non-temporal: the output is larger than the last-level cache, or the caller said that its buffers are
+//   kStreaming  non-temporal: the output fills most of the last-level cache, or the caller said that its buffers are
 //               not cache-resident
 enum Stores { kOrdinary, kThrough, kStreaming };
 
