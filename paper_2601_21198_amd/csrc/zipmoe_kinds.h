@@ -166,7 +166,7 @@ inline Bundle bundle_of(bool long_codes, const Streams &s, Stores stores)
     if (s.shortest != s.longest || 2 * s.raw_values > s.values || s.e_bytes > 1024 * s.n || s.e_bytes < 80 * s.n) return none;
     const bool streaming = stores == kStreaming;
     switch (s.longest) {
-    case 512u: return s.n > 8 * kSimds ? Bundle{8u, long_codes ? kMany : kFitting} : none;
+    case 512u: return s.n > (long_codes ? 7 : 8) * kSimds ? Bundle{8u, long_codes ? kMany : kFitting} : none;
     case 1024u:
         if (s.n <= (long_codes ? 7 : streaming ? 8 : 10) * kSimds) return none;
         return s.n <= 16 * kSimds ? Bundle{4u, kFitting} : long_codes ? Bundle{4u, kMany} : none;
