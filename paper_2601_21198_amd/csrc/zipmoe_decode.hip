@@ -8,7 +8,7 @@
 //
 // Work decomposition
 //   grid    x: workgroups of kWaves consecutive streams, y: tensor (or x through all tensors)
-//   wave    one stream: stream_values consecutive values, tiles of 512
+//   wave    one stream: stream_values consecutive values, tiles of 512 (or eight tiles of several short streams, decode_bundle)
 //   lane j  owns values 8j..8j+7 of every tile: one 64-bit load of
 //           sign-mantissa bytes and one 128-bit store of bf16 words per tile,
 //           both contiguous across the wave (512 B and 1 KiB per instruction)
@@ -18,7 +18,7 @@
 //      lane-length bytes, then the 64 lane bitstreams back to back) are requested with 128-bit loads (a4), because
 //      decoding can not start without them, and go to LDS;
 //   2. the sign-mantissa bytes of the stream's first tiles are requested behind them, the others as tiles are finished;
-//   3. the decode table goes to LDS (a3) as 16-bit entries, code length in the low byte and symbol in the high byte:
+//   3. the decode table goes to LDS (a3) as 16-bit entries, code length in the low bits and symbol where a bf16 word has it:
 //      256 entries for codes of at most eight bits; longer codes take 16 more for each beginning that they share;
 //   4. a wavefront prefix sum over the 64 lane-length bytes gives every lane the first and the last bit of
 //      its own bitstream (a6): what varies from lane to lane is where its input lies, its output positions
@@ -27,10 +27,10 @@
 //      and the second half, last symbol first, from its last bit downwards, so every lane runs two independent
 //      decode chains at once (the lookups of one overlap the latency of the other).  Per chain it keeps two
 //      words of the bitstream, a bit position and the index of its next word; per round it extracts a 32-bit
-//      window with one funnel shift (one chain's is bit-reversed) and decodes four symbols by table lookup, or
+//      window with one funnel shift (one chain reads reversed bits) and decodes four symbols by table lookup, or
 //      two where longer codes do not fit; the next word is requested at the start of the round, so that a chain that crosses a word
 //      boundary finds it there;
-//   6. the eight decoded exponent bytes are merged with the sign-mantissa bytes
+//   6. the eight decoded entries are merged with the sign-mantissa bytes
 //      by byte-parallel bit operations and stored (a8).
 #include <hip/hip_runtime.h>
 
