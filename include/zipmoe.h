@@ -396,7 +396,7 @@ int zm_cache_pack_expert(const zm_cache_config *config, const zm_tensor_info *in
  * memory of at least zm_cache_arena_bytes bytes, 256-byte aligned, owned by the
  * caller and used by the cache until zm_cache_destroy.  The decode tables and
  * chunk tables of all tensors are uploaded at once (the call returns when they
- * are resident); all pools start empty.  The cache creates one HIP stream and two
+ * are resident); all pools start empty.  The cache creates one HIP stream and three
  * events of its own and allocates no device memory.
  * ZM_E_ARG, ZM_E_SIZE (arena too small), ZM_E_NOMEM, ZM_E_HIP. */
 int zm_cache_create(const zm_cache_config *config, const void *const *host_blobs, const void *const *host_images,
@@ -425,8 +425,11 @@ int zm_cache_fetch(zm_cache *cache, const int32_t *expert_ids, int n_selected, v
 /* The pool `expert` is in now (ZM_POOL_*), or ZM_E_ARG. */
 int zm_cache_pool_of(const zm_cache *cache, int expert);
 
-/* Waits for the cache's own stream, destroys it and the events, frees host
- * bookkeeping.  The arena goes back to the caller.  NULL is allowed. */
+/* Waits for the cache's own stream and for the last fetch that was issued on a
+ * caller's stream (and so for what that stream had in front of it), also if the
+ * fetch failed half-way; what a caller has captured is not waited for.  Destroys
+ * stream and events, frees host bookkeeping.  The arena goes back to the caller.
+ * NULL is allowed. */
 void zm_cache_destroy(zm_cache *cache);
 
 /* ---- Cache-pool planning (Sec. 3.4 "Hierarchical Cache Planning", App. C, App. D) ----

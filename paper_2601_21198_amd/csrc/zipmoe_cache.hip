@@ -212,6 +212,7 @@ struct zm_cache {
     std::vector<int32_t> limbo[kPools];        // slots released by the current fetch, reusable from the next one
     hipStream_t copy_stream = nullptr;
     hipEvent_t ev_start = nullptr, ev_copied = nullptr;
+    hipEvent_t ev_fetched = nullptr;           // behind what was fetched on a caller's stream, outside of captures
     bool broken = false;                       // a fetch failed half-way: slots and bookkeeping may disagree
     // work lists of a fetch (sized at creation for max_selected experts; a fetch is not re-entrant anyway)
     struct Plan { int expert, found, target, slot; };
@@ -313,7 +314,8 @@ int zm_cache_create(const zm_cache_config *config, const void *const *host_blobs
     } catch (const std::bad_alloc &) { delete c; return ZM_E_NOMEM; }
     if (hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_start, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_copied, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&c->ev_copied, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_fetched, hipEventDisableTiming) != hipSuccess) {
         zm_cache_destroy(c);
         return ZM_E_HIP;
     }
@@ -338,10 +340,11 @@ void zm_cache_destroy(zm_cache *c)
 {
     if (!c) return;
     // what was fetched on a caller's stream is waited for through its event
-    if (c->copy_stream && c->ev_copied && hipStreamWaitEvent(c->copy_stream, c->ev_copied, 0) != hipSuccess) (void)hipGetLastError();
+    if (c->copy_stream && c->ev_fetched && hipStreamWaitEvent(c->copy_stream, c->ev_fetched, 0) != hipSuccess) (void)hipGetLastError();
     if (c->copy_stream) { (void)hipStreamSynchronize(c->copy_stream); (void)hipStreamDestroy(c->copy_stream); }
     if (c->ev_start) (void)hipEventDestroy(c->ev_start);
     if (c->ev_copied) (void)hipEventDestroy(c->ev_copied);
+    if (c->ev_fetched) (void)hipEventDestroy(c->ev_fetched);
     delete c;
 }
 
@@ -530,8 +533,13 @@ int zm_cache_fetch(zm_cache *c, const int32_t *expert_ids, int n_selected, void 
         std::copy(infos_later, infos_later + n_later, infos_now + n_now);
         std::copy(out_later, out_later + n_later, out_now + n_now);
         if (rc == ZM_OK) rc = zm_decode_tensors(parts_now, infos_now, n_now + n_later, out_now, stream);
-        // zm_cache_destroy waits for it: until then the kernel may read the host's memory
-        if (rc == ZM_OK && any && hipEventRecord(c->ev_copied, main_stream) != hipSuccess) rc = ZM_E_HIP;
+        // zm_cache_destroy waits for it: until then the kernel may read the host's memory, also where the decode behind it was refused.  What a capture
+        // records is no work of the cache's yet, and its event, for which nothing outside of the graph can wait, would stand in place of a former fetch's.
+        if (any) {
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(main_stream, &capture) != hipSuccess ||
+                (capture == hipStreamCaptureStatusNone && hipEventRecord(c->ev_fetched, main_stream) != hipSuccess)) rc = ZM_E_HIP;
+        }
     }
     if (rc != ZM_OK) c->broken = true;
     return rc;

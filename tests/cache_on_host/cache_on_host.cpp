@@ -1,8 +1,11 @@
 // zipmoe_cache.hip built as host code, with a runtime that knows which memory a kernel could reach.  Each scenario
 // creates a cache of two experts, one tensor each, fetches both and prints what moved and whether a launch would have
 // left mapped memory:  "<bytes that differ> <parts by kernel> <parts by copy> <unmapped reads> <misaligned parts>"
+// With a third argument that names how a fetch ends it prints how many copies and launches nothing has waited for when the
+// cache is gone.
 #include "zipmoe_cache.hip"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -36,15 +39,52 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDevicept
     *base = const_cast<uint8_t *>(it->first); *size = it->second;
     return hipSuccess;
 }
-hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
-hipError_t hipMemcpyAsync(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t)
+
+// What is under way: work is numbered per stream; an event, and a stream, know up to which number each stream's is over once they are passed.
+using Passed = std::map<hipStream_t, long>;
+static std::map<hipStream_t, long> issued;
+static std::map<hipStream_t, Passed> behind;
+static std::map<hipEvent_t, Passed> recorded;
+static std::map<hipEvent_t, bool> in_capture;              // recorded in a capture: nothing outside of it can wait for that
+static Passed over;                                        // what the host has waited for
+static bool capturing;                                     // the caller's stream
+static uintptr_t handles;
+static void pass(Passed &to, const Passed &from) { for (const auto &[s, n] : from) to[s] = std::max(to[s], n); }
+static void issue(hipStream_t s) { if (!capturing) ++issued[s]; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = reinterpret_cast<hipStream_t>(++handles); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = reinterpret_cast<hipEvent_t>(++handles); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
+    in_capture[e] = capturing;
+    recorded[e].clear();
+    if (!capturing) { recorded[e] = behind[s]; recorded[e][s] = issued[s]; }
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
+{
+    if (in_capture[e] && !capturing) return last_error = hipErrorCapturedEvent;
+    pass(behind[s], recorded[e]);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) { pass(over, behind[s]); over[s] = issued[s]; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *status)
+{
+    *status = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+static long under_way() { long n = 0; for (const auto &[s, k] : issued) n += k - over[s]; return n; }
+
+hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t stream)
+{
+    issue(stream);
     std::memcpy(dst, src, bytes);
     by_copy += kind == hipMemcpyHostToDevice;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t, hipStream_t)
+hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t, hipStream_t stream)
 {
+    issue(stream);
     if (kernel != reinterpret_cast<const void *>(&zm_cache_fetch_kernel)) std::abort();
     const Parts P = *static_cast<const Parts *>(args[0]);
     by_kernel += P.n_parts;
@@ -62,10 +102,12 @@ hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **arg
 static std::vector<std::vector<uint8_t>> want_sm, want_e;
 static long differing;
 static int decoded;
+static bool refuse;                                        // as the decoder does with streams that do not fit its LDS
 extern "C" int zm_decode_tensors(const zm_tensor_parts *parts, const zm_tensor_info *, int n, void *const *, void *)
 {
+    if (refuse && n) return ZM_E_ARG;
     for (int i = 0; i < n; ++i, ++decoded) {
-        const auto &sm = want_sm[decoded], &e = want_e[decoded];
+        const auto &sm = want_sm[decoded % 2], &e = want_e[decoded % 2];
         for (size_t k = 0; k < sm.size(); ++k) differing += static_cast<const uint8_t *>(parts[i].sm)[k] != sm[k];
         for (size_t k = 0; k < e.size(); ++k) differing += static_cast<const uint8_t *>(parts[i].echunks)[k] != e[k];
     }
@@ -111,6 +153,21 @@ int main(int argc, char **argv)
     if (what == "unmapped-later") allocations.clear();  // still valid memory, as the contract asks
     const int32_t ids[2] = {0, 1};
     void *out[2];
+    if (argc > 3) {
+        const std::string_view ends = argv[3];
+        over = issued;                                  // the tables: creation has waited for them
+        if (ends == "captured") {
+            if (zm_cache_fetch(cache, ids, 2, out, nullptr, nullptr) != ZM_OK) return 6;
+            capturing = true;
+        }
+        refuse = ends == "refused";
+        if (zm_cache_fetch(cache, ids, 2, out, nullptr, nullptr) != (refuse ? ZM_E_ARG : ZM_OK)) return 6;
+        capturing = false;
+        const bool any = under_way() > 0;
+        zm_cache_destroy(cache);
+        std::printf("%d %ld %ld\n", any, under_way(), differing);
+        return 0;
+    }
     if (zm_cache_fetch(cache, ids, 2, out, nullptr, nullptr) != ZM_OK) return 6;
     zm_cache_destroy(cache);
     if (last_error != hipErrorInvalidValue) return 7;   // not the cache's to clear

@@ -1,5 +1,6 @@
 // What zipmoe_cache.hip needs of the HIP runtime, for its build as ordinary host code: "device" memory is process memory,
-// copies and launches run at once, and the process keeps a list of what a kernel could reach.  cache_on_host.cpp has the
+// copies and launches run at once, and the process keeps a list of what a kernel could reach and of what a real
+// runtime could still have under way.  cache_on_host.cpp has the
 // definitions.
 #pragma once
 #include <cstddef>
@@ -8,7 +9,7 @@
 #define __global__
 #define __launch_bounds__(...)
 
-enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorNotFound = 500 };
+enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorNotFound = 500, hipErrorCapturedEvent = 907 };
 enum hipMemoryType { hipMemoryTypeUnregistered = 0, hipMemoryTypeHost = 1, hipMemoryTypeDevice = 2, hipMemoryTypeManaged = 3 };
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToDevice = 3 };
 constexpr unsigned hipStreamNonBlocking = 1, hipEventDisableTiming = 2;
@@ -33,10 +34,12 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDevicept
 hipError_t hipGetLastError();
 hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream);
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t stream);
-inline hipError_t hipStreamCreateWithFlags(hipStream_t *, unsigned) { return hipSuccess; }
-inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
+hipError_t hipStreamCreateWithFlags(hipStream_t *stream, unsigned flags);
+hipError_t hipStreamSynchronize(hipStream_t stream);
+hipError_t hipStreamWaitEvent(hipStream_t stream, hipEvent_t event, unsigned flags);
+hipError_t hipStreamIsCapturing(hipStream_t stream, hipStreamCaptureStatus *status);
+hipError_t hipEventCreateWithFlags(hipEvent_t *event, unsigned flags);
+hipError_t hipEventRecord(hipEvent_t event, hipStream_t stream);
 inline hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-inline hipError_t hipEventCreateWithFlags(hipEvent_t *, unsigned) { return hipSuccess; }
 inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }

@@ -45,3 +45,12 @@ def test_the_kernel_reads_nothing_that_is_not_mapped_when_the_fetch_is_issued(pr
     # first and last page mapped, by an allocation each, and pageable memory between them: what lies in the last page alone
     # is the blobs' E regions
     assert fetch(program, "hole", source) == ((0, 2, 2, 0, 0) if source == "blobs" else (0, 0, 2, 0, 0))
+
+
+@pytest.mark.parametrize("source", ["blobs", "packed"])
+@pytest.mark.parametrize("memory", ["whole", "pageable"])
+@pytest.mark.parametrize("ends", ["decoded", "refused", "captured"])
+def test_what_a_fetch_has_issued_is_over_when_the_cache_is_gone(program, source, memory, ends):
+    """a fetch that is decoded, one whose decode is refused behind the fetch, and one issued before another is captured: (something was
+    under way, copies and launches that destruction has not waited for, bytes that differ)"""
+    assert fetch(program, memory, source, ends) == (1, 0, 0)
