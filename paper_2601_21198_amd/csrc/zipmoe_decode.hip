@@ -808,12 +808,17 @@ __device__ __forceinline__ void decode_stream(const Task &t, uint32_t g, uint16_
 
 // kBundle consecutive streams of a tensor, eight tiles together, by one wave: where streams are short, a wave's life is mostly the chain of
 // dependent reads in front of a few look-ups, and this puts eight tiles behind one chain and interleaves the look-ups of two streams.  Lane k
-// reads the chunk-table entry of stream k; the streams follow one another in memory and are fetched as one piece.  That is for whole coded streams;
-// others (raw ones, what a damaged table has) are decoded one after another, and so is the rest of a tensor that is no whole bundle, by a wave each.
+// reads the chunk-table entry of stream k; the streams follow one another in memory, coded and raw ones, and are fetched as one piece.  Raw ones are
+// merged from it, coded ones beside raw ones decoded one at a time.  A round of long codes that had more bits than a window is done again in two halves;
+// where the decoders as they were would cost a wave per SIMD (110 registers instead of 95), the stream is.  One wave that went through its
+// streams one after another, each with its own reads, held up a whole launch (us for 24000 streams of
+// 512 values, a wave per stream / such waves / now: codes of up to 12 bits, rows scaled by exp(N(0,1)), 12.3 / 17.3 / 8.6; one piece of 4096 values in a thousand raw
+// 10.2 / 13.3 / 8.5).  That is left for what a damaged table has.  The rest of a tensor that is no whole bundle is decoded by a wave per stream.
 template <bool kLong, Stores kStores, Kind kKind, int kBundle>
 __device__ __forceinline__ void decode_bundle(const Task &t, uint32_t wave_of_tensor, uint16_t *tab, uint32_t *words, uint32_t cap_words, uint32_t long_slots)
 {
     constexpr uint32_t kTilesEach = kGroup / kBundle, kValues = kTilesEach * kTile;
+    constexpr bool kAgain = kLong && (kTilesEach <= 2 || kKind == kMany);      // rounds are done again, not streams
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t bundles = whole_bundles(t.n_streams, t.last_values, kBundle);
     const uint32_t alone = wave_of_tensor - min(wave_of_tensor, bundles), g0 = (wave_of_tensor - alone) * kBundle + alone;
@@ -832,18 +837,35 @@ __device__ __forceinline__ void decode_bundle(const Task &t, uint32_t wave_of_te
         TableStage<kLong> stage_table;
         stage_table.ask(t, lane);
 
-        const uint64_t chunk = ent & ~15ull, from = reinterpret_cast<uint64_t>(t.echunks) + (chunk - t.e_offset) + o0;
-        const uint32_t bytes = o1 - o0;
-        const uint64_t from0 = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(from >> 32), 0))) << 32 |
-                               static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(from), 0));
-        const uint32_t rel = static_cast<uint32_t>(from - from0), end = rel + bytes;
-        const uint32_t before = __builtin_amdgcn_update_dpp(0u, end, 0x111, 0xf, 0xf, false);       // row_shr:1
-        const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(end), kBundle - 1));
-        constexpr uint32_t kHeld = 4;
-        const bool simple = (ent & 15ull) == ZM_MODE_CODED && stream_inside(chunk, o0, o1, t.e_offset, t.e_size) && !((from | bytes) & 15u) && from - from0 <= 1024u * kHeld &&
-                            (k_of == 0 || rel == before) && end <= min(1024u * kHeld, 4u * kBundle * cap_words) && !(kLong && 2u * bytes > kValues);
+        constexpr uint32_t kHeld = 4;        // KiB that wait in registers
+        const uint32_t room = 4u * kBundle * cap_words;
+        const uint64_t chunk = ent & ~15ull;
+        uint64_t from0;
+        uint32_t rel, total, raws = 0;       // this lane's stream and the end of the last one, from from0; bit k of raws: stream g0 + k is raw
+        // whether all lanes' streams, `bytes` at `at` in the region, are one piece that finds room
+        auto one_piece = [&](bool inside, uint64_t at, uint32_t bytes) {
+            const uint64_t from = reinterpret_cast<uint64_t>(t.echunks) + (chunk - t.e_offset) + at;
+            from0 = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(from >> 32), 0))) << 32 |
+                    static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(from), 0));
+            rel = static_cast<uint32_t>(from - from0);
+            const uint32_t end = rel + bytes, before = __builtin_amdgcn_update_dpp(0u, end, 0x111, 0xf, 0xf, false);       // row_shr:1
+            total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(end), kBundle - 1));
+            const bool simple = inside && !((from | bytes) & 15u) && from - from0 <= room && (k_of == 0 || rel == before) && bytes <= room && end <= room;
+            return __builtin_amdgcn_ballot_w64(simple) == ~0ull;
+        };
+        const bool coded = (ent & 15ull) == ZM_MODE_CODED && stream_inside(chunk, o0, o1, t.e_offset, t.e_size);
+        bool piece_found = one_piece(coded, o0, o1 - o0);
+        if (__builtin_expect(!piece_found, 0)) {
+            const uint64_t raw_at = static_cast<uint64_t>(s) * kValues;
+            const bool raw = (ent & 15ull) == ZM_MODE_RAW;
+            raws = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(raw)) & ((1u << kBundle) - 1u);
+            piece_found = one_piece(raw ? raw_stream_inside(chunk, raw_at, kValues, t.e_offset, t.e_size) : coded, raw ? raw_at : o0, raw ? kValues : o1 - o0);
+        }
         one_by_one = (1u << kBundle) - 1u;
-        if (__builtin_amdgcn_ballot_w64(simple) == ~0ull) {
+        if (piece_found) {
+            const u32x4 *const piece_at = reinterpret_cast<const u32x4 *>(from0);
+            if (__builtin_expect(total > 1024u * kHeld, 0))
+                for (uint32_t i = 64u * kHeld + lane; i < total / 16u; i += 64u) reinterpret_cast<u32x4 *>(words)[i] = piece_at[i];
             u32x4 held[kHeld];
             const __amdgpu_buffer_rsrc_t piece = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(from0), 0, static_cast<int>(total), kRawBuffer);
 #pragma unroll
@@ -870,43 +892,88 @@ __device__ __forceinline__ void decode_bundle(const Task &t, uint32_t wave_of_te
             if (!narrow) {
                 const Sink<kStores> out(t.out + v0, kGroupValues, lane);
                 one_by_one = 0;
+                uint32_t rest = 0;           // bit k: stream g0 + k is left for the loop below
+                auto place_of = [&](uint32_t k) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rel), static_cast<int>(k))) / 4u; };      // words
+                if (__builtin_expect(raws != 0, 0)) {
+                    rest = raws ^ ((1u << kBundle) - 1u);
 #pragma unroll
-                for (int k = 0; k < kBundle; k += 2) {
-                    const uint32_t at0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rel), k)) / 4u, at1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(rel), k + 1)) / 4u;
-                    const uint32_t *const w0 = words + at0, *const w1 = words + at1;
-                    // two streams' prefix sums in one: 64 lanes of at most 8 * 4 + 2 * 255 bits
-                    const uint32_t bits0 = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(w0)[lane], bits1 = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(w1)[lane];
-                    const uint32_t first = wave_exclusive_sum(bits0 | bits1 << 16);
-                    Decoder<kLong> d0, d1;
-                    d0.words = w0; d1.words = w1;
-                    d0.last_word = kBundle * cap_words - 1u - at0;
-                    d1.last_word = kBundle * cap_words - 1u - at1;
-                    d0.table = d1.table = table;
-                    d0.start(first & 0xffffu, (first & 0xffffu) + bits0);
-                    d1.start(first >> 16, (first >> 16) + bits1);
-                    uint32_t most0 = 0, most1 = 0;
-                    const uint32_t done = k * kTilesEach;          // tiles
-                    auto more = [&](uint32_t i) { if (i + kAhead < kGroup) byte8[i + kAhead] = sm.load(tile_of(i + kAhead)); };
-                    if constexpr (kTilesEach == 1) {
-                        const auto a0 = d0.quad(tab, most0), a1 = d1.quad(tab, most1);
-                        out.store(done, merge8(a0.up, a0.down, byte8[done]));
-                        out.store(done + 1u, merge8(a1.up, a1.down, byte8[done + 1u]));
-                        more(done); more(done + 1u);
-                    } else {
+                    for (uint32_t i = kAhead; i < kGroup; ++i) byte8[i] = sm.load(tile_of(i));
 #pragma unroll
-                        for (uint32_t p = 0; p < kTilesEach / 2u; ++p) {
-                            const auto a0 = d0.quad(tab, most0), a1 = d1.quad(tab, most1), b0 = d0.quad(tab, most0), b1 = d1.quad(tab, most1);
-                            const uint32_t i = done + 4u * p;
-                            out.store(tile_of(i), merge8(a0.up, b0.up, byte8[i]));
-                            out.store(tile_of(i + 1u), merge8(b0.down, a0.down, byte8[i + 1u]));
-                            out.store(tile_of(i + 2u), merge8(a1.up, b1.up, byte8[i + 2u]));
-                            out.store(tile_of(i + 3u), merge8(b1.down, a1.down, byte8[i + 3u]));
-                            more(i); more(i + 1u); more(i + 2u); more(i + 3u);
+                    for (uint32_t i = 0; i < kGroup; ++i) {
+                        const uint32_t k = tile_of(i) / kTilesEach;
+                        if (raws >> k & 1u)
+                            out.store(tile_of(i), recover8(reinterpret_cast<const uint2 *>(words + place_of(k))[tile_of(i) % kTilesEach * 64u + lane], byte8[i]));
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kBundle; k += 2) {
+                        const uint32_t at0 = place_of(k), at1 = place_of(k + 1);
+                        const uint32_t *const w0 = words + at0, *const w1 = words + at1;
+                        // two streams' prefix sums in one: 64 lanes of at most 8 * 4 + 2 * 255 bits
+                        const uint32_t bits0 = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(w0)[lane], bits1 = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(w1)[lane];
+                        const uint32_t first = wave_exclusive_sum(bits0 | bits1 << 16);
+                        Decoder<kLong> d0, d1;
+                        d0.words = w0; d1.words = w1;
+                        d0.last_word = kBundle * cap_words - 1u - at0;
+                        d1.last_word = kBundle * cap_words - 1u - at1;
+                        d0.table = d1.table = table;
+                        d0.start(first & 0xffffu, (first & 0xffffu) + bits0);
+                        d1.start(first >> 16, (first >> 16) + bits1);
+                        const uint32_t done = k * kTilesEach;          // tiles
+                        auto more = [&](uint32_t i) { if (i + kAhead < kGroup) byte8[i + kAhead] = sm.load(tile_of(i + kAhead)); };
+                        uint32_t most0 = 0, most1 = 0;
+                        auto again = [&] { return kAgain && __builtin_expect(__builtin_amdgcn_ballot_w64(max(most0, most1) > 32u) != 0, 0); };
+                        if constexpr (kTilesEach == 1) {
+                            const Decoder<kLong> before0 = d0, before1 = d1;
+                            auto a0 = d0.quad(tab, most0), a1 = d1.quad(tab, most1);
+                            if (again()) {
+                                d0 = before0; d1 = before1;
+                                a0 = d0.safe_quad(tab); a1 = d1.safe_quad(tab);
+                            }
+                            out.store(done, merge8(a0.up, a0.down, byte8[done]));
+                            out.store(done + 1u, merge8(a1.up, a1.down, byte8[done + 1u]));
+                            more(done); more(done + 1u);
+                        } else {
+#pragma unroll
+                            for (uint32_t p = 0; p < kTilesEach / 2u; ++p) {
+                                const Decoder<kLong> before0 = d0, before1 = d1;
+                                if (kAgain) most0 = most1 = 0;
+                                auto a0 = d0.quad(tab, most0), a1 = d1.quad(tab, most1), b0 = d0.quad(tab, most0), b1 = d1.quad(tab, most1);
+                                if (again()) {
+                                    d0 = before0; d1 = before1;
+                                    a0 = d0.safe_quad(tab); a1 = d1.safe_quad(tab);
+                                    b0 = d0.safe_quad(tab); b1 = d1.safe_quad(tab);
+                                }
+                                const uint32_t i = done + 4u * p;
+                                out.store(tile_of(i), merge8(a0.up, b0.up, byte8[i]));
+                                out.store(tile_of(i + 1u), merge8(b0.down, a0.down, byte8[i + 1u]));
+                                out.store(tile_of(i + 2u), merge8(a1.up, b1.up, byte8[i + 2u]));
+                                out.store(tile_of(i + 3u), merge8(b1.down, a1.down, byte8[i + 3u]));
+                                more(i); more(i + 1u); more(i + 2u); more(i + 3u);
+                            }
+                            if constexpr (kLong && !kAgain)
+                                rest |= (__builtin_amdgcn_ballot_w64(most0 > 32u) ? 1u << k : 0u) | (__builtin_amdgcn_ballot_w64(most1 > 32u) ? 2u << k : 0u);
                         }
                     }
-                    // long codes: a stream in which some lane's four symbols had more bits than a window is done again
-                    if constexpr (kLong)
-                        one_by_one |= (__builtin_amdgcn_ballot_w64(most0 > 32u) ? 1u << k : 0u) | (__builtin_amdgcn_ballot_w64(most1 > 32u) ? 2u << k : 0u);
+                }
+                while (__builtin_expect(rest != 0, 0)) {
+                    const uint32_t k = static_cast<uint32_t>(__builtin_ctz(rest)), at = place_of(k);
+                    rest &= rest - 1u;
+                    const ByteSource its_sm(t.sm + v0 + k * kValues, kValues, lane);
+                    uint2 up[kPairs], down[kPairs];
+#pragma unroll
+                    for (uint32_t i = 0; i < 2; ++i) {
+                        up[i] = its_sm.load(i);
+                        down[i] = its_sm.load(kTilesEach - 1u - i);
+                    }
+                    const uint32_t bits = 8u * kTilesEach + quantum * reinterpret_cast<const uint8_t *>(words + at)[lane], first = wave_exclusive_sum(bits);
+                    Decoder<kLong> dec;
+                    dec.words = words + at;
+                    dec.last_word = kBundle * cap_words - 1u - at;
+                    dec.table = table;
+                    dec.start(first, first + bits);
+                    decode_any_stream<kLong, false, 2>(dec, tab, Sink<kStores>(t.out + v0 + k * kValues, kValues, lane), its_sm, 0u, kTilesEach,
+                                                       static_cast<int32_t>(kValues) - static_cast<int32_t>(lane * 8u), up, down);
                 }
             }
         }

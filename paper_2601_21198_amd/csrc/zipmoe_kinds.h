@@ -132,7 +132,7 @@ struct Bundle {
     Kind kind;
 };
 
-// us, three tensors, a wave per stream / bundles as kFitting / as kMany; cached: three sets in turn, device-scope stores; else nothing cached.
+// us, three tensors of Gaussian weights, a wave per stream / bundles as kFitting / as kMany; cached: three sets in turn, device-scope stores; else nothing cached.
 //   short codes, streams        cached                 dev                    nt
 //     512:   8000                4.9 /  5.0 /  4.9      6.3 /  6.6 /  6.6      6.2 /  6.3 /  6.4
 //            9000                5.4 /  5.2 /  5.2      7.0 /  6.9 /  6.9      6.7 /  6.6 /  6.6
@@ -158,20 +158,36 @@ struct Bundle {
 //            4500                7.9 /  8.2 /  8.1     11.4 / 10.0 /  9.9     10.1 /  9.2 /  9.8
 //            8000               11.1 / 10.3 / 11.8     16.0 / 14.1 / 14.7     13.0 / 12.1 / 12.9
 //           24000               36.7 / 33.6 / 32.7     36.3 / 33.4 / 32.4     33.2 / 32.3 / 31.7
+//   denser long codes, a wave per stream / bundles; e: bytes a stream
+//     512:   9500, e 296          6.5 /  6.5             8.2 /  7.9             7.9 /  7.6
+//            9500, e 347          6.7 /  6.9             8.2 /  9.2             8.0 /  8.4
+//           12000, e 347          7.6 /  7.1             9.6 /  9.6             9.2 /  9.0
+//           24000, e 347         12.3 / 10.1            14.6 / 12.7            14.2 / 12.0
+//    1024:   8000, e 521          7.3 /  7.6             9.9 /  9.0             9.7 /  8.7
+//           12000, e 521          9.7 /  9.5            11.9 / 11.0            11.9 / 11.4
+//            8000, e 623          7.6 /  8.2            10.2 /  9.4             9.9 /  9.2
+//           24000, e 623         19.1 / 19.5            20.4 / 20.0            19.6 / 19.1
+//    2048:   8000, e 976         11.5 / 11.8            16.1 / 14.8            13.5 / 13.4
+//           12000, e 976         18.7 / 18.4            22.2 / 19.5            20.0 / 18.6
 // So waves of one stream stay where all of them find places, and for short codes in large launches where they are bound by the memory
-// already; device-scope stores of few streams that stay cached decide where the lines lie, though cold ones would gain earlier.  Raw streams are not bundled, nor dense ones of more than a kilobyte, nor what has no room for its streams at all.
+// already; device-scope stores of few streams that stay cached decide where the lines lie, though cold ones would gain earlier.  Raw tensors are not
+// bundled, nor streams of more than a kilobyte, nor what has no room for its streams at all.  Raw chunks among coded ones make no difference.  What is left: 4096 long
+// codes of rare symbols in a row, 2048 values a stream, where most rounds are done again: one such piece in a hundred, 6500 streams, 10.7 / 12.2, 14.7 / 15.2, 12.5 / 13.7.
 inline Bundle bundle_of(bool long_codes, const Streams &s, Stores stores)
 {
     const Bundle none{1u, kShortStreams};
     if (s.shortest != s.longest || 2 * s.raw_values > s.values || s.e_bytes > 1024 * s.n || s.e_bytes < 80 * s.n) return none;
     const bool streaming = stores == kStreaming;
+    // long codes: more bytes a stream than these; a sixty-four of them are lengths
+    auto denser = [&](uint64_t bytes) { return long_codes && s.e_bytes > bytes * s.n; };
     switch (s.longest) {
-    case 512u: return s.n > (long_codes ? 7 : 8) * kSimds ? Bundle{8u, long_codes ? kMany : kFitting} : none;
+    case 512u: return s.n > (denser(320) ? 12 : 9) * kSimds ? Bundle{8u, long_codes ? kMany : kFitting} : none;
     case 1024u:
-        if (s.n <= (long_codes ? 7 : streaming ? 8 : 10) * kSimds) return none;
+        if (!streaming && denser(576)) return none;
+        if (s.n <= (streaming ? (long_codes ? 7 : 8) : denser(464) ? 12 : long_codes ? 7 : 10) * kSimds) return none;
         return s.n <= 16 * kSimds ? Bundle{4u, kFitting} : long_codes ? Bundle{4u, kMany} : none;
     case 2048u:
-        if (s.n <= (!streaming ? 6 : long_codes ? 4 : 5) * kSimds) return none;
+        if (s.n <= (streaming ? (long_codes ? 4 : 5) : denser(864) ? 9 : 6) * kSimds) return none;
         return s.n <= 9 * kSimds ? Bundle{2u, kFitting} : long_codes || !streaming ? Bundle{2u, kMany} : none;
     default: return none;
     }

@@ -781,8 +781,8 @@ def test_streams_that_a_table_places_outside_are_left_alone(W, max_len, damage):
 
 
 def bundle_tensor(n, W, max_len, seed):
-    """Gaussian weights with streams that a bundle can not take: a stretch that is stored raw, one that is dense in rare exponents, and lanes whose
-    symbols all have the longest codes"""
+    """Gaussian weights with streams that a bundle has to treat apart: a chunk and four chunks that are stored raw, half a stream and two streams of
+    rare exponents, and lanes whose symbols all have the longest codes"""
     rng = np.random.default_rng(seed)
     w = synth.special_tensor("gauss", n, seed).copy()
 
@@ -795,21 +795,30 @@ def bundle_tensor(n, W, max_len, seed):
     rare(n // 3 // W * W + W // 2, min(W // 2, n // 64))
     if n > 256 * W:
         rare(n // 2 // (4 * W) * 4 * W, 4 * W)
+        rare(n // 5 // (16 * W) * 16 * W, 16 * W)
+        rare(n // 4 // (4 * W) * 4 * W, 2 * W)
     return w
 
 
 @pytest.mark.parametrize("count,ragged,stores", [(1, False, zm.STORES_CACHED), (7, True, zm.STORES_STREAMING), (60, False, zm.STORES_CACHED)])
-@pytest.mark.parametrize("W,max_len,streams", [(512, 8, 8192), (512, 8, 8193), (512, 12, 7169), (1024, 8, 10241), (1024, 8, 16385), (1024, 12, 7169), (1024, 12, 16385),
-                                               (2048, 8, 6145), (2048, 8, 9217), (2048, 12, 6145), (2048, 12, 9217)])
-def test_waves_that_take_several_short_streams(W, max_len, streams, count, ragged, stores):
-    """at the lines from which on they do: tensors of no whole bundle and a cut-off last stream, with streams in between that go one by one; whole
+@pytest.mark.parametrize("W,max_len,streams,cached,streaming", [
+    (512, 8, 9180, 1, 1), (512, 8, 9217, 8, 8), (512, 12, 9217, 8, 8), (512, 12, 30000, 8, 8), (1024, 8, 10241, 4, 4), (1024, 8, 16385, 1, 1), (1024, 12, 7169, 4, 4),
+    (1024, 12, 16385, 4, 4), (2048, 8, 6145, 2, 2), (2048, 8, 9217, 2, 1), (2048, 12, 6145, 2, 2), (2048, 12, 9217, 2, 2)])
+def test_waves_that_take_several_short_streams(W, max_len, streams, cached, streaming, count, ragged, stores):
+    """at the lines from which on they do: tensors of no whole bundle and a cut-off last stream, with streams in between that are treated apart; whole
     blobs alike, tensors of very different lengths, many in a launch; and what a damaged chunk table places outside stays as it was"""
     import torch
     lengths = [max(1, (streams // (2 ** k if k else 1)) // 2) for k in range(count)] if ragged else [-(-streams // count)] * count
     lengths[0] += max(0, streams - sum(lengths))
-    tensors = [[bundle_tensor(s * W - (5 if k % 2 or count == 1 else 0), W, max_len, seed=k % 3)] for k, s in enumerate(lengths)]
+    cut = [5 if k % 2 or count == 1 else 0 for k in range(count)]
+    tensors = [[bundle_tensor(s * W - cut[k], W, max_len, seed=k % 3)] for k, s in enumerate(lengths)]
     flat, blobs, got, shapes = layer_calls(tensors, 4 * W, W, max_len, stores)
-    assert {int(zm.blob_info(b).max_len > 8) for b in blobs} == {int(max_len > 8)} and len(shapes) == (1 if count < 60 else len(shapes))
+    assert {int(zm.blob_info(b).max_len > 8) for b in blobs} == {int(max_len > 8)} and len(shapes) == 1
+    # the launch is one of bundles, or is not: a wave for each whole bundle and for each other stream, two waves a workgroup
+    bundle = streaming if stores == zm.STORES_STREAMING else cached
+    whole = [s - (c > 0) for s, c in zip(lengths, cut)]
+    blocks = [(w // bundle + w % bundle + (c > 0) + 1) // 2 for w, c in zip(whole, cut)]
+    assert shapes[0].workgroups in (max(blocks), sum(blocks))
     assert count == 60 or set(chunk_modes(blobs[0])) == {0, 1}
     for a, g in zip(flat, got):
         assert np.array_equal(g, a)

@@ -100,3 +100,98 @@ def test_nearly_whole_groups_run_seven_waves(kind_of, streaming):
     assert kind_of([(2048, 30000)], streaming=streaming) == ("short", 8, 2)
     for w in (2560, 3584):
         assert kind_of([(w, 20000)], streaming=streaming)[:2] == ("fitting", 7)
+
+
+BUNDLES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "zipmoe_kinds.h"
+// long_codes streaming {stream_values n_streams last_values e_size}...: streams that a wave takes, the kind of kernel, waves of every tensor
+int main(int argc, char **argv)
+{
+    zipmoe::Streams s;
+    for (int i = 3; i + 3 < argc; i += 4)
+        s.add(std::strtoul(argv[i], nullptr, 10), std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10), std::strtoull(argv[i + 3], nullptr, 10));
+    const zipmoe::Bundle b = zipmoe::bundle_of(argv[1][0] == '1', s, argv[2][0] == '1' ? zipmoe::kStreaming : zipmoe::kThrough);
+    std::printf("%u %s", b.streams, b.streams == 1 ? "-" : b.kind == zipmoe::kMany ? "many" : b.kind == zipmoe::kFitting ? "fitting" : "?");
+    for (int i = 3; i + 3 < argc; i += 4) std::printf(" %u", zipmoe::waves_of(std::strtoul(argv[i + 1], nullptr, 10), std::strtoul(argv[i + 2], nullptr, 10), b.streams));
+    std::printf("\n");
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def bundle_of(tmp_path_factory):
+    at = tmp_path_factory.mktemp("bundles")
+    (at / "bundles.cpp").write_text(BUNDLES)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2601_21198_amd", "csrc"), str(at / "bundles.cpp"), "-o", str(at / "bundles")])
+
+    def ask(tensors, long_codes=False, streaming=False, e=None):
+        """tensors: (stream_values, streams[, last_values]) with e bytes a stream in the E region: (streams a wave takes, kind, waves of every tensor)"""
+        args = [str(x) for w, n, *last in tensors for x in (w, n, last[0] if last else w, n * (e if e is not None else 64 + w * 3 // 8))]
+        streams, kind, *waves = subprocess.check_output([str(at / "bundles"), str(int(long_codes)), str(int(streaming)), *args], text=True).split()
+        return int(streams), kind, [int(x) for x in waves]
+    return ask
+
+
+@pytest.mark.parametrize("long_codes,streaming,w,line,bundle,kind", [
+    (False, False, 512, 9, 8, "fitting"), (False, True, 512, 9, 8, "fitting"), (True, False, 512, 9, 8, "many"), (True, True, 512, 9, 8, "many"),
+    (False, False, 1024, 10, 4, "fitting"), (False, True, 1024, 8, 4, "fitting"), (True, False, 1024, 7, 4, "fitting"), (True, True, 1024, 7, 4, "fitting"),
+    (False, False, 2048, 6, 2, "fitting"), (False, True, 2048, 5, 2, "fitting"), (True, False, 2048, 6, 2, "fitting"), (True, True, 2048, 4, 2, "fitting")])
+def test_from_which_line_on_a_wave_takes_several_streams(bundle_of, long_codes, streaming, w, line, bundle, kind):
+    ask = lambda tensors: bundle_of(tensors, long_codes, streaming)
+    n = line * 1024
+    assert ask([(w, n)])[:2] == (1, "-")
+    assert ask([(w, n + 1)])[:2] == (bundle, kind)
+    # the launch counts, not the tensor
+    assert ask([(w, n // 4)] * 4)[:2] == (1, "-")
+    assert ask([(w, n // 4)] * 3 + [(w, n // 4 + 1)])[:2] == (bundle, kind)
+
+
+def test_large_launches_of_short_streams(bundle_of):
+    for long_codes in (False, True):
+        for streaming in (False, True):
+            ask = lambda w, n: bundle_of([(w, n)], long_codes, streaming)[:2]
+            assert ask(512, 1 << 20) == (8, "many" if long_codes else "fitting")
+            assert ask(1024, 16 * 1024) == (4, "fitting")
+            assert ask(1024, 16 * 1024 + 1) == ((4, "many") if long_codes else (1, "-"))
+            assert ask(2048, 9 * 1024) == (2, "fitting")
+            assert ask(2048, 9 * 1024 + 1) == ((2, "many") if long_codes or not streaming else (1, "-"))
+
+
+def test_launches_that_no_bundle_is_made_of(bundle_of):
+    many = 1 << 15
+    for w in (1536, 2560, 4096, 8192):
+        assert bundle_of([(w, many)])[0] == 1
+    assert bundle_of([(512, many), (1024, many)])[0] == 1                       # streams of two lengths
+    assert bundle_of([(2048, many)], e=1024)[0] == 2 and bundle_of([(2048, many)], e=1025)[0] == 1
+    assert bundle_of([(512, many)], e=79)[0] == 1 and bundle_of([(512, many)], e=80)[0] == 8
+    # raw tensors: as many bytes in the E region as values
+    assert bundle_of([(512, many)], e=511)[0] == 8 and bundle_of([(512, many)], e=512)[0] == 1
+
+
+@pytest.mark.parametrize("w,bytes_,line,dense", [(512, 320, 9, 12), (1024, 464, 7, 12), (2048, 864, 6, 9)])
+def test_launches_of_dense_long_codes_need_more_streams(bundle_of, w, bytes_, line, dense):
+    """with stores that may stay cached; of 512 values whatever the stores"""
+    for streaming in (False, True):
+        late = dense if not streaming or w == 512 else line
+        for e, at in ((bytes_, line), (bytes_ + 1, late)):
+            if streaming and w == 2048:
+                at = 4
+            assert bundle_of([(w, at * 1024)], True, streaming, e)[0] == 1
+            assert bundle_of([(w, at * 1024 + 1)], True, streaming, e)[0] == 4096 // w
+    assert bundle_of([(w, 11 * 1024)], False, False, bytes_ + 1)[0] == 4096 // w        # four short codes always fit a window
+    assert bundle_of([(1024, 1 << 15)], True, False, 577)[0] == 1 and bundle_of([(1024, 1 << 15)], True, True, 577)[0] == 4
+
+
+@pytest.mark.parametrize("w,bundle", [(512, 8), (1024, 4), (2048, 2)])
+def test_waves_of_tensors_that_are_no_whole_bundles(bundle_of, w, bundle):
+    """every stream is in one bundle or has a wave of its own, and a cut-off one has"""
+    tensors = [(w, 1 << 15)]
+    for n in list(range(1, 2 * bundle + 2)) + [1000 * bundle - 1, 1000 * bundle, 1000 * bundle + 1]:
+        tensors += [(w, n), (w, n, 1), (w, n, w - 8)]
+    streams, _, waves = bundle_of(tensors, long_codes=True)
+    assert streams == bundle
+    for (_, n, *last), got in zip(tensors, waves):
+        whole = n - (1 if last else 0)
+        assert got == whole // bundle + whole % bundle + (1 if last else 0), (n, last)
