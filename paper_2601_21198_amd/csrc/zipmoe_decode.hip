@@ -560,7 +560,9 @@ __device__ __forceinline__ void decode_any_stream(Decoder<kLong, kFromBlob> &dec
     };
 #pragma unroll 1
     for (;; first += kTurns) {
-        if (pair(std::integral_constant<int, 0>()) || pair(std::integral_constant<int, 1>())) return;
+        if (pair(std::integral_constant<int, 0>())) return;
+        if constexpr (kTurns > 1)
+            if (pair(std::integral_constant<int, 1>())) return;
         if constexpr (kTurns == 4)
             if (pair(std::integral_constant<int, 2>()) || pair(std::integral_constant<int, 3>())) return;
     }
@@ -786,8 +788,8 @@ __device__ __forceinline__ void decode_stream(const Task &t, uint32_t g, uint16_
             dec.words = words; dec.last_word = cap_words - 1u;
             dec.table = table;
             dec.start(first, first + bits);
-            if (kAhead < 2) ask(1);
-            decode_any_stream<true, true, 2>(dec, stage_table.lut, out, sm, 0u, tiles, mine, up, down);
+            // one turn: with two, for tables that only a damaged blob has, streams shorter than a group took 65 registers, seven waves per SIMD
+            decode_any_stream<true, true, 1>(dec, stage_table.lut, out, sm, 0u, tiles, mine, up, down);
             return;
         }
     }
