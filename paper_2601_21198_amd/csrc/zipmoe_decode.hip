@@ -663,8 +663,8 @@ struct TableStage {
 };
 
 // Stream g of a tensor, by one wave.  kLong: codes of more than eight bits; kStores: how the output is written; tab: LDS for the decode
-// table; words: LDS for the stream, cap_words of it; long_slots: as in Launch
-template <bool kLong, Stores kStores, Kind kKind>
+// table; words: LDS for the stream, cap_words of it; long_slots: as in Launch; kOneTile: many of the streams are of one tile
+template <bool kLong, Stores kStores, Kind kKind, bool kOneTile>
 __device__ __forceinline__ void decode_stream(const Task &t, uint32_t g, uint16_t *tab, uint32_t *words, uint32_t cap_words, uint32_t long_slots)
 {
     const uint32_t lane = threadIdx.x & 63u;
@@ -792,6 +792,17 @@ __device__ __forceinline__ void decode_stream(const Task &t, uint32_t g, uint16_
             decode_any_stream<true, true, 1>(dec, stage_table.lut, out, sm, 0u, tiles, mine, up, down);
             return;
         }
+    }
+    // A stream of one tile has no turns to take, and in their loop it waited for all that its turns would have asked for.  us: 2000 / 8000 streams of 512 values,
+    // cached 2.96 / 4.88 -> 2.86 / 4.68, long codes 3.41 / 5.87 -> 3.33 / 5.61.
+    if (kOneTile && tiles == 1u) {
+        Decoder<kLong> dec;
+        dec.words = words; dec.last_word = cap_words - 1u;
+        dec.table = table;
+        dec.start(first, first + bits);
+        const auto e = dec.safe_quad(tab);
+        finish_tile(out, 0u, merge8(e.up, e.down, up[0]), mine);
+        return;
     }
     Decoder<kLong> dec;
     dec.words = words; dec.last_word = cap_words - 1u;
@@ -983,7 +994,7 @@ __device__ __forceinline__ void decode_bundle(const Task &t, uint32_t wave_of_te
     while (one_by_one) {
         const uint32_t k = static_cast<uint32_t>(__builtin_ctz(one_by_one));
         one_by_one &= one_by_one - 1u;
-        decode_stream<kLong, kStores, kShortStreams>(t, g0 + k, tab, words, cap_words, long_slots);
+        decode_stream<kLong, kStores, kShortStreams, false>(t, g0 + k, tab, words, cap_words, long_slots);
     }
 }
 
@@ -1002,7 +1013,7 @@ __device__ __forceinline__ void decode_block(const Task &t, uint32_t block, uint
     const uint32_t g = block * kWaves + wave;
     uint32_t *words = dynamic_lds + (kLong ? long_table_words(long_slots) : 0u) + wave * cap_words * kBundle;
     if constexpr (kBundle > 1) decode_bundle<kLong, kStores, kKind, kBundle>(t, g, tab, words, cap_words, long_slots);
-    else if (g < t.n_streams) decode_stream<kLong, kStores, kKind>(t, g, tab, words, cap_words, long_slots);
+    else if (g < t.n_streams) decode_stream<kLong, kStores, kKind, kKind == kShortStreams>(t, g, tab, words, cap_words, long_slots);
 }
 
 template <bool kLong, int kWaves, Stores kStores, Kind kKind, int kBundle, class Args>
