@@ -210,7 +210,7 @@ int zm_decode_experts(const void *const *blobs, const uint64_t *const *chunk_off
 
 
 /* The same call with the store policy chosen by the caller, who knows what becomes of the output buffers:
- *   ZM_STORES_AUTO       what zm_decode_experts does: non-temporal stores iff one launch writes three quarters of what the
+ *   ZM_STORES_AUTO       what zm_decode_experts does: non-temporal stores iff one launch writes seven eighths of what the
  *                        256 MB last-level cache holds, or more
  *   ZM_STORES_CACHED     stores that leave their lines cached (device-scope stores, with which a launch ends sooner, or
  *                        ordinary ones where those are ahead): right when the same buffers are rewritten call after call (the lines

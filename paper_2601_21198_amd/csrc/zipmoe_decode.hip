@@ -1119,15 +1119,17 @@ constexpr uint64_t kLastLevelCacheBytes = 256ull << 20;   // MI355X Infinity Cac
 // five / six at 48 MiB: 14.0 / 14.4 / 14.7 / 14.5), and these keep ordinary stores.
 constexpr uint64_t kThroughBytes = 36ull << 20;
 
-// From three quarters of the last-level cache on non-temporal stores are ahead whatever the caller does: outputs so large leave the cache before
-// they are read or written again, and push out what is read meanwhile.  us device-scope / non-temporal, experts of 1024 x 2048 x 3 (long codes):
-//   out, MiB                              156                          192                          228                          252
-//   one set                               42.9 / 40.6  (51.6 / 41.7)   52.4 / 49.7  (61.4 / 50.6)   66.3 / 58.7  (72.5 / 60.0)   74.1 / 64.7  (79.4 / 65.9)
-//   inputs from HBM, one output set       41.3 / 46.1  (45.0 / 51.0)   55.8 / 55.5  (60.3 / 61.2)   67.3 / 65.5  (74.0 / 73.0)   74.0 / 72.4  (80.1 / 79.8)
-//   neither cached                        48.1 / 46.1  (51.4 / 50.8)   57.6 / 55.6  (62.3 / 60.8)   67.4 / 65.7  (73.7 / 72.7)   73.7 / 72.0  (80.3 / 79.8)
-//   the same and a product that reads     156.1 / 156.1                190.6 / 190.6                216.8 / 216.9                248.7 / 248.1
-// Experts of 512 x 1024 x 3: one set 159 MiB 44.0 / 41.8, 192 55.3 / 49.9; inputs from HBM 42.0 / 47.8, 58.3 / 56.7.
-constexpr uint64_t kStreamingBytes = kLastLevelCacheBytes / 4 * 3;
+// From seven eighths of the last-level cache on non-temporal stores are ahead whatever the caller does: outputs so large leave the cache before they are read or
+// written again, and push out what is read meanwhile.  Below, the decode by itself is, but a product that reads the output next finds nothing of it in the
+// cache.  us device-scope / non-temporal, experts of 1024 x 2048 x 3 (long codes), one output set; read: with a product over all of it:
+//   out, MiB                              168                          192                          216                          228                          252
+//   one set                               46.7 / 43.6  (56.6 / 44.7)   54.8 / 49.6  (62.7 / 50.5)   62.7 / 55.6  (69.0 / 57.0)   67.0 / 58.6  (73.4 / 59.9)   73.9 / 64.6  (80.1 / 65.6)
+//   the same, read                        70.8 / 74.8  (74.8 / 76.6)   83.1 / 85.4  (86.6 / 88.8)   98.2 / 98.6  (102.0 / 103.5) 108.8 / 104.1 (113.9 / 112.8) 128.8 / 117.8 (132.6 / 125.5)
+//   inputs from HBM                       45.8 / 48.9  (49.9 / 54.6)   57.4 / 55.4  (62.0 / 60.9)   64.0 / 62.2  (69.2 / 69.1)   66.9 / 65.4  (73.4 / 72.6)   73.8 / 71.9  (79.9 / 79.5)
+//   the same, read                        71.6 / 80.4  (75.0 / 85.7)   82.5 / 90.9  (86.0 / 96.0)   99.0 / 101.3 (103.3 / 107.9) 109.7 / 106.6 (113.9 / 113.4) 127.4 / 117.1 (131.6 / 124.6)
+//   neither cached, read                  78.1 / 80.7  (81.6 / 85.9)   92.4 / 90.6  (95.8 / 96.3)   107.5 / 101.2 (111.9 / 108.0) 113.8 / 106.3 (118.3 / 113.8) 128.0 / 116.8 (132.0 / 124.3)
+// Experts of 512 x 1024 x 3, inputs from HBM, read: 192 84.1 / 91.9, 216 99.6 / 102.1, 228 109.8 / 107.2.
+constexpr uint64_t kStreamingBytes = kLastLevelCacheBytes / 8 * 7;
 
 // How a launch writes, for the caller's policy.
 Stores stores_of(int policy, const Streams &s)

@@ -535,7 +535,7 @@ def test_one_launch_of_many_tensors_only_where_their_lengths_agree(big, small, c
 
 @pytest.mark.parametrize("max_len", [8, 12])
 def test_the_line_from_which_on_a_launch_streams_its_stores(max_len):
-    """three quarters of the last-level cache, in one launch; only where the policy is left to the library"""
+    """seven eighths of the last-level cache, in one launch; only where the policy is left to the library"""
     info = zm.blob_info(zm.compress(synth.special_tensor("gauss" if max_len == 8 else "wide", 5000, 3), 16384, 4096, max_len)[0])
 
     def infos(total):
@@ -546,7 +546,7 @@ def test_the_line_from_which_on_a_launch_streams_its_stores(max_len):
         t.blob_size = t.e_offset + t.n_values // 3 // 256 * 256
         return [t] * 3
 
-    n = 3 << 25
+    n = (7 << 24) + 2                # values, in three tensors alike
     for stores, want in ((zm.STORES_AUTO, [0, 1]), (zm.STORES_CACHED, [0, 0]), (zm.STORES_STREAMING, [1, 1])):
         assert [s.streaming_stores for v in (n - 3, n) for s in zm.decode_launch_shapes(infos(v), stores)] == want
 
