@@ -337,8 +337,10 @@ int zm_decode_host_tensors(const void *const *host_blobs, const zm_tensor_info *
  * F < C < S < E: F keeps recovered bf16 tensors, C keeps E-chunks and SM-chunks,
  * S keeps SM-chunks, E keeps E-chunks.  Whatever an expert's pool does not hold
  * is fetched from the host copy of its blobs (Sec. 6: host memory is the tier
- * below device memory), by a kernel where that copy is mapped for the device, as
- * pinned memory is, by copies else, while the experts that need none decode.  Every fetch counts one activation of each named
+ * below device memory): by a kernel where that copy is mapped for the device, as
+ * pinned memory is, on the caller's stream and in front of one decode of all
+ * experts; by copies on the cache's own stream else, while the experts that need
+ * none decode, and so the kernel too where more than 80 MiB of them do.  Every fetch counts one activation of each named
  * expert; an expert whose rank r in the activation counts (0 = most activated,
  * ties to the lower id) satisfies r < tau_i = slots[0] + .. + slots[i] +
  * tolerance is dispatched to the first such pool i (pools of capacity 0 are

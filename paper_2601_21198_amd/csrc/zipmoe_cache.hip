@@ -143,11 +143,14 @@ int fetch_parts(const Part *part, size_t n, hipStream_t stream)
 
 // bf16 bytes of the experts that need no copy from which on they are decoded beside the fetch, whose kernel then has a stream of its own.  Handing over to
 // that stream and back costs 10 to 15 us on the GPU; the decode, while the host link is busy, takes up to four times as long as by itself.  us per
-// fetch, beside / behind each other, one expert of 1024 x 2048 x 3 missing:
-//   MiB decoded beside    0.75 (128 x 512)    3 (256 x 1024)    12            24            48              84              144
-//                         21.4 /  9.9         43.2 / 30.0       51.7 / 47.0   94.1 / 87.4   179.6 / 170.3   180.2 / 179.4   180.5 / 197.8
-// experts of 4096 x 4096 x 3: 96 MiB 650.8 / 646.5, 288 MiB 1243 / 1286.
-constexpr uint64_t kDecodeBeside = 64ull << 20;
+// fetch, beside / behind each other, one expert missing (two):
+//   MiB decoded beside    12             48                72                               96                               120                              192
+//   512 x 1024 x 3                                         52.7 /  52.9                     71.4 /  76.4                     83.1 /  88.6
+//   1024 x 2048 x 3       51.7 / 47.0    69.8 /  67.6      101.1 / 100.1 (186.5 / 184.4)    138.1 / 139.0 (258.5 / 261.3)    180.0 / 194.9 (332.6 / 345.6)    180.0 / 221.5
+//   2048 x 2048 x 3                                        179.9 / 177.9                    234.2 / 234.2                    287.6 / 293.6
+//   4096 x 4096 x 3                                                                         647.9 / 648.2                                                     1243 / 1266
+// (1024 x 2048 x 3, 84 MiB: 116.5 / 116.4; 128 x 512 x 3, 0.75 MiB: 21.4 / 9.9; 256 x 1024 x 3, 3 MiB: 43.2 / 30.0.)
+constexpr uint64_t kDecodeBeside = 80ull << 20;
 
 // Host memory that a kernel may read, asked for range by range: what has been found mapped stays known until the object
 // goes, which is to be within one call, since the caller may unmap and map his memory between calls.

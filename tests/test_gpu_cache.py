@@ -207,10 +207,10 @@ def test_a_fetch_can_be_captured_and_replayed(monkeypatch, packed, pinned):
 
 
 def test_fetches_beside_and_in_front_of_the_decode():
-    """with 64 MiB or more to decode meanwhile a fetch has a stream of its own, else it lies in front of the decode; in turn, with nothing but the stream
+    """with more than 80 MiB to decode meanwhile a fetch has a stream of its own, else it lies in front of the decode; in turn, with nothing but the stream
     between them, parts that change pool included, and the cache destroyed while the last fetch may be on its way"""
     import torch
-    n = 6 << 20
+    n = 7 << 20                       # six of them
     tensors, blobs = make_layer(8, (n,), seed=5)
     cache = zm.ExpertCache(blobs, (0, 6, 1, 0), 0, max_selected=7)
     stream = torch.cuda.current_stream().cuda_stream
