@@ -11,7 +11,8 @@ CSRC = os.path.join(_HERE, "csrc")
 # ZIPMOE_LIBRARY points the binding at another build of the same sources (same ABI)
 LIB_PATH = os.environ.get("ZIPMOE_LIBRARY", os.path.join(_HERE, "libzipmoe.so"))
 SOURCES = [os.path.join(CSRC, f) for f in ("zipmoe_host.cpp", "zipmoe_plan.cpp", "zipmoe_sched.cpp", "zipmoe_decode.hip", "zipmoe_cache.hip", "zipmoe_staged.hip", "zipmoe_probe.hip", "zipmoe_layer.hip")]
-NATIVE_SOURCE, NATIVE_PATH = os.path.join(CSRC, "zipmoe_python.cpp"), os.path.join(_HERE, "_native.so")
+# for the interpreter that builds it; others find none and call through ctypes
+NATIVE_SOURCE, NATIVE_PATH = os.path.join(CSRC, "zipmoe_python.cpp"), os.path.join(_HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",

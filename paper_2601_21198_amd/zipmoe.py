@@ -3,11 +3,13 @@
 Every step of the decode path runs in the library's HIP kernels; PyTorch is used
 by callers for device memory and streams.  The library must have been built
 (``python -m paper_2601_21198_amd.build`` or ``__graft_entry__.build()``);
-loading fails loudly otherwise -- there is no fallback path.
+loading fails loudly otherwise -- there is no fallback path.  The extension module
+marshals arguments only: where the interpreter that runs has none, ctypes does.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import List, Optional, Sequence, Tuple
 
@@ -104,14 +106,36 @@ _native = None                          # the extension module, and the addresse
 _fn = {}
 
 
+class _NoNative:
+    """Stands in for an extension module that was not built for this interpreter: every call is left to ctypes, as the module leaves unusual types."""
+    Prepared = None
+
+    class Target:
+        def __init__(self, *arrays):
+            self.decode = _NoNative.recover
+
+    @staticmethod
+    def recover(*args):
+        return None
+
+    layer_decode = recover
+
+
+def _load_native():
+    if not os.path.exists(NATIVE_PATH):
+        return _NoNative
+    spec = importlib.util.spec_from_file_location(f"{__package__}._native", NATIVE_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
 def lib() -> ctypes.CDLL:
     global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2601_21198_amd.build`")
-        if not os.path.exists(NATIVE_PATH):
-            raise ImportError(f"{NATIVE_PATH} is not built; run `python -m paper_2601_21198_amd.build`")
-        from . import _native as native
+        native = _load_native()
         L = ctypes.CDLL(LIB_PATH)
         c = ctypes
         u8p, u16p, u64p = c.POINTER(c.c_uint8), c.POINTER(c.c_uint16), c.POINTER(c.c_uint64)
@@ -395,7 +419,7 @@ class ExpertLayer:
         # one for every tensor of an expert, or an IndexError (a list, what alloc_outputs returns, is read at once)
         offsets = [2 * s for s in (starts[:t] if type(starts) is list and len(starts) >= t else [starts[m] for m in range(t if bases else 0)])]
         outs = (ctypes.c_void_p * (len(expert_ids) * t))(*[base + o for base in bases for o in offsets])
-        if type(stores) is int and -(1 << 31) <= stores < 1 << 31:
+        if _native.Prepared and type(stores) is int and -(1 << 31) <= stores < 1 << 31:
             return _native.Prepared(*self._arrays, ctypes.addressof(ids), len(expert_ids), ctypes.addressof(outs), stores,
                                     (ids, outs, out_buffers), (self.blob_ptrs, self.table_ptrs, self.infos), _raise_decode)
         f = (_lib or lib()).zm_decode_experts_stores

@@ -594,3 +594,15 @@ def test_calls_of_unusual_types_are_what_they_are_for_usual_ones():
             zm.recover(*args)
         assert e.value.status == zm.E_ARG
     assert zm.recover(0, 0, 0, 0) is None
+
+
+def test_without_the_extension_module_calls_are_what_they_are_with_it(monkeypatch, tmp_path):
+    """a library that was built without it, another interpreter: everything goes through ctypes; and a file of another interpreter's is not taken for it"""
+    import sysconfig
+    assert zm.NATIVE_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    with_it = type(zm.ExpertLayer([[zm.compress(synth.special_tensor("gauss", 600, 0), 4096, 4096)[0]]], device="cpu").make_call([], [], [0]))
+    for name, value in (("NATIVE_PATH", str(tmp_path / "none.so")), ("_lib", None), ("_native", None)):
+        monkeypatch.setattr(zm, name, value)
+    test_calls_of_unusual_types_are_what_they_are_for_usual_ones()
+    without = type(zm.ExpertLayer([[zm.compress(synth.special_tensor("gauss", 600, 0), 4096, 4096)[0]]], device="cpu").make_call([], [], [0]))
+    assert without is not with_it and with_it.__name__ == "Prepared"
