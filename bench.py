@@ -51,7 +51,7 @@ def measured_traffic(workload: str, stream_values: int = 4096, max_len: int = 8)
 
 def kernel_names(infos, shapes):
     """The kernels that one call of these tensors launches with streaming stores: what zm_decode_launch_shapes tells, the kind of arguments (up to six
-    tensors cut alike have their own) and, for streams of 4096 values, the kind that their number decides."""
+    tensors cut alike have their own), for streams of 4096 values the kind that their number decides, and for short ones whether a wave takes several."""
     names = []
     for sh in shapes:
         long_codes = sh.round_symbols == 2
@@ -63,6 +63,12 @@ def kernel_names(infos, shapes):
             kind = ", kMany" if sum(-(-int(i.n_values) // 4096) for i in group) > 7168 else ", kFitting"
         names.append("zm_decode_%skernel<%s, %d, %s%s>" % ("few_" if few else "", "true" if long_codes else "false", sh.waves_per_workgroup,
                                                            "kStreaming" if sh.streaming_stores else "kThrough", kind))
+        width = group[0].stream_values
+        if len(shapes) == 1 and width in (512, 1024, 2048) and all(i.stream_values == width for i in group):
+            # one wave a stream has these numbers of workgroups, for the largest tensor or for all
+            blocks = [(-(-int(i.n_values) // width) + 1) // 2 for i in group]
+            if sh.workgroups not in (max(blocks), sum(blocks)):
+                names[-1] += ", %d streams a wave" % (4096 // width)
     return names
 
 

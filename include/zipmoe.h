@@ -266,7 +266,8 @@ void zm_layer_destroy(zm_layer *layer);
 typedef struct zm_launch_shape {
     uint32_t round_symbols;        /* symbols that are sure to fit a 32-bit window: 4 (codes <= 8 bits) or 2
                                       (longer codes, of which four are tried first)                        */
-    uint32_t waves_per_workgroup;  /* streams that share a workgroup                                       */
+    uint32_t waves_per_workgroup;  /* a wave decodes a stream; in launches of many streams of 512, 1024 or 2048
+                                      values eight, four or two of them, and there are fewer workgroups    */
     uint32_t streaming_stores;     /* 1: non-temporal stores                                               */
     uint32_t workgroups;           /* grid x: workgroups of the largest tensor of the launch, or of all its
                                       tensors together where their lengths differ much                     */

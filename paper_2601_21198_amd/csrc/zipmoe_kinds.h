@@ -132,32 +132,31 @@ struct Bundle {
     Kind kind;
 };
 
-// us, three tensors of Gaussian weights, a wave per stream / bundles as kFitting / as kMany; cached: three sets in turn, device-scope stores; else nothing cached.
+// us, three tensors of Gaussian weights, a wave per stream / bundles as kFitting / as kMany (one figure where there is only one); cached: three sets in
+// turn, device-scope stores; else nothing cached.
 //   short codes, streams        cached                 dev                    nt
-//     512:   8000                4.9 /  5.0 /  4.9      6.3 /  6.6 /  6.6      6.2 /  6.3 /  6.4
-//            9000                5.4 /  5.2 /  5.2      7.0 /  6.9 /  6.9      6.7 /  6.6 /  6.6
-//           24000               10.3 /  8.4 /  8.2     12.9 / 10.5 / 10.5     12.5 /  9.6 / 10.0
-//           98304               45.1 / 34.3            45.0 / 34.4            42.5 / 32.4
-//    1024:   8000                6.1 /  6.2 /  6.2      8.4 /  8.6 /  8.6      8.3 /  7.2 /  8.5
-//           12000                8.6 /  8.2 /  8.2     10.6 / 10.1 / 10.0     10.6 /  9.1 / 10.0
-//           18000               11.6 / 11.8 / 11.8     14.5 / 15.2 / 15.3     13.9 / 13.9 / 14.7
-//           50000               32.0 / 34.2 / 33.9     32.1 / 34.3 / 34.1     31.5 / 32.4 / 33.1
-//    2048:   4500                6.7 /  7.0 /  7.0      9.7 /  9.2 /  9.2      7.8 /  7.9 /  9.3
-//            6000                8.1 /  8.2 /  8.2     11.1 / 10.0 /  9.9      9.8 /  9.0 /  9.9
-//            8000               10.4 /  9.8 / 11.2     14.1 / 12.8 / 13.7     11.9 / 10.6 / 12.3
-//           12000               14.4 / 15.0 / 14.2     18.9 / 18.4 / 17.8     17.3 / 17.6 / 17.1
-//           24000               32.0 / 31.9 / 31.1     32.0 / 31.9 / 31.1     30.5 / 31.0 / 30.6
+//     512:   9000              5.2 /  5.4             6.9 /  6.9             6.6 /  6.6
+//           24000              9.9 /  8.5            12.8 / 10.5            12.5 /  9.8
+//    1024:  12000              8.5 /  8.2            10.5 / 10.1            10.6 /  9.2
+//           24000             14.3 / 15.2            17.7 / 18.7            17.0 / 18.0
+//    2048:   6500              9.0 /  8.7 / 10.3     11.9 / 10.8 / 12.3     10.4 /  9.4
+//            8000             10.3 /  9.9 / 11.2     14.2 / 12.8 / 13.9     11.9 / 10.7
+//           12000             14.2 / 14.9 / 14.0     18.6 / 18.1 / 17.6     17.4 / 17.7
+//           24000             31.9 / 32.0 / 30.9     32.0 / 32.0 / 31.0     30.3 / 31.2
 //   long codes
-//     512:   8000                5.9 /  5.9 /  5.9      7.3 /  7.1 /  7.1      6.9 /  7.1 /  7.0
-//           24000               12.7 /  9.5 /  9.0     14.8 / 11.3 / 11.0     14.1 / 11.7 / 10.7
-//    1024:   6000                6.2 /  6.6 /  6.6      7.8 /  8.1 /  8.1      7.4 /  7.6 /  8.0
-//            8000                7.4 /  6.9 /  6.9     10.0 /  8.8 /  8.8      9.4 /  8.0 /  8.8
-//           16000               11.9 / 10.0 / 11.2     14.9 / 13.7 / 14.5     13.4 / 12.1 / 12.8
-//           24000               16.1 / 15.2 / 14.9     19.8 / 19.4 / 18.5     19.3 / 19.2 / 18.0
-//    2048:   3000                6.7 /  7.1 /  7.0      8.9 /  8.8 /  8.8      7.6 /  7.9 /  8.4
-//            4500                7.9 /  8.2 /  8.1     11.4 / 10.0 /  9.9     10.1 /  9.2 /  9.8
-//            8000               11.1 / 10.3 / 11.8     16.0 / 14.1 / 14.7     13.0 / 12.1 / 12.9
-//           24000               36.7 / 33.6 / 32.7     36.3 / 33.4 / 32.4     33.2 / 32.3 / 31.7
+//     512:   8000              5.5 /  6.2             7.3 /  7.2             7.0 /  7.1
+//            9500              6.3 /  6.3             8.2 /  7.8             7.8 /  7.4
+//           24000             11.9 /  8.5            14.6 / 10.8            13.9 / 10.7
+//    1024:   6000              6.1 /  6.5 /  6.4      7.9 /  7.8 /  7.7      7.5 /  7.4 /  7.6
+//            8000              7.2 /  6.8 /  6.7     10.1 /  8.8 /  8.9      9.4 /  7.8 /  8.8
+//           16000             11.7 / 10.2 / 11.9     15.3 / 14.7 / 14.5     13.3 / 11.9 / 13.1
+//           24000             15.8 / 15.7 / 14.6     19.9 / 19.5 / 19.0     19.1 / 19.1 / 18.3
+//    2048:   3000              6.2 /  6.7 /  6.3      8.5 /  7.9 /  7.7      7.3 /  7.5 /  7.6
+//            4500              7.4 /  8.0 /  7.7     10.7 /  9.8 /  9.5      9.5 /  9.2 /  9.4
+//            6500              9.2 /  9.0 / 10.7     13.5 / 11.5 / 12.6     11.9 / 11.1 / 12.0
+//            8000             10.6 /  9.9 / 11.8     15.7 / 14.1 / 14.1     12.9 / 12.0 / 13.0
+//           12000             14.5 / 15.3 / 14.5     20.4 / 19.0 / 18.5     18.4 / 18.8 / 17.6
+//           24000             35.3 / 33.7 / 32.2     35.8 / 33.8 / 32.2     32.5 / 32.4 / 31.3
 //   denser long codes, a wave per stream / bundles; e: bytes a stream
 //     512:   9500, e 296          6.5 /  6.5             8.2 /  7.9             7.9 /  7.6
 //            9500, e 347          6.7 /  6.9             8.2 /  9.2             8.0 /  8.4
@@ -178,7 +177,7 @@ inline Bundle bundle_of(bool long_codes, const Streams &s, Stores stores)
     const Bundle none{1u, kShortStreams};
     if (s.shortest != s.longest || 2 * s.raw_values > s.values || s.e_bytes > 1024 * s.n || s.e_bytes < 80 * s.n) return none;
     const bool streaming = stores == kStreaming;
-    // long codes: more bytes a stream than these; a sixty-four of them are lengths
+    // long codes: more bytes a stream than these, of which 64 are lengths
     auto denser = [&](uint64_t bytes) { return long_codes && s.e_bytes > bytes * s.n; };
     switch (s.longest) {
     case 512u: return s.n > (denser(320) ? 12 : 9) * kSimds ? Bundle{8u, long_codes ? kMany : kFitting} : none;
