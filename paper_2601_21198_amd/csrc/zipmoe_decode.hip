@@ -1190,9 +1190,9 @@ int launch_bundles(void *args, const Plan &p, Stores kind)
             if (many) return launch_stores<kLong, 2, kMany, Args, 4>(args, p, kind);
         return launch_stores<kLong, 2, kFitting, Args, 4>(args, p, kind);
     }
-    if (!many) return launch_stores<kLong, 2, kFitting, Args, 2>(args, p, kind);
-    if constexpr (kLong) return launch_stores<kLong, 2, kMany, Args, 2>(args, p, kind);
-    else return launch_kernel<kLong, 2, kThrough, kMany, 2, Args>(args, p);
+    if constexpr (kLong)
+        if (many) return launch_stores<kLong, 2, kMany, Args, 2>(args, p, kind);
+    return launch_stores<kLong, 2, kFitting, Args, 2>(args, p, kind);
 }
 
 template <bool kLong, int kWaves, class Args>

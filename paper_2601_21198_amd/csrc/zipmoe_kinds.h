@@ -143,6 +143,7 @@ struct Bundle {
 //            8000             10.3 /  9.9 / 11.2     14.2 / 12.8 / 13.9     11.9 / 10.7
 //           12000             14.2 / 14.9 / 14.0     18.6 / 18.1 / 17.6     17.4 / 17.7
 //           24000             31.9 / 32.0 / 30.9     32.0 / 32.0 / 31.0     30.3 / 31.2
+//           24576, 24 tensors 32.1 /      / 33.2     32.0 /      / 33.1     31.0
 //   long codes
 //     512:   8000              5.5 /  6.2             7.3 /  7.2             7.0 /  7.1
 //            9500              6.3 /  6.3             8.2 /  7.8             7.8 /  7.4
@@ -169,7 +170,7 @@ struct Bundle {
 //    2048:   8000, e 976         11.5 / 11.8            16.1 / 14.8            13.5 / 13.4
 //           12000, e 976         18.7 / 18.4            22.2 / 19.5            20.0 / 18.6
 // So waves of one stream stay where all of them find places, and for short codes in large launches where they are bound by the memory
-// already; device-scope stores of few streams that stay cached decide where the lines lie, though cold ones would gain earlier.  Raw tensors are not
+// already (2048 values as kMany gain with three large tensors, but lose with the many of a usual call); device-scope stores of few streams that stay cached decide where the lines lie, though cold ones would gain earlier.  Raw tensors are not
 // bundled, nor streams of more than a kilobyte, nor what has no room for its streams at all.  Raw chunks among coded ones make no difference.  What is left: 4096 long
 // codes of rare symbols in a row, 2048 values a stream, where most rounds are done again: one such piece in a hundred, 6500 streams, 10.7 / 12.2, 14.7 / 15.2, 12.5 / 13.7.
 inline Bundle bundle_of(bool long_codes, const Streams &s, Stores stores)
@@ -187,7 +188,7 @@ inline Bundle bundle_of(bool long_codes, const Streams &s, Stores stores)
         return s.n <= 16 * kSimds ? Bundle{4u, kFitting} : long_codes ? Bundle{4u, kMany} : none;
     case 2048u:
         if (s.n <= (streaming ? (long_codes ? 4 : 5) : denser(864) ? 9 : 6) * kSimds) return none;
-        return s.n <= 9 * kSimds ? Bundle{2u, kFitting} : long_codes || !streaming ? Bundle{2u, kMany} : none;
+        return s.n <= 9 * kSimds ? Bundle{2u, kFitting} : long_codes ? Bundle{2u, kMany} : none;
     default: return none;
     }
 }

@@ -156,7 +156,7 @@ def test_large_launches_of_short_streams(bundle_of):
             assert ask(1024, 16 * 1024) == (4, "fitting")
             assert ask(1024, 16 * 1024 + 1) == ((4, "many") if long_codes else (1, "-"))
             assert ask(2048, 9 * 1024) == (2, "fitting")
-            assert ask(2048, 9 * 1024 + 1) == ((2, "many") if long_codes or not streaming else (1, "-"))
+            assert ask(2048, 9 * 1024 + 1) == ((2, "many") if long_codes else (1, "-"))
 
 
 def test_launches_that_no_bundle_is_made_of(bundle_of):
@@ -164,7 +164,7 @@ def test_launches_that_no_bundle_is_made_of(bundle_of):
     for w in (1536, 2560, 4096, 8192):
         assert bundle_of([(w, many)])[0] == 1
     assert bundle_of([(512, many), (1024, many)])[0] == 1                       # streams of two lengths
-    assert bundle_of([(2048, many)], e=1024)[0] == 2 and bundle_of([(2048, many)], e=1025)[0] == 1
+    assert bundle_of([(2048, 8192)], e=1024)[0] == 2 and bundle_of([(2048, 8192)], e=1025)[0] == 1
     assert bundle_of([(512, many)], e=79)[0] == 1 and bundle_of([(512, many)], e=80)[0] == 8
     # raw tensors: as many bytes in the E region as values
     assert bundle_of([(512, many)], e=511)[0] == 8 and bundle_of([(512, many)], e=512)[0] == 1
@@ -180,7 +180,7 @@ def test_launches_of_dense_long_codes_need_more_streams(bundle_of, w, bytes_, li
                 at = 4
             assert bundle_of([(w, at * 1024)], True, streaming, e)[0] == 1
             assert bundle_of([(w, at * 1024 + 1)], True, streaming, e)[0] == 4096 // w
-    assert bundle_of([(w, 11 * 1024)], False, False, bytes_ + 1)[0] == 4096 // w        # four short codes always fit a window
+    assert bundle_of([(w, {512: 10, 1024: 11, 2048: 8}[w] * 1024)], False, False, bytes_ + 1)[0] == 4096 // w        # four short codes always fit a window
     assert bundle_of([(1024, 1 << 15)], True, False, 577)[0] == 1 and bundle_of([(1024, 1 << 15)], True, True, 577)[0] == 4
 
 
