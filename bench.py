@@ -30,8 +30,8 @@ HBM_PEAK_GBPS = 8000.0        # MI355X published peak HBM3E bandwidth
 # with, and for streams of 4096 values, codes of up to 8 bits and streaming stores: else "traffic" is null.
 KERNEL_SOURCES = ("zipmoe_decode.hip", "zipmoe_kinds.h", "zipmoe_extent.h")
 MEASURED_TRAFFIC = {
-    "kernel_sha256_16": "2bc7247590248b98",
-    "bytes_per_launch": {"cfg5": 117.14e6, "cfg3": 170.41e6, "cfg4": 1195.73e6, "split-cfg4": 234.93e6},
+    "kernel_sha256_16": "e82cc52e697d8602",
+    "bytes_per_launch": {"cfg5": 117.14e6, "cfg3": 170.39e6, "cfg4": 1195.72e6, "split-cfg4": 234.91e6},
 }
 
 
